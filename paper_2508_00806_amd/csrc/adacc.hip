@@ -252,6 +252,19 @@ static int batch_kind(const adacc_method* m, const Plan& p) {
 }
 
 static uint32_t decompress_pieces(uint64_t numel) { return (uint32_t)((numel + 2047ull) / 2048ull); }
+// ceil(2^64 / n); 0 for n = 1, which the kernels know
+static uint64_t reciprocal64(uint32_t n) { return n > 1u ? ~0ull / n + 1ull : 0ull; }
+// 1 / n moved up by three units in the last place: the binary32 product with an integer below 4096 then lies at or
+// above the quotient where that is an integer, and below the next integer everywhere else (n <= 2048)
+static float reciprocal_up(uint32_t n) {
+  const float r = 1.0f / (float)n;
+  uint32_t bits;
+  std::memcpy(&bits, &r, sizeof bits);
+  bits += 3u;
+  float up;
+  std::memcpy(&up, &bits, sizeof up);
+  return up;
+}
 
 // Workspace of one tensor that keeps outliers: [cnt: one word per tile][flag][block_sum][slots],
 // block sums and slots for ABS / STD only.  Offsets relative to the tensor's region.
@@ -297,7 +310,6 @@ static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, cons
     d->block_sum = reinterpret_cast<uint32_t*>(r + w.block_sum_off);
     d->slot = reinterpret_cast<uint2*>(r + w.slot_off);
   }
-  (void)numel;
   d->numel = p.numel_main;
   d->tail = p.tail;
   d->n_tiles = p.n_tiles;
@@ -311,9 +323,17 @@ static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, cons
   d->generic = p.generic ? 1u : 0u;
   d->n_blocks = place_blocks(p);
   d->lgt = p.tile_elems == 4096 ? 12u : 11u;
-  if (dst && !p.generic) {  // decompression counts pieces of 2048 elements
-    d->n_tiles = decompress_pieces(p.numel_main);
+  if (dst) {  // decompression counts pieces of 2048 elements of the whole tensor
+    d->numel = numel;
+    d->tail = 0;
+    d->n_tiles = decompress_pieces(numel);
     d->ptr_shift = p.tile_elems == 4096 ? 1u : 0u;
+    d->per_tile = m->outlier_mode == ADACC_OUTLIER_TOPK ? m->topk * (p.tile_elems / d->gs) : 0u;
+    if (p.generic) {
+      d->magic_q = reciprocal64(m->quant_group / 8u);
+      d->magic_t = reciprocal64(p.tile_elems / 8u);
+      d->recip_q = reciprocal_up(m->quant_group / 8u);
+    }
   }
   d->lgq = p.lgq;
   d->lgs = p.lgs;
@@ -718,6 +738,15 @@ int adacc_compress_noalloc(const adacc_method* method, const void* src, uint64_t
   return compress_one(method, src, numel, blob, blob_bytes, ws, hip_stream);
 }
 
+static int launch_decompress(const adacc_method* m, const Plan& p, const TensorDesc& d, int dst_dtype, hipStream_t s) {
+  DecompressFn fn = ADACC_PICK(p.half, decompress_fn(m->bits, m->asym, dst_dtype == ADACC_DST_F32, p.generic));
+  uint32_t grid = 0;
+  const int rc = grid_for(d.n_tiles, reinterpret_cast<const void*>(fn), &grid);
+  if (rc != ADACC_OK) return rc;
+  hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, s, d, p.outliers ? 1u : 0u);
+  return launch_check("decompress_kernel");
+}
+
 int adacc_decompress(const adacc_method* method, const void* blob, uint64_t blob_bytes, uint64_t numel, void* dst,
                      int dst_dtype, void* hip_stream) {
   if (!method) return ADACC_ENULL;
@@ -734,24 +763,7 @@ int adacc_decompress(const adacc_method* method, const void* blob, uint64_t blob
   TensorDesc d;
   fill_desc(method, numel, p, L, nullptr, const_cast<void*>(blob), dst, dst_dtype, nullptr, &d);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  if (p.generic) {
-    hipLaunchKernelGGL(ADACC_PICK(p.half, decompress_generic_fn()), dim3(p.n_tiles), dim3(ADACC_PICK(p.half, generic_threads())), 0, s, d);
-    return launch_check("decompress_generic_kernel");
-  }
-  DecompressFn fn = ADACC_PICK(p.half, decompress_fn(method->bits, method->asym, dst_dtype == ADACC_DST_F32));
-  if (d.n_tiles != 0) {
-    uint32_t grid = 0;
-    rc = grid_for(d.n_tiles, reinterpret_cast<const void*>(fn), &grid);
-    if (rc != ADACC_OK) return rc;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, s, d, p.outliers ? 1u : 0u);
-    rc = launch_check("decompress_kernel");
-    if (rc != ADACC_OK) return rc;
-  }
-  if (p.tail != 0) {  // writes elements the kernel above does not touch
-    hipLaunchKernelGGL(ADACC_PICK(p.half, decompress_tail_fn()), dim3(1), dim3(kWave), 0, s, d);
-    rc = launch_check("decompress_tail_kernel");
-  }
-  return rc;
+  return launch_decompress(method, p, d, dst_dtype, s);
 }
 
 static int batch_prepare(uint32_t n, const adacc_method* methods, const uint64_t* numels, std::vector<Plan>* plans,
@@ -926,38 +938,24 @@ int adacc_decompress_batch(uint32_t n, const adacc_method* methods, const void* 
     kind[i] = plans[origin[i]].half ? kBatchKinds : 0;
   }
   group_launches(units, kind, &members, &launches);
-  // The table goes up in the order of the launches' member lists, so that the main kernels find the entry of
-  // blockIdx.y at table + first_member without looking a number up first; the tail kernels keep their lists.
-  const uint32_t n_listed = (uint32_t)members.size();
-  std::vector<uint32_t> place(nt, 0xFFFFFFFFu);
+  // The table goes up in the order of the launches, so that the kernels find the entry of blockIdx.y at table +
+  // first_member without looking a number up first.  (Tensors with groups that the batch kernel does not take are
+  // launched one by one.)
   std::vector<TensorDesc> ordered;
-  ordered.reserve(nt);
-  for (uint32_t j = 0; j < n_listed; ++j) { place[members[j]] = j; ordered.push_back(descs[members[j]]); }
-  for (uint32_t i = 0; i < nt; ++i)
-    if (place[i] == 0xFFFFFFFFu) { place[i] = (uint32_t)ordered.size(); ordered.push_back(descs[i]); }
-  std::vector<GroupLaunch> tails;
-  for (uint32_t i = 0; i < nt; ++i) units[i] = descs[i].tail != 0u ? 1u : 0u;
-  group_launches(units, kind, &members, &tails);
-  for (uint32_t j = n_listed; j < (uint32_t)members.size(); ++j) members[j] = place[members[j]];
+  ordered.reserve(members.size());
+  for (const uint32_t i : members) ordered.push_back(descs[i]);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  unsigned char* mem = static_cast<unsigned char*>(ws->device_mem);
-  TensorDesc* dt = reinterpret_cast<TensorDesc*>(mem);
-  uint32_t* dm = reinterpret_cast<uint32_t*>(mem + bp.members_off);
+  TensorDesc* dt = static_cast<TensorDesc*>(ws->device_mem);
   rc = upload_table(ordered, dt, s);
-  if (rc == ADACC_OK && members.size() > n_listed) rc = upload_words(members, dm, s);
   if (rc != ADACC_OK) return rc;
   for (const GroupLaunch& g : launches)
     hipLaunchKernelGGL(ADACC_PICK(g.kind >= kBatchKinds, decompress_batch_fn(dst_dtype == ADACC_DST_F32)),
                        dim3((g.max_units + kWavesPerWg - 1) / kWavesPerWg, g.n_members), dim3(kThreads), 0, s,
                        dt + g.first_member, static_cast<const uint32_t*>(nullptr));
-  for (const GroupLaunch& g : tails)
-    hipLaunchKernelGGL(ADACC_PICK(g.kind >= kBatchKinds, decompress_tail_batch_fn()), dim3(g.n_members), dim3(kWave), 0, s, dt,
-                       dm + g.first_member);
-  for (uint32_t i = 0; i < nt; ++i)
-    if (descs[i].generic)
-      hipLaunchKernelGGL(ADACC_PICK(plans[origin[i]].half, decompress_generic_fn()), dim3(descs[i].n_tiles),
-                         dim3(ADACC_PICK(plans[origin[i]].half, generic_threads())), 0, s, descs[i]);
-  return launch_check("decompress_batch_kernel");
+  rc = launch_check("decompress_batch_kernel");
+  for (uint32_t i = 0; i < nt && rc == ADACC_OK; ++i)
+    if (descs[i].generic) rc = launch_decompress(&methods[origin[i]], plans[origin[i]], descs[i], dst_dtype, s);
+  return rc;
 }
 
 int adacc_read_status(const void* blob, const adacc_layout* layout, void* hip_stream, uint32_t status_out[4]) {

@@ -86,8 +86,11 @@ struct TensorDesc {
   uint2* slot;              // compress, workspace (ABS / STD): kSlot records (index, value) per tile, the tile's
                             //   outliers until the placement kernel has moved them to the stream
   uint32_t* flag;           // compress, workspace (TOPK): set to the epoch by a tile whose count is not the regular one
-  uint64_t numel;           // elements the tile kernels take: the whole groups of the larger kind
-  uint32_t tail;            // elements after those (fewer than the larger group), done by the tail kernels
+  uint64_t numel;           // compress: elements the tile kernels take, the whole groups of the larger kind; decompress: all
+  uint64_t magic_q, magic_t;  // decompress, fallback: ceil(2^64 / n) for the octets of a quantisation group resp. a tile (0: n = 1)
+  float recip_q;            // decompress, fallback: 1 / octets of a quantisation group, moved up (see group_of)
+  uint32_t per_tile;        // decompress, TOPK: outliers of a regular tile
+  uint32_t tail;            // compress: elements after numel (fewer than the larger group), done by the tail kernels
   uint32_t n_tiles;         // tiles of the first numel elements (decompress: pieces of 2048 of them)
   uint32_t n_tiles_all;     // tiles of the whole tensor, tail included: tile_ptr has one entry more
   uint32_t bits, asym, mode;  // the method, for kernels that do not get it as template arguments

@@ -1,4 +1,4 @@
-// Decompression of one tile by one wavefront (Section 3.2: X^ = code * S, resp. code * S + O,
+// Decompression of one piece by one wavefront (Section 3.2: X^ = code * S, resp. code * S + O,
 // then the outliers are written back; Fig. 3(c) decompression workflow).
 #pragma once
 
@@ -8,19 +8,28 @@
 namespace adacc {
 namespace ADACC_DT_NS {
 
-// Decompression always works on pieces of E = 4 rows (2048 elements), whatever the tile of the
-// blob: a piece of a 4096-element tile looks through the outliers of the whole tile and takes
-// those that fall inside it.
+// Decompression always works on pieces of E = 4 rows (2048 elements) of the flat tensor, one per wavefront, whatever
+// the tile of the blob and whatever the group sizes: a piece looks through the outliers of the tiles it touches and
+// takes those that fall inside it.
 //
-// A piece whose tile has up to 64 outliers, no two of them in the same octet, takes them into the output
-// words in registers before they are stored: the lanes that hold the entries of the stream drop them into a
-// mailbox of the wavefront in LDS (one word per octet of the piece, 1 KiB), every lane picks up the four
-// words of its own octets.  Otherwise the outliers are written over the dequantised values in memory: the
-// piece is stored first, the wavefront waits until those stores have reached the L2 (its store counter at
-// zero), and then stores the outliers of the piece, 2 (or 4) bytes each, to their positions.  Both rounds of
-// stores come from the same wavefront and the second is issued only after the first is complete,
-// so the outliers are what stays.  (Staging the whole piece in LDS to patch it there cost a round trip
-// through LDS for every piece of a TOPK tensor, a third of the kernel's time.)
+// A complete piece takes its outliers into the output words in registers before they are stored, so nothing is
+// written twice and nothing waits for a store:
+//   - at most 64 entries, no two of them in the same octet (every piece of a TOPK tensor with few, nearly all others):
+//     the lanes that hold the entries drop them into a mailbox of the wavefront in LDS (one word per octet of the
+//     piece, 1 KiB), every lane picks up the four words of its own octets;
+//   - otherwise the entries go, 64 at a time, to a picture of the piece in LDS (the 16-bit pattern at the element's
+//     place, and a bit per element that says so); every lane merges its four octets with it.  The picture is not
+//     cleared, only its bits are.  (Before, such a piece was stored, waited for its own stores and wrote the
+//     outliers over them, 2 or 4 bytes each: 16.8 M values of 2051-element rows with 1 % outliers restored as
+//     binary32 took 31 + 4.5 us with the launch for the short end, 28 us now.)
+// The last piece of a tensor, when it is not complete, is stored first; the wavefront waits until those stores have
+// reached the L2 (its store counter at zero), and then stores the outliers of the piece to their positions.
+//
+// GENERIC: methods whose groups are no powers of two or exceed 4096.  Group and tile numbers of the piece's first
+// octet come from a multiplication by the 64-bit reciprocal that the host prepared, those of a lane's octets from
+// the binary32 one (exact below 4096 octets).  The entries of the piece are found by a 64-way search where the
+// tile holds more than a wavefront looks at once.  (A workgroup per tile, as the compression has it, went through
+// a row of 11008 values in 5.4 rounds with a barrier before the outliers: [8192, 11008], int4, 70 us; 43 us now.)
 // One row (512 elements, 8 per lane) of a piece: codes and scale (offset) of the lane's octet.
 template <int BITS>
 struct RowCodes {
@@ -28,44 +37,71 @@ struct RowCodes {
   float s, o;
 };
 
+// grp: the quantisation group of the lane's octet
 template <int BITS, bool ASYM>
-__device__ __forceinline__ void load_row_codes(const TensorDesc& d, uint64_t e0, RowCodes<BITS>& r) {
+__device__ __forceinline__ void load_row_codes(const TensorDesc& d, uint64_t e0, uint64_t grp, RowCodes<BITS>& r) {
   if constexpr (BITS == 8) {
     const uint2 w = *reinterpret_cast<const uint2*>(d.codes + e0);
     r.w[0] = w.x; r.w[1] = w.y;
   } else {
     r.w[0] = *reinterpret_cast<const uint32_t*>(d.codes + (e0 >> 1));
   }
-  const uint64_t g = e0 >> d.lgq;
-  r.s = d.scales[g];
+  r.s = d.scales[grp];
   r.o = 0.0f;
-  if constexpr (ASYM) r.o = d.zp[g];
+  if constexpr (ASYM) r.o = d.zp[grp];
 }
 
+// What goes over the dequantised values of a row before they are stored.
+struct NoPatch {
+  template <int WORDS>
+  __device__ __forceinline__ void operator()(uint32_t (&)[WORDS]) const {}
+};
 // What a lane finds in the mailbox for one of its octets: 0, or bit 31 set, the element (0..7) in bits 16..18
-// and the outlier's 16-bit pattern in the low half.  Applied to the output words of that row before they are
-// stored: WORDS = 4 (two 16-bit values per word) or 8 (binary32).
+// and the outlier's 16-bit pattern in the low half.  WORDS = 4 (two 16-bit values per word) or 8 (binary32).
 constexpr uint32_t kMailFull = 0x80000000u;
-template <int WORDS>
-__device__ __forceinline__ void patch_row_words(uint32_t (&w)[WORDS], uint32_t mail) {
-  const bool mine = mail != 0u;
-  const uint32_t e = (mail >> 16) & 7u;
-  const uint32_t pat = mail & 0xFFFFu;
-  if constexpr (WORDS == 8) {
-    const uint32_t bits = __float_as_uint(widen_lo(pat));
+struct MailPatch {
+  uint32_t mail;
+  template <int WORDS>
+  __device__ __forceinline__ void operator()(uint32_t (&w)[WORDS]) const {
+    const bool mine = mail != 0u;
+    const uint32_t e = (mail >> 16) & 7u;
+    const uint32_t pat = mail & 0xFFFFu;
+    if constexpr (WORDS == 8) {
+      const uint32_t bits = __float_as_uint(widen_lo(pat));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = (mine && e == (uint32_t)k) ? bits : w[k];
-  } else {
-    const uint32_t keep = (e & 1u) ? 0x0000FFFFu : 0xFFFF0000u;
-    const uint32_t put = (e & 1u) ? pat << 16 : pat;
+      for (int k = 0; k < 8; ++k) w[k] = (mine && e == (uint32_t)k) ? bits : w[k];
+    } else {
+      const uint32_t keep = (e & 1u) ? 0x0000FFFFu : 0xFFFF0000u;
+      const uint32_t put = (e & 1u) ? pat << 16 : pat;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] = (mine && (e >> 1) == (uint32_t)k) ? ((w[k] & keep) | put) : w[k];
+      for (int k = 0; k < 4; ++k) w[k] = (mine && (e >> 1) == (uint32_t)k) ? ((w[k] & keep) | put) : w[k];
+    }
   }
-}
+};
+// The octet of the picture in LDS and its 8 bits
+struct PicturePatch {
+  uint32_t bits;
+  uint32_t pat[4];
+  template <int WORDS>
+  __device__ __forceinline__ void operator()(uint32_t (&w)[WORDS]) const {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2 * k, 1);      // 0 or all ones
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2 * k + 1, 1);
+      if constexpr (WORDS == 8) {
+        w[2 * k] = lo != 0u ? __float_as_uint(widen_lo(pat[k])) : w[2 * k];
+        w[2 * k + 1] = hi != 0u ? __float_as_uint(widen_hi(pat[k])) : w[2 * k + 1];
+      } else {
+        const uint32_t take = (lo & 0x0000FFFFu) | (hi & 0xFFFF0000u);
+        w[k] = (w[k] & ~take) | (pat[k] & take);
+      }
+    }
+  }
+};
 
 // a9 for one row: unpack, dequantise, [patch a few outliers in,] store
-template <int BITS, bool ASYM, bool F32, bool PATCH = false>
-__device__ __forceinline__ void store_row_values(const TensorDesc& d, uint64_t e0, const RowCodes<BITS>& r, uint32_t mail = 0u) {
+template <int BITS, bool ASYM, bool F32, class Patch>
+__device__ __forceinline__ void store_row_values(const TensorDesc& d, uint64_t e0, const RowCodes<BITS>& r, const Patch& patch) {
   int c[kOct];
   if constexpr (BITS == 8) {
 #pragma unroll
@@ -84,7 +120,7 @@ __device__ __forceinline__ void store_row_values(const TensorDesc& d, uint64_t e
     uint32_t w[8];
 #pragma unroll
     for (int e = 0; e < kOct; ++e) w[e] = __float_as_uint(v[e]);
-    if constexpr (PATCH) patch_row_words<8>(w, mail);
+    patch(w);
     float* p = reinterpret_cast<float*>(d.dst) + e0;
     ADACC_STORE16(p, make_uint4(w[0], w[1], w[2], w[3]));
     ADACC_STORE16(p + 4, make_uint4(w[4], w[5], w[6], w[7]));
@@ -92,51 +128,97 @@ __device__ __forceinline__ void store_row_values(const TensorDesc& d, uint64_t e
     uint32_t w[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) w[k] = narrow_pair(v[2 * k], v[2 * k + 1]);
-    if constexpr (PATCH) patch_row_words<4>(w, mail);
+    patch(w);
     ADACC_STORE16(reinterpret_cast<uint16_t*>(d.dst) + e0, make_uint4(w[0], w[1], w[2], w[3]));
   }
 }
 
-// What the kernels that call decompress_tile keep in LDS: a mailbox of one word per octet of a piece for
-// every wavefront of the workgroup.
+// What the kernels that call decompress_piece keep in LDS for every wavefront of the workgroup (17 KiB in all: eight
+// workgroups of a CU, as many as its wavefronts allow, fit).
 struct DecompressShared {
-  uint32_t mailbox[kWavesPerWg][kWave][4];
+  uint4 picture[kWavesPerWg][4 * kWave];  // 16-bit patterns of the piece; its first KiB serves as the mailbox
+  uint32_t bits[kWavesPerWg][kWave];      // byte j of word l: elements of lane l's octet in row j that the picture holds
 };
 
-template <int BITS, bool ASYM, int E, bool F32>
-__device__ __forceinline__ void decompress_tile(const TensorDesc& d, uint32_t tile /* piece */, bool has_outliers,
-                                                DecompressShared& shared) {
-  static_assert(E == 4, "pieces of 2048 elements");
+// floor(x / n) for x < 2^39 with the host's m = ceil(2^64 / n), 1 < n <= 2^11; m = 0 stands for n = 1
+__device__ __forceinline__ uint64_t div_by_magic(uint64_t x, uint64_t m) { return m == 0ull ? x : __umul64hi(x, m); }
+
+// The range [p0, p1) of the stream narrowed to the entries whose index lies in [first, end), or a little more: 64
+// probes at a time.  Ends with at most 64 entries, or when a step no longer takes away a quarter.
+__device__ __forceinline__ void narrow_entries(const TensorDesc& d, uint64_t first, uint64_t end, uint32_t& p0, uint32_t& p1) {
+  const uint32_t lane = (uint32_t)__lane_id();
+  while (p1 - p0 > (uint32_t)kWave) {  // uniform
+    const uint32_t n = p1 - p0, step = (n + (uint32_t)kWave - 1u) / (uint32_t)kWave;
+    const bool probes = lane * step < n;
+    const uint64_t v = probes ? (uint32_t)d.idx[p0 + lane * step] : 0u;
+    // probes ascend: those below `first` and those below `end` are the lowest lanes
+    const uint32_t below = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(probes && v < first));
+    const uint32_t upto = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(probes && v < end));
+    const uint32_t q0 = below != 0u ? p0 + (below - 1u) * step : p0;
+    const uint32_t q1 = upto * step < n ? p0 + upto * step : p1;
+    p0 = q0;
+    p1 = q1 > q0 ? q1 : q0;
+    if (p1 - p0 > n - n / 4u) break;
+  }
+}
+
+template <int BITS, bool ASYM, bool F32, bool GENERIC>
+__device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t piece, bool has_outliers, DecompressShared& shared) {
+  constexpr int E = 4;
   const int lane = (int)__lane_id();
-  const uint64_t tile_base = (uint64_t)tile * (uint64_t)(E * kRow);
-  const uint64_t lane_base = tile_base + (uint64_t)lane * kOct;
-  const bool complete = tile_base + (uint64_t)(E * kRow) <= d.numel;  // uniform; only a tensor's last piece can be short
+  const uint64_t base = (uint64_t)piece * (uint64_t)(E * kRow);
+  const uint64_t lane_base = base + (uint64_t)lane * kOct;
+  const bool complete = base + (uint64_t)(E * kRow) <= d.numel;  // uniform; only a tensor's last piece can be short
+
+  // group of a lane's octet in row j
+  const uint64_t first_oct = (uint64_t)piece * (uint64_t)(E * kWave);
+  uint64_t first_grp = 0ull;    // GENERIC: group of the piece's first octet ...
+  uint32_t oct_in_grp = 0u;     // ... and that octet's number in it
+  if constexpr (GENERIC) {
+    first_grp = div_by_magic(first_oct, d.magic_q);
+    oct_in_grp = (uint32_t)(first_oct - first_grp * (uint64_t)(d.gq >> 3));
+  }
+  auto group = [&](int j) -> uint64_t {
+    if constexpr (GENERIC)
+      return first_grp + (uint64_t)(uint32_t)((float)(oct_in_grp + (uint32_t)lane + (uint32_t)(j * kWave)) * d.recip_q);
+    else return (lane_base + (uint64_t)j * kRow) >> d.lgq;
+  };
 
   // All loads of the piece are issued before anything waits for one of them: a complete piece
   // (every piece but possibly the last) has no branch between them.
   RowCodes<BITS> rc[E];
   if (complete) {
 #pragma unroll
-    for (int j = 0; j < E; ++j) load_row_codes<BITS, ASYM>(d, lane_base + (uint64_t)j * kRow, rc[j]);
+    for (int j = 0; j < E; ++j) load_row_codes<BITS, ASYM>(d, lane_base + (uint64_t)j * kRow, group(j), rc[j]);
   } else {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
       const uint64_t e0 = lane_base + (uint64_t)j * kRow;
-      if (e0 < d.numel) load_row_codes<BITS, ASYM>(d, e0, rc[j]);
+      if (e0 + kOct <= d.numel) load_row_codes<BITS, ASYM>(d, e0, group(j), rc[j]);
     }
   }
 
-  // This tile's slice of the outlier stream and its first 64 entries.  The entries can only be asked for when
-  // the slice is known, a second round trip to memory behind the first - except for TOPK, where the slice of
-  // tile T is [T * k * groups per tile, + k * groups per tile) unless some group held more than k values that
-  // are not finite: there the entries of that slice are asked for at once, together with the tile's offsets,
-  // and are used if the offsets turn out to be those.
+  // The slice of the outlier stream that belongs to the tiles of this piece, and its first 64 entries.  The entries
+  // can only be asked for when the slice is known, a second round trip to memory behind the first - except for TOPK,
+  // where every tile has k entries per group unless some group held more than k values that are not finite: there
+  // the entries of that slice are asked for at once, together with the tiles' offsets, and are used if the offsets
+  // turn out to be those.
+  uint32_t t0 = 0u, t1 = 0u;  // uniform: tile_ptr[t0] .. tile_ptr[t1]
+  if (has_outliers) {
+    if constexpr (GENERIC) {
+      t0 = (uint32_t)div_by_magic(first_oct, d.magic_t);
+      t1 = (uint32_t)div_by_magic(first_oct + (uint64_t)(E * kWave) - 1u, d.magic_t) + 1u;
+      t1 = t1 < d.n_tiles_all ? t1 : d.n_tiles_all;
+    } else {
+      t0 = piece >> d.ptr_shift;  // (a short last group lies inside the last tile)
+      t1 = t0 + 1u;
+    }
+  }
   const bool guess = has_outliers && d.mode == kModeTopk;  // uniform
   uint32_t g0 = 0u, g1 = 0u, o_idx = 0u, o_val = 0u;
   if (guess) {
-    const uint32_t per_tile = d.topk << (d.lgt - d.lgs);
-    g0 = per_tile * (tile >> d.ptr_shift);
-    g1 = g0 + per_tile;
+    g0 = d.per_tile * t0;
+    g1 = d.per_tile * t1;
     g0 = g0 < d.cap ? g0 : d.cap;
     g1 = g1 < d.cap ? g1 : d.cap;
     if (g0 + (uint32_t)lane < g1) {
@@ -146,14 +228,21 @@ __device__ __forceinline__ void decompress_tile(const TensorDesc& d, uint32_t ti
   }
   uint32_t p0 = 0u, p1 = 0u;
   if (has_outliers) {
-    p0 = d.tile_ptr[tile >> d.ptr_shift];
-    p1 = d.tile_ptr[(tile >> d.ptr_shift) + 1];
+    p0 = d.tile_ptr[t0];
+    p1 = d.tile_ptr[t1];
     p0 = p0 < d.cap ? p0 : d.cap;
     p1 = p1 < d.cap ? p1 : d.cap;
     if (p1 < p0) p1 = p0;
   }
+  bool fetched = guess && p0 == g0 && p1 == g1;  // uniform
+  if constexpr (GENERIC) {
+    if (p1 - p0 > (uint32_t)kWave) {  // uniform
+      narrow_entries(d, base, base + (uint64_t)(E * kRow), p0, p1);
+      fetched = false;
+    }
+  }
   const bool patch = p1 > p0;  // uniform over the wavefront
-  if (patch && !(guess && p0 == g0 && p1 == g1)) {  // uniform
+  if (patch && !fetched) {     // uniform
     o_idx = 0u; o_val = 0u;
     if (p0 + (uint32_t)lane < p1) {
       o_idx = (uint32_t)d.idx[p0 + (uint32_t)lane];
@@ -161,51 +250,98 @@ __device__ __forceinline__ void decompress_tile(const TensorDesc& d, uint32_t ti
     }
   }
 
-  // ---- a9: unpack, dequantise, store.  A complete piece whose tile has at most 64 outliers (TOPK tensors:
-  // every piece), no two in one octet, takes them in on the way, in registers: nothing is written twice and
-  // nothing waits for a store.  The stream is ascending, so two entries of one octet are neighbours in it.
-  if (complete && patch && p1 - p0 <= (uint32_t)kWave) {
-    const uint32_t rel = o_idx - (uint32_t)tile_base;  // a tensor that keeps outliers has fewer than 2^31 elements
-    const bool valid = (uint32_t)lane < p1 - p0 && rel < (uint32_t)(E * kRow);  // also: not in a 4096-element tile's other half
-    const uint32_t oct = rel >> 3;
-    const uint32_t prev_oct = (uint32_t)__shfl_up((int)oct, 1, kWave);
-    if (__builtin_amdgcn_ballot_w64(valid && lane != 0 && oct == prev_oct) == 0ull) {  // uniform
-      uint32_t(*box)[E] = shared.mailbox[threadIdx.x / kWave];
+  // ---- a9 / a10: unpack, dequantise, take the outliers in, store
+  if (complete && patch) {
+    const uint32_t w = threadIdx.x / kWave;
+    uint32_t rel = o_idx - (uint32_t)base;  // a tensor that keeps outliers has fewer than 2^31 elements
+    bool valid = (uint32_t)lane < p1 - p0 && rel < (uint32_t)(E * kRow);  // also: not in the tile's other pieces
+    // the stream is ascending, so two entries of one octet are neighbours in it
+    const uint32_t prev_oct = (uint32_t)__shfl_up((int)(rel >> 3), 1, kWave);
+    if (p1 - p0 <= (uint32_t)kWave && __builtin_amdgcn_ballot_w64(valid && lane != 0 && rel >> 3 == prev_oct) == 0ull) {  // uniform
+      uint32_t(*box)[E] = reinterpret_cast<uint32_t(*)[E]>(shared.picture[w]);
       *reinterpret_cast<uint4*>(box[lane]) = make_uint4(0u, 0u, 0u, 0u);
       __builtin_amdgcn_wave_barrier();  // LDS takes a wavefront's accesses in order: nothing may be moved across
-      if (valid) box[oct & 63u][oct >> 6] = kMailFull | ((rel & 7u) << 16) | (o_val & 0xFFFFu);
+      if (valid) box[(rel >> 3) & 63u][rel >> 9] = kMailFull | ((rel & 7u) << 16) | (o_val & 0xFFFFu);
       __builtin_amdgcn_wave_barrier();
       const uint4 mail = *reinterpret_cast<const uint4*>(box[lane]);
       __builtin_amdgcn_wave_barrier();  // the next piece of this wavefront clears the mailbox only after this
       const uint32_t m[E] = {mail.x, mail.y, mail.z, mail.w};
 #pragma unroll
       for (int j = 0; j < E; ++j)
-        store_row_values<BITS, ASYM, F32, true>(d, lane_base + (uint64_t)j * kRow, rc[j], m[j]);
+        store_row_values<BITS, ASYM, F32>(d, lane_base + (uint64_t)j * kRow, rc[j], MailPatch{m[j]});
       return;
     }
-  }
-  if (complete) {
-#pragma unroll
-    for (int j = 0; j < E; ++j) store_row_values<BITS, ASYM, F32>(d, lane_base + (uint64_t)j * kRow, rc[j]);
-  } else {
+    uint16_t* picture = reinterpret_cast<uint16_t*>(shared.picture[w]);
+    shared.bits[w][lane] = 0u;
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t c = p0;;) {  // uniform
+      if (valid) {
+        picture[rel] = (uint16_t)o_val;
+        atomicOr(&shared.bits[w][(rel >> 3) & 63u], 1u << ((rel >> 9) * 8u + (rel & 7u)));
+      }
+      c += (uint32_t)kWave;
+      if (c >= p1) break;
+      valid = c + (uint32_t)lane < p1;
+      if (valid) {
+        rel = (uint32_t)d.idx[c + (uint32_t)lane] - (uint32_t)base;
+        o_val = d.val[c + (uint32_t)lane];
+        valid = rel < (uint32_t)(E * kRow);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t mine = shared.bits[w][lane];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
       const uint64_t e0 = lane_base + (uint64_t)j * kRow;
-      if (e0 < d.numel) store_row_values<BITS, ASYM, F32>(d, e0, rc[j]);
+      PicturePatch pic;
+      pic.bits = (mine >> (8 * j)) & 0xFFu;
+      if (__builtin_amdgcn_ballot_w64(pic.bits != 0u) != 0ull) {  // uniform
+        const uint4 v = shared.picture[w][j * kWave + lane];  // (what no entry was written to is not used)
+        pic.pat[0] = v.x; pic.pat[1] = v.y; pic.pat[2] = v.z; pic.pat[3] = v.w;
+        store_row_values<BITS, ASYM, F32>(d, e0, rc[j], pic);
+      } else {
+        store_row_values<BITS, ASYM, F32>(d, e0, rc[j], NoPatch{});
+      }
     }
+    __builtin_amdgcn_wave_barrier();
+    return;
+  }
+  if (complete) {
+#pragma unroll
+    for (int j = 0; j < E; ++j) store_row_values<BITS, ASYM, F32>(d, lane_base + (uint64_t)j * kRow, rc[j], NoPatch{});
+    return;
   }
 
-  // ---- a10: the outliers overwrite their positions
+  // the tensor's last piece, not complete: whole octets, then what is left of a ragged octet, one by one
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    const uint64_t e0 = lane_base + (uint64_t)j * kRow;
+    if (e0 + kOct <= d.numel) {
+      store_row_values<BITS, ASYM, F32>(d, e0, rc[j], NoPatch{});
+    } else if (e0 < d.numel) {
+      const uint64_t grp = group(j);
+      const float s = d.scales[grp];
+      for (uint64_t i = e0; i < d.numel; ++i) {
+        int code;
+        if constexpr (BITS == 8) code = (int)(int8_t)d.codes[i];
+        else code = ((int)((uint32_t)d.codes[i >> 1] << (28u - 4u * (uint32_t)(i & 1ull)))) >> 28;
+        float v = (float)code * s;
+        if constexpr (ASYM) v = __fmaf_rn((float)code, s, d.zp[grp]);
+        if constexpr (F32) reinterpret_cast<float*>(d.dst)[i] = v;
+        else reinterpret_cast<uint16_t*>(d.dst)[i] = (uint16_t)narrow_pair(v, 0.0f);
+      }
+    }
+  }
+  // its outliers overwrite their positions
   if (patch) {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the stores above are complete
-    const uint64_t piece_end = complete ? tile_base + (uint64_t)(E * kRow) : d.numel;
     for (uint32_t cpos = p0 + (uint32_t)lane; cpos < p1; cpos += kWave) {
       if (cpos >= p0 + (uint32_t)kWave) {  // past the entries fetched at the start
         o_idx = (uint32_t)d.idx[cpos];
         o_val = d.val[cpos];
       }
       const uint64_t i = o_idx;
-      if (i >= tile_base && i < piece_end) {  // a damaged stream must not write outside the piece
+      if (i >= base && i < d.numel) {  // a damaged stream must not write outside the piece
         if constexpr (F32) reinterpret_cast<float*>(d.dst)[i] = widen_lo(o_val);
         else reinterpret_cast<uint16_t*>(d.dst)[i] = (uint16_t)o_val;
       }

@@ -29,6 +29,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
 // adacc::bf16 and adacc::f16 (the same sources compiled twice).
 //   e8: tiles of 8 rows; rowwise: every group inside a row; whole (TOPK): the statistics group is the tile;
 //   rows (TOPK): statistics group = quantisation group, inside a row
+//   generic: groups that the tile kernels do not take
 //   kind: kBatch* of adacc_common.hpp
 //   generic_threads, generic_lds_bytes: workgroup size and dynamic LDS of the fallback kernels (one segment per workgroup;
 //     topk_groups: TOPK over several statistics groups of a segment); compress_generic_fn(fixup): the second launch
@@ -45,7 +46,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   CompressFn compress_fn_abs(uint32_t bits, uint32_t asym, bool e8, bool rowwise);     \
   CompressFn compress_fn_std(uint32_t bits, uint32_t asym, bool e8, bool rowwise);     \
   CompressFn compress_fn_topk(uint32_t bits, uint32_t asym, bool e8, bool whole, bool rows); \
-  DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32);                  \
+  DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic);    \
   BatchCompressFn compress_batch_fn4(int kind);                                        \
   BatchCompressFn compress_batch_fn8(int kind);                                        \
   BatchDecompressFn decompress_batch_fn(bool f32);                                     \
@@ -55,10 +56,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   PlaceBatchFn place_batch_fn();                                                       \
   TailFn compress_tail_fn();                                                           \
   TailBatchFn compress_tail_batch_fn();                                                \
-  TailFn decompress_tail_fn();                                                         \
-  TailBatchFn decompress_tail_batch_fn();                                              \
   CompressFn compress_generic_fn(uint32_t tile_elems, bool fixup);                     \
-  TailFn decompress_generic_fn();                                                      \
   uint32_t generic_threads();                                                          \
   uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups);      \
   ChannelPartialFn channel_partial_fn(bool stream);                                    \

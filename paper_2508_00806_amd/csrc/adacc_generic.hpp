@@ -1,4 +1,4 @@
-// Compression and decompression for methods outside the fast kernels' shapes (Section 3.2 asks for groups
+// Compression for methods outside the fast kernels' shapes (Section 3.2 asks for groups
 // of the activation and treats a tensor of any shape as a flat array; nothing there makes the groups powers
 // of two): quantisation groups of any multiple of 8 elements, statistics groups of any multiple of the
 // quantisation group up to 16384 elements (a whole 11008-wide row as one STD / TOPK group).  The fast
@@ -797,71 +797,6 @@ __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentSha
   }
 }
 
-// a9 / a10 for one segment
-__device__ __forceinline__ void decompress_segment(const TensorDesc& d, uint32_t seg) {
-  const uint32_t tid = threadIdx.x;
-  const uint64_t first_elem = (uint64_t)seg * d.tile_elems;
-  const uint64_t left = d.numel - first_elem;
-  const uint32_t cnt = left < (uint64_t)d.tile_elems ? (uint32_t)left : d.tile_elems;
-  const uint64_t first_group = first_elem / d.gq;
-  // an octet at a time: it lies inside one quantisation group (groups are multiples of 8, the segment starts
-  // on a group), so one scale serves it; what is left of a tensor's ragged end goes one by one
-  const uint32_t octs = cnt / (uint32_t)kOct;
-  for (uint32_t o = tid; o < octs; o += kSegThreads) {
-    const uint64_t e0 = first_elem + (uint64_t)o * kOct;
-    int code[kOct];
-    if (d.bits == 8u) {
-      const uint2 w = *reinterpret_cast<const uint2*>(d.codes + e0);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        code[e] = (int)(int8_t)((w.x >> (8 * e)) & 0xFFu);
-        code[4 + e] = (int)(int8_t)((w.y >> (8 * e)) & 0xFFu);
-      }
-    } else {
-      const uint32_t w = *reinterpret_cast<const uint32_t*>(d.codes + (e0 >> 1));
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) code[e] = ((int)(w << (28 - 4 * e))) >> 28;  // sign-extended nibble
-    }
-    const uint64_t grp = first_group + (o * (uint32_t)kOct) / d.gq;
-    const float s = d.scales[grp];
-    const float z = d.asym ? d.zp[grp] : 0.0f;
-    float v[kOct];
-#pragma unroll
-    for (int e = 0; e < kOct; ++e) v[e] = d.asym ? __fmaf_rn((float)code[e], s, z) : (float)code[e] * s;
-    if (d.dst_f32) {
-      float* p = reinterpret_cast<float*>(d.dst) + e0;
-      *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-      *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
-    } else {
-      *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(d.dst) + e0) =
-          make_uint4(narrow_pair(v[0], v[1]), narrow_pair(v[2], v[3]), narrow_pair(v[4], v[5]), narrow_pair(v[6], v[7]));
-    }
-  }
-  for (uint32_t i = octs * kOct + tid; i < cnt; i += kSegThreads) {
-    int code;
-    if (d.bits == 8u) code = (int)(int8_t)d.codes[first_elem + i];
-    else code = ((int)((uint32_t)d.codes[(first_elem + i) >> 1] << (28u - 4u * (i & 1u)))) >> 28;  // first_elem is even
-    const uint64_t grp = first_group + i / d.gq;
-    const float s = d.scales[grp];
-    const float v = d.asym ? __fmaf_rn((float)code, s, d.zp[grp]) : (float)code * s;
-    if (d.dst_f32) reinterpret_cast<float*>(d.dst)[first_elem + i] = v;
-    else reinterpret_cast<uint16_t*>(d.dst)[first_elem + i] = (uint16_t)narrow_pair(v, 0.0f);
-  }
-  if (d.mode == kModeNone) return;
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's stores above are complete ...
-  __syncthreads();                       // ... and so are those of the other wavefronts of the segment
-  uint32_t p0 = d.tile_ptr[seg], p1 = d.tile_ptr[seg + 1u];
-  p0 = p0 < d.cap ? p0 : d.cap;
-  p1 = p1 < d.cap ? p1 : d.cap;
-  for (uint32_t p = p0 + tid; p < p1; p += kSegThreads) {
-    const uint64_t i = (uint32_t)d.idx[p];
-    if (i < first_elem || i >= first_elem + cnt) continue;  // a damaged stream must not write outside the segment
-    const uint32_t pat = d.val[p];
-    if (d.dst_f32) reinterpret_cast<float*>(d.dst)[i] = widen_lo(pat);
-    else reinterpret_cast<uint16_t*>(d.dst)[i] = (uint16_t)pat;
-  }
-}
-
 // wavefronts per SIMD (= workgroups per CU) the registers are held to: the kernel is a chain of memory and LDS
 // round trips with barriers between, which only other resident workgroups can fill
 template <int SL>
@@ -872,7 +807,6 @@ __global__ __launch_bounds__(kSegThreads, (generic_min_waves<SL>())) void compre
   SegmentShared sh = segment_shared<SL>(segment_lds, d.tile_elems, d.gq);
   compress_segment<SL, FIXUP>(d, sh, blockIdx.x, epoch);
 }
-__global__ __launch_bounds__(kSegThreads) void decompress_generic_kernel(TensorDesc d) { decompress_segment(d, blockIdx.x); }
 
 }  // namespace ADACC_DT_NS
 }  // namespace adacc

@@ -4,13 +4,14 @@
 namespace adacc {
 namespace ADACC_DT_NS {
 
-DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32) {
-  if (bits == 4) {
-    if (asym) return f32 ? decompress_kernel<4, true, true> : decompress_kernel<4, true, false>;
-    return f32 ? decompress_kernel<4, false, true> : decompress_kernel<4, false, false>;
-  }
-  if (asym) return f32 ? decompress_kernel<8, true, true> : decompress_kernel<8, true, false>;
-  return f32 ? decompress_kernel<8, false, true> : decompress_kernel<8, false, false>;
+template <int BITS, bool ASYM>
+static DecompressFn pick(bool f32, bool generic) {
+  if (generic) return f32 ? decompress_kernel<BITS, ASYM, true, true> : decompress_kernel<BITS, ASYM, false, true>;
+  return f32 ? decompress_kernel<BITS, ASYM, true, false> : decompress_kernel<BITS, ASYM, false, false>;
+}
+DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic) {
+  if (bits == 4) return asym ? pick<4, true>(f32, generic) : pick<4, false>(f32, generic);
+  return asym ? pick<8, true>(f32, generic) : pick<8, false>(f32, generic);
 }
 
 BatchDecompressFn decompress_batch_fn(bool f32) {

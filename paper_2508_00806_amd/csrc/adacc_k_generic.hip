@@ -12,7 +12,6 @@ CompressFn compress_generic_fn(uint32_t tile_elems, bool fixup) {
   if (slices <= 6u) return fixup ? compress_generic_kernel<6, true> : compress_generic_kernel<6, false>;
   return fixup ? compress_generic_kernel<8, true> : compress_generic_kernel<8, false>;
 }
-TailFn decompress_generic_fn() { return decompress_generic_kernel; }
 uint32_t generic_threads() { return kSegThreads; }
 uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups) {
   const uint32_t slices = ((tile_elems + 7u) / 8u + kSegThreads - 1u) / kSegThreads;

@@ -206,36 +206,6 @@ __device__ __forceinline__ void compress_tail(const TensorDesc& d, TailShared& s
   }
 }
 
-// a9 / a10 for the tail
-__device__ __forceinline__ void decompress_tail(const TensorDesc& d) {
-  const uint32_t lane = (uint32_t)lane_id();
-  const uint32_t r = d.tail;
-  const uint64_t first_group = d.numel >> d.lgq;
-  for (uint32_t i = lane; i < r; i += kWave) {
-    int code;
-    if (d.bits == 8u) code = (int)(int8_t)d.codes[d.numel + i];
-    else code = ((int)((uint32_t)d.codes[(d.numel >> 1) + (i >> 1)] << (28u - 4u * (i & 1u)))) >> 28;
-    const uint64_t grp = first_group + (i >> d.lgq);
-    const float s = d.scales[grp];
-    const float v = d.asym ? __fmaf_rn((float)code, s, d.zp[grp]) : (float)code * s;
-    if (d.dst_f32) reinterpret_cast<float*>(d.dst)[d.numel + i] = v;
-    else reinterpret_cast<uint16_t*>(d.dst)[d.numel + i] = (uint16_t)narrow_pair(v, 0.0f);
-  }
-  if (d.mode == kModeNone) return;
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the stores above are complete
-  __syncthreads();
-  const uint32_t tile = (uint32_t)(d.numel >> d.lgt);
-  uint32_t p0 = d.tile_ptr[tile], p1 = d.tile_ptr[d.n_tiles_all];
-  p1 = p1 < d.cap ? p1 : d.cap;
-  for (uint32_t p = p0 + lane; p < p1; p += kWave) {
-    const uint64_t i = (uint32_t)d.idx[p];
-    if (i < d.numel || i >= d.numel + r) continue;  // the main part's, or a damaged stream
-    const uint32_t pat = d.val[p];
-    if (d.dst_f32) reinterpret_cast<float*>(d.dst)[i] = widen_lo(pat);
-    else reinterpret_cast<uint16_t*>(d.dst)[i] = (uint16_t)pat;
-  }
-}
-
 __global__ __launch_bounds__(kWave) void compress_tail_kernel(TensorDesc d) {
   __shared__ TailShared sh;
   compress_tail(d, sh);
@@ -245,12 +215,6 @@ __global__ __launch_bounds__(kWave) void compress_tail_batch_kernel(const Tensor
   __shared__ TailShared sh;
   const TensorDesc d = table[members[blockIdx.x]];
   compress_tail(d, sh);
-}
-__global__ __launch_bounds__(kWave) void decompress_tail_kernel(TensorDesc d) { decompress_tail(d); }
-__global__ __launch_bounds__(kWave) void decompress_tail_batch_kernel(const TensorDesc* __restrict__ table,
-                                                                      const uint32_t* __restrict__ members) {
-  const TensorDesc d = table[members[blockIdx.x]];
-  decompress_tail(d);
 }
 
 }  // namespace ADACC_DT_NS
