@@ -488,11 +488,12 @@ static void group_launches(const std::vector<uint32_t>& units, const std::vector
   }
 }
 
-// one wavefront per strip of 512 channels and `rows` tokens, four wavefronts per workgroup
-static uint32_t strip_grid(uint64_t tokens, uint32_t hidden, uint32_t rows) {
-  const uint64_t units = ((tokens + rows - 1) / rows) * ((hidden + 511u) / 512u);
+// one wavefront per strip of `width` channels (512, or 256 for a binary32 output) and `rows` tokens, four per workgroup
+static uint32_t strip_grid(uint64_t tokens, uint32_t hidden, uint32_t rows, uint32_t width = 512u) {
+  const uint64_t units = ((tokens + rows - 1) / rows) * ((hidden + width - 1u) / width);
   return (uint32_t)((units + kWavesPerWg - 1) / kWavesPerWg);  // tokens * hidden < 2^32: far below 2^31
 }
+static uint32_t strip_width(int dst_dtype) { return dst_dtype == ADACC_DST_F32 ? 256u : 512u; }
 
 // ---- outlier channels (Section 3.2, Eq. 1)
 struct ChannelPlan {
@@ -740,9 +741,7 @@ int adacc_compress_noalloc(const adacc_method* method, const void* src, uint64_t
 
 static int launch_decompress(const adacc_method* m, const Plan& p, const TensorDesc& d, int dst_dtype, hipStream_t s) {
   DecompressFn fn = ADACC_PICK(p.half, decompress_fn(m->bits, m->asym, dst_dtype == ADACC_DST_F32, p.generic));
-  uint32_t grid = 0;
-  const int rc = grid_for(d.n_tiles, reinterpret_cast<const void*>(fn), &grid);
-  if (rc != ADACC_OK) return rc;
+  const uint32_t grid = (d.n_tiles + kWavesPerWg - 1) / kWavesPerWg;  // one piece per wavefront
   hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, s, d, p.outliers ? 1u : 0u);
   return launch_check("decompress_kernel");
 }
@@ -1056,7 +1055,7 @@ int adacc_channel_decompress(const adacc_channel_method* method, const void* blo
   ChannelDesc c;
   fill_channel_desc(method, tokens, hidden, L, const_cast<void*>(blob), &c);
   ChannelFn fn = ADACC_PICK(cp.plan.half, channel_decompress_fn(method->bits, method->asym, dst_dtype == ADACC_DST_F32));
-  const uint32_t grid = strip_grid(tokens, hidden, ADACC_PICK(cp.plan.half, channel_strip_rows()));
+  const uint32_t grid = strip_grid(tokens, hidden, ADACC_PICK(cp.plan.half, channel_strip_rows()), strip_width(dst_dtype));
   hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(hip_stream), d, c);
   return launch_check("channel_decompress_kernel");
 }
@@ -1166,7 +1165,7 @@ int adacc_channelwise_decompress(uint32_t bits, uint32_t dtype, const void* blob
   channelwise_desc(bits, 0, tokens, hidden, L, const_cast<void*>(blob), &c);
   c.dst = dst;
   ChannelwiseFn fn = ADACC_PICK(dtype == ADACC_DTYPE_F16, channelwise_dequantise_fn(bits, dst_dtype == ADACC_DST_F32));
-  const uint32_t grid = strip_grid(tokens, hidden, ADACC_PICK(dtype == ADACC_DTYPE_F16, channelwise_strip_rows()));
+  const uint32_t grid = strip_grid(tokens, hidden, ADACC_PICK(dtype == ADACC_DTYPE_F16, channelwise_strip_rows()), strip_width(dst_dtype));
   hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(hip_stream), c);
   return launch_check("channelwise_dequantise_kernel");
 }

@@ -434,37 +434,43 @@ __global__ __launch_bounds__(kThreads) void channel_compress_strip_kernel(Tensor
 }
 
 // ---- decompression: dequantise, put the outlier channels back, store.
-// A wavefront takes a strip of 512 adjacent channels (8 per lane) over kChannelStripRows consecutive tokens:
-// which of a lane's 8 channels are outlier channels, and where their values start in a token's record, is
+// A wavefront takes a strip of 512 adjacent channels (8 per lane; binary32: 256, 4 per lane, see chunk_elems) over
+// kChannelStripRows consecutive tokens: which of a lane's channels are outlier channels, and where their values start in a token's record, is
 // the same for every token, so it is looked up once (no table in LDS, no division per octet).  The loads of
 // four tokens (codes, scale, offset, the first kept value of the octet) are issued before their first store;
 // a second outlier channel in the same octet is rare and fetched when it is needed.
 template <int BITS, bool ASYM, bool F32>
 __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc d, ChannelDesc c) {
+  constexpr int V = chunk_elems<F32>();
+  constexpr uint32_t W = (uint32_t)(kWave * V);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (c.status[1] != 0u) return;  // not a usable blob
   uint32_t n_ch = __builtin_amdgcn_readfirstlane(c.status[0]);
   if (n_ch > c.max_channels) n_ch = c.max_channels;  // a damaged blob must not make the reads leave it
-  const uint32_t strips = (c.hidden + (uint32_t)kRow - 1u) / (uint32_t)kRow;
+  const uint32_t strips = (c.hidden + W - 1u) / W;
   const uint32_t unit = blockIdx.x * kWavesPerWg + wave;
   const uint32_t block = unit / strips;
   const uint32_t row0 = block * kChannelStripRows;
-  const uint32_t col = (unit - block * strips) * (uint32_t)kRow + (uint32_t)lane_id() * kOct;
+  const uint32_t col = (unit - block * strips) * W + (uint32_t)(lane_id() * V);
   if (row0 >= c.tokens || col >= c.hidden) return;
   const uint32_t rows = c.tokens - row0 < kChannelStripRows ? c.tokens - row0 : kChannelStripRows;
 
-  // the lane's 8 channels: which are outlier channels, and the rank of the first of them
+  // the lane's channels: which are outlier channels, and the rank of the first of them
   uint32_t m = 0u, first = 0u;
   if (n_ch != 0u) {
     m = c.mask[col >> 3];
     first = c.base[col >> 3];
+    if constexpr (V == 4) {  // the octet's lower or upper half
+      first += (col & 4u) ? (uint32_t)__popc(m & 0xFu) : 0u;
+      m = (col & 4u) ? m >> 4 : m & 0xFu;
+    }
     if (first >= n_ch) m = 0u;  // a damaged blob must not be read past its end
   }
   const uint32_t lowest = m & (0u - m);
   const uint32_t rest = m ^ lowest;
 
   for (uint32_t r = 0; r < rows; r += 4u) {
-    uint32_t cw[4][2];
+    uint32_t cw[4][V * BITS > 32 ? 2 : 1];
     float sc[4], zp[4];
     uint32_t pre[4];
     const uint16_t* src[4];
@@ -472,12 +478,14 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
     for (uint32_t i = 0; i < 4u; ++i) {  // rows past the end re-read the last one
       const uint32_t row = row0 + (r + i < rows ? r + i : rows - 1u);
       const uint64_t e0 = (uint64_t)row * c.hidden + col;
-      if constexpr (BITS == 8) {
-        const uint2 w = *reinterpret_cast<const uint2*>(d.codes + e0);
+      const uint8_t* p = d.codes + e0 * BITS / 8;
+      if constexpr (V * BITS == 64) {
+        const uint2 w = *reinterpret_cast<const uint2*>(p);
         cw[i][0] = w.x; cw[i][1] = w.y;
+      } else if constexpr (V * BITS == 32) {
+        cw[i][0] = *reinterpret_cast<const uint32_t*>(p);
       } else {
-        cw[i][0] = *reinterpret_cast<const uint32_t*>(d.codes + (e0 >> 1));
-        cw[i][1] = 0u;
+        cw[i][0] = *reinterpret_cast<const uint16_t*>(p);
       }
       const uint64_t grp = e0 >> d.lgq;
       sc[i] = d.scales[grp];
@@ -490,28 +498,19 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
     for (uint32_t i = 0; i < 4u; ++i) {
       if (r + i >= rows) break;
       const uint64_t e0 = (uint64_t)(row0 + r + i) * c.hidden + col;
-      int code[kOct];
-      if constexpr (BITS == 8) {
+      int code[V];
+      unpack_codes<BITS, V>(cw[i], code);
+      float v[V];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          code[e] = (int)(int8_t)((cw[i][0] >> (8 * e)) & 0xFFu);
-          code[4 + e] = (int)(int8_t)((cw[i][1] >> (8 * e)) & 0xFFu);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < kOct; ++e) code[e] = ((int)(cw[i][0] << (28 - 4 * e))) >> 28;
-      }
-      float v[kOct];
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) v[e] = ASYM ? __fmaf_rn((float)code[e], sc[i], zp[i]) : (float)code[e] * sc[i];
+      for (int e = 0; e < V; ++e) v[e] = ASYM ? __fmaf_rn((float)code[e], sc[i], zp[i]) : (float)code[e] * sc[i];
 
       // the kept channels of this octet, as their stored 16-bit patterns (hold[e] valid where keep has bit e)
-      uint32_t keep = lowest, hold[kOct];
+      uint32_t keep = lowest, hold[V];
 #pragma unroll
-      for (int e = 0; e < kOct; ++e) hold[e] = lowest == (1u << e) ? pre[i] : 0u;
+      for (int e = 0; e < V; ++e) hold[e] = lowest == (1u << e) ? pre[i] : 0u;
       if (rest != 0u) {
 #pragma unroll
-        for (int e = 1; e < kOct; ++e)
+        for (int e = 1; e < V; ++e)
           if (rest & (1u << e)) {
             const uint32_t rank = (uint32_t)__popc(m & ((1u << e) - 1u));
             if (rank < n_ch - first) { hold[e] = src[i][rank]; keep |= 1u << e; }
@@ -521,11 +520,10 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
       if constexpr (F32) {
         if (keep != 0u) {
 #pragma unroll
-          for (int e = 0; e < kOct; ++e) v[e] = (keep & (1u << e)) ? widen_lo(hold[e]) : v[e];
+          for (int e = 0; e < V; ++e) v[e] = (keep & (1u << e)) ? widen_lo(hold[e]) : v[e];
         }
         float* p = reinterpret_cast<float*>(d.dst) + e0;
         ADACC_STORE16(p, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
-        ADACC_STORE16(p + 4, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])));
       } else {
         uint32_t w[4];
 #pragma unroll

@@ -8,20 +8,20 @@
 namespace adacc {
 namespace ADACC_DT_NS {
 
-// Decompression always works on pieces of E = 4 rows (2048 elements) of the flat tensor, one per wavefront, whatever
+// Decompression always works on pieces of 2048 elements of the flat tensor, one per wavefront, whatever
 // the tile of the blob and whatever the group sizes: a piece looks through the outliers of the tiles it touches and
 // takes those that fall inside it.
 //
 // A complete piece takes its outliers into the output words in registers before they are stored, so nothing is
 // written twice and nothing waits for a store:
-//   - at most 64 entries, no two of them in the same octet (every piece of a TOPK tensor with few, nearly all others):
-//     the lanes that hold the entries drop them into a mailbox of the wavefront in LDS (one word per octet of the
-//     piece, 1 KiB), every lane picks up the four words of its own octets;
+//   - at most 64 entries, no two of them in the same chunk (every piece of a TOPK tensor with few, nearly all others):
+//     the lanes that hold the entries drop them into a mailbox of the wavefront in LDS (one word per chunk of the
+//     piece), every lane picks up the words of its own chunks;
 //   - otherwise the entries go, 64 at a time, to a picture of the piece in LDS (the 16-bit pattern at the element's
-//     place, and a bit per element that says so); every lane merges its four octets with it.  The picture is not
+//     place, and a bit per element that says so); every lane merges its chunks with it.  The picture is not
 //     cleared, only its bits are.  (Before, such a piece was stored, waited for its own stores and wrote the
 //     outliers over them, 2 or 4 bytes each: 16.8 M values of 2051-element rows with 1 % outliers restored as
-//     binary32 took 31 + 4.5 us with the launch for the short end, 28 us now.)
+//     binary32 took 31 + 4.5 us with the launch for the short end, 18 us now with the chunks below.)
 // The last piece of a tensor, when it is not complete, is stored first; the wavefront waits until those stores have
 // reached the L2 (its store counter at zero), and then stores the outliers of the piece to their positions.
 //
@@ -30,46 +30,66 @@ namespace ADACC_DT_NS {
 // the binary32 one (exact below 4096 octets).  The entries of the piece are found by a 64-way search where the
 // tile holds more than a wavefront looks at once.  (A workgroup per tile, as the compression has it, went through
 // a row of 11008 values in 5.4 rounds with a barrier before the outliers: [8192, 11008], int4, 70 us; 43 us now.)
-// One row (512 elements, 8 per lane) of a piece: codes and scale (offset) of the lane's octet.
-template <int BITS>
+// What a lane takes at a time ("chunk"): as many consecutive elements as one 16-byte store holds, V = 8 of a 16-bit
+// output and V = 4 of a binary32 one, so that every store instruction of a wavefront covers 1 KiB without gaps.  A row
+// is the 64 chunks of one such instruction; a piece has 4 resp. 8 rows.  (With octets for both, a lane wrote its 32
+// bytes of binary32 in two stores 32 bytes apart from its neighbour's: 49.5 M values of int8 codes took 68 .. 74 us,
+// 3.4 TB/s; 46 us now, 5.3 TB/s.)
+constexpr int kPiece = 2048;
+template <bool F32>
+constexpr int chunk_elems() { return F32 ? 4 : 8; }
+
+template <int BITS, int V>
 struct RowCodes {
-  uint32_t w[BITS == 8 ? 2 : 1];
+  uint32_t w[V * BITS > 32 ? 2 : 1];
   float s, o;
 };
 
-// grp: the quantisation group of the lane's octet
-template <int BITS, bool ASYM>
-__device__ __forceinline__ void load_row_codes(const TensorDesc& d, uint64_t e0, uint64_t grp, RowCodes<BITS>& r) {
-  if constexpr (BITS == 8) {
-    const uint2 w = *reinterpret_cast<const uint2*>(d.codes + e0);
+// grp: the quantisation group of the lane's chunk
+template <int BITS, int V, bool ASYM>
+__device__ __forceinline__ void load_row_codes(const TensorDesc& d, uint64_t e0, uint64_t grp, RowCodes<BITS, V>& r) {
+  const uint8_t* p = d.codes + e0 * BITS / 8;
+  if constexpr (V * BITS == 64) {
+    const uint2 w = *reinterpret_cast<const uint2*>(p);
     r.w[0] = w.x; r.w[1] = w.y;
+  } else if constexpr (V * BITS == 32) {
+    r.w[0] = *reinterpret_cast<const uint32_t*>(p);
   } else {
-    r.w[0] = *reinterpret_cast<const uint32_t*>(d.codes + (e0 >> 1));
+    r.w[0] = *reinterpret_cast<const uint16_t*>(p);
   }
   r.s = d.scales[grp];
   r.o = 0.0f;
   if constexpr (ASYM) r.o = d.zp[grp];
 }
 
+// the codes of a chunk, sign-extended
+template <int BITS, int V>
+__device__ __forceinline__ void unpack_codes(const uint32_t (&w)[V * BITS > 32 ? 2 : 1], int (&c)[V]) {
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    if constexpr (BITS == 8) c[e] = (int)(int8_t)((w[e >> 2] >> (8 * (e & 3))) & 0xFFu);
+    else c[e] = ((int)(w[0] << (28 - 4 * e))) >> 28;
+  }
+}
+
 // What goes over the dequantised values of a row before they are stored.
 struct NoPatch {
-  template <int WORDS>
-  __device__ __forceinline__ void operator()(uint32_t (&)[WORDS]) const {}
+  __device__ __forceinline__ void words(uint32_t (&)[4]) const {}
 };
-// What a lane finds in the mailbox for one of its octets: 0, or bit 31 set, the element (0..7) in bits 16..18
-// and the outlier's 16-bit pattern in the low half.  WORDS = 4 (two 16-bit values per word) or 8 (binary32).
+// What a lane finds in the mailbox for one of its chunks: 0, or bit 31 set, the element (0 .. V - 1) in bits 16..18
+// and the outlier's 16-bit pattern in the low half.
 constexpr uint32_t kMailFull = 0x80000000u;
+template <bool F32>
 struct MailPatch {
   uint32_t mail;
-  template <int WORDS>
-  __device__ __forceinline__ void operator()(uint32_t (&w)[WORDS]) const {
+  __device__ __forceinline__ void words(uint32_t (&w)[4]) const {
     const bool mine = mail != 0u;
     const uint32_t e = (mail >> 16) & 7u;
     const uint32_t pat = mail & 0xFFFFu;
-    if constexpr (WORDS == 8) {
+    if constexpr (F32) {
       const uint32_t bits = __float_as_uint(widen_lo(pat));
 #pragma unroll
-      for (int k = 0; k < 8; ++k) w[k] = (mine && e == (uint32_t)k) ? bits : w[k];
+      for (int k = 0; k < 4; ++k) w[k] = (mine && e == (uint32_t)k) ? bits : w[k];
     } else {
       const uint32_t keep = (e & 1u) ? 0x0000FFFFu : 0xFFFF0000u;
       const uint32_t put = (e & 1u) ? pat << 16 : pat;
@@ -78,17 +98,17 @@ struct MailPatch {
     }
   }
 };
-// The octet of the picture in LDS and its 8 bits
+// The chunk of the picture in LDS (16-bit patterns, two per word) and its V bits
+template <bool F32>
 struct PicturePatch {
   uint32_t bits;
-  uint32_t pat[4];
-  template <int WORDS>
-  __device__ __forceinline__ void operator()(uint32_t (&w)[WORDS]) const {
+  uint32_t pat[F32 ? 2 : 4];
+  __device__ __forceinline__ void words(uint32_t (&w)[4]) const {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < (F32 ? 2 : 4); ++k) {
       const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2 * k, 1);      // 0 or all ones
       const uint32_t hi = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2 * k + 1, 1);
-      if constexpr (WORDS == 8) {
+      if constexpr (F32) {
         w[2 * k] = lo != 0u ? __float_as_uint(widen_lo(pat[k])) : w[2 * k];
         w[2 * k + 1] = hi != 0u ? __float_as_uint(widen_hi(pat[k])) : w[2 * k + 1];
       } else {
@@ -99,45 +119,32 @@ struct PicturePatch {
   }
 };
 
-// a9 for one row: unpack, dequantise, [patch a few outliers in,] store
+// a9 for one row: unpack, dequantise, [patch outliers in,] store
 template <int BITS, bool ASYM, bool F32, class Patch>
-__device__ __forceinline__ void store_row_values(const TensorDesc& d, uint64_t e0, const RowCodes<BITS>& r, const Patch& patch) {
-  int c[kOct];
-  if constexpr (BITS == 8) {
+__device__ __forceinline__ void store_row_values(const TensorDesc& d, uint64_t e0, const RowCodes<BITS, chunk_elems<F32>()>& r,
+                                                 const Patch& patch) {
+  constexpr int V = chunk_elems<F32>();
+  int c[V];
+  unpack_codes<BITS, V>(r.w, c);
+  float v[V];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      c[e] = (int)(int8_t)((r.w[0] >> (8 * e)) & 0xFFu);
-      c[4 + e] = (int)(int8_t)((r.w[1] >> (8 * e)) & 0xFFu);
-    }
-  } else {
+  for (int e = 0; e < V; ++e) v[e] = ASYM ? __fmaf_rn((float)c[e], r.s, r.o) : (float)c[e] * r.s;
+  uint32_t w[4];
 #pragma unroll
-    for (int e = 0; e < kOct; ++e) c[e] = ((int)(r.w[0] << (28 - 4 * e))) >> 28;  // sign-extended nibble
+  for (int k = 0; k < 4; ++k) {
+    if constexpr (F32) w[k] = __float_as_uint(v[k]);
+    else w[k] = narrow_pair(v[2 * k], v[2 * k + 1]);
   }
-  float v[kOct];
-#pragma unroll
-  for (int e = 0; e < kOct; ++e) v[e] = ASYM ? __fmaf_rn((float)c[e], r.s, r.o) : (float)c[e] * r.s;
-  if constexpr (F32) {
-    uint32_t w[8];
-#pragma unroll
-    for (int e = 0; e < kOct; ++e) w[e] = __float_as_uint(v[e]);
-    patch(w);
-    float* p = reinterpret_cast<float*>(d.dst) + e0;
-    ADACC_STORE16(p, make_uint4(w[0], w[1], w[2], w[3]));
-    ADACC_STORE16(p + 4, make_uint4(w[4], w[5], w[6], w[7]));
-  } else {
-    uint32_t w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] = narrow_pair(v[2 * k], v[2 * k + 1]);
-    patch(w);
-    ADACC_STORE16(reinterpret_cast<uint16_t*>(d.dst) + e0, make_uint4(w[0], w[1], w[2], w[3]));
-  }
+  patch.words(w);
+  if constexpr (F32) ADACC_STORE16(reinterpret_cast<float*>(d.dst) + e0, make_uint4(w[0], w[1], w[2], w[3]));
+  else ADACC_STORE16(reinterpret_cast<uint16_t*>(d.dst) + e0, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
 // What the kernels that call decompress_piece keep in LDS for every wavefront of the workgroup (17 KiB in all: eight
 // workgroups of a CU, as many as its wavefronts allow, fit).
 struct DecompressShared {
-  uint4 picture[kWavesPerWg][4 * kWave];  // 16-bit patterns of the piece; its first KiB serves as the mailbox
-  uint32_t bits[kWavesPerWg][kWave];      // byte j of word l: elements of lane l's octet in row j that the picture holds
+  uint4 picture[kWavesPerWg][kPiece / 8];  // 16-bit patterns of the piece; its first 1 or 2 KiB serve as the mailbox
+  uint32_t bits[kWavesPerWg][kWave];       // V bits per row: elements of lane l's chunk in that row that the picture holds
 };
 
 // floor(x / n) for x < 2^39 with the host's m = ceil(2^64 / n), 1 < n <= 2^11; m = 0 stands for n = 1
@@ -164,14 +171,14 @@ __device__ __forceinline__ void narrow_entries(const TensorDesc& d, uint64_t fir
 
 template <int BITS, bool ASYM, bool F32, bool GENERIC>
 __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t piece, bool has_outliers, DecompressShared& shared) {
-  constexpr int E = 4;
+  constexpr int V = chunk_elems<F32>(), E = kPiece / (kWave * V), W = kWave * V;  // W: elements of a row
   const int lane = (int)__lane_id();
-  const uint64_t base = (uint64_t)piece * (uint64_t)(E * kRow);
-  const uint64_t lane_base = base + (uint64_t)lane * kOct;
-  const bool complete = base + (uint64_t)(E * kRow) <= d.numel;  // uniform; only a tensor's last piece can be short
+  const uint64_t base = (uint64_t)piece * (uint64_t)kPiece;
+  const uint64_t lane_base = base + (uint64_t)(lane * V);
+  const bool complete = base + (uint64_t)kPiece <= d.numel;  // uniform; only a tensor's last piece can be short
 
-  // group of a lane's octet in row j
-  const uint64_t first_oct = (uint64_t)piece * (uint64_t)(E * kWave);
+  // group of a lane's chunk in row j
+  const uint64_t first_oct = (uint64_t)piece * (uint64_t)(kPiece / kOct);
   uint64_t first_grp = 0ull;    // GENERIC: group of the piece's first octet ...
   uint32_t oct_in_grp = 0u;     // ... and that octet's number in it
   if constexpr (GENERIC) {
@@ -180,21 +187,21 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
   }
   auto group = [&](int j) -> uint64_t {
     if constexpr (GENERIC)
-      return first_grp + (uint64_t)(uint32_t)((float)(oct_in_grp + (uint32_t)lane + (uint32_t)(j * kWave)) * d.recip_q);
-    else return (lane_base + (uint64_t)j * kRow) >> d.lgq;
+      return first_grp + (uint64_t)(uint32_t)((float)(oct_in_grp + ((uint32_t)(lane * V + j * W) >> 3)) * d.recip_q);
+    else return (lane_base + (uint64_t)(j * W)) >> d.lgq;
   };
 
   // All loads of the piece are issued before anything waits for one of them: a complete piece
   // (every piece but possibly the last) has no branch between them.
-  RowCodes<BITS> rc[E];
+  RowCodes<BITS, V> rc[E];
   if (complete) {
 #pragma unroll
-    for (int j = 0; j < E; ++j) load_row_codes<BITS, ASYM>(d, lane_base + (uint64_t)j * kRow, group(j), rc[j]);
+    for (int j = 0; j < E; ++j) load_row_codes<BITS, V, ASYM>(d, lane_base + (uint64_t)(j * W), group(j), rc[j]);
   } else {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const uint64_t e0 = lane_base + (uint64_t)j * kRow;
-      if (e0 + kOct <= d.numel) load_row_codes<BITS, ASYM>(d, e0, group(j), rc[j]);
+      const uint64_t e0 = lane_base + (uint64_t)(j * W);
+      if (e0 + V <= d.numel) load_row_codes<BITS, V, ASYM>(d, e0, group(j), rc[j]);
     }
   }
 
@@ -207,7 +214,7 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
   if (has_outliers) {
     if constexpr (GENERIC) {
       t0 = (uint32_t)div_by_magic(first_oct, d.magic_t);
-      t1 = (uint32_t)div_by_magic(first_oct + (uint64_t)(E * kWave) - 1u, d.magic_t) + 1u;
+      t1 = (uint32_t)div_by_magic(first_oct + (uint64_t)(kPiece / kOct) - 1u, d.magic_t) + 1u;
       t1 = t1 < d.n_tiles_all ? t1 : d.n_tiles_all;
     } else {
       t0 = piece >> d.ptr_shift;  // (a short last group lies inside the last tile)
@@ -237,7 +244,7 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
   bool fetched = guess && p0 == g0 && p1 == g1;  // uniform
   if constexpr (GENERIC) {
     if (p1 - p0 > (uint32_t)kWave) {  // uniform
-      narrow_entries(d, base, base + (uint64_t)(E * kRow), p0, p1);
+      narrow_entries(d, base, base + (uint64_t)kPiece, p0, p1);
       fetched = false;
     }
   }
@@ -254,21 +261,27 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
   if (complete && patch) {
     const uint32_t w = threadIdx.x / kWave;
     uint32_t rel = o_idx - (uint32_t)base;  // a tensor that keeps outliers has fewer than 2^31 elements
-    bool valid = (uint32_t)lane < p1 - p0 && rel < (uint32_t)(E * kRow);  // also: not in the tile's other pieces
-    // the stream is ascending, so two entries of one octet are neighbours in it
-    const uint32_t prev_oct = (uint32_t)__shfl_up((int)(rel >> 3), 1, kWave);
-    if (p1 - p0 <= (uint32_t)kWave && __builtin_amdgcn_ballot_w64(valid && lane != 0 && rel >> 3 == prev_oct) == 0ull) {  // uniform
+    bool valid = (uint32_t)lane < p1 - p0 && rel < (uint32_t)kPiece;  // also: not in the tile's other pieces
+    // the stream is ascending, so two entries of one chunk are neighbours in it
+    const uint32_t prev = (uint32_t)__shfl_up((int)(rel / V), 1, kWave);
+    if (p1 - p0 <= (uint32_t)kWave && __builtin_amdgcn_ballot_w64(valid && lane != 0 && rel / V == prev) == 0ull) {  // uniform
       uint32_t(*box)[E] = reinterpret_cast<uint32_t(*)[E]>(shared.picture[w]);
-      *reinterpret_cast<uint4*>(box[lane]) = make_uint4(0u, 0u, 0u, 0u);
+      uint4* mine = reinterpret_cast<uint4*>(box[lane]);
+#pragma unroll
+      for (int i = 0; i < E / 4; ++i) mine[i] = make_uint4(0u, 0u, 0u, 0u);
       __builtin_amdgcn_wave_barrier();  // LDS takes a wavefront's accesses in order: nothing may be moved across
-      if (valid) box[(rel >> 3) & 63u][rel >> 9] = kMailFull | ((rel & 7u) << 16) | (o_val & 0xFFFFu);
+      if (valid) box[(rel / V) & 63u][rel / W] = kMailFull | ((rel % V) << 16) | (o_val & 0xFFFFu);
       __builtin_amdgcn_wave_barrier();
-      const uint4 mail = *reinterpret_cast<const uint4*>(box[lane]);
+      uint32_t m[E];
+#pragma unroll
+      for (int i = 0; i < E / 4; ++i) {
+        const uint4 mail = mine[i];
+        m[4 * i] = mail.x; m[4 * i + 1] = mail.y; m[4 * i + 2] = mail.z; m[4 * i + 3] = mail.w;
+      }
       __builtin_amdgcn_wave_barrier();  // the next piece of this wavefront clears the mailbox only after this
-      const uint32_t m[E] = {mail.x, mail.y, mail.z, mail.w};
 #pragma unroll
       for (int j = 0; j < E; ++j)
-        store_row_values<BITS, ASYM, F32>(d, lane_base + (uint64_t)j * kRow, rc[j], MailPatch{m[j]});
+        store_row_values<BITS, ASYM, F32>(d, lane_base + (uint64_t)(j * W), rc[j], MailPatch<F32>{m[j]});
       return;
     }
     uint16_t* picture = reinterpret_cast<uint16_t*>(shared.picture[w]);
@@ -277,7 +290,7 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
     for (uint32_t c = p0;;) {  // uniform
       if (valid) {
         picture[rel] = (uint16_t)o_val;
-        atomicOr(&shared.bits[w][(rel >> 3) & 63u], 1u << ((rel >> 9) * 8u + (rel & 7u)));
+        atomicOr(&shared.bits[w][(rel / V) & 63u], 1u << (rel / W * V + rel % V));
       }
       c += (uint32_t)kWave;
       if (c >= p1) break;
@@ -285,19 +298,25 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
       if (valid) {
         rel = (uint32_t)d.idx[c + (uint32_t)lane] - (uint32_t)base;
         o_val = d.val[c + (uint32_t)lane];
-        valid = rel < (uint32_t)(E * kRow);
+        valid = rel < (uint32_t)kPiece;
       }
     }
     __builtin_amdgcn_wave_barrier();
     const uint32_t mine = shared.bits[w][lane];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const uint64_t e0 = lane_base + (uint64_t)j * kRow;
-      PicturePatch pic;
-      pic.bits = (mine >> (8 * j)) & 0xFFu;
+      const uint64_t e0 = lane_base + (uint64_t)(j * W);
+      PicturePatch<F32> pic;
+      pic.bits = (mine >> (V * j)) & ((1u << V) - 1u);
       if (__builtin_amdgcn_ballot_w64(pic.bits != 0u) != 0ull) {  // uniform
-        const uint4 v = shared.picture[w][j * kWave + lane];  // (what no entry was written to is not used)
-        pic.pat[0] = v.x; pic.pat[1] = v.y; pic.pat[2] = v.z; pic.pat[3] = v.w;
+        // (what no entry was written to is not used)
+        if constexpr (F32) {
+          const uint2 v = reinterpret_cast<const uint2*>(shared.picture[w])[j * kWave + lane];
+          pic.pat[0] = v.x; pic.pat[1] = v.y;
+        } else {
+          const uint4 v = shared.picture[w][j * kWave + lane];
+          pic.pat[0] = v.x; pic.pat[1] = v.y; pic.pat[2] = v.z; pic.pat[3] = v.w;
+        }
         store_row_values<BITS, ASYM, F32>(d, e0, rc[j], pic);
       } else {
         store_row_values<BITS, ASYM, F32>(d, e0, rc[j], NoPatch{});
@@ -308,15 +327,15 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
   }
   if (complete) {
 #pragma unroll
-    for (int j = 0; j < E; ++j) store_row_values<BITS, ASYM, F32>(d, lane_base + (uint64_t)j * kRow, rc[j], NoPatch{});
+    for (int j = 0; j < E; ++j) store_row_values<BITS, ASYM, F32>(d, lane_base + (uint64_t)(j * W), rc[j], NoPatch{});
     return;
   }
 
-  // the tensor's last piece, not complete: whole octets, then what is left of a ragged octet, one by one
+  // the tensor's last piece, not complete: whole chunks, then what is left of a ragged one, element by element
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    const uint64_t e0 = lane_base + (uint64_t)j * kRow;
-    if (e0 + kOct <= d.numel) {
+    const uint64_t e0 = lane_base + (uint64_t)(j * W);
+    if (e0 + V <= d.numel) {
       store_row_values<BITS, ASYM, F32>(d, e0, rc[j], NoPatch{});
     } else if (e0 < d.numel) {
       const uint64_t grp = group(j);

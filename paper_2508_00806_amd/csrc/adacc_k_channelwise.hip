@@ -129,14 +129,17 @@ struct Strip {
   uint32_t rows;   // tokens of the strip (the last block of tokens may be short)
   bool live;
 };
+// V: channels per lane (8, or 4 for a binary32 output: one 16-byte access per token either way), strips of 64 * V
+template <int V>
 __device__ __forceinline__ Strip strip_of(const ChannelwiseDesc& c) {
+  constexpr uint32_t W = (uint32_t)(kWave * V);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint32_t strips = (c.hidden + (uint32_t)kRow - 1u) / (uint32_t)kRow;
+  const uint32_t strips = (c.hidden + W - 1u) / W;
   const uint32_t unit = blockIdx.x * kWavesPerWg + wave;
   const uint32_t block = unit / strips;
   const uint32_t row0 = block * kStripRows;
   Strip s;
-  s.col = (unit - block * strips) * (uint32_t)kRow + (uint32_t)lane_id() * kOct;
+  s.col = (unit - block * strips) * W + (uint32_t)(lane_id() * V);
   s.live = row0 < c.tokens && s.col < c.hidden;
   s.rows = s.live ? (c.tokens - row0 < kStripRows ? c.tokens - row0 : kStripRows) : 0u;
   s.first = (size_t)row0 * c.hidden + s.col;
@@ -147,7 +150,7 @@ __device__ __forceinline__ Strip strip_of(const ChannelwiseDesc& c) {
 template <int BITS>
 __global__ __launch_bounds__(kThreads) void channelwise_quantise_kernel(ChannelwiseDesc c) {
   constexpr int Q = 1 << (BITS - 1);
-  const Strip s = strip_of(c);
+  const Strip s = strip_of<kOct>(c);
   if (!s.live) return;
   const float4 i0 = *reinterpret_cast<const float4*>(c.inv + s.col);
   const float4 i1 = *reinterpret_cast<const float4*>(c.inv + s.col + 4);
@@ -183,51 +186,48 @@ __global__ __launch_bounds__(kThreads) void channelwise_quantise_kernel(Channelw
   }
 }
 
-// ---- decompression: X^ = code * S_h
+// ---- decompression: X^ = code * S_h.  Binary32: 4 channels per lane (see chunk_elems)
 template <int BITS, bool F32>
 __global__ __launch_bounds__(kThreads) void channelwise_dequantise_kernel(ChannelwiseDesc c) {
-  const Strip s = strip_of(c);
+  constexpr int V = chunk_elems<F32>();
+  const Strip s = strip_of<V>(c);
   if (!s.live) return;
-  const float4 s0 = *reinterpret_cast<const float4*>(c.scales + s.col);
-  const float4 s1 = *reinterpret_cast<const float4*>(c.scales + s.col + 4);
-  const float sc[kOct] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+  float sc[V];
+#pragma unroll
+  for (int k = 0; k < V; k += 4) {
+    const float4 f = *reinterpret_cast<const float4*>(c.scales + s.col + k);
+    sc[k] = f.x; sc[k + 1] = f.y; sc[k + 2] = f.z; sc[k + 3] = f.w;
+  }
   for (uint32_t r = 0; r < s.rows; r += 4u) {
-    uint32_t cw[4][2];
+    uint32_t cw[4][V * BITS > 32 ? 2 : 1];
 #pragma unroll
     for (uint32_t i = 0; i < 4u; ++i) {
       const uint32_t row = r + i < s.rows ? r + i : s.rows - 1u;
-      const size_t e0 = s.first + (size_t)row * c.hidden;
-      if constexpr (BITS == 8) {
-        const uint2 w = *reinterpret_cast<const uint2*>(c.codes + e0);
+      const uint8_t* p = c.codes + (s.first + (size_t)row * c.hidden) * BITS / 8;
+      if constexpr (V * BITS == 64) {
+        const uint2 w = *reinterpret_cast<const uint2*>(p);
         cw[i][0] = w.x; cw[i][1] = w.y;
+      } else if constexpr (V * BITS == 32) {
+        cw[i][0] = *reinterpret_cast<const uint32_t*>(p);
       } else {
-        cw[i][0] = *reinterpret_cast<const uint32_t*>(c.codes + (e0 >> 1));
-        cw[i][1] = 0u;
+        cw[i][0] = *reinterpret_cast<const uint16_t*>(p);
       }
     }
 #pragma unroll
     for (uint32_t i = 0; i < 4u; ++i) {
       if (r + i >= s.rows) break;
       const size_t e0 = s.first + (size_t)(r + i) * c.hidden;
-      float v[kOct];
+      int code[V];
+      unpack_codes<BITS, V>(cw[i], code);
+      float v[V];
 #pragma unroll
-      for (int e = 0; e < kOct; ++e) {
-        int code;
-        if constexpr (BITS == 8) code = (int)(int8_t)((cw[i][e >> 2] >> (8 * (e & 3))) & 0xFFu);
-        else code = ((int)(cw[i][0] << (28 - 4 * e))) >> 28;
-        v[e] = (float)code * sc[e];
-      }
+      for (int e = 0; e < V; ++e) v[e] = (float)code[e] * sc[e];
       if constexpr (F32) {
-        float* p = reinterpret_cast<float*>(c.dst) + e0;
-        ADACC_STORE16(p, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
-        ADACC_STORE16(p + 4, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])));
+        ADACC_STORE16(reinterpret_cast<float*>(c.dst) + e0,
+                      make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
       } else {
-        uint4 w;
-        w.x = narrow_pair(v[0], v[1]);
-        w.y = narrow_pair(v[2], v[3]);
-        w.z = narrow_pair(v[4], v[5]);
-        w.w = narrow_pair(v[6], v[7]);
-        ADACC_STORE16(reinterpret_cast<uint16_t*>(c.dst) + e0, w);
+        ADACC_STORE16(reinterpret_cast<uint16_t*>(c.dst) + e0,
+                      make_uint4(narrow_pair(v[0], v[1]), narrow_pair(v[2], v[3]), narrow_pair(v[4], v[5]), narrow_pair(v[6], v[7])));
       }
     }
   }

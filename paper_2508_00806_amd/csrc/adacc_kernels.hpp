@@ -38,11 +38,11 @@ __device__ __forceinline__ bool topk_whole(const TensorDesc& d) { return d.lgs =
 
 // d.n_tiles counts pieces of 2048 elements here
 template <int BITS, bool ASYM, bool F32, bool GENERIC>
-__global__ __launch_bounds__(kThreads, 8) void decompress_kernel(TensorDesc d, uint32_t has_outliers) {
+__global__ __launch_bounds__(kThreads) void decompress_kernel(TensorDesc d, uint32_t has_outliers) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
   __shared__ DecompressShared shared;
-  for (uint32_t t = blockIdx.x * kWavesPerWg + wave; t < d.n_tiles; t += gridDim.x * kWavesPerWg)
-    decompress_piece<BITS, ASYM, F32, GENERIC>(d, t, has_outliers != 0u, shared);
+  const uint32_t piece = blockIdx.x * kWavesPerWg + wave;  // (no loop over pieces: it would cost 20 registers)
+  if (piece < d.n_tiles) decompress_piece<BITS, ASYM, F32, GENERIC>(d, piece, has_outliers != 0u, shared);
 }
 
 // ---- batch
