@@ -269,7 +269,7 @@ static float reciprocal_up(uint32_t n) {
 // Workspace of one tensor that keeps outliers: [cnt: one word per tile][flag][block_sum][slots],
 // block sums and slots for ABS / STD only.  Offsets relative to the tensor's region.
 struct WsPlan { uint64_t cnt_off, flag_off, block_sum_off, slot_off, bytes; };
-static uint32_t place_blocks(const Plan& p) { return p.outliers ? (p.n_tiles + kPlaceTiles - 1) / kPlaceTiles : 0u; }
+static uint32_t blocks_of(uint32_t n, int per) { return (n + (uint32_t)per - 1u) / (uint32_t)per; }
 static WsPlan ws_plan(const adacc_method* m, const Plan& p) {
   WsPlan w;
   std::memset(&w, 0, sizeof w);
@@ -278,16 +278,25 @@ static WsPlan ws_plan(const adacc_method* m, const Plan& p) {
   w.cnt_off = off;  off = align256(off + 4ull * p.n_tiles);
   w.flag_off = off; off += 256;
   if (m->outlier_mode != ADACC_OUTLIER_TOPK) {
-    w.block_sum_off = off; off = align256(off + 4ull * place_blocks(p));
-    w.slot_off = off; off = align256(off + 8ull * kSlot * p.n_tiles);
+    w.block_sum_off = off; off = align256(off + 4ull * blocks_of(p.n_tiles, kSumTiles));
+    w.slot_off = off; off = align256(off + 4ull * kSlot * p.n_tiles);
   }
   w.bytes = off;
   return w;
 }
 // does the placement of this tensor start from per-block sums (a kernel of its own computes them)?
 static bool needs_block_sums(const adacc_method* m, const Plan& p) {
-  return p.outliers && m->outlier_mode != ADACC_OUTLIER_TOPK && place_blocks(p) > kPlaceDirectBlocks;
+  return p.outliers && m->outlier_mode != ADACC_OUTLIER_TOPK && p.n_tiles > kPlaceDirectTiles;
 }
+// workgroups of the placement: one per kPlaceTiles tiles (kSumTiles of a long tensor), one more for the end that the
+// groups do not divide
+static uint32_t place_grid(const adacc_method* m, const Plan& p) {
+  if (!p.outliers) return 0u;
+  if (p.generic) return blocks_of(p.n_tiles, kPlaceSegments);
+  return blocks_of(p.n_tiles, needs_block_sums(m, p) ? kSumTiles : kPlaceTiles) + (p.tail != 0 ? 1u : 0u);
+}
+// wavefronts of the tile launch: one per tile, one more for the end of a tensor without outliers
+static uint32_t tile_waves(const Plan& p) { return p.n_tiles + (!p.outliers && p.tail != 0 ? 1u : 0u); }
 
 static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, const adacc_layout& L, const void* src,
                       void* blob, void* dst, int dst_dtype, void* ws_region, TensorDesc* d) {
@@ -308,7 +317,7 @@ static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, cons
     d->cnt = reinterpret_cast<uint32_t*>(r + w.cnt_off);
     d->flag = reinterpret_cast<uint32_t*>(r + w.flag_off);
     d->block_sum = reinterpret_cast<uint32_t*>(r + w.block_sum_off);
-    d->slot = reinterpret_cast<uint2*>(r + w.slot_off);
+    d->slot = reinterpret_cast<uint32_t*>(r + w.slot_off);
   }
   d->numel = p.numel_main;
   d->tail = p.tail;
@@ -321,7 +330,7 @@ static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, cons
   d->gs = (m->outlier_mode == ADACC_OUTLIER_STD || m->outlier_mode == ADACC_OUTLIER_TOPK) ? m->stat_group : m->quant_group;
   d->tile_elems = p.tile_elems;
   d->generic = p.generic ? 1u : 0u;
-  d->n_blocks = place_blocks(p);
+  d->from_sums = needs_block_sums(m, p) ? 1u : 0u;
   d->lgt = p.tile_elems == 4096 ? 12u : 11u;
   if (dst) {  // decompression counts pieces of 2048 elements of the whole tensor
     d->numel = numel;
@@ -613,28 +622,26 @@ int adacc_workspace_init(adacc_workspace* ws, void* device_mem, uint64_t bytes, 
   return ADACC_OK;
 }
 
-// The fallback kernels for one tensor: count, offsets, then everything (one launch without outliers).
+// The tiles' counts in blocks, where the placement starts from those.
+static int launch_block_sums(const adacc_method* method, const Plan& p, const TensorDesc& d, hipStream_t s) {
+  if (!needs_block_sums(method, p)) return ADACC_OK;
+  hipLaunchKernelGGL(ADACC_PICK(p.half, place_sum_fn()), dim3(blocks_of(p.n_tiles, kSumTiles)), dim3(kPlaceThreads), 0, s, d);
+  return launch_check("place_sum_kernel");
+}
+
+// The fallback kernels for one tensor: everything but the places of the outliers, then those.
 static int launch_generic_compress(const adacc_method* method, const Plan& p, const TensorDesc& d, uint32_t epoch,
                                    hipStream_t s) {
-  int rc = ADACC_OK;
   const bool topk = method->outlier_mode == ADACC_OUTLIER_TOPK;
   const uint32_t lds = ADACC_PICK(p.half, generic_lds_bytes(p.tile_elems, method->quant_group, topk && d.gs < p.tile_elems));
   const uint32_t threads = ADACC_PICK(p.half, generic_threads());
   hipLaunchKernelGGL(ADACC_PICK(p.half, compress_generic_fn(p.tile_elems, false)), dim3(p.n_tiles), dim3(threads), lds, s, d, epoch);
-  rc = launch_check("compress_generic_kernel");
+  int rc = launch_check("compress_generic_kernel");
   if (rc != ADACC_OK || !p.outliers) return rc;
-  if (needs_block_sums(method, p)) {
-    hipLaunchKernelGGL(ADACC_PICK(p.half, place_sum_fn()), dim3(d.n_blocks), dim3(kPlaceThreads), 0, s, d);
-    rc = launch_check("place_sum_kernel");
-    if (rc != ADACC_OK) return rc;
-  }
-  hipLaunchKernelGGL(ADACC_PICK(p.half, place_fn()), dim3(d.n_blocks), dim3(kPlaceThreads), 0, s, d, epoch);
-  rc = launch_check("place_kernel");
+  rc = launch_block_sums(method, p, d, s);
   if (rc != ADACC_OK) return rc;
-  // segments whose outliers the first launch could not place (more than a slot holds; TOPK: some group with
-  // another count than k): every other workgroup of this launch leaves at once
-  hipLaunchKernelGGL(ADACC_PICK(p.half, compress_generic_fn(p.tile_elems, true)), dim3(p.n_tiles), dim3(threads), lds, s, d, epoch);
-  return launch_check("compress_generic_kernel (outliers again)");
+  hipLaunchKernelGGL(ADACC_PICK(p.half, compress_generic_fn(p.tile_elems, true)), dim3(place_grid(method, p)), dim3(threads), lds, s, d, epoch);
+  return launch_check("place_generic_kernel");
 }
 
 static int compress_one(const adacc_method* method, const void* src, uint64_t numel, void* blob, uint64_t blob_bytes,
@@ -669,30 +676,22 @@ static int compress_one(const adacc_method* method, const void* src, uint64_t nu
     return launch_generic_compress(method, p, d, epoch, s);
   }
   CompressFn fn = compress_fn(method, p.tile_elems == 4096, p.rowwise || topk_in_rows(method, p), topk_whole_tile(method, p));
-  const uint32_t grid = (p.n_tiles + kWavesPerWg - 1) / kWavesPerWg;  // one tile per wavefront
+  const uint32_t grid = blocks_of(tile_waves(p), kWavesPerWg);  // one tile per wavefront
   uint32_t epoch = 0;
   if (p.outliers) {
     rc = next_epoch(ws, s, &epoch);
     if (rc != ADACC_OK) return rc;
   }
-  if (p.n_tiles != 0) {
+  if (grid != 0) {
     hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, s, d, epoch);
     rc = launch_check("compress_kernel");
     if (rc != ADACC_OK) return rc;
-    if (p.outliers) {
-      if (needs_block_sums(method, p)) {
-        hipLaunchKernelGGL(ADACC_PICK(p.half, place_sum_fn()), dim3(d.n_blocks), dim3(kPlaceThreads), 0, s, d);
-        rc = launch_check("place_sum_kernel");
-        if (rc != ADACC_OK) return rc;
-      }
-      hipLaunchKernelGGL(ADACC_PICK(p.half, place_fn()), dim3(d.n_blocks), dim3(kPlaceThreads), 0, s, d, epoch);
-      rc = launch_check("place_kernel");
-      if (rc != ADACC_OK) return rc;
-    }
   }
-  if (p.tail != 0) {  // after the placement: the tail's outliers go behind those of the main part
-    hipLaunchKernelGGL(ADACC_PICK(p.half, compress_tail_fn()), dim3(1), dim3(kWave), 0, s, d);
-    rc = launch_check("compress_tail_kernel");
+  if (p.outliers) {
+    rc = launch_block_sums(method, p, d, s);
+    if (rc != ADACC_OK) return rc;
+    hipLaunchKernelGGL(ADACC_PICK(p.half, place_fn()), dim3(place_grid(method, p)), dim3(kPlaceThreads), 0, s, d, epoch);
+    rc = launch_check("place_kernel");
   }
   return rc;
 }
@@ -846,10 +845,10 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
   const uint32_t nt = (uint32_t)descs.size();
   std::vector<uint32_t> units(nt), members;
   std::vector<int> kind(nt);
-  std::vector<GroupLaunch> tiles, sums, places, tails;
+  std::vector<GroupLaunch> tiles, sums, places;
   // (tensors that go through the fallback kernels are launched one by one, after the others)
   for (uint32_t i = 0; i < nt; ++i) {
-    units[i] = descs[i].generic ? 0u : descs[i].n_tiles;
+    units[i] = descs[i].generic ? 0u : tile_waves(plans[origin[i]]);
     kind[i] = batch_kind(&methods[origin[i]], plans[origin[i]]) + (plans[origin[i]].half ? kBatchKinds : 0);
   }
   group_launches(units, kind, &members, &tiles);
@@ -863,14 +862,12 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
   for (uint32_t i = 0; i < nt; ++i)
     if (place[i] == 0xFFFFFFFFu) { place[i] = (uint32_t)ordered.size(); ordered.push_back(descs[i]); }
   for (uint32_t i = 0; i < nt; ++i) {
-    units[i] = (!descs[i].generic && needs_block_sums(&methods[origin[i]], plans[origin[i]])) ? descs[i].n_blocks : 0u;
+    units[i] = (!descs[i].generic && needs_block_sums(&methods[origin[i]], plans[origin[i]])) ? blocks_of(descs[i].n_tiles, kSumTiles) : 0u;
     kind[i] = plans[origin[i]].half ? kBatchKinds : 0;
   }
   group_launches(units, kind, &members, &sums);
-  for (uint32_t i = 0; i < nt; ++i) units[i] = descs[i].generic ? 0u : descs[i].n_blocks;
+  for (uint32_t i = 0; i < nt; ++i) units[i] = descs[i].generic ? 0u : place_grid(&methods[origin[i]], plans[origin[i]]);
   group_launches(units, kind, &members, &places);
-  for (uint32_t i = 0; i < nt; ++i) units[i] = descs[i].tail != 0u ? 1u : 0u;
-  group_launches(units, kind, &members, &tails);
   for (uint32_t j = n_listed; j < (uint32_t)members.size(); ++j) members[j] = place[members[j]];
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   uint32_t epoch = 0;
@@ -895,10 +892,6 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
                        dm + g.first_member, epoch);
   rc = launch_check("place_batch_kernel");
   if (rc != ADACC_OK) return rc;
-  for (const GroupLaunch& g : tails)  // one workgroup per tensor that has a tail, after the placement
-    hipLaunchKernelGGL(ADACC_PICK(g.kind >= kBatchKinds, compress_tail_batch_fn()), dim3(g.n_members), dim3(kWave), 0, s, dt,
-                       dm + g.first_member);
-  rc = launch_check("compress_tail_batch_kernel");
   for (uint32_t i = 0; i < nt && rc == ADACC_OK; ++i)
     if (descs[i].generic) rc = launch_generic_compress(&methods[origin[i]], plans[origin[i]], descs[i], epoch, s);
   return rc;

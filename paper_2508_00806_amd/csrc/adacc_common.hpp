@@ -82,22 +82,22 @@ struct TensorDesc {
   uint16_t* val;
   uint32_t* status;
   uint32_t* cnt;            // compress, workspace: outliers found in every tile
-  uint32_t* block_sum;      // compress, workspace (ABS / STD): outliers in every block of kPlaceTiles tiles
-  uint2* slot;              // compress, workspace (ABS / STD): kSlot records (index, value) per tile, the tile's
-                            //   outliers until the placement kernel has moved them to the stream
+  uint32_t* block_sum;      // compress, workspace (ABS / STD): outliers in every block of kSumTiles tiles
+  uint32_t* slot;           // compress, workspace (ABS / STD): kSlot records (number in the tile << 16 | value) per
+                            //   tile, the tile's outliers until the placement kernel has moved them to the stream
   uint32_t* flag;           // compress, workspace (TOPK): set to the epoch by a tile whose count is not the regular one
   uint64_t numel;           // compress: elements the tile kernels take, the whole groups of the larger kind; decompress: all
   uint64_t magic_q, magic_t;  // decompress, fallback: ceil(2^64 / n) for the octets of a quantisation group resp. a tile (0: n = 1)
   float recip_q;            // decompress, fallback: 1 / octets of a quantisation group, moved up (see group_of)
   uint32_t per_tile;        // decompress, TOPK: outliers of a regular tile
-  uint32_t tail;            // compress: elements after numel (fewer than the larger group), done by the tail kernels
+  uint32_t tail;            // compress: elements after numel (fewer than the larger group): one short group
   uint32_t n_tiles;         // tiles of the first numel elements (decompress: pieces of 2048 of them)
   uint32_t n_tiles_all;     // tiles of the whole tensor, tail included: tile_ptr has one entry more
   uint32_t bits, asym, mode;  // the method, for kernels that do not get it as template arguments
   uint32_t gq, gs;          // group sizes as numbers (the fallback kernels take groups that are no powers of two)
   uint32_t tile_elems;      // elements per tile of the blob
   uint32_t generic;         // 1: the method goes through the fallback kernels
-  uint32_t n_blocks;        // compress: blocks of kPlaceTiles tiles (placement kernels)
+  uint32_t from_sums;       // compress: 1 = the placement starts from block_sum (a kernel of its own forms them)
   uint32_t lgt;             // log2(elements per tile): 11 or 12
   uint32_t lgq;         // log2(quant group)
   uint32_t lgs;         // log2(stat group) (STD / TOPK)
@@ -145,12 +145,19 @@ struct ChannelwiseDesc {
 
 // Outliers of a tile that travel through the tile's slot in the workspace (ABS / STD); a tile with
 // more is selected a second time by the placement kernel.
-constexpr int kSlot = 32;
-// The placement kernels: a workgroup of kPlaceThreads threads takes kPlaceTiles consecutive tiles, one per thread.
+constexpr int kSlot = 64;
+// The placement kernels: a workgroup of kPlaceThreads threads takes kPlaceTiles consecutive tiles, or kPlaceSegments
+// segments of the fallback kernels (which the whole workgroup selects again where a slot does not do).
 constexpr int kPlaceThreads = 256;
-constexpr int kPlaceTiles = 256;
-// Tensors of at most this many blocks do without the kernel that adds up the blocks' counts.
-constexpr uint32_t kPlaceDirectBlocks = 8;
+constexpr int kPlaceTiles = 64;
+constexpr int kPlaceSegments = 16;
+// Tensors of more tiles than this add their counts up in blocks of kSumTiles first, in a kernel of its own, and a
+// workgroup of the placement takes such a block.  Below, every workgroup adds up all counts before its own: at most
+// four rounds of eight loads of 16 bytes per thread, about as long as that launch (4.5 us).  (Blocks of 64 tiles
+// behind the sums: 524288 tiles with an outlier each take 24.6 us, 8192 workgroups of which a CU holds four; blocks of
+// 256 10.8 us, where a thread per record and a bisection took 14.1.)
+constexpr int kSumTiles = 256;
+constexpr uint32_t kPlaceDirectTiles = 32768;
 // The workspace's launch counter ("epoch", kept on the host in adacc_workspace) marks what a launch
 // wrote: a word that holds an older epoch reads as not set, so nothing has to be cleared per call.
 constexpr uint32_t kEpochMax = 0x3FFFFFFFu;

@@ -431,11 +431,12 @@ struct StreamSink {
     val[pos] = (uint16_t)bits;
   }
 };
-// ... or of a tile's slot in the workspace (one 8-byte record per entry: index, value) ...
+// ... or of a tile's slot in the workspace (one word per entry: the element's number in the tile, its pattern) ...
 struct SlotSink {
-  uint2* rec;
+  uint32_t* rec;
+  uint32_t first;  // index of the tile's first element
   __device__ __forceinline__ void operator()(uint32_t pos, uint32_t index, uint32_t bits) const {
-    rec[pos] = make_uint2(index, bits);
+    rec[pos] = ((index - first) << 16) | bits;
   }
 };
 // ... or nowhere (tiles without outliers)
@@ -1334,7 +1335,7 @@ __device__ __forceinline__ void compress_tile_outliers(const TensorDesc& d, uint
       }
     }
   } else {
-    const SlotSink sink{d.slot + (uint64_t)tile * (uint64_t)kSlot};
+    const SlotSink sink{d.slot + (uint64_t)tile * (uint64_t)kSlot, tile * (uint32_t)(E * kRow)};
     uint32_t total;
     if (!last) {
       load_tile<E, true>(d, tile, raw);
@@ -1350,19 +1351,22 @@ __device__ __forceinline__ void compress_tile_outliers(const TensorDesc& d, uint
 }
 
 // ------------------------------------------------------------------ placement of the outliers (a4)
-// One workgroup of kPlaceThreads threads takes a block of kPlaceTiles consecutive tiles, one per
-// thread.  It needs the number of outliers in all tiles before its block: for ABS / STD a kernel in
-// between (place_sum_block) has added up the counts of every block, and the workgroup adds those
-// sums; for short tensors, and for TOPK (where this kernel has work only if some group was
-// irregular), it adds the counts themselves.  Nobody waits for anybody.  Then it scans the counts of
-// its own tiles, writes their offsets, and moves the outliers of its tiles from the slots to their
-// final positions, output position by output position (coalesced stores; the tile of a position is
-// found by bisection over the block's offsets in LDS).  Tiles that hold more outliers than a slot
-// takes (or all tiles, `reselect_all`) are selected again from the source, one wavefront per tile,
-// and written straight to the stream.
+// One workgroup of kPlaceThreads threads takes kPlaceTiles consecutive tiles (kPlaceSegments of the fallback kernels'
+// segments; kSumTiles tiles of a long tensor).  It needs the number of outliers in all tiles before them: a workgroup
+// adds up the counts itself, or, for a long tensor, the sums of blocks of kSumTiles counts that a kernel in between has
+// formed.  Nobody waits for anybody.  Every wavefront then scans counts, a lane per tile, and moves the outliers of its
+// share of the tiles from the slots to their final positions, a lane per record.  Tiles that hold more outliers than a slot takes (or all tiles,
+// `reselect_all`) are selected again from the source, one wavefront per tile, and written straight to the stream.
+// (Bound by round trips to memory and by how few workgroups there are: with 256 tiles to a workgroup, a thread per
+// output position found by bisection and slots of 32 records, 8203 tiles of 20 outliers took 17.8 us on 33
+// workgroups, and 4.5 us for the sums, 6.5 us now; the two-byte index in the tile makes a record one word, so that a slot of 256 bytes
+// holds 64: 37 tiles of 4096 values with 35 outliers each were all selected again, 25.6 us, 5.5 us now.)
 struct PlaceShared {
-  uint32_t excl[kPlaceTiles + 1];  // offsets of the block's tiles relative to the block, and the block total
   uint32_t part[kPlaceThreads / kWave];
+  uint32_t window[kPlaceThreads / kWave];
+};
+struct PlaceListShared : PlaceShared {
+  uint16_t list[kPlaceThreads / kWave][kWave * kSlot];  // 8 KiB per wavefront: every slot of a window full
 };
 
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
@@ -1388,30 +1392,44 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t (&part)[k
   return s;
 }
 
-// sum of n 32-bit words (16-byte aligned) over the workgroup; four loads of 16 bytes per thread are
-// in flight at a time
-__device__ __forceinline__ uint32_t sum_words(const uint32_t* words, uint32_t n, uint32_t (&part)[kPlaceThreads / kWave]) {
+// this thread's share of the sum of n 32-bit words (16-byte aligned); eight loads of 16 bytes per thread are in flight
+// at a time
+__device__ __forceinline__ uint32_t sum_share(const uint32_t* words, uint32_t n) {
   const uint4* w4 = reinterpret_cast<const uint4*>(words);
   const uint32_t n4 = n / 4u;
   uint32_t acc = 0u;
-  for (uint32_t i0 = 0u; i0 < n4; i0 += 4u * (uint32_t)kPlaceThreads) {
-    uint4 v[4];
+  for (uint32_t i0 = 0u; i0 < n4; i0 += 8u * (uint32_t)kPlaceThreads) {
+    uint4 v[8];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < 8; ++k) {
       const uint32_t i = i0 + (uint32_t)k * (uint32_t)kPlaceThreads + threadIdx.x;
       v[k] = i < n4 ? w4[i] : make_uint4(0u, 0u, 0u, 0u);
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc += (v[k].x + v[k].y) + (v[k].z + v[k].w);
+    for (int k = 0; k < 8; ++k) acc += (v[k].x + v[k].y) + (v[k].z + v[k].w);
   }
   if (threadIdx.x < (n & 3u)) acc += words[4u * n4 + threadIdx.x];
-  return block_sum_u32(acc, part);
+  return acc;
+}
+
+// outliers in the first `tiles` tiles, to every thread of the workgroup
+__device__ __forceinline__ uint32_t outliers_before(const TensorDesc& d, uint32_t tiles, bool from_sums, PlaceShared& sh) {
+  uint32_t acc;
+  if (from_sums) {  // uniform
+    const uint32_t blocks = tiles / (uint32_t)kSumTiles;
+    const uint32_t t = blocks * (uint32_t)kSumTiles + threadIdx.x;  // kSumTiles = kPlaceThreads
+    acc = sum_share(d.block_sum, blocks) + (t < tiles ? d.cnt[t] : 0u);
+  } else {
+    acc = sum_share(d.cnt, tiles);
+  }
+  return block_sum_u32(acc, sh.part);
 }
 
 // block_sum[block] = outliers in the block's tiles
-__device__ __forceinline__ void place_sum_block(const TensorDesc& d, uint32_t block, uint32_t (&part)[kPlaceThreads / kWave]) {
-  const uint32_t t = block * (uint32_t)kPlaceTiles + threadIdx.x;
-  const uint32_t s = block_sum_u32(t < d.n_tiles ? d.cnt[t] : 0u, part);
+__device__ __forceinline__ void place_sum_block(const TensorDesc& d, uint32_t block, PlaceShared& sh) {
+  static_assert(kSumTiles == kPlaceThreads, "a thread per tile");
+  const uint32_t t = block * (uint32_t)kSumTiles + threadIdx.x;
+  const uint32_t s = block_sum_u32(t < d.n_tiles ? d.cnt[t] : 0u, sh.part);
   if (threadIdx.x == 0) d.block_sum[block] = s;
 }
 
@@ -1428,120 +1446,126 @@ __device__ __forceinline__ void reselect_tile(const TensorDesc& d, uint32_t tile
   encode_tile<MODE, 8, false, E, ROWWISE, WHOLE, false>(d, g, raw, tile, StreamSink{d.idx, d.val}, pos, end < d.cap ? end : d.cap);
 }
 
-// The offsets of a block's tiles from the counts: tile_ptr for the block's tiles, and in the block that holds the
-// last tile the total and the overflow flag.  Leaves in sh.excl the offsets relative to the block (and the
-// block's total behind them).  Returns the number of outliers before the block; n_here: tiles of the block.
-// `from_sums`: the counts of the blocks are in d.block_sum (else the counts of the tiles are added up)
-// mine: outliers of this thread's tile
-__device__ __forceinline__ uint32_t place_offsets_block(const TensorDesc& d, uint32_t block, bool from_sums, PlaceShared& sh,
-                                                        uint32_t& n_here, uint32_t& total, uint32_t& mine) {
-  const uint32_t tid = threadIdx.x;
-  const uint32_t first = block * (uint32_t)kPlaceTiles;
-  // outliers of all tiles before this block
-  const uint32_t base = from_sums ? sum_words(d.block_sum, block, sh.part) : sum_words(d.cnt, first, sh.part);
-  // this thread's tile
-  const uint32_t t = first + tid;
-  const uint32_t c = t < d.n_tiles ? d.cnt[t] : 0u;
-  mine = c;
-  // exclusive scan over the workgroup: inside the wavefront by shuffles, across wavefronts through LDS
-  uint32_t incl = c;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t up = (uint32_t)__shfl_up((int)incl, off);
-    if (lane_id() >= off) incl += up;
-  }
-  const uint32_t wave = tid / kWave;
-  __syncthreads();
-  if (lane_id() == kWave - 1) sh.part[wave] = incl;
-  __syncthreads();
-  uint32_t wave_before = 0u;
-  total = 0u;
-#pragma unroll
-  for (int i = 0; i < kPlaceThreads / kWave; ++i) {
-    wave_before += (uint32_t)i < wave ? sh.part[i] : 0u;
-    total += sh.part[i];
-  }
-  const uint32_t e0 = wave_before + incl - c;  // relative to the block
-  sh.excl[tid] = e0;
-  if (tid == 0) sh.excl[kPlaceTiles] = total;
-  if (t < d.n_tiles) d.tile_ptr[t] = base + e0;
-  n_here = d.n_tiles - first < (uint32_t)kPlaceTiles ? d.n_tiles - first : (uint32_t)kPlaceTiles;
-  if (first + n_here == d.n_tiles && tid == 0) {  // the block that holds the last tile also closes the blob
-    const uint32_t n_out = base + total;
-    d.tile_ptr[d.n_tiles] = n_out;
-    d.status[0] = n_out; d.status[1] = n_out > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u;
-  }
-  return base;
-}
+// What a wavefront of the placement knows of a window of up to 64 tiles (lane j: tile first + j)
+struct PlacedTiles {
+  uint32_t first, n_here;  // uniform
+  uint32_t base;           // uniform: outliers of all tiles before the window
+  uint32_t count, excl;    // outliers of the lane's tile, and of the window's tiles before it
+};
 
-// The offsets of a block's tiles, and the outliers of its tiles from the slots to the stream: four positions per
-// thread at a time, so that their loads overlap.  Tiles with more outliers than a slot takes are left out.
-// Returns the number of outliers before the block; n_here: tiles of the block.  `move`: false = offsets only
-__device__ __forceinline__ uint32_t place_moves_block(const TensorDesc& d, uint32_t block, bool from_sums, bool move,
-                                                      PlaceShared& sh, uint32_t& n_here, uint32_t& mine) {
-  const uint32_t tid = threadIdx.x;
-  const uint32_t first = block * (uint32_t)kPlaceTiles;
-  uint32_t total;
-  const uint32_t base = place_offsets_block(d, block, from_sums, sh, n_here, total, mine);
-  __syncthreads();
-  if (move) {
-    for (uint32_t p0 = 0u; p0 < total; p0 += 4u * (uint32_t)kPlaceThreads) {
-      uint64_t src[4];
-      uint32_t dst[4];
-      bool ok[4];
-      // last tile j with excl[j] <= p (tiles without outliers share their successor's offset): the four
-      // bisections step together, so that a step is one round trip to LDS for all of them (a block has at
-      // most 2^8 tiles)
-      uint32_t lo[4], hi[4];
+// The offsets of TILES tiles from the counts: tile_ptr, and by the workgroup that holds the last tile the total and the
+// overflow flag (unless elements behind the last tile still have to be added, then those do it).  `move`: the records
+// of tiles that fit their slot go to the stream.  TILES <= 64: the window of all wavefronts is the workgroup's tiles,
+// each moves its share; TILES = 256: a window per wavefront.
+template <int TILES, class Shared>
+__device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t block, bool from_sums, bool move, Shared& sh) {
+  constexpr bool OWN = TILES > kWave;  // a window per wavefront
+  constexpr int WINDOW = OWN ? kWave : TILES;
+  constexpr int WAVES = kPlaceThreads / kWave;
+  static_assert(!OWN || TILES == WAVES * kWave, "a lane per tile");
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  PlacedTiles p;
+  const uint32_t first = block * (uint32_t)TILES;
+  p.first = first + (OWN ? wave * (uint32_t)kWave : 0u);
+  const uint32_t left = p.first < d.n_tiles ? d.n_tiles - p.first : 0u;
+  p.n_here = left < (uint32_t)WINDOW ? left : (uint32_t)WINDOW;
+  p.count = lane < p.n_here ? d.cnt[p.first + lane] : 0u;  // (asked for ahead of the sums)
+  if constexpr (OWN) {
+    const uint32_t mine = wave_sum_u32(p.count);
+    if (lane == 0u) sh.window[wave] = mine;  // (read behind the barriers of outliers_before)
+  }
+  p.base = outliers_before(d, first, from_sums, sh);
+  if constexpr (OWN) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { lo[k] = 0u; hi[k] = n_here; }
+    for (int w = 0; w < WAVES - 1; ++w) p.base += (uint32_t)w < wave ? sh.window[w] : 0u;
+  }
+  uint32_t incl = p.count;
 #pragma unroll
-      for (int step = 0; step < 8; ++step) {
-        uint32_t mid[4], at[4];
+  for (int off = 1; off < WINDOW; off <<= 1) {
+    const uint32_t up = (uint32_t)__shfl_up((int)incl, off);
+    if (lane >= (uint32_t)off) incl += up;
+  }
+  p.excl = incl - p.count;
+  if ((OWN || wave == 0u) && p.n_here != 0u) {  // uniform
+    if (lane < p.n_here) d.tile_ptr[p.first + lane] = p.base + p.excl;
+    if (p.first + p.n_here == d.n_tiles && lane == p.n_here - 1u) {  // the blob's last tile closes it
+      const uint32_t n_out = p.base + incl;
+      if (d.n_tiles_all > d.n_tiles || d.tail == 0u) d.tile_ptr[d.n_tiles] = n_out;
+      if (d.tail == 0u) { d.status[0] = n_out; d.status[1] = n_out > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u; }
+    }
+  }
+  if (move && __builtin_amdgcn_ballot_w64(p.count != 0u) != 0ull) {  // uniform
+    if constexpr (OWN) {
+      // Long tensors, where few tiles may have any: a list of the window's records in LDS (tile and number in its
+      // slot), written by the lanes of the tiles, then a lane per record.
+      const uint32_t in_slot = p.count <= (uint32_t)kSlot ? p.count : 0u;
+      uint32_t at = p.excl, total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+      if (__builtin_amdgcn_ballot_w64(p.count > (uint32_t)kSlot) != 0ull) {  // rare: the records' numbers without such tiles
+        uint32_t sum = in_slot;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { mid[k] = (lo[k] + hi[k]) >> 1; at[k] = sh.excl[mid[k]]; }
+        for (int off = 1; off < kWave; off <<= 1) {
+          const uint32_t up = (uint32_t)__shfl_up((int)sum, off);
+          if (lane >= (uint32_t)off) sum += up;
+        }
+        at = sum - in_slot;
+        total = (uint32_t)__builtin_amdgcn_readlane((int)sum, kWave - 1);
+      }
+      uint16_t* list = sh.list[wave];
+      for (uint32_t k = 0; __builtin_amdgcn_ballot_w64(k < in_slot) != 0ull; ++k)  // at most kSlot rounds
+        if (k < in_slot) list[at + k] = (uint16_t)(lane << 8 | k);
+      __builtin_amdgcn_wave_barrier();  // LDS takes a wavefront's accesses in order
+      for (uint32_t r0 = 0u; r0 < total; r0 += 4u * (uint32_t)kWave) {  // uniform
+        uint32_t rec[4], pos[4], tile[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t p = p0 + (uint32_t)k * (uint32_t)kPlaceThreads + tid;
-          if (hi[k] - lo[k] > 1u) {
-            if (at[k] <= p) lo[k] = mid[k]; else hi[k] = mid[k];
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t r = r0 + (uint32_t)(i * kWave) + lane;
+          const uint32_t e = r < total ? list[r] : 0u;
+          tile[i] = e >> 8;
+          pos[i] = p.base + (uint32_t)__shfl((int)p.excl, (int)tile[i]) + (e & 0xFFu);
+          rec[i] = d.slot[(uint64_t)(p.first + tile[i]) * (uint64_t)kSlot + (e & 0xFFu)];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (r0 + (uint32_t)(i * kWave) + lane < total && pos[i] < d.cap) {
+            d.idx[pos[i]] = (int32_t)((p.first + tile[i]) * d.tile_elems + (rec[i] >> 16));
+            d.val[pos[i]] = (uint16_t)rec[i];
           }
         }
       }
+    } else {
+      // a lane per record, the loads of all tiles of this wavefront in flight at once
+      constexpr int PER = TILES / WAVES;
+      const uint32_t j0 = wave * (uint32_t)PER;
+      uint32_t rec[PER];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t p = p0 + (uint32_t)k * (uint32_t)kPlaceThreads + tid;
-        const uint32_t n_tile = sh.excl[lo[k] + 1u] - sh.excl[lo[k]];
-        dst[k] = base + p;
-        ok[k] = p < total && n_tile <= (uint32_t)kSlot && dst[k] < d.cap;
-        src[k] = ok[k] ? (uint64_t)(first + lo[k]) * (uint64_t)kSlot + (p - sh.excl[lo[k]]) : 0ull;
+      for (int i = 0; i < PER; ++i) {  // a lane without a record reads a tile's first word
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j0 + i);
+        const uint32_t t = j0 + (uint32_t)i < p.n_here ? p.first + j0 + (uint32_t)i : p.first;
+        rec[i] = d.slot[(uint64_t)t * (uint64_t)kSlot + (lane < n ? lane : 0u)];
       }
-      uint2 rec[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) rec[k] = d.slot[src[k]];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (ok[k]) { d.idx[dst[k]] = (int32_t)rec[k].x; d.val[dst[k]] = (uint16_t)rec[k].y; }
+      for (int i = 0; i < PER; ++i) {
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j0 + i);
+        const uint32_t pos = p.base + (uint32_t)__builtin_amdgcn_readlane((int)p.excl, (int)j0 + i) + lane;
+        if (n <= (uint32_t)kSlot && lane < n && pos < d.cap) {
+          d.idx[pos] = (int32_t)((p.first + j0 + (uint32_t)i) * d.tile_elems + (rec[i] >> 16));
+          d.val[pos] = (uint16_t)rec[i];
+        }
       }
     }
   }
-  return base;
+  return p;
 }
 
+// the tiles of the window whose outliers are not (all) in a slot: once more from the source, by this wavefront those
+// from `j` on in steps of `step`
 template <int MODE, int E, bool ROWWISE, bool WHOLE>
-__device__ __forceinline__ void place_block(const TensorDesc& d, uint32_t block, bool from_sums, bool reselect_all,
-                                            PlaceShared& sh) {
-  const uint32_t tid = threadIdx.x;
-  const uint32_t first = block * (uint32_t)kPlaceTiles;
-  uint32_t n_here, mine;
-  const uint32_t base = place_moves_block(d, block, from_sums, !reselect_all, sh, n_here, mine);
-  // tiles whose outliers are not (all) in a slot: once more from the source, a wavefront per tile
-  if (__syncthreads_or(mine > (reselect_all ? 0u : (uint32_t)kSlot) ? 1 : 0) == 0) return;  // the usual case: none
-  const uint32_t w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  for (uint32_t j = w; j < n_here; j += (uint32_t)(kPlaceThreads / kWave)) {
-    const uint32_t n_tile = sh.excl[j + 1u] - sh.excl[j];
-    if (n_tile > (reselect_all ? 0u : (uint32_t)kSlot))
-      reselect_tile<MODE, E, ROWWISE, WHOLE>(d, first + j, base + sh.excl[j], n_tile);
+__device__ __forceinline__ void reselect_tiles(const TensorDesc& d, const PlacedTiles& p, uint32_t room, uint32_t j, uint32_t step) {
+  for (; j < p.n_here; j += step) {
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j);
+    if (n > room)
+      reselect_tile<MODE, E, ROWWISE, WHOLE>(d, p.first + j, p.base + (uint32_t)__builtin_amdgcn_readlane((int)p.excl, (int)j), n);
   }
 }
 
@@ -1561,6 +1585,87 @@ __device__ __forceinline__ void compress_tile_plain(const TensorDesc& d, uint32_
   if (tile == 0 && lane_id() == 0) {
     d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u;
   }
+}
+
+// The end of a tensor without outliers that its groups do not divide: d.tail elements behind d.numel, one short group,
+// by one wavefront of the same launch.  (A launch of its own behind the tiles': 4.5 us.)
+template <int BITS, bool ASYM>
+__device__ __forceinline__ void compress_plain_tail(const TensorDesc& d) {
+  constexpr int Q = 1 << (BITS - 1);
+  constexpr uint32_t kRound = 4u * (uint32_t)kRow;  // four octets per lane at a time, at most two rounds
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint16_t* sp = d.src + d.numel;
+  uint32_t raw[4][4];
+  auto load = [&](uint32_t i0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t i = i0 + (uint32_t)(j * kRow) + lane * kOct;
+      uint4 v = make_uint4(0u, 0u, 0u, 0u);
+      if (i + kOct <= d.tail) v = *reinterpret_cast<const uint4*>(sp + i);
+      raw[j][0] = v.x; raw[j][1] = v.y; raw[j][2] = v.z; raw[j][3] = v.w;
+      if (i < d.tail && i + kOct > d.tail) {  // the ragged end, element by element
+#pragma unroll
+        for (int e = 0; e < kOct - 1; ++e)
+          if (i + (uint32_t)e < d.tail) raw[j][e >> 1] |= (uint32_t)sp[i + (uint32_t)e] << (16 * (e & 1));
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {  // what is not finite counts as zero
+        if ((raw[j][k] & 0x7FFFu) >= kNonfiniteMag) raw[j][k] &= 0xFFFF0000u;
+        if (((raw[j][k] >> 16) & 0x7FFFu) >= kNonfiniteMag) raw[j][k] &= 0x0000FFFFu;
+      }
+    }
+  };
+  uint32_t am = 0u;
+  int32_t hi = (int32_t)0x80000000, lo = (int32_t)0x7FFFFFFF;
+#pragma nounroll
+  for (uint32_t i0 = 0; i0 < d.tail; i0 += kRound) {
+    load(i0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (!ASYM) {
+        am = OpUMax()(am, mag_bits32(octet_magnitude(raw[j])));
+      } else {
+        const uint32_t i = i0 + (uint32_t)(j * kRow) + lane * kOct;
+#pragma unroll
+        for (int e = 0; e < kOct; ++e) {
+          const int32_t k = float_key(ADACC_ELEM_F32(raw[j], e));
+          hi = (i + (uint32_t)e < d.tail && k > hi) ? k : hi;
+          lo = (i + (uint32_t)e < d.tail && k < lo) ? k : lo;
+        }
+      }
+    }
+  }
+  float scl, inv, off;
+  if constexpr (!ASYM) group_scale<false>(d, lanes_reduce<kWave>(am, OpUMax()), 0, 0, scl, inv, off);
+  else group_scale<true>(d, 0u, lanes_reduce<kWave>(hi, OpIMax()), lanes_reduce<kWave>(lo, OpIMin()), scl, inv, off);
+  const uint64_t grp = d.numel >> d.lgq;
+  if (lane == 0u) {
+    d.scales[grp] = scl;
+    if constexpr (ASYM) d.zp[grp] = off;
+  }
+  uint8_t* out = d.codes + d.numel * BITS / 8;  // behind the codes of the tiles, which end on a multiple of 8 elements
+#pragma nounroll
+  for (uint32_t i0 = 0; i0 < d.tail; i0 += kRound) {
+    if (d.tail > kRound) load(i0);  // uniform
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t i = i0 + (uint32_t)(j * kRow) + lane * kOct;
+      uint32_t c[kOct];
+#pragma unroll
+      for (int e = 0; e < kOct; ++e) {
+        const float y = ADACC_ELEM_F32(raw[j], e);
+        c[e] = code_bits<Q, true>(ASYM ? y - off : y, inv) & (uint32_t)(2 * Q - 1);
+        c[e] = i + (uint32_t)e < d.tail ? c[e] : 0u;  // an odd end: the high nibble is 0
+      }
+#pragma unroll
+      for (int k = 0; k < BITS; ++k) {  // byte by byte: a few hundred bytes in all
+        uint32_t byte = c[k * 8 / BITS];
+        if constexpr (BITS == 4) byte |= c[2 * k + 1] << 4;
+        if (i + (uint32_t)(k * 8 / BITS) < d.tail) out[(i * BITS) / 8 + (uint32_t)k] = (uint8_t)byte;
+      }
+    }
+  }
+  if (d.n_tiles == 0u && lane == 0u) { d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u; }
 }
 
 }  // namespace ADACC_DT_NS

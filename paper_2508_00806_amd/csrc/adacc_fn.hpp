@@ -14,8 +14,6 @@ typedef void (*PlaceSumFn)(TensorDesc);
 typedef void (*PlaceFn)(TensorDesc, uint32_t);
 typedef void (*PlaceSumBatchFn)(const TensorDesc*, const uint32_t*);
 typedef void (*PlaceBatchFn)(const TensorDesc*, const uint32_t*, uint32_t);
-typedef void (*TailFn)(TensorDesc);
-typedef void (*TailBatchFn)(const TensorDesc*, const uint32_t*);
 
 // Types of the channel and channel-wise kernels
 typedef void (*ChannelPartialFn)(const uint16_t*, uint32_t, uint32_t, float*, uint32_t);
@@ -32,7 +30,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
 //   generic: groups that the tile kernels do not take
 //   kind: kBatch* of adacc_common.hpp
 //   generic_threads, generic_lds_bytes: workgroup size and dynamic LDS of the fallback kernels (one segment per workgroup;
-//     topk_groups: TOPK over several statistics groups of a segment); compress_generic_fn(fixup): the second launch
+//     topk_groups: TOPK over several statistics groups of a segment); compress_generic_fn(place): their placement
 //   stream: the statistics pass reads with the streaming hint (tensors beyond kStatsKeepBytes)
 //   channel_score_channels: channels per workgroup of the score kernel
 //   channel_select_threads: size of the one workgroup of the select kernel
@@ -54,9 +52,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   PlaceFn place_fn();                                                                  \
   PlaceSumBatchFn place_sum_batch_fn();                                                \
   PlaceBatchFn place_batch_fn();                                                       \
-  TailFn compress_tail_fn();                                                           \
-  TailBatchFn compress_tail_batch_fn();                                                \
-  CompressFn compress_generic_fn(uint32_t tile_elems, bool fixup);                     \
+  CompressFn compress_generic_fn(uint32_t tile_elems, bool place);                     \
   uint32_t generic_threads();                                                          \
   uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups);      \
   ChannelPartialFn channel_partial_fn(bool stream);                                    \

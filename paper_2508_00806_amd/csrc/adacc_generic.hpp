@@ -14,13 +14,12 @@
 // of two, add neighbours level by level), mean and variance over the group's own count, the k largest by
 // (magnitude, lower index), the correctly rounded D / max, the same rounding of the codes.
 //
-// Outliers take the ways of the tile kernels.  ABS / STD: a segment's outliers go to its slot of kSlot
-// records in the workspace and its count to cnt[]; the placement kernels turn the counts into offsets and move
-// the slots' records to the stream; a segment with more outliers than a slot holds is selected once more, by a
-// second launch of this kernel (FIXUP) in which every other workgroup leaves at once.  TOPK: the offsets are
-// known in advance (k per group), the outliers go straight to the stream, and a segment that finds another
-// count (values that are not finite) raises the tensor's flag; only then do the placement kernel and the
-// second launch anything: offsets from the counts, and every segment's outliers written again.
+// Outliers take the ways of the tile kernels.  ABS / STD: a segment's outliers go to its slot of kSlot records in the
+// workspace and its count to cnt[]; the placement (place_generic_kernel) turns the counts into offsets and moves the
+// slots' records to the stream, and selects a segment with more outliers than a slot holds once more.  TOPK: the
+// offsets are known in advance (k per group), the outliers go straight to the stream, and a segment that finds another
+// count (values that are not finite) raises the tensor's flag; only then does the placement anything: offsets from
+// the counts, and every segment's outliers written again.
 // The segment is the blob's tile (adacc_layout.tile_elems).
 #pragma once
 
@@ -717,83 +716,73 @@ __device__ __forceinline__ const TensorDesc& descriptor_again() {
   return *(const TensorDesc*)p;
 }
 
-// One segment (d.tile_elems elements, the last one of the tensor may be short).
-// FIXUP: the second launch - only the outliers, straight to the stream at the offsets the placement kernel
-// has written, and only where the first launch could not place them.
+// One segment (d.tile_elems elements, the last one of the tensor may be short), loaded, its outliers known.
 // d: the kernel's first argument
-template <int SL, bool FIXUP>
-__device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentShared& sh, uint32_t seg, uint32_t epoch) {
-  const uint32_t tid = threadIdx.x;
-  const bool topk = d.mode == kModeTopk;
-  if constexpr (FIXUP) {
-    if (topk) {
-      if (__hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) return;  // uniform
-    } else if (d.cnt[seg] <= (uint32_t)kSlot) {
-      return;  // uniform
-    }
-  }
+template <int SL>
+__device__ __forceinline__ SegmentGeo load_and_select(const TensorDesc& d, SegmentShared& sh, uint32_t seg, uint32_t (&raw)[SL][4],
+                                                      uint32_t (&omag)[SL], uint32_t (&mask)[SL]) {
   SegmentGeo g;
   g.first_elem = (uint64_t)seg * d.tile_elems;
   const uint64_t left = d.numel - g.first_elem;
   g.cnt = left < (uint64_t)d.tile_elems ? (uint32_t)left : d.tile_elems;
   g.octs = (g.cnt + (uint32_t)kOct - 1u) / (uint32_t)kOct;
   g.full = g.cnt == d.tile_elems && (d.tile_elems & 7u) == 0u;
-  uint32_t raw[SL][4];
   segment_load(d, g, raw);
-  uint32_t mask[SL], omag[SL];
 #pragma unroll
   for (int j = 0; j < SL; ++j) omag[j] = octet_magnitude(raw[j]);
   if (d.mode != kModeNone) {
     segment_select(descriptor_again(), g, sh, raw, omag, mask);
-#pragma unroll
-    for (int j = 0; j < SL; ++j)  // what cannot be quantised at all is always kept exactly
-      if (omag[j] >= kNonfiniteMag) mask[j] |= octet_nonfinite(raw[j]);
-    if constexpr (FIXUP) {
-      const uint32_t pos0 = d.tile_ptr[seg], end = d.tile_ptr[seg + 1u];
-      segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
-      return;
-    } else if (topk) {
-      const uint32_t gps = d.tile_elems / d.gs;  // groups of a whole segment
-      const uint32_t pos0 = seg * gps * d.topk;
-      const uint32_t whole = g.cnt / d.gs, rest = g.cnt - whole * d.gs;
-      const uint32_t expected = whole * d.topk + (rest < d.topk ? rest : d.topk);
-      const uint32_t end = pos0 + expected;
-      const uint32_t total = segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
-      if (tid == 0u) {
-        d.tile_ptr[seg] = pos0;
-        d.cnt[seg] = total;
-        if (total != expected) *d.flag = epoch;
-        if (seg + 1u == d.n_tiles) {
-          d.tile_ptr[d.n_tiles] = end;
-          d.status[0] = end; d.status[1] = end > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u;
-        }
-      }
-    } else {
-      const uint32_t total = segment_emit(g, sh, raw, mask, SlotSink{d.slot + (uint64_t)seg * (uint64_t)kSlot}, 0u, (uint32_t)kSlot);
-      if (tid == 0u) d.cnt[seg] = total;
-    }
   } else {
 #pragma unroll
-    for (int j = 0; j < SL; ++j) mask[j] = omag[j] >= kNonfiniteMag ? octet_nonfinite(raw[j]) : 0u;
-    if (seg == 0u && tid == 0u) {
-      d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u;
-    }
+    for (int j = 0; j < SL; ++j) mask[j] = 0u;
   }
-  if constexpr (!FIXUP) {
-    const TensorDesc& d = descriptor_again();
-    // a5: from here on the outliers, and every value that is not finite, count as zero
 #pragma unroll
-    for (int j = 0; j < SL; ++j) {
-      if (mask[j] != 0u) {
-        clear_elements(raw[j], mask[j]);
-        omag[j] = octet_magnitude(raw[j]);
+  for (int j = 0; j < SL; ++j)  // what cannot be quantised at all is always kept exactly
+    if (omag[j] >= kNonfiniteMag) mask[j] |= octet_nonfinite(raw[j]);
+  return g;
+}
+
+template <int SL>
+__device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentShared& sh, uint32_t seg, uint32_t epoch) {
+  const uint32_t tid = threadIdx.x;
+  uint32_t raw[SL][4], mask[SL], omag[SL];
+  const SegmentGeo g = load_and_select<SL>(d, sh, seg, raw, omag, mask);
+  if (d.mode == kModeTopk) {
+    const uint32_t gps = d.tile_elems / d.gs;  // groups of a whole segment
+    const uint32_t pos0 = seg * gps * d.topk;
+    const uint32_t whole = g.cnt / d.gs, rest = g.cnt - whole * d.gs;
+    const uint32_t expected = whole * d.topk + (rest < d.topk ? rest : d.topk);
+    const uint32_t end = pos0 + expected;
+    const uint32_t total = segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
+    if (tid == 0u) {
+      d.tile_ptr[seg] = pos0;
+      d.cnt[seg] = total;
+      if (total != expected) *d.flag = epoch;
+      if (seg + 1u == d.n_tiles) {
+        d.tile_ptr[d.n_tiles] = end;
+        d.status[0] = end; d.status[1] = end > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u;
       }
     }
-    if (d.bits == 8u) {
-      if (d.asym) segment_quantise<8, true, SL>(d, g, sh, raw, omag); else segment_quantise<8, false, SL>(d, g, sh, raw, omag);
-    } else {
-      if (d.asym) segment_quantise<4, true, SL>(d, g, sh, raw, omag); else segment_quantise<4, false, SL>(d, g, sh, raw, omag);
+  } else if (d.mode != kModeNone) {
+    const SlotSink sink{d.slot + (uint64_t)seg * (uint64_t)kSlot, (uint32_t)g.first_elem};
+    const uint32_t total = segment_emit(g, sh, raw, mask, sink, 0u, (uint32_t)kSlot);
+    if (tid == 0u) d.cnt[seg] = total;
+  } else if (seg == 0u && tid == 0u) {
+    d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u;
+  }
+  const TensorDesc& again = descriptor_again();
+  // a5: from here on the outliers, and every value that is not finite, count as zero
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    if (mask[j] != 0u) {
+      clear_elements(raw[j], mask[j]);
+      omag[j] = octet_magnitude(raw[j]);
     }
+  }
+  if (again.bits == 8u) {
+    if (again.asym) segment_quantise<8, true, SL>(again, g, sh, raw, omag); else segment_quantise<8, false, SL>(again, g, sh, raw, omag);
+  } else {
+    if (again.asym) segment_quantise<4, true, SL>(again, g, sh, raw, omag); else segment_quantise<4, false, SL>(again, g, sh, raw, omag);
   }
 }
 
@@ -801,11 +790,35 @@ __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentSha
 // round trips with barriers between, which only other resident workgroups can fill
 template <int SL>
 constexpr int generic_min_waves() { return SL <= 2 ? 8 : SL <= 4 ? 6 : SL <= 6 ? 4 : 3; }
-template <int SL, bool FIXUP>
+template <int SL>
 __global__ __launch_bounds__(kSegThreads, (generic_min_waves<SL>())) void compress_generic_kernel(TensorDesc d, uint32_t epoch) {
   extern __shared__ __attribute__((aligned(16))) unsigned char segment_lds[];
   SegmentShared sh = segment_shared<SL>(segment_lds, d.tile_elems, d.gq);
-  compress_segment<SL, FIXUP>(d, sh, blockIdx.x, epoch);
+  compress_segment<SL>(d, sh, blockIdx.x, epoch);
+}
+
+// The placement of kPlaceSegments segments, and those that no slot held once more from the source, the whole workgroup
+// on one after the other.  (That was a launch of its own behind the placement, in which nearly every workgroup left at
+// once: 4.5 us on every call.)
+template <int SL>
+__global__ __launch_bounds__(kSegThreads, SL <= 4 ? 4 : 2) void place_generic_kernel(TensorDesc d, uint32_t epoch) {
+  static_assert(kSegThreads == (uint32_t)kPlaceThreads, "one workgroup for both");
+  extern __shared__ __attribute__((aligned(16))) unsigned char segment_lds[];
+  __shared__ PlaceShared place;
+  const bool topk = d.mode == kModeTopk;
+  if (topk && __hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) return;  // uniform
+  const PlacedTiles p = place_tiles<kPlaceSegments>(d, blockIdx.x, d.from_sums != 0u, !topk, place);
+  const uint32_t room = topk ? 0u : (uint32_t)kSlot;
+  if (__builtin_amdgcn_ballot_w64(p.count > room) == 0ull) return;  // the same in every wavefront
+  SegmentShared sh = segment_shared<SL>(segment_lds, d.tile_elems, d.gq);
+  for (uint32_t j = 0; j < p.n_here; ++j) {
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j);
+    if (n <= room) continue;  // uniform over the workgroup
+    uint32_t raw[SL][4], mask[SL], omag[SL];
+    const SegmentGeo g = load_and_select<SL>(d, sh, p.first + j, raw, omag, mask);
+    const uint32_t pos0 = p.base + (uint32_t)__builtin_amdgcn_readlane((int)p.excl, (int)j), end = pos0 + n;
+    segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
+  }
 }
 
 }  // namespace ADACC_DT_NS

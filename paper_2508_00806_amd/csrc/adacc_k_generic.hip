@@ -5,12 +5,12 @@
 namespace adacc {
 namespace ADACC_DT_NS {
 
-CompressFn compress_generic_fn(uint32_t tile_elems, bool fixup) {
+CompressFn compress_generic_fn(uint32_t tile_elems, bool place) {
   const uint32_t slices = ((tile_elems + 7u) / 8u + kSegThreads - 1u) / kSegThreads;  // octets per thread
-  if (slices <= 2u) return fixup ? compress_generic_kernel<2, true> : compress_generic_kernel<2, false>;
-  if (slices <= 4u) return fixup ? compress_generic_kernel<4, true> : compress_generic_kernel<4, false>;
-  if (slices <= 6u) return fixup ? compress_generic_kernel<6, true> : compress_generic_kernel<6, false>;
-  return fixup ? compress_generic_kernel<8, true> : compress_generic_kernel<8, false>;
+  if (slices <= 2u) return place ? place_generic_kernel<2> : compress_generic_kernel<2>;
+  if (slices <= 4u) return place ? place_generic_kernel<4> : compress_generic_kernel<4>;
+  if (slices <= 6u) return place ? place_generic_kernel<6> : compress_generic_kernel<6>;
+  return place ? place_generic_kernel<8> : compress_generic_kernel<8>;
 }
 uint32_t generic_threads() { return kSegThreads; }
 uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups) {

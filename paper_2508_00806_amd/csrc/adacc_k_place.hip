@@ -1,46 +1,102 @@
-// The kernels that place the outliers in the stream (single tensor and batch): one workgroup per block
-// of kPlaceTiles tiles of one tensor, whatever the method (the choice of the selection code for tiles
-// that have to be looked at again is a uniform switch).
+// The kernels that place the outliers in the stream (single tensor and batch): a workgroup per kPlaceTiles (kSumTiles) tiles
+// of one tensor, whatever the method (the choice of the selection code for tiles that have to be looked at again is a uniform
+// switch), and one more for the end of a tensor that its groups do not divide.
+#include "adacc_generic.hpp"
 #include "adacc_kernels.hpp"
 
 namespace adacc {
 namespace ADACC_DT_NS {
 
-__device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t block, uint32_t epoch, PlaceShared& sh) {
-  const bool e8 = (d.variant & 1u) != 0u;
-  const bool from_sums = d.n_blocks > kPlaceDirectBlocks;
-  if (d.generic != 0u) {
-    // The fallback kernels select a segment's outliers again themselves (a second launch), where the slot did
-    // not hold them or a TOPK group was irregular: here the offsets, and what the slots hold.
-    uint32_t n_here, mine;
-    if (d.mode == kModeTopk) {
-      if (__hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) return;
-      place_moves_block(d, block, false, false, sh, n_here, mine);
-    } else {
-      place_moves_block(d, block, from_sums, true, sh, n_here, mine);
+// ---- the end of a tensor with outliers: d.tail elements behind d.numel, fewer than the larger group, at most one short
+// statistics group cut into quantisation groups the last of which may be short.  A segment of the fallback kernels
+// (they know short groups) of two octets per thread, done by a workgroup of its own next to those that place the
+// tiles' outliers; its own go behind those of the tiles.  (One wavefront in a launch behind the placement, with plain
+// loops over LDS arrays, took 14 us for 141 elements of a statistics group of 512, and 41 us for 1455 of one of 4096;
+// now it is hidden behind the placement.)
+constexpr int kTailOcts = 2;  // per thread: 4096 elements
+constexpr uint32_t kTailLdsBytes = kSegHeadBytes + 4u * (2u * kTailOcts * kSegThreads + 2u * 4096u / 8u);
+__device__ __forceinline__ void compress_tail(const TensorDesc& whole, uint32_t total_main, unsigned char* lds) {
+  TensorDesc d = whole;
+  d.tile_elems = d.gs;  // the segment is one statistics group
+  SegmentShared sh = segment_shared<kTailOcts>(lds, d.tile_elems, d.gq);
+  SegmentGeo g;
+  g.first_elem = d.numel;
+  g.cnt = d.tail;
+  g.octs = (d.tail + (uint32_t)kOct - 1u) / (uint32_t)kOct;
+  g.full = false;
+  uint32_t raw[kTailOcts][4], mask[kTailOcts], omag[kTailOcts];
+  segment_load(d, g, raw);
+#pragma unroll
+  for (int j = 0; j < kTailOcts; ++j) omag[j] = octet_magnitude(raw[j]);
+  segment_select(d, g, sh, raw, omag, mask);
+#pragma unroll
+  for (int j = 0; j < kTailOcts; ++j)
+    if (omag[j] >= kNonfiniteMag) mask[j] |= octet_nonfinite(raw[j]);
+  const uint32_t total = total_main + segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, total_main, d.cap);
+  if (threadIdx.x == 0u) {
+    if (d.n_tiles == 0u) d.tile_ptr[0] = 0u;
+    d.tile_ptr[d.n_tiles_all] = total;
+    d.status[0] = total; d.status[1] = total > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u;
+  }
+#pragma unroll
+  for (int j = 0; j < kTailOcts; ++j) {
+    if (mask[j] != 0u) {
+      clear_elements(raw[j], mask[j]);
+      omag[j] = octet_magnitude(raw[j]);
     }
+  }
+  if (d.bits == 8u) {
+    if (d.asym) segment_quantise<8, true, kTailOcts>(d, g, sh, raw, omag); else segment_quantise<8, false, kTailOcts>(d, g, sh, raw, omag);
+  } else {
+    if (d.asym) segment_quantise<4, true, kTailOcts>(d, g, sh, raw, omag); else segment_quantise<4, false, kTailOcts>(d, g, sh, raw, omag);
+  }
+}
+
+union PlaceLds {  // a workgroup places tiles or does the tensor's end
+  PlaceListShared place;
+  __attribute__((aligned(16))) unsigned char tail[sizeof(PlaceShared) + 16 + kTailLdsBytes];
+};
+
+// block: of kPlaceTiles tiles (kSumTiles of a long tensor), or the one behind the last: the tensor's end
+__device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t block, uint32_t epoch, PlaceLds& lds) {
+  const bool from_sums = d.from_sums != 0u;
+  const bool topk = d.mode == kModeTopk;
+  // TOPK: regular counts everywhere (the usual case): the compression kernel has placed everything already
+  const bool regular = topk && __hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch;
+  const uint32_t per = from_sums ? (uint32_t)kSumTiles : (uint32_t)kPlaceTiles;
+  const uint32_t blocks = (d.n_tiles + per - 1u) / per;
+  if (block >= blocks) {
+    if (d.tail == 0u || block != blocks) return;
+    const uint32_t before = regular ? d.topk * (uint32_t)(d.numel >> d.lgs) : outliers_before(d, d.n_tiles, from_sums, lds.place);
+    compress_tail(d, before, lds.tail + sizeof(PlaceShared));  // (the sums above went through the words before)
     return;
   }
+  if (regular) return;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const PlacedTiles p = from_sums ? place_tiles<kSumTiles>(d, block, true, !topk, lds.place)
+                                  : place_tiles<kPlaceTiles>(d, block, false, !topk, lds.place);
+  const uint32_t room = topk ? 0u : (uint32_t)kSlot;
+  if (__builtin_amdgcn_ballot_w64(p.count > room) == 0ull) return;  // the usual case: every tile is in its slot
+  const uint32_t j = from_sums ? 0u : wave, step = from_sums ? 1u : (uint32_t)(kPlaceThreads / kWave);
+  const bool e8 = (d.variant & 1u) != 0u;
   switch (d.variant >> 3) {
     case kModeAbs:
-      if (d.rowwise) place_block<kModeAbs, 4, true, false>(d, block, from_sums, false, sh);
-      else if (e8) place_block<kModeAbs, 8, false, false>(d, block, from_sums, false, sh);
-      else place_block<kModeAbs, 4, false, false>(d, block, from_sums, false, sh);
+      if (d.rowwise) reselect_tiles<kModeAbs, 4, true, false>(d, p, room, j, step);
+      else if (e8) reselect_tiles<kModeAbs, 8, false, false>(d, p, room, j, step);
+      else reselect_tiles<kModeAbs, 4, false, false>(d, p, room, j, step);
       break;
     case kModeStd:
-      if (d.rowwise) place_block<kModeStd, 4, true, false>(d, block, from_sums, false, sh);
-      else if (e8) place_block<kModeStd, 8, false, false>(d, block, from_sums, false, sh);
-      else place_block<kModeStd, 4, false, false>(d, block, from_sums, false, sh);
+      if (d.rowwise) reselect_tiles<kModeStd, 4, true, false>(d, p, room, j, step);
+      else if (e8) reselect_tiles<kModeStd, 8, false, false>(d, p, room, j, step);
+      else reselect_tiles<kModeStd, 4, false, false>(d, p, room, j, step);
       break;
     case kModeTopk:
-      // regular counts everywhere (the usual case): the compression kernel has placed everything already
-      if (__hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) return;
       if (topk_whole(d)) {
-        if (e8) place_block<kModeTopk, 8, false, true>(d, block, false, true, sh);
-        else place_block<kModeTopk, 4, false, true>(d, block, false, true, sh);
+        if (e8) reselect_tiles<kModeTopk, 8, false, true>(d, p, room, j, step);
+        else reselect_tiles<kModeTopk, 4, false, true>(d, p, room, j, step);
       } else {
-        if (e8) place_block<kModeTopk, 8, false, false>(d, block, false, true, sh);
-        else place_block<kModeTopk, 4, false, false>(d, block, false, true, sh);
+        if (e8) reselect_tiles<kModeTopk, 8, false, false>(d, p, room, j, step);
+        else reselect_tiles<kModeTopk, 4, false, false>(d, p, room, j, step);
       }
       break;
     default: break;
@@ -49,29 +105,29 @@ __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t blo
 
 // single tensor: blockIdx.x is the block of tiles
 __global__ __launch_bounds__(kPlaceThreads) void place_sum_kernel(TensorDesc d) {
-  __shared__ uint32_t part[kPlaceThreads / kWave];
-  place_sum_block(d, blockIdx.x, part);
+  __shared__ PlaceShared sh;
+  place_sum_block(d, blockIdx.x, sh);
 }
 
 // The selection code for tiles that have to be looked at again (rare) would take 173 registers and leave room
 // for two wavefronts per SIMD; the kernel is a chain of dependent memory round trips, so it is held to 128.
 __global__ __launch_bounds__(kPlaceThreads, 4) void place_kernel(TensorDesc d, uint32_t epoch) {
-  __shared__ PlaceShared sh;
-  place_dispatch(d, blockIdx.x, epoch, sh);
+  __shared__ PlaceLds lds;
+  place_dispatch(d, blockIdx.x, epoch, lds);
 }
 
 // a group of tensors of a table: blockIdx.y picks the tensor, blockIdx.x its block of tiles
 __global__ __launch_bounds__(kPlaceThreads) void place_sum_batch_kernel(const TensorDesc* table, const uint32_t* members) {
-  __shared__ uint32_t part[kPlaceThreads / kWave];
+  __shared__ PlaceShared sh;
   const TensorDesc d = table[members[blockIdx.y]];
-  if (blockIdx.x < d.n_blocks) place_sum_block(d, blockIdx.x, part);
+  if (blockIdx.x < (d.n_tiles + (uint32_t)kSumTiles - 1u) / (uint32_t)kSumTiles) place_sum_block(d, blockIdx.x, sh);
 }
 
 __global__ __launch_bounds__(kPlaceThreads, 4) void place_batch_kernel(const TensorDesc* table, const uint32_t* members,
                                                                     uint32_t epoch) {
-  __shared__ PlaceShared sh;
+  __shared__ PlaceLds lds;
   const TensorDesc d = table[members[blockIdx.y]];
-  if (blockIdx.x < d.n_blocks) place_dispatch(d, blockIdx.x, epoch, sh);
+  place_dispatch(d, blockIdx.x, epoch, lds);
 }
 
 PlaceSumFn place_sum_fn() { return place_sum_kernel; }

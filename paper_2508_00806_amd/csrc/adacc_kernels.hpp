@@ -28,7 +28,12 @@ __global__ __launch_bounds__(kThreads, (compress_min_waves<E, ROWWISE, WHOLE>())
   // one tile per wavefront and no loop: inside a loop over tiles the compiler would prepare, ahead of
   // the loop, the lane's addresses for every group size the encoders can be asked for
   const uint32_t t = blockIdx.x * kWavesPerWg + wave;
-  if (t >= d.n_tiles) return;
+  if (t >= d.n_tiles) {
+    if constexpr (MODE == kModeNone) {
+      if (t == d.n_tiles && d.tail != 0u) compress_plain_tail<BITS, ASYM>(d);
+    }
+    return;
+  }
   if constexpr (MODE == kModeNone) compress_tile_plain<BITS, ASYM, E, ROWWISE>(d, t);
   else compress_tile_outliers<MODE, BITS, ASYM, E, ROWWISE, WHOLE>(d, t, epoch);
 }
@@ -91,7 +96,17 @@ __global__ __launch_bounds__(kThreads, (batch_min_waves<KIND>())) void compress_
   // order of these launches): one round trip to memory less before the wavefront's first load
   const TensorDesc d = table[members ? members[blockIdx.y] : blockIdx.y];
   const uint32_t tile = blockIdx.x * kWavesPerWg + wave;
-  if (tile >= d.n_tiles) return;
+  if (tile >= d.n_tiles) {
+    if (tile == d.n_tiles && d.tail != 0u && d.variant >> 3 == kModeNone) {  // the end of a tensor without outliers
+      switch (d.variant & 6u) {
+        case 0: compress_plain_tail<4, false>(d); break;
+        case 2: compress_plain_tail<4, true>(d); break;
+        case 4: compress_plain_tail<8, false>(d); break;
+        default: compress_plain_tail<8, true>(d); break;
+      }
+    }
+    return;
+  }
   constexpr int E = (KIND == kBatchAny8 || KIND == kBatchTopk8) ? 8 : 4;
   if constexpr (KIND == kBatchTopk4 || KIND == kBatchTopk8) {
     compress_dispatch<kModeTopk, E, false, true>(d, tile, epoch);

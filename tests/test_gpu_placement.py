@@ -1,0 +1,44 @@
+"""The places of the outliers in the stream: tiles at and beyond what a slot of the workspace holds, short tensors (every
+workgroup adds up all counts before its own) and long ones (sums of blocks first), tiles and the fallback kernels'
+segments, and the end that the groups do not divide, with outliers of its own."""
+import pytest
+import torch
+
+from helpers import run_parity
+
+pytestmark = pytest.mark.gpu
+
+# (quantisation group, elements of a tile, whole tiles, elements behind them)
+SHAPES = [(64, 2048, 64, 63), (64, 2048, 65, 0), (4096, 4096, 9, 4095), (512, 2048, 0, 511), (40, 4080, 17, 1001), (11008, 11008, 16, 0),
+          (64, 2048, 32768 + 260, 33), (40, 4080, 32768 + 17, 9)]
+
+
+@pytest.mark.parametrize("gq,tile,tiles,rest", SHAPES)
+def test_slots_at_their_limit(gq, tile, tiles, rest):
+    n = tile * tiles + rest
+    g = torch.Generator().manual_seed(n)
+    x = (torch.rand(n, generator=g) - 0.5).to(torch.bfloat16)
+    # 63, 64, 65 outliers and a tile full of them, at both ends and across the workgroups' and sums' blocks
+    for t, k in ((0, 64), (1, 65), (3, 63), (7, tile), (8, 1), (15, 65), (16, 64), (63, 64), (64, 65), (255, 70), (256, 3), (32767, 65),
+                 (32768, 64), (tiles - 1, 65)):
+        if 0 <= t < tiles:
+            at = t * tile + torch.randperm(tile, generator=g)[:k]
+            x[at] = 2.0 + torch.rand(k, generator=g).to(torch.bfloat16)
+    if rest:
+        x[n - rest:n - rest + 3] = -3.0
+        x[n - 1] = float("inf")
+    print(f"[placement] gq={gq} tiles={tiles} rest={rest}", flush=True)
+    oc, *_ = run_parity(x, dict(bits=8, quant_group=gq, asym=0, outlier_mode="abs", stat_group=0, thresh=1.0, topk=0))
+    assert oc.n_out > 0
+
+
+@pytest.mark.parametrize("mode", ["none", "abs", "std", "topk"])
+@pytest.mark.parametrize("rest", [1, 8, 1999, 2048, 2049, 4095])
+def test_the_end_of_a_tensor_that_its_groups_do_not_divide(mode, rest):
+    for gq, gs, bits, asym, dtype in ((64, 4096, 4, 0, torch.bfloat16), (4096, 4096, 8, 1, torch.float16), (4096, 4096, 4, 0, torch.bfloat16)):
+        for whole in (0, 4096):
+            x = torch.randn(whole + rest, generator=torch.Generator().manual_seed(rest)).to(dtype)
+            x[-1] = float("nan")
+            print(f"[end] {mode} rest={rest} gq={gq} bits={bits} asym={asym} whole={whole}", flush=True)
+            run_parity(x, dict(bits=bits, quant_group=gq, asym=asym, outlier_mode=mode, stat_group=gs,
+                               thresh=2.0 if mode in ("abs", "std") else 0.0, topk=7 if mode == "topk" else 0))
