@@ -176,30 +176,47 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
 // and leaves that integer, in two's complement, in the low mantissa bits; the clip is a median
 // with the two bounds shifted the same way ("values greater than 7 are capped at 7"); a NaN
 // lands on the lower bound.
-// Symmetric codes need the upper bound only: |y| <= max and inv = RN(D / max) (or less, when that was cut
-// to the largest finite value) give |y * inv| <= D * (1 + 2^-24), which rounds to at most D <= Q in
+// Symmetric codes need the upper bound only (pack_codes): |y| <= max and inv = RN(D / max) (or less, when that was
+// cut to the largest finite value) give |y * inv| <= D * (1 + 2^-24), which rounds to at most D <= Q in
 // magnitude, -Q is a code, and neither factor can be a NaN or infinite.  (Asymmetric codes keep both
 // bounds: a group of huge values can make O infinite and the product a NaN.)
 constexpr float kMagic = 12582912.0f;
-template <int Q, bool BOTH_BOUNDS = true>
-__device__ __forceinline__ uint32_t code_bits(float y, float inv) {
-  const float p = __fmul_rn(y, inv);
-  const float r = __fadd_rn(p, kMagic);
-  if constexpr (BOTH_BOUNDS) return __float_as_uint(fminf(fmaxf(r, kMagic - (float)Q), kMagic + (float)(Q - 1)));
-  else return __float_as_uint(fminf(r, kMagic + (float)(Q - 1)));
+template <int Q>
+__device__ __forceinline__ uint32_t code_bits(float p) {
+  return __float_as_uint(fminf(fmaxf(__fadd_rn(p, kMagic), kMagic - (float)Q), kMagic + (float)(Q - 1)));
 }
 
-__device__ __forceinline__ uint32_t pack_bytes4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  const uint32_t ab = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);  // [a.0, b.0, 0, 0]
-  const uint32_t cd = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
-  return ab | (cd << 16);
+typedef short i16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_min_i16(uint32_t a, int16_t bound) {
+  const i16x2_t q = {bound, bound};
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(i16x2_t, a), q));
 }
-// 8 codes -> 8 nibbles, element e in nibble e: the even and the odd elements are gathered
-// byte-wise first, then one shift and one bit-select interleave them.
-__device__ __forceinline__ uint32_t pack_nibbles8(const uint32_t (&c)[kOct]) {
-  const uint32_t even = pack_bytes4(c[0], c[2], c[4], c[6]);
-  const uint32_t odd = pack_bytes4(c[1], c[3], c[5], c[7]);
-  return (even & 0x0F0F0F0Fu) | ((odd << 4) & 0xF0F0F0F0u);
+// The codes of an octet from its products y * inv, packed: 8 bytes in w[0], w[1], or 8 nibbles in w[0] (element e in nibble e).  Two codes meet
+// in the halves of a word first, e and e + 2 resp. e and e + 4; symmetric codes are clipped there, two at a time
+// (|code| <= D before the clip: 16 bits hold it), asymmetric ones before (their products know no bound).
+template <int BITS, bool ASYM>
+__device__ __forceinline__ void pack_codes(const float (&p)[kOct], uint32_t (&w)[2]) {
+  constexpr int Q = 1 << (BITS - 1);
+  uint32_t c[kOct];
+#pragma unroll
+  for (int e = 0; e < kOct; ++e) c[e] = ASYM ? code_bits<Q>(p[e]) : __float_as_uint(__fadd_rn(p[e], kMagic));
+  constexpr int STEP = BITS == 8 ? 2 : 4;
+  uint32_t h[4];  // BITS 8: (0,2) (1,3) (4,6) (5,7); BITS 4: (0,4) (1,5) (2,6) (3,7)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int e = BITS == 8 ? (i >> 1) * 4 + (i & 1) : i;
+    h[i] = __builtin_amdgcn_perm(c[e + STEP], c[e], 0x05040100u);  // the low halves
+    if constexpr (!ASYM) h[i] = pk_min_i16(h[i], (int16_t)(Q - 1));
+  }
+  if constexpr (BITS == 8) {
+    w[0] = __builtin_amdgcn_perm(h[1], h[0], 0x06020400u);
+    w[1] = __builtin_amdgcn_perm(h[3], h[2], 0x06020400u);
+  } else {
+    const uint32_t t01 = (h[0] & 0x000F000Fu) | ((h[1] << 4) & ~0x000F000Fu);
+    const uint32_t t23 = (h[2] & 0x000F000Fu) | ((h[3] << 4) & ~0x000F000Fu);
+    w[0] = (t01 & 0x00FF00FFu) | ((t23 << 8) & ~0x00FF00FFu);
+    w[1] = 0u;
+  }
 }
 
 // ------------------------------------------------------------------ tile geometry, loads and stores
@@ -289,9 +306,10 @@ __device__ __forceinline__ void widen_row(const uint32_t (&oct)[4], float (&x)[k
 // compiler's wait-count bookkeeping, and the wait for the prefetched tile would then also wait
 // for these stores.  In a tensor's last tile, octets past the end go to a scrap area in the
 // unused part of the blob's status block; all lanes of a group store their (identical) scale.
+// y: the values to be quantised (asymmetric: less the offset)
 template <int BITS, bool ASYM, int E, bool STRIP>
 __device__ __forceinline__ void store_row(const TensorDesc& d, const TileGeo<E, STRIP>& g, int j,
-                                          const uint32_t (&c)[kOct], float scl, float off) {
+                                          const float (&y)[kOct], float scl, float inv, float off) {
   // The lane's offset is formed here, per row, from a copy the compiler knows nothing about: else it
   // prepares the offsets (and the group numbers) of all rows ahead of the first row, for every
   // group size the caller can be asked for, and keeps them in registers.
@@ -301,14 +319,13 @@ __device__ __forceinline__ void store_row(const TensorDesc& d, const TileGeo<E, 
   unsigned char* cp = d.codes + g.base * BITS / 8;       // uniform
   float* sp = d.scales + (g.base >> d.lgq);                // uniform
   const uint32_t gl = eo >> d.lgq;
-  uint2 w8;
-  uint32_t w4 = 0u;
-  if constexpr (BITS == 8) {
-    w8.x = pack_bytes4(c[0], c[1], c[2], c[3]);
-    w8.y = pack_bytes4(c[4], c[5], c[6], c[7]);
-  } else {
-    w4 = pack_nibbles8(c);
-  }
+  float p[kOct];
+#pragma unroll
+  for (int e = 0; e < kOct; ++e) p[e] = __fmul_rn(y[e], inv);
+  uint32_t w[2];
+  pack_codes<BITS, ASYM>(p, w);
+  const uint2 w8 = make_uint2(w[0], w[1]);
+  const uint32_t w4 = w[0];
   if (g.full) {
     if constexpr (BITS == 8) ADACC_STORE8(cp + eo, w8);
     else ADACC_STORE4(cp + (eo >> 1), w4);
@@ -536,7 +553,6 @@ __device__ __forceinline__ void scale_sym_clean(const TensorDesc& d, uint32_t am
 template <int BITS, bool ASYM, int E, int LANES, bool STRIP>
 __device__ __forceinline__ void encode_clean_row(const TensorDesc& d, const TileGeo<E, STRIP>& g, int j,
                                                  const uint32_t (&oct)[4], uint32_t top) {
-  constexpr int Q = 1 << (BITS - 1);
   float x[kOct];
   widen_row(oct, x);
   float scl, inv, off = 0.0f;
@@ -549,10 +565,11 @@ __device__ __forceinline__ void encode_clean_row(const TensorDesc& d, const Tile
     const int32_t k1 = lanes_reduce<LANES>(float_key(ext1), OpIMin());
     group_scale<true>(d, 0u, k0, k1, scl, inv, off);
   }
-  uint32_t c[kOct];
+  if constexpr (ASYM) {
 #pragma unroll
-  for (int e = 0; e < kOct; ++e) c[e] = code_bits<Q, ASYM>(ASYM ? x[e] - off : x[e], inv);
-  store_row<BITS, ASYM, E>(d, g, j, c, scl, off);
+    for (int e = 0; e < kOct; ++e) x[e] = x[e] - off;
+  }
+  store_row<BITS, ASYM, E>(d, g, j, x, scl, inv, off);
 }
 
 // ------------------------------------------------------------------ TOPK over groups inside a row
@@ -593,7 +610,6 @@ __device__ __forceinline__ uint32_t encode_rows(const TensorDesc& d, const TileG
                                                 const uint32_t (&raw)[E][4], uint32_t tile, const Sink& sink,
                                                 uint32_t pos0, uint32_t limit) {
   static_assert(!STRIP || MODE == kModeNone, "element indices of outliers are formed for adjacent rows only");
-  constexpr int Q = 1 << (BITS - 1);
   const float inv_gs = __uint_as_float((127u - d.lgs) << 23);  // 2^-lgs, exact
   const uint32_t lane_first = tile * (uint32_t)(E * kRow) + (uint32_t)lane_id() * kOct;
   uint32_t total = 0u;  // uniform: outliers of the rows so far
@@ -677,10 +693,11 @@ __device__ __forceinline__ uint32_t encode_rows(const TensorDesc& d, const TileG
         const int32_t k1 = lanes_reduce<LANES>(float_key(ext1), OpIMin());
         group_scale<true>(d, 0u, k0, k1, scl, inv, off);
       }
-      uint32_t c[kOct];
+      if constexpr (ASYM) {
 #pragma unroll
-      for (int e = 0; e < kOct; ++e) c[e] = code_bits<Q, ASYM>(ASYM ? y[e] - off : y[e], inv);
-      store_row<BITS, ASYM, E>(d, g, j, c, scl, off);
+        for (int e = 0; e < kOct; ++e) y[e] = y[e] - off;
+      }
+      store_row<BITS, ASYM, E>(d, g, j, y, scl, inv, off);
     }
     if constexpr (MODE != kModeNone) {
       if (any) {  // uniform: the row's outliers leave at once, nothing about them is kept
@@ -926,7 +943,6 @@ template <int BITS, bool ASYM, int E>
 __device__ __forceinline__ void finish_tile(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4],
                                             const float (&ext0)[E], const float (&ext1)[E],
                                             const TileOutliers<E>& out) {
-  constexpr int Q = 1 << (BITS - 1);
   // ---- a6: per-group scale (and offset).  Cross-lane max / min run on integer images of the floats.
   // Every lane of a group would compute the same scale; with at least 4 lanes per group and 4 rows,
   // lane l of every quad takes row l instead, so that one division serves the whole tile, and the
@@ -988,10 +1004,11 @@ __device__ __forceinline__ void finish_tile(const TensorDesc& d, const TileGeo<E
         y[e] = __uint_as_float(__float_as_uint(y[e]) & keep);
       }
     }
-    uint32_t c[kOct];
+    if constexpr (ASYM) {
 #pragma unroll
-    for (int e = 0; e < kOct; ++e) c[e] = code_bits<Q, ASYM>(ASYM ? y[e] - off[j] : y[e], inv[j]);
-    store_row<BITS, ASYM, E>(d, g, j, c, scl[j], off[j]);
+      for (int e = 0; e < kOct; ++e) y[e] = y[e] - off[j];
+    }
+    store_row<BITS, ASYM, E>(d, g, j, y, scl[j], inv[j], off[j]);
   }
 }
 
@@ -1654,7 +1671,7 @@ __device__ __forceinline__ void compress_plain_tail(const TensorDesc& d) {
 #pragma unroll
       for (int e = 0; e < kOct; ++e) {
         const float y = ADACC_ELEM_F32(raw[j], e);
-        c[e] = code_bits<Q, true>(ASYM ? y - off : y, inv) & (uint32_t)(2 * Q - 1);
+        c[e] = code_bits<Q>(__fmul_rn(ASYM ? y - off : y, inv)) & (uint32_t)(2 * Q - 1);
         c[e] = i + (uint32_t)e < d.tail ? c[e] : 0u;  // an odd end: the high nibble is 0
       }
 #pragma unroll

@@ -241,16 +241,220 @@ __device__ __forceinline__ uint32_t octet_nonfinite(const uint32_t (&oct)[4]) {
   return m;
 }
 
+// The k-th largest key of a segment that is one group, by rounds.  The k largest elements lie in the k octets with the
+// largest octet maxima (an element outside them is beaten by one element of each of them), and those octets are among
+// the k best octets of every wavefront.  So: (1) every wavefront picks its k best octets by k rounds of a maximum over
+// its own lanes - keys in registers, the winner's owner only zeroes one key -, (2) the four lists meet in LDS
+// and every wavefront finds the k best octets overall by k rounds over the 4 k keys; the owner of each
+// of them (3) writes the keys of its 8 elements to an entry of a list in LDS, and (4) every wavefront finds
+// the k-th largest of those 8 k element keys.  Three barriers whatever k is, and no step where one thread works while
+// the workgroup waits.  Keys: magnitude above the reversed octet number resp. element index; 0 = nothing.
+template <int SL>
+__device__ __forceinline__ uint32_t topk_rounds(const SegmentGeo& g, SegmentShared& sh, const uint32_t (&raw)[SL][4],
+                                                const uint32_t (&omag)[SL], uint32_t rounds) {
+  const uint32_t tid = threadIdx.x;
+  const uint32_t lane = (uint32_t)lane_id(), wave = tid / (uint32_t)kWave;
+  uint32_t okey[SL];
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    const uint32_t o = tid + (uint32_t)j * kSegThreads;
+    okey[j] = o < g.octs ? (omag[j] << 16) | (0xFFFFu - o) : 0u;  // (elements that do not exist are zeros: they do not raise omag)
+  }
+  {  // (1)
+    uint32_t live[SL], cand = 0u;
+#pragma unroll
+    for (int j = 0; j < SL; ++j) live[j] = okey[j];
+    for (uint32_t r = 0; r < rounds; ++r) {  // uniform
+      uint32_t best = 0u;
+#pragma unroll
+      for (int j = 0; j < SL; ++j) best = live[j] > best ? live[j] : best;
+      const uint32_t w = wave_max_u32_scalar(best);
+#pragma unroll
+      for (int j = 0; j < SL; ++j) live[j] = live[j] == w ? 0u : live[j];
+      cand = lane == r ? w : cand;
+    }
+    if (lane < 32u) sh.a[wave * 32u + lane] = cand;
+    sh.b[tid] = 0u;  // the list of (3): 8 keys for each of up to 32 octets
+    if (tid == 0u) sh.head[0] = 0u;  // and the number of its entries in use
+  }
+  __syncthreads();
+  uint32_t least = 0u;  // the smallest key among the k best octets overall (0: there are fewer octets, all are taken)
+  {  // (2)
+    if (rounds <= 16u) {  // uniform: the first 16 keys of the four lists, one per lane
+      uint32_t c0 = sh.a[(lane >> 4) * 32u + (lane & 15u)];  // lane = 16 * wavefront + entry
+      for (uint32_t r = 0; r < rounds; ++r) {
+        least = wave_max_u32_scalar(c0);
+        c0 = c0 == least ? 0u : c0;
+      }
+    } else {
+      uint32_t c0 = sh.a[lane], c1 = sh.a[(uint32_t)kWave + lane];
+      for (uint32_t r = 0; r < rounds; ++r) {
+        least = wave_max_u32_scalar(c0 > c1 ? c0 : c1);
+        c0 = c0 == least ? 0u : c0;
+        c1 = c1 == least ? 0u : c1;
+      }
+    }
+  }
+  // (3): which entry of the list an octet gets does not matter, a counter in LDS hands them out
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    if (okey[j] != 0u && okey[j] >= least) {  // at most k octets of the workgroup
+      const uint32_t o = tid + (uint32_t)j * kSegThreads;
+      const uint32_t nv = octet_valid(g, o);
+      const uint32_t entry = atomicAdd(&sh.head[0], 1u) & 31u;  // (below 32 anyway: keys are unique)
+#pragma unroll
+      for (int e = 0; e < kOct; ++e)
+        sh.b[entry * (uint32_t)kOct + (uint32_t)e] =
+            (uint32_t)e < nv ? (ADACC_ELEM_MAG(raw[j], e) << 16) | (0xFFFFu - (o * (uint32_t)kOct + (uint32_t)e)) : 0u;
+    }
+  }
+  __syncthreads();
+  uint32_t limit = 0u;
+  {  // (4)
+    // (never 0: the octets of (2) hold at least `rounds` elements)
+    if (rounds <= 8u) {  // uniform: at most 64 keys, one per lane
+      uint32_t c = sh.b[lane];
+      for (uint32_t r = 0; r < rounds; ++r) {
+        limit = wave_max_u32_scalar(c);
+        c = c == limit ? 0u : c;
+      }
+    } else {
+      uint32_t c[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] = sh.b[(uint32_t)k * (uint32_t)kWave + lane];
+      for (uint32_t r = 0; r < rounds; ++r) {
+        const uint32_t m0 = c[0] > c[1] ? c[0] : c[1], m1 = c[2] > c[3] ? c[2] : c[3];
+        limit = wave_max_u32_scalar(m0 > m1 ? m0 : m1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[k] = c[k] == limit ? 0u : c[k];
+      }
+    }
+  }
+  return limit;
+}
+
+// The k-th largest key of a segment that is one group, k <= 8.  A magnitude that at least k lanes of a wavefront reach
+// (found by halving, with ballots: the vector unit compares once per step, the rest is scalar) is a lower bound of the
+// k-th largest; with the highest of the four wavefronts' bounds some 15 to 30 octets are left.  They meet in LDS,
+// and one wavefront - another one for every segment, so that no SIMD has them all - takes an octet per lane, finds the
+// k-th largest magnitude by halving again, over the lanes' two largest first (and over all where a lane holds more
+// of the k), and the last of its equals that still belongs to the k.  Returns false (uniform) when more than 64
+// octets are left, a constant segment for one.
+// (The rounds, k dependent maxima over the wavefront three times over, took 60 of the 103 us that [8192, 11008] with
+// k = 8 took; 88 us with the halving.)
+template <class Count>
+__device__ __forceinline__ uint32_t kth_by_halving(uint32_t k, Count count) {  // the largest t < 2^15 with count(t) >= k, or 0
+  uint32_t t = 0u;
+#pragma unroll
+  for (int bit = 14; bit >= 0; --bit) {
+    const uint32_t c = t | (1u << bit);
+    t = count(c) >= k ? c : t;
+  }
+  return t;
+}
+__device__ __forceinline__ uint32_t lanes_where(bool v) { return (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(v)); }
+template <int SL>
+__device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh, const uint32_t (&raw)[SL][4],
+                                         const uint32_t (&omag)[SL], uint32_t k, uint32_t& limit) {
+  const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / (uint32_t)kWave);
+  uint32_t m = 0u;
+#pragma unroll
+  for (int j = 0; j < SL; ++j) m = omag[j] > m ? omag[j] : m;
+  const uint32_t mine = kth_by_halving(k, [&](uint32_t t) { return lanes_where(m >= t); });
+  if (lane == 0u) sh.head[40u + wave] = mine;
+  if (tid == 0u) sh.head[0] = 0u;  // octets in the list
+  __syncthreads();
+  uint32_t bound = 0u;
+#pragma unroll
+  for (uint32_t w = 0; w < kSegWaves; ++w) bound = sh.head[40u + w] > bound ? sh.head[40u + w] : bound;
+  uint4* list = reinterpret_cast<uint4*>(sh.a);
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    const uint32_t o = tid + (uint32_t)j * kSegThreads;
+    if (omag[j] >= bound && o < g.octs) {
+      const uint32_t entry = atomicAdd(&sh.head[0], 1u);  // in any order
+      if (entry < (uint32_t)kWave) {
+        list[entry] = make_uint4(raw[j][0], raw[j][1], raw[j][2], raw[j][3]);
+        sh.b[entry] = o;
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t n = __builtin_amdgcn_readfirstlane(sh.head[0]);
+  if (n > (uint32_t)kWave) {
+    __syncthreads();  // everybody has read the number before the list is used for something else
+    return false;
+  }
+  if (wave == (blockIdx.x & (kSegWaves - 1u))) {  // uniform
+    int32_t mag[kOct];  // -1: does not exist
+    uint32_t o = 0u;
+    {
+      uint4 v = make_uint4(0u, 0u, 0u, 0u);
+      if (lane < n) { v = list[lane]; o = sh.b[lane]; }
+      const uint32_t nv = lane < n ? octet_valid(g, o) : 0u;
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < kOct; ++e) mag[e] = (uint32_t)e < nv ? (int32_t)ADACC_ELEM_MAG(w, e) : -1;
+    }
+    int32_t m1 = -1, m2 = -1;  // the lane's two largest
+#pragma unroll
+    for (int e = 0; e < kOct; ++e) {
+      const int32_t lo = mag[e] < m1 ? mag[e] : m1;
+      m2 = lo > m2 ? lo : m2;
+      m1 = mag[e] > m1 ? mag[e] : m1;
+    }
+    auto reach = [&](int32_t t) {
+      uint32_t c = 0u;
+#pragma unroll
+      for (int e = 0; e < kOct; ++e) c += lanes_where(mag[e] >= t);
+      return c;
+    };
+    uint32_t t = kth_by_halving(k, [&](uint32_t c) { return lanes_where(m1 >= (int32_t)c) + lanes_where(m2 >= (int32_t)c); });
+    uint32_t above = reach((int32_t)t + 1);
+    if (above >= k) {  // uniform, rare: a lane holds three of the k largest
+      t = kth_by_halving(k, [&](uint32_t c) { return reach((int32_t)c); });
+      above = reach((int32_t)t + 1);
+    }
+    uint32_t last = 0u;  // reversed index of the last element of magnitude t that belongs to the k (0: all do)
+    const uint32_t need = k - above;
+    if (reach((int32_t)t) - above != need) {  // uniform: more equals than are needed, the lowest indices are taken
+      last = 0xFFFFFFFFu;
+      for (uint32_t r = 0; r < need; ++r) {
+        uint32_t best = 0u;
+#pragma unroll
+        for (int e = 0; e < kOct; ++e) {
+          const uint32_t rev = 0xFFFFu - (o * (uint32_t)kOct + (uint32_t)e);
+          best = (mag[e] == (int32_t)t && rev < last && rev > best) ? rev : best;
+        }
+        last = wave_max_u32_scalar(best);
+      }
+    }
+    if (lane == 0u) sh.head[44] = (t << 16) | last;
+  }
+  __syncthreads();
+  limit = sh.head[44];
+  return true;
+}
+
+// How a segment's outliers are chosen, as a template argument of the compression: the mode, or kSegTopkWhole where the
+// segment is one TOPK group (kModeTopk: several), or kSegAny: by the descriptor.  (One kernel for all modes held the
+// registers of the hungriest: 128 for 6 octets per thread, four wavefronts per SIMD, where 84 are enough for TOPK over
+// the segment; [8192, 11008]: 88 -> 77 us.)
+constexpr int kSegTopkWhole = 4, kSegAny = 5;
+
 // ---- a2 / a3: mask[j] bit e = element e of the thread's octet j is an outlier by the method's rule
 // omag[j]: the largest magnitude of octet j, as the 15 low bits of the pattern
-template <int SL>
+template <int SL, int KIND>
 __device__ __forceinline__ void segment_select(const TensorDesc& d, const SegmentGeo& g, SegmentShared& sh,
                                                const uint32_t (&raw)[SL][4], const uint32_t (&omag)[SL],
                                                uint32_t (&mask)[SL]) {
   const uint32_t tid = threadIdx.x;
 #pragma unroll
   for (int j = 0; j < SL; ++j) mask[j] = 0u;
-  if (d.mode == kModeAbs) {
+  const bool whole = KIND == kSegTopkWhole || (KIND == kSegAny && d.gs >= d.tile_elems);
+  const uint32_t mode = KIND == kSegAny ? d.mode : KIND == kSegTopkWhole ? (uint32_t)kModeTopk : (uint32_t)KIND;
+  if (mode == kModeAbs) {
 #pragma unroll
     for (int j = 0; j < SL; ++j) {
       // no element passes where the octet's largest magnitude does not (an octet with a NaN is looked at)
@@ -259,7 +463,7 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
         for (int e = 0; e < kOct; ++e) mask[j] |= (fabsf(ADACC_ELEM_F32(raw[j], e)) > d.param ? 1u : 0u) << e;
       }
     }
-  } else if (d.mode == kModeStd) {
+  } else if (mode == kModeStd) {
     // the three lowest levels of the pairwise sums inside the octet, the rest over the octets' words
 #pragma unroll
     for (int j = 0; j < SL; ++j) {
@@ -273,6 +477,7 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
     }
     __syncthreads();
     const uint32_t opg = d.gs / (uint32_t)kOct;
+    forget_derived<SL>(raw);
     groups_tree<true, float>(sh, sh.a, sh.b, g.octs, opg, 0.0f, 0.0f, OpAdd(), OpAdd(), [&](uint32_t grp, float s1, float s2) {
       const uint32_t left = g.cnt - grp * d.gs;
       const float n = (float)(left < d.gs ? left : d.gs);
@@ -300,99 +505,19 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
       }
     }
     __syncthreads();  // a, b, g0, g1 are free again
-  } else if (d.mode == kModeTopk) {
-    if (d.gs >= d.tile_elems) {
-      // The segment is one group.  The k largest elements lie in the k octets with the largest octet maxima (an
-      // element outside them is beaten by one element of each of them), and those octets are among the k best
-      // octets of every wavefront.  So: (1) every wavefront picks its k best octets by k rounds of a maximum over
-      // its own lanes - keys in registers, the winner's owner only zeroes one key -, (2) the four lists meet in LDS
-      // and every wavefront finds the k best octets overall by k rounds over the 4 k keys; the owner of each
-      // of them (3) writes the keys of its 8 elements to an entry of a list in LDS, and (4) every wavefront finds
-      // the k-th largest of those 8 k element keys, the threshold: an element is an outlier if its key reaches
-      // it.  Three barriers whatever k is, and no step where one thread works while the workgroup waits.
-      // Keys: magnitude above the reversed octet number resp. element index; 0 = nothing.
-      const uint32_t lane = (uint32_t)lane_id(), wave = tid / (uint32_t)kWave;
+  } else if (mode == kModeTopk) {
+    if (whole) {
+      // The segment is one group.  The threshold is the k-th largest key (magnitude above the reversed element index:
+      // unique, ties go to the lower index): an element is an outlier if its key reaches it.  Few keep k <= 8:
+      // topk_few; otherwise, and where too many octets come into question there, by rounds:
+      // topk_rounds.
       const uint32_t rounds = d.topk < g.cnt ? d.topk : g.cnt;  // at most 32
-      uint32_t okey[SL];
+      uint32_t limit = 0u;
+      if (rounds > 8u || !topk_few<SL>(g, sh, raw, omag, rounds, limit)) limit = topk_rounds<SL>(g, sh, raw, omag, rounds);  // uniform
 #pragma unroll
       for (int j = 0; j < SL; ++j) {
         const uint32_t o = tid + (uint32_t)j * kSegThreads;
-        okey[j] = o < g.octs ? (omag[j] << 16) | (0xFFFFu - o) : 0u;  // (elements that do not exist are zeros: they do not raise omag)
-      }
-      {  // (1)
-        uint32_t live[SL], cand = 0u;
-#pragma unroll
-        for (int j = 0; j < SL; ++j) live[j] = okey[j];
-        for (uint32_t r = 0; r < rounds; ++r) {  // uniform
-          uint32_t best = 0u;
-#pragma unroll
-          for (int j = 0; j < SL; ++j) best = live[j] > best ? live[j] : best;
-          const uint32_t w = wave_max_u32_scalar(best);
-#pragma unroll
-          for (int j = 0; j < SL; ++j) live[j] = live[j] == w ? 0u : live[j];
-          cand = lane == r ? w : cand;
-        }
-        if (lane < 32u) sh.a[wave * 32u + lane] = cand;
-        sh.b[tid] = 0u;  // the list of (3): 8 keys for each of up to 32 octets
-        if (tid == 0u) sh.head[0] = 0u;  // and the number of its entries in use
-      }
-      __syncthreads();
-      uint32_t least = 0u;  // the smallest key among the k best octets overall (0: there are fewer octets, all are taken)
-      {  // (2)
-        if (rounds <= 16u) {  // uniform: the first 16 keys of the four lists, one per lane
-          uint32_t c0 = sh.a[(lane >> 4) * 32u + (lane & 15u)];  // lane = 16 * wavefront + entry
-          for (uint32_t r = 0; r < rounds; ++r) {
-            least = wave_max_u32_scalar(c0);
-            c0 = c0 == least ? 0u : c0;
-          }
-        } else {
-          uint32_t c0 = sh.a[lane], c1 = sh.a[(uint32_t)kWave + lane];
-          for (uint32_t r = 0; r < rounds; ++r) {
-            least = wave_max_u32_scalar(c0 > c1 ? c0 : c1);
-            c0 = c0 == least ? 0u : c0;
-            c1 = c1 == least ? 0u : c1;
-          }
-        }
-      }
-      // (3): which entry of the list an octet gets does not matter, a counter in LDS hands them out
-#pragma unroll
-      for (int j = 0; j < SL; ++j) {
-        if (okey[j] != 0u && okey[j] >= least) {  // at most k octets of the workgroup
-          const uint32_t o = tid + (uint32_t)j * kSegThreads;
-          const uint32_t nv = octet_valid(g, o);
-          const uint32_t entry = atomicAdd(&sh.head[0], 1u) & 31u;  // (below 32 anyway: keys are unique)
-#pragma unroll
-          for (int e = 0; e < kOct; ++e)
-            sh.b[entry * (uint32_t)kOct + (uint32_t)e] =
-                (uint32_t)e < nv ? (ADACC_ELEM_MAG(raw[j], e) << 16) | (0xFFFFu - (o * (uint32_t)kOct + (uint32_t)e)) : 0u;
-        }
-      }
-      __syncthreads();
-      uint32_t limit = 0u;
-      {  // (4)
-        // (never 0: the octets of (2) hold at least `rounds` elements)
-        if (rounds <= 8u) {  // uniform: at most 64 keys, one per lane
-          uint32_t c = sh.b[lane];
-          for (uint32_t r = 0; r < rounds; ++r) {
-            limit = wave_max_u32_scalar(c);
-            c = c == limit ? 0u : c;
-          }
-        } else {
-          uint32_t c[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) c[k] = sh.b[(uint32_t)k * (uint32_t)kWave + lane];
-          for (uint32_t r = 0; r < rounds; ++r) {
-            const uint32_t m0 = c[0] > c[1] ? c[0] : c[1], m1 = c[2] > c[3] ? c[2] : c[3];
-            limit = wave_max_u32_scalar(m0 > m1 ? m0 : m1);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) c[k] = c[k] == limit ? 0u : c[k];
-          }
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < SL; ++j) {
-        if (okey[j] != 0u && ((omag[j] << 16) | 0xFFFFu) >= limit) {  // few octets get here
-          const uint32_t o = tid + (uint32_t)j * kSegThreads;
+        if (o < g.octs && ((omag[j] << 16) | 0xFFFFu) >= limit) {  // few octets get here
           const uint32_t nv = octet_valid(g, o);
 #pragma unroll
           for (int e = 0; e < kOct; ++e) {
@@ -401,7 +526,7 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
           }
         }
       }
-      __syncthreads();  // a, b are free again
+      __syncthreads();  // head, a, b are free again
     } else {
       // Several groups (of at most 2048 elements): the patterns go to LDS, a wavefront takes a group at a time
       // with the keys of its elements in registers (2, 8 or 32 per lane by the size of the groups), k rounds of a
@@ -472,11 +597,12 @@ __device__ __forceinline__ uint32_t segment_emit(const SegmentGeo& g, SegmentSha
                                                  uint32_t limit) {
   const uint32_t tid = threadIdx.x, wave = tid / (uint32_t)kWave;
   uint32_t* counts = sh.head + 8u;  // [slice][wavefront]
+  forget_derived<SL>(raw);
   // outliers of each of this wavefront's octet slices (element order is slice, wavefront, lane)
 #pragma unroll
   for (int j = 0; j < SL; ++j) {
-    uint32_t c = 0u;
-    if (__builtin_amdgcn_ballot_w64(mask[j] != 0u) != 0ull) c = wave_sum_u32(__builtin_popcount(mask[j]));
+    uint32_t c = lanes_where(mask[j] != 0u);
+    if (c != 0u && __builtin_amdgcn_ballot_w64((mask[j] & (mask[j] - 1u)) != 0u) != 0ull) c = wave_sum_u32(__builtin_popcount(mask[j]));
     if (lane_id() == 0) counts[(uint32_t)j * kSegWaves + wave] = c;
   }
   __syncthreads();
@@ -492,6 +618,7 @@ __device__ __forceinline__ uint32_t segment_emit(const SegmentGeo& g, SegmentSha
   if (total != 0u) {  // uniform
 #pragma unroll
     for (int j = 0; j < SL; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
       const uint64_t any = __builtin_amdgcn_ballot_w64(mask[j] != 0u);
       if (any == 0ull) continue;  // uniform
       const bool sparse = __builtin_amdgcn_ballot_w64((mask[j] & (mask[j] - 1u)) != 0u) == 0ull;
@@ -519,56 +646,51 @@ __device__ __forceinline__ uint32_t segment_emit(const SegmentGeo& g, SegmentSha
 // ---- a6 .. a8: scales (offsets) of the quantisation groups and the codes of the thread's octets, from which
 // outliers and values that are not finite are gone
 
-// a7 / a8 for the thread's octet j = octet o of the segment, in group grp (of the segment), whose extremes are
-// known: gm (symmetric: the largest magnitude) or the keys hi, lo (asymmetric).  Everything but the stores also
-// for an octet that does not exist.
+// Where a segment's codes and scales go: uniform bases, so that an octet's addresses are 32-bit offsets
+struct SegmentOut {
+  uint8_t* codes;
+  float* scales;
+  float* zp;
+};
+// a7 / a8 for the thread's octet o of the segment, in group grp (of the segment), whose extremes are known: gm
+// (symmetric: the largest magnitude) or the keys hi, lo (asymmetric).  here: the octet exists (else everything but the
+// stores is done); leads: it writes its group's scale
 template <int BITS, bool ASYM>
-__device__ __forceinline__ void octet_quantise(const TensorDesc& d, const SegmentGeo& g, const uint32_t (&oct)[4], uint32_t o,
-                                               uint32_t grp, uint32_t opg, uint64_t first_group, uint32_t gm, int32_t hi,
-                                               int32_t lo) {
-  constexpr int Q = 1 << (BITS - 1);
+__device__ __forceinline__ void octet_quantise(const TensorDesc& d, const SegmentGeo& g, const SegmentOut& out, const uint32_t (&oct)[4],
+                                               uint32_t o, bool here, uint32_t grp, bool leads, uint32_t gm, int32_t hi, int32_t lo) {
+  __builtin_amdgcn_sched_barrier(0);  // one octet after the other: interleaving them costs the registers of a wavefront
   float scl, inv, off = 0.0f;
   if constexpr (!ASYM) scale_sym_clean(d, mag_bits32(gm), scl, inv);
   else group_scale<true>(d, 0u, hi, lo, scl, inv, off);
-  uint32_t c[kOct];
+  float p[kOct];
 #pragma unroll
-  for (int e = 0; e < kOct; ++e) {
-    const float y = ADACC_ELEM_F32(oct, e);
-    c[e] = code_bits<Q, ASYM>(ASYM ? y - off : y, inv);  // symmetric codes cannot pass the lower bound
-  }
-  uint2 w8 = make_uint2(0u, 0u);
-  uint32_t w4 = 0u;
-  if constexpr (BITS == 8) {
-    w8.x = pack_bytes4(c[0], c[1], c[2], c[3]);
-    w8.y = pack_bytes4(c[4], c[5], c[6], c[7]);
-  } else {
-    w4 = pack_nibbles8(c);
-  }
-  if (o < g.octs) {
-    if (grp * opg == o) {  // the group's first octet
-      d.scales[first_group + grp] = scl;
-      if constexpr (ASYM) d.zp[first_group + grp] = off;
+  for (int e = 0; e < kOct; ++e) p[e] = __fmul_rn(ASYM ? ADACC_ELEM_F32(oct, e) - off : ADACC_ELEM_F32(oct, e), inv);
+  uint32_t w[2];
+  pack_codes<BITS, ASYM>(p, w);
+  if (here) {
+    if (leads) {
+      out.scales[grp] = scl;
+      if constexpr (ASYM) out.zp[grp] = off;
     }
-    const uint64_t e0 = g.first_elem + (uint64_t)o * kOct;
     const uint32_t nv = g.full ? (uint32_t)kOct : octet_valid(g, o);
     if constexpr (BITS == 8) {
       if (nv == (uint32_t)kOct) {
-        ADACC_STORE8(d.codes + e0, w8);
+        ADACC_STORE8(out.codes + o * 8u, make_uint2(w[0], w[1]));
       } else {  // the tensor's ragged end, byte by byte
 #pragma unroll
         for (int e = 0; e < kOct - 1; ++e)
-          if ((uint32_t)e < nv) d.codes[e0 + e] = (uint8_t)((e < 4 ? w8.x : w8.y) >> (8 * (e & 3)));
+          if ((uint32_t)e < nv) out.codes[o * 8u + (uint32_t)e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
       }
     } else {
       if (nv == (uint32_t)kOct) {
-        ADACC_STORE4(d.codes + (e0 >> 1), w4);
+        ADACC_STORE4(out.codes + o * 4u, w[0]);
       } else {  // an odd end: the high nibble of the last byte is 0
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           if ((uint32_t)(2 * b) < nv) {
-            uint32_t v = (w4 >> (8 * b)) & 0xFFu;
+            uint32_t v = (w[0] >> (8 * b)) & 0xFFu;
             if ((uint32_t)(2 * b + 1) >= nv) v &= 0x0Fu;
-            d.codes[(e0 >> 1) + b] = (uint8_t)v;
+            out.codes[o * 4u + (uint32_t)b] = (uint8_t)v;
           }
         }
       }
@@ -606,6 +728,9 @@ __device__ __forceinline__ void segment_quantise(const TensorDesc& d, const Segm
   const uint32_t tid = threadIdx.x;
   const uint32_t opg = d.gq / (uint32_t)kOct;
   const uint64_t first_group = g.first_elem / d.gq;
+  const SegmentOut out{d.codes + g.first_elem * BITS / 8, d.scales + first_group, d.zp + first_group};
+  // octet j of every thread exists (uniform); else the thread has to look
+  auto exists = [&](int j, uint32_t o) { return ((uint32_t)j + 1u) * kSegThreads <= g.octs || o < g.octs; };
   if ((opg & (opg - 1u)) == 0u && opg <= (uint32_t)kWave) {  // uniform
     // A group of 1, 2, 4, .. 64 octets is as many adjacent lanes of one wavefront (the segment starts on a group,
     // and 256 octets are whole groups): the extremes meet by the xor butterfly, in registers.  An octet that does
@@ -616,7 +741,7 @@ __device__ __forceinline__ void segment_quantise(const TensorDesc& d, const Segm
       const uint32_t o = tid + (uint32_t)j * kSegThreads;
       if constexpr (!ASYM) {
         const uint32_t gm = lanes_reduce_lg(omag[j], lg, OpUMax());  // (zeros cannot raise the maximum)
-        octet_quantise<BITS, false>(d, g, raw[j], o, o >> lg, opg, first_group, gm, 0, 0);
+        octet_quantise<BITS, false>(d, g, out, raw[j], o, exists(j, o), o >> lg, true, gm, 0, 0);  // (the same value from all lanes of a group)
       } else {
         int32_t hi, lo;
         octet_extreme_keys(g, raw[j], o, hi, lo);
@@ -624,7 +749,7 @@ __device__ __forceinline__ void segment_quantise(const TensorDesc& d, const Segm
         lo = o < g.octs ? lo : (int32_t)0x7FFFFFFF;
         hi = lanes_reduce_lg(hi, lg, OpIMax());
         lo = lanes_reduce_lg(lo, lg, OpIMin());
-        octet_quantise<BITS, true>(d, g, raw[j], o, o >> lg, opg, first_group, 0u, hi, lo);
+        octet_quantise<BITS, true>(d, g, out, raw[j], o, exists(j, o), o >> lg, true, 0u, hi, lo);
       }
     }
     return;
@@ -665,8 +790,10 @@ __device__ __forceinline__ void segment_quantise(const TensorDesc& d, const Segm
       }
     }
 #pragma unroll
-    for (int j = 0; j < SL; ++j)
-      octet_quantise<BITS, ASYM>(d, g, raw[j], tid + (uint32_t)j * kSegThreads, 0u, opg, first_group, gm, hi, lo);
+    for (int j = 0; j < SL; ++j) {
+      const uint32_t o = tid + (uint32_t)j * kSegThreads;
+      octet_quantise<BITS, ASYM>(d, g, out, raw[j], o, exists(j, o), 0u, o == 0u, gm, hi, lo);
+    }
     return;
   }
   // Other groups: one word (two) per octet to LDS (an octet that does not exist writes a word that nobody reads) ..
@@ -700,8 +827,8 @@ __device__ __forceinline__ void segment_quantise(const TensorDesc& d, const Segm
     const uint32_t o = tid + (uint32_t)j * kSegThreads;
     uint32_t grp = group_of(o, recip);  // (an octet that does not exist takes the last group's values)
     grp = grp < last_grp ? grp : last_grp;
-    if constexpr (!ASYM) octet_quantise<BITS, false>(d, g, raw[j], o, grp, opg, first_group, sh.g0[grp], 0, 0);
-    else octet_quantise<BITS, true>(d, g, raw[j], o, grp, opg, first_group, 0u, (int32_t)sh.g0[grp], (int32_t)sh.g1[grp]);
+    if constexpr (!ASYM) octet_quantise<BITS, false>(d, g, out, raw[j], o, exists(j, o), grp, grp * opg == o, sh.g0[grp], 0, 0);
+    else octet_quantise<BITS, true>(d, g, out, raw[j], o, exists(j, o), grp, grp * opg == o, 0u, (int32_t)sh.g0[grp], (int32_t)sh.g1[grp]);
   }
 }
 
@@ -718,7 +845,7 @@ __device__ __forceinline__ const TensorDesc& descriptor_again() {
 
 // One segment (d.tile_elems elements, the last one of the tensor may be short), loaded, its outliers known.
 // d: the kernel's first argument
-template <int SL>
+template <int SL, int KIND>
 __device__ __forceinline__ SegmentGeo load_and_select(const TensorDesc& d, SegmentShared& sh, uint32_t seg, uint32_t (&raw)[SL][4],
                                                       uint32_t (&omag)[SL], uint32_t (&mask)[SL]) {
   SegmentGeo g;
@@ -730,8 +857,8 @@ __device__ __forceinline__ SegmentGeo load_and_select(const TensorDesc& d, Segme
   segment_load(d, g, raw);
 #pragma unroll
   for (int j = 0; j < SL; ++j) omag[j] = octet_magnitude(raw[j]);
-  if (d.mode != kModeNone) {
-    segment_select(descriptor_again(), g, sh, raw, omag, mask);
+  if (KIND == kSegAny ? d.mode != kModeNone : KIND != (int)kModeNone) {
+    segment_select<SL, KIND>(descriptor_again(), g, sh, raw, omag, mask);
   } else {
 #pragma unroll
     for (int j = 0; j < SL; ++j) mask[j] = 0u;
@@ -742,12 +869,12 @@ __device__ __forceinline__ SegmentGeo load_and_select(const TensorDesc& d, Segme
   return g;
 }
 
-template <int SL>
+template <int SL, int KIND>
 __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentShared& sh, uint32_t seg, uint32_t epoch) {
   const uint32_t tid = threadIdx.x;
   uint32_t raw[SL][4], mask[SL], omag[SL];
-  const SegmentGeo g = load_and_select<SL>(d, sh, seg, raw, omag, mask);
-  if (d.mode == kModeTopk) {
+  const SegmentGeo g = load_and_select<SL, KIND>(d, sh, seg, raw, omag, mask);
+  if constexpr (KIND == (int)kModeTopk || KIND == kSegTopkWhole) {
     const uint32_t gps = d.tile_elems / d.gs;  // groups of a whole segment
     const uint32_t pos0 = seg * gps * d.topk;
     const uint32_t whole = g.cnt / d.gs, rest = g.cnt - whole * d.gs;
@@ -763,7 +890,7 @@ __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentSha
         d.status[0] = end; d.status[1] = end > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u;
       }
     }
-  } else if (d.mode != kModeNone) {
+  } else if constexpr (KIND != (int)kModeNone) {
     const SlotSink sink{d.slot + (uint64_t)seg * (uint64_t)kSlot, (uint32_t)g.first_elem};
     const uint32_t total = segment_emit(g, sh, raw, mask, sink, 0u, (uint32_t)kSlot);
     if (tid == 0u) d.cnt[seg] = total;
@@ -771,9 +898,11 @@ __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentSha
     d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u;
   }
   const TensorDesc& again = descriptor_again();
+  forget_derived<SL>(raw);  // (nothing widened for the selection is kept for the codes)
   // a5: from here on the outliers, and every value that is not finite, count as zero
 #pragma unroll
   for (int j = 0; j < SL; ++j) {
+    __builtin_amdgcn_sched_barrier(0);
     if (mask[j] != 0u) {
       clear_elements(raw[j], mask[j]);
       omag[j] = octet_magnitude(raw[j]);
@@ -788,13 +917,13 @@ __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentSha
 
 // wavefronts per SIMD (= workgroups per CU) the registers are held to: the kernel is a chain of memory and LDS
 // round trips with barriers between, which only other resident workgroups can fill
-template <int SL>
-constexpr int generic_min_waves() { return SL <= 2 ? 8 : SL <= 4 ? 6 : SL <= 6 ? 4 : 3; }
-template <int SL>
-__global__ __launch_bounds__(kSegThreads, (generic_min_waves<SL>())) void compress_generic_kernel(TensorDesc d, uint32_t epoch) {
+template <int SL, int KIND>
+constexpr int generic_min_waves() { return SL <= 4 ? 8 : SL <= 6 ? 5 : 4; }
+template <int SL, int KIND>
+__global__ __launch_bounds__(kSegThreads, (generic_min_waves<SL, KIND>())) void compress_generic_kernel(TensorDesc d, uint32_t epoch) {
   extern __shared__ __attribute__((aligned(16))) unsigned char segment_lds[];
   SegmentShared sh = segment_shared<SL>(segment_lds, d.tile_elems, d.gq);
-  compress_segment<SL>(d, sh, blockIdx.x, epoch);
+  compress_segment<SL, KIND>(d, sh, blockIdx.x, epoch);
 }
 
 // The placement of kPlaceSegments segments, and those that no slot held once more from the source, the whole workgroup
@@ -815,7 +944,7 @@ __global__ __launch_bounds__(kSegThreads, SL <= 4 ? 4 : 2) void place_generic_ke
     const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j);
     if (n <= room) continue;  // uniform over the workgroup
     uint32_t raw[SL][4], mask[SL], omag[SL];
-    const SegmentGeo g = load_and_select<SL>(d, sh, p.first + j, raw, omag, mask);
+    const SegmentGeo g = load_and_select<SL, kSegAny>(d, sh, p.first + j, raw, omag, mask);
     const uint32_t pos0 = p.base + (uint32_t)__builtin_amdgcn_readlane((int)p.excl, (int)j), end = pos0 + n;
     segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
   }

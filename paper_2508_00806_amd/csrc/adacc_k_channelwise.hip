@@ -149,7 +149,6 @@ __device__ __forceinline__ Strip strip_of(const ChannelwiseDesc& c) {
 // ---- step 3: code = clip(round(x * (D / max_h))), packed, in the tensor's own order
 template <int BITS>
 __global__ __launch_bounds__(kThreads) void channelwise_quantise_kernel(ChannelwiseDesc c) {
-  constexpr int Q = 1 << (BITS - 1);
   const Strip s = strip_of<kOct>(c);
   if (!s.live) return;
   const float4 i0 = *reinterpret_cast<const float4*>(c.inv + s.col);
@@ -166,22 +165,18 @@ __global__ __launch_bounds__(kThreads) void channelwise_quantise_kernel(Channelw
     for (uint32_t i = 0; i < 4u; ++i) {
       if (r + i >= s.rows) break;
       const uint32_t w[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
-      uint32_t code[kOct];
+      float p[kOct];
 #pragma unroll
       for (int e = 0; e < kOct; ++e) {
         float x = ADACC_ELEM_F32(w, e);
         if (is_nonfinite(x)) x = 0.0f;  // counts as zero
-        code[e] = code_bits<Q>(x, iv[e]);
+        p[e] = __fmul_rn(x, iv[e]);
       }
+      uint32_t o[2];
+      pack_codes<BITS, false>(p, o);
       const size_t e0 = s.first + (size_t)(r + i) * c.hidden;
-      if constexpr (BITS == 8) {
-        uint2 o;
-        o.x = pack_bytes4(code[0], code[1], code[2], code[3]);
-        o.y = pack_bytes4(code[4], code[5], code[6], code[7]);
-        ADACC_STORE8(c.codes + e0, o);
-      } else {
-        ADACC_STORE4(c.codes + (e0 >> 1), pack_nibbles8(code));
-      }
+      if constexpr (BITS == 8) ADACC_STORE8(c.codes + e0, make_uint2(o[0], o[1]));
+      else ADACC_STORE4(c.codes + (e0 >> 1), o[0]);
     }
   }
 }

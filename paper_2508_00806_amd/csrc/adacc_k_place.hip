@@ -28,7 +28,7 @@ __device__ __forceinline__ void compress_tail(const TensorDesc& whole, uint32_t 
   segment_load(d, g, raw);
 #pragma unroll
   for (int j = 0; j < kTailOcts; ++j) omag[j] = octet_magnitude(raw[j]);
-  segment_select(d, g, sh, raw, omag, mask);
+  segment_select<kTailOcts, kSegAny>(d, g, sh, raw, omag, mask);
 #pragma unroll
   for (int j = 0; j < kTailOcts; ++j)
     if (omag[j] >= kNonfiniteMag) mask[j] |= octet_nonfinite(raw[j]);
