@@ -164,6 +164,25 @@ __device__ __forceinline__ uint32_t wave_max_u32_scalar(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// The largest t < 2^15 with count(t) >= k (0 if there is none), count falling in t: bit by bit, uniform.
+template <class Count>
+__device__ __forceinline__ uint32_t kth_by_halving(uint32_t k, Count count) {
+  uint32_t t = 0u;
+#pragma unroll
+  for (int bit = 14; bit >= 0; --bit) {
+    const uint32_t c = t | (1u << bit);
+    t = count(c) >= k ? c : t;
+  }
+  return t;
+}
+// lanes for which v holds
+__device__ __forceinline__ uint32_t lanes_where(bool v) { return (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(v)); }
+// LDS takes a wavefront's accesses in order; this keeps the compiler from moving any of them across.
+__device__ __forceinline__ void lds_in_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // number of set bits of a wavefront mask in the lanes below this one
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -310,15 +329,14 @@ __device__ __forceinline__ void widen_row(const uint32_t (&oct)[4], float (&x)[k
 template <int BITS, bool ASYM, int E, bool STRIP>
 __device__ __forceinline__ void store_row(const TensorDesc& d, const TileGeo<E, STRIP>& g, int j,
                                           const float (&y)[kOct], float scl, float inv, float off) {
-  // The lane's offset is formed here, per row, from a copy the compiler knows nothing about: else it
-  // prepares the offsets (and the group numbers) of all rows ahead of the first row, for every
-  // group size the caller can be asked for, and keeps them in registers.
-  uint32_t lane_off = g.lane_off;
-  asm volatile("" : "+v"(lane_off));
-  const uint32_t eo = lane_off + g.row_offset(j);  // element offset from the tile's first element
-  unsigned char* cp = d.codes + g.base * BITS / 8;       // uniform
-  float* sp = d.scales + (g.base >> d.lgq);                // uniform
-  const uint32_t gl = eo >> d.lgq;
+  // What differs from row to row is uniform: the lanes' offsets are the same two registers for all rows.  (Groups are
+  // powers of two and rows multiples of 512, so that row and lane add up to the group's number separately.)
+  const uint32_t ro = g.row_offset(j);  // uniform
+  unsigned char* cp = d.codes + (g.base + ro) * BITS / 8;                       // uniform
+  float* sp = d.scales + ((g.base >> d.lgq) + (uint64_t)(ro >> d.lgq));        // uniform
+  float* zp = d.zp + ((g.base >> d.lgq) + (uint64_t)(ro >> d.lgq));
+  const uint32_t co = g.lane_off * (uint32_t)BITS / 8u;
+  const uint32_t gl = g.lane_off >> d.lgq;
   float p[kOct];
 #pragma unroll
   for (int e = 0; e < kOct; ++e) p[e] = __fmul_rn(y[e], inv);
@@ -327,17 +345,17 @@ __device__ __forceinline__ void store_row(const TensorDesc& d, const TileGeo<E, 
   const uint2 w8 = make_uint2(w[0], w[1]);
   const uint32_t w4 = w[0];
   if (g.full) {
-    if constexpr (BITS == 8) ADACC_STORE8(cp + eo, w8);
-    else ADACC_STORE4(cp + (eo >> 1), w4);
+    if constexpr (BITS == 8) ADACC_STORE8(cp + co, w8);
+    else ADACC_STORE4(cp + co, w4);
     sp[gl] = scl;
-    if constexpr (ASYM) (d.zp + (g.base >> d.lgq))[gl] = off;
+    if constexpr (ASYM) zp[gl] = off;
   } else {
-    const bool valid = eo < g.rem;
+    const bool valid = ro + g.lane_off < g.rem;
     unsigned char* scrap = reinterpret_cast<unsigned char*>(d.status) + 64;
-    if constexpr (BITS == 8) ADACC_STORE8(valid ? cp + eo : scrap, w8);
-    else ADACC_STORE4(valid ? cp + (eo >> 1) : scrap, w4);
+    if constexpr (BITS == 8) ADACC_STORE8(valid ? cp + co : scrap, w8);
+    else ADACC_STORE4(valid ? cp + co : scrap, w4);
     *(valid ? sp + gl : reinterpret_cast<float*>(scrap + 16)) = scl;
-    if constexpr (ASYM) *(valid ? d.zp + (g.base >> d.lgq) + gl : reinterpret_cast<float*>(scrap + 32)) = off;
+    if constexpr (ASYM) *(valid ? zp + gl : reinterpret_cast<float*>(scrap + 32)) = off;
   }
 }
 
@@ -750,31 +768,66 @@ __device__ __forceinline__ void row_magnitudes(const uint32_t (&raw)[E][4], uint
   }
 }
 
+// The same two rows to a word (row 2i in the low half of pm[i], row 2i + 1 in the high half): half the registers, and
+// the maxima of a lane's rows come two at a time.
+__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t,
+                            __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
+}
+template <int E>
+struct RowMags {
+  uint32_t pm[E / 2];
+  __device__ __forceinline__ uint32_t at(int j) const { return (j & 1) ? pm[j >> 1] >> 16 : pm[j >> 1] & 0xFFFFu; }
+  __device__ __forceinline__ void set(int j, uint32_t m) {
+    pm[j >> 1] = (j & 1) ? (pm[j >> 1] & 0x0000FFFFu) | (m << 16) : (pm[j >> 1] & 0xFFFF0000u) | m;
+  }
+  __device__ __forceinline__ void of(const uint32_t (&raw)[E][4]) {
+    constexpr uint32_t kMag2 = 0x7FFF7FFFu;
+#pragma unroll
+    for (int j = 0; j < E; j += 2) {
+      uint32_t m[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        m[i] = pk_max_u16(pk_max_u16(raw[j + i][0] & kMag2, raw[j + i][1] & kMag2),
+                          pk_max_u16(raw[j + i][2] & kMag2, raw[j + i][3] & kMag2));
+      pm[j / 2] = pk_max_u16(__builtin_amdgcn_perm(m[1], m[0], 0x05040100u), __builtin_amdgcn_perm(m[1], m[0], 0x07060302u));
+    }
+  }
+};
+
 // One group per tile, in straight-line code: t16 <- the k-th largest of the candidates the lanes offer, as
 // a 15-bit magnitude.  Returns (uniform) false when the tile holds an Inf or NaN.
 // Every lane offers its two largest row maxima: the threshold then fails to cut off exactly k
 // elements only when a lane holds three of the k largest, or two of them in one octet, or on a tie.
 template <int E>
-__device__ __forceinline__ bool topk_whole_threshold(const TensorDesc& d, const uint32_t (&rowmag)[E], uint32_t& t16) {
-  const uint32_t lane = (uint32_t)lane_id();
-  uint32_t m1 = rowmag[0], m2 = 0u;
+__device__ __forceinline__ bool topk_whole_threshold(const TensorDesc& d, const RowMags<E>& rowmag, uint32_t& t16) {
+  uint32_t p1 = rowmag.pm[0], p2 = 0u;  // the two largest of the even and of the odd rows
 #pragma unroll
-  for (int j = 1; j < E; ++j) {
-    const uint32_t lo = m1 < rowmag[j] ? m1 : rowmag[j];
-    m2 = m2 > lo ? m2 : lo;
-    m1 = m1 > rowmag[j] ? m1 : rowmag[j];
+  for (int i = 1; i < E / 2; ++i) {
+    p2 = pk_max_u16(p2, pk_min_u16(p1, rowmag.pm[i]));
+    p1 = pk_max_u16(p1, rowmag.pm[i]);
   }
+  const uint32_t a1 = p1 & 0xFFFFu, b1 = p1 >> 16, a2 = p2 & 0xFFFFu, b2 = p2 >> 16;
+  const uint32_t m1 = a1 > b1 ? a1 : b1;
+  uint32_t m2 = a1 > b1 ? b1 : a1;
+  m2 = m2 > a2 ? m2 : a2;
+  m2 = m2 > b2 ? m2 : b2;
   const bool finite = __builtin_amdgcn_ballot_w64(m1 >= kNonfiniteMag) == 0ull;
-  uint32_t cur = (m1 << 6) | lane;  // unique per lane: equal maxima are taken one after the other
-  uint32_t nxt = (m2 << 6) | lane;
-  uint32_t win = 0u;                // uniform
-  for (uint32_t r = 0; r < d.topk; ++r) {
-    win = wave_max_u32_scalar(cur);
-    const bool won = cur == win;
-    cur = won ? nxt : cur;
-    nxt = won ? 0u : nxt;
+  // The k-th largest of the 128.  Two rounds of a maximum over the wavefront take 22 vector instructions, more of them 11
+  // each; halving takes 30 comparisons whatever k is, and scalar work.  ([32768, 2048], k = 2: 31.1 us by rounds, 31.7 by
+  // halving; [8192, 4096], k = 4, is faster by halving.)
+  if (d.topk <= 2u) {  // uniform
+    const uint32_t lane = (uint32_t)lane_id();
+    uint32_t cur = (m1 << 6) | lane;  // unique per lane: equal maxima are taken one after the other
+    uint32_t win = wave_max_u32_scalar(cur);
+    if (d.topk == 2u) {
+      cur = cur == win ? (m2 << 6) | lane : cur;
+      win = wave_max_u32_scalar(cur);
+    }
+    t16 = win >> 6;
+  } else {
+    t16 = kth_by_halving(d.topk, [&](uint32_t t) { return lanes_where(m1 >= t) + lanes_where(m2 >= t); });
   }
-  t16 = win >> 6;
   return finite;
 }
 
@@ -1168,94 +1221,111 @@ __device__ __forceinline__ uint32_t topk_extract_by_keys(const TensorDesc& d, ui
   return total;
 }
 
-// The elements of one octet (that of lane `owner`, a uniform number) whose magnitude reaches t16 leave for
-// the sink, in index order from entry `pos` on, and are cleared in the owner's registers.  The octet is
-// broadcast through scalar registers and lanes 0..7 take one element each.  Returns their number (uniform).
-template <class Sink>
-__device__ __forceinline__ uint32_t extract_octet(uint32_t (&oct)[4], uint32_t owner, uint32_t t16, uint32_t first_index,
-                                                  const Sink& sink, uint32_t pos, uint32_t limit) {
-  const uint32_t lane = (uint32_t)lane_id();
-  const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)oct[0], (int)owner);
-  const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)oct[1], (int)owner);
-  const uint32_t w2 = (uint32_t)__builtin_amdgcn_readlane((int)oct[2], (int)owner);
-  const uint32_t w3 = (uint32_t)__builtin_amdgcn_readlane((int)oct[3], (int)owner);
-  const uint32_t e = lane & 7u;
-  const uint32_t lo = (e & 4u) ? w2 : w0;
-  const uint32_t hi = (e & 4u) ? w3 : w1;
-  const uint32_t word = (e & 2u) ? hi : lo;
-  const uint32_t pat = (e & 1u) ? word >> 16 : word & 0xFFFFu;
-  const bool hit = lane < 8u && (pat & 0x7FFFu) >= t16;
-  const uint32_t m8 = (uint32_t)__builtin_amdgcn_ballot_w64(hit);  // bit e: element e
-  if (hit) {
-    const uint32_t p = pos + __builtin_amdgcn_mbcnt_lo(m8, 0u);
-    if (p < limit) sink(p, first_index + e, pat);
-  }
-  if (lane == owner) clear_elements(oct, m8);
-  return (uint32_t)__builtin_popcount(m8);
-}
-
 // The extraction: finds the k largest, hands them to the sink, clears them in `raw`.  rowmag: the
 // lane's largest magnitude per row of what is left.  Returns the number of outliers (uniform).
+//
+// Only octets whose largest magnitude reaches the threshold of the lanes' maxima can hold any of the k: as a rule k of
+// them.  Up to 16 go to a list of the wavefront in LDS, in index order, all octets of a row at once; then a lane takes
+// an element (two beyond 8 octets) and the selection is two ballots: all that reach the threshold, if those are k, else
+// (equals at the k-th place, two of the largest in one octet) the k-th largest by halving and the lowest of its equals.
+// The outliers leave with one store, are zeroed in the list, and the octets' owners read them back.  (Before, octets
+// were taken one by one through scalar registers, and a tile with equals at the k-th place - one in 70 of bf16
+// rows - was read and decided again by keys, which took so long that a launch of 8192 tiles waited for the last of
+// them: 26 us, 21 us now.)
+struct TopkList {
+  uint4 oct[16];
+  uint32_t where[16];  // the octet's first element, in the tile
+};
 template <int E, bool STORE, class Sink>
-__device__ __forceinline__ uint32_t topk_extract(const TensorDesc& d, uint32_t (&raw)[E][4], uint32_t (&rowmag)[E],
+__device__ __forceinline__ uint32_t topk_extract(const TensorDesc& d, uint32_t (&raw)[E][4], RowMags<E>& rowmag,
                                                  uint32_t tile, const Sink& sink, uint32_t pos0, uint32_t limit) {
-  row_magnitudes<E>(raw, rowmag);
-  const uint32_t tile_first = tile * (uint32_t)(E * kRow);
-  uint32_t total = 0u;  // uniform: outliers found
-  bool done = false;    // uniform
-  if (d.topk <= 8u) {
-    uint32_t t16;
-    if (topk_whole_threshold<E>(d, rowmag, t16)) {  // false if the tile holds an Inf or a NaN
-      // Selection |x| >= t: it is the answer if exactly k elements pass.  Only octets whose largest magnitude
-      // reaches t can hold any; there are at most k of them if the selection is to stand, so they are
-      // taken one at a time (a constant tile, where every octet passes, goes straight to the keys).
-      uint64_t cand[E];
-      uint32_t octets = 0u;
+  __shared__ TopkList lists[kWavesPerWg];
+  rowmag.of(raw);
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t k = d.topk;
+  uint32_t t16;
+  if (k <= 8u && topk_whole_threshold<E>(d, rowmag, t16)) {  // false if the tile holds an Inf or a NaN
+    uint64_t cand[E];
+    uint32_t octets = 0u;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      cand[j] = __builtin_amdgcn_ballot_w64(rowmag.at(j) >= t16);
+      octets += (uint32_t)__builtin_popcountll(cand[j]);
+    }
+    if (octets <= 16u) {  // uniform (a constant tile, where every octet passes, is done by keys)
+      TopkList& list = lists[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];
+      uint16_t* elem = reinterpret_cast<uint16_t*>(list.oct);
+      uint32_t before = 0u;  // uniform
 #pragma unroll
       for (int j = 0; j < E; ++j) {
-        cand[j] = __builtin_amdgcn_ballot_w64(rowmag[j] >= t16);
-        octets += (uint32_t)__builtin_popcountll(cand[j]);
+        if (cand[j] == 0ull) continue;  // uniform
+        if (__builtin_amdgcn_inverse_ballot_w64(cand[j])) {
+          const uint32_t c = before + lanes_below(cand[j]);
+          list.oct[c] = make_uint4(raw[j][0], raw[j][1], raw[j][2], raw[j][3]);
+          list.where[c] = (uint32_t)(j * kRow) + lane * kOct;
+        }
+        before += (uint32_t)__builtin_popcountll(cand[j]);
       }
-      if (octets <= d.topk) {
-        // The outliers leave and are cleared as they are found; if in the end they were not k (two of
-        // the largest in one octet, a tie at the k-th place) the tile is read again and done by keys.
+      lds_in_order();
+      // elements `lane` and 64 + `lane` of the list (-1: not there)
+      const uint32_t pa = elem[lane], pb = elem[kWave + lane];
+      const int32_t ma = lane < octets * kOct ? (int32_t)(pa & 0x7FFFu) : -1;
+      const int32_t mb = lane + kWave < octets * kOct ? (int32_t)(pb & 0x7FFFu) : -1;
+      uint64_t hit_a = __builtin_amdgcn_ballot_w64(ma >= (int32_t)t16), hit_b = __builtin_amdgcn_ballot_w64(mb >= (int32_t)t16);
+      if ((uint32_t)(__builtin_popcountll(hit_a) + __builtin_popcountll(hit_b)) != k) {  // uniform
+        const int32_t t = (int32_t)kth_by_halving(k, [&](uint32_t c) { return lanes_where(ma >= (int32_t)c) + lanes_where(mb >= (int32_t)c); });
+        hit_a = __builtin_amdgcn_ballot_w64(ma > t);
+        hit_b = __builtin_amdgcn_ballot_w64(mb > t);
+        uint64_t eq_a = __builtin_amdgcn_ballot_w64(ma == t), eq_b = __builtin_amdgcn_ballot_w64(mb == t);
+        for (uint32_t n = (uint32_t)(__builtin_popcountll(hit_a) + __builtin_popcountll(hit_b)); n < k; ++n) {  // k <= 8 rounds
+          if (eq_a != 0ull) { hit_a |= eq_a & (0ull - eq_a); eq_a &= eq_a - 1ull; }
+          else { hit_b |= eq_b & (0ull - eq_b); eq_b &= eq_b - 1ull; }
+        }
+      }
+      const uint32_t tile_first = tile * (uint32_t)(E * kRow);
+      if (__builtin_amdgcn_inverse_ballot_w64(hit_a)) {
+        const uint32_t pos = pos0 + lanes_below(hit_a);
+        if (pos < limit) sink(pos, tile_first + list.where[lane >> 3] + (lane & 7u), pa);
+        if constexpr (STORE) elem[lane] = 0;
+      }
+      if (hit_b != 0ull) {  // uniform
+        if (__builtin_amdgcn_inverse_ballot_w64(hit_b)) {
+          const uint32_t pos = pos0 + (uint32_t)__builtin_popcountll(hit_a) + lanes_below(hit_b);
+          if (pos < limit) sink(pos, tile_first + list.where[8u + (lane >> 3)] + (lane & 7u), pb);
+          if constexpr (STORE) elem[kWave + lane] = 0;
+        }
+      }
+      if constexpr (STORE) {
+        lds_in_order();
+        before = 0u;
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          uint64_t todo = cand[j];
-          if (todo == 0ull) continue;  // uniform
-          do {
-            const uint32_t owner = (uint32_t)__builtin_ctzll(todo);
-            todo &= todo - 1ull;
-            total += extract_octet(raw[j], owner, t16, tile_first + (uint32_t)(j * kRow) + owner * kOct, sink, pos0 + total, limit);
-          } while (todo != 0ull);
-          rowmag[j] = octet_magnitude(raw[j]);
+          if (cand[j] == 0ull) continue;  // uniform
+          if (__builtin_amdgcn_inverse_ballot_w64(cand[j])) {
+            const uint4 v = list.oct[before + lanes_below(cand[j])];
+            raw[j][0] = v.x; raw[j][1] = v.y; raw[j][2] = v.z; raw[j][3] = v.w;
+            rowmag.set(j, octet_magnitude(raw[j]));
+          }
+          before += (uint32_t)__builtin_popcountll(cand[j]);
         }
-        done = total == d.topk;
       }
+      return k;
     }
   }
-  if (!done) {
-    if (total != 0u) {
-      // some outliers have left and are cleared already: start over from the source, once the
-      // stores of the first attempt are complete (the second attempt writes the same entries)
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      load_tile<E, true>(d, tile, raw);
-    }
-    total = topk_extract_by_keys<E>(d, raw, tile, sink, pos0, limit);
-    if constexpr (STORE) row_magnitudes<E>(raw, rowmag);
-  }
+  const uint32_t total = topk_extract_by_keys<E>(d, raw, tile, sink, pos0, limit);
+  if constexpr (STORE) rowmag.of(raw);
   return total;
 }
 
 template <int BITS, bool ASYM, int E, int LANES>
 __device__ __forceinline__ void encode_clean_rows(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4],
-                                                  const uint32_t (&rowmag)[E]) {
+                                                  const RowMags<E>& rowmag) {
 #pragma unroll
   for (int j = 0; j < E; ++j) {
     // one row after the other: the compiler shall not start on the next rows to hide this row's
     // latencies (other wavefronts do that), it would pay for it with the registers of a wavefront
     __builtin_amdgcn_sched_barrier(0);
-    encode_clean_row<BITS, ASYM, E, LANES>(d, g, j, raw[j], mag_bits32(rowmag[j]));
+    encode_clean_row<BITS, ASYM, E, LANES>(d, g, j, raw[j], mag_bits32(rowmag.at(j)));
   }
 }
 
@@ -1263,7 +1333,7 @@ template <int BITS, bool ASYM, int E, bool STORE, class Sink>
 __device__ __forceinline__ uint32_t encode_tile_topk_whole(const TensorDesc& d, const TileGeo<E>& g,
                                                            uint32_t (&raw)[E][4], uint32_t tile, const Sink& sink,
                                                            uint32_t pos0, uint32_t limit) {
-  uint32_t rowmag[E];
+  RowMags<E> rowmag;
   const uint32_t total = topk_extract<E, STORE>(d, raw, rowmag, tile, sink, pos0, limit);
   if constexpr (STORE) {
     switch (d.lgq) {  // one switch per tile selects straight-line code for the group size
@@ -1531,7 +1601,7 @@ __device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t
       uint16_t* list = sh.list[wave];
       for (uint32_t k = 0; __builtin_amdgcn_ballot_w64(k < in_slot) != 0ull; ++k)  // at most kSlot rounds
         if (k < in_slot) list[at + k] = (uint16_t)(lane << 8 | k);
-      __builtin_amdgcn_wave_barrier();  // LDS takes a wavefront's accesses in order
+      lds_in_order();
       for (uint32_t r0 = 0u; r0 < total; r0 += 4u * (uint32_t)kWave) {  // uniform
         uint32_t rec[4], pos[4], tile[4];
 #pragma unroll

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "adacc_common.hpp"
+#include "adacc_compress.hpp"
 #include "adacc_dtype.hpp"
 
 namespace adacc {
@@ -269,16 +270,16 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
       uint4* mine = reinterpret_cast<uint4*>(box[lane]);
 #pragma unroll
       for (int i = 0; i < E / 4; ++i) mine[i] = make_uint4(0u, 0u, 0u, 0u);
-      __builtin_amdgcn_wave_barrier();  // LDS takes a wavefront's accesses in order: nothing may be moved across
+      lds_in_order();
       if (valid) box[(rel / V) & 63u][rel / W] = kMailFull | ((rel % V) << 16) | (o_val & 0xFFFFu);
-      __builtin_amdgcn_wave_barrier();
+      lds_in_order();
       uint32_t m[E];
 #pragma unroll
       for (int i = 0; i < E / 4; ++i) {
         const uint4 mail = mine[i];
         m[4 * i] = mail.x; m[4 * i + 1] = mail.y; m[4 * i + 2] = mail.z; m[4 * i + 3] = mail.w;
       }
-      __builtin_amdgcn_wave_barrier();  // the next piece of this wavefront clears the mailbox only after this
+      lds_in_order();  // the next piece of this wavefront clears the mailbox only after this
 #pragma unroll
       for (int j = 0; j < E; ++j)
         store_row_values<BITS, ASYM, F32>(d, lane_base + (uint64_t)(j * W), rc[j], MailPatch<F32>{m[j]});
@@ -286,7 +287,7 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
     }
     uint16_t* picture = reinterpret_cast<uint16_t*>(shared.picture[w]);
     shared.bits[w][lane] = 0u;
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();
     for (uint32_t c = p0;;) {  // uniform
       if (valid) {
         picture[rel] = (uint16_t)o_val;
@@ -301,7 +302,7 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
         valid = rel < (uint32_t)kPiece;
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();
     const uint32_t mine = shared.bits[w][lane];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
@@ -322,7 +323,7 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
         store_row_values<BITS, ASYM, F32>(d, e0, rc[j], NoPatch{});
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    lds_in_order();
     return;
   }
   if (complete) {

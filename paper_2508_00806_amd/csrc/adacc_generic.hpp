@@ -342,17 +342,6 @@ __device__ __forceinline__ uint32_t topk_rounds(const SegmentGeo& g, SegmentShar
 // octets are left, a constant segment for one.
 // (The rounds, k dependent maxima over the wavefront three times over, took 60 of the 103 us that [8192, 11008] with
 // k = 8 took; 88 us with the halving.)
-template <class Count>
-__device__ __forceinline__ uint32_t kth_by_halving(uint32_t k, Count count) {  // the largest t < 2^15 with count(t) >= k, or 0
-  uint32_t t = 0u;
-#pragma unroll
-  for (int bit = 14; bit >= 0; --bit) {
-    const uint32_t c = t | (1u << bit);
-    t = count(c) >= k ? c : t;
-  }
-  return t;
-}
-__device__ __forceinline__ uint32_t lanes_where(bool v) { return (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(v)); }
 template <int SL>
 __device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh, const uint32_t (&raw)[SL][4],
                                          const uint32_t (&omag)[SL], uint32_t k, uint32_t& limit) {

@@ -1,4 +1,4 @@
-"""TOPK over a segment that is one group: the threshold by halving, where it can go wrong - several of the k in one octet,
+"""TOPK over a tile or a segment that is one group: the threshold by halving, where it can go wrong - several of the k in one octet,
 equals at the k-th place in one octet, one wavefront or all over the segment, more octets in question than a wavefront
 looks at (a constant segment), values that are not finite, fewer elements than k."""
 import pytest
@@ -24,6 +24,10 @@ def rows(kind, gs, g):
     elif kind == "zeros":
         x[:] = 0.0
         x[gs // 2] = 1e-3
+    elif kind in ("9", "16", "17"):  # octets with equals, the last of them with two
+        at = 8 * torch.randperm(gs // 8, generator=g)[:int(kind)]
+        x[at] = 2.0
+        x[at[-1] + 5] = 2.0
     elif kind == "sixty_four_octets":
         x[8 * torch.randperm(gs // 8, generator=g)[:64]] = 2.0
     elif kind == "sixty_five_octets":
@@ -35,11 +39,11 @@ def rows(kind, gs, g):
 
 
 @pytest.mark.parametrize("k", [1, 2, 3, 5, 8, 9])
-@pytest.mark.parametrize("gs", [5160, 8192, 11008, 16384])
+@pytest.mark.parametrize("gs", [2048, 4096, 5160, 8192, 11008, 16384])
 def test_threshold_of_a_row(k, gs):
     g = torch.Generator().manual_seed(k * gs)
     kinds = ["random", "one_octet", "equals_in_an_octet", "equals_all_over", "constant", "zeros", "sixty_four_octets",
-             "sixty_five_octets", "not_finite", "random"]
+             "sixty_five_octets", "not_finite", "9", "16", "17", "random"]
     for dtype, end in ((torch.bfloat16, 5), (torch.float16, 1001)):
         x = torch.cat([rows(kind, gs, g) for kind in kinds] + [rows("equals_all_over", gs, g)[:end]]).to(dtype)
         print(f"[topk row] k={k} gs={gs} {dtype}", flush=True)
