@@ -242,9 +242,12 @@ def _nbytes(t):
 
 
 def _stream(stream):
+    """The HIP stream a call goes to: the given one, or the current stream of the current device."""
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
     import torch
+    if torch.cuda.is_initialized():  # the handle without the Stream object around it: 0.3 instead of 2.5 us a call
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 

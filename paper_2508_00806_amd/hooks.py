@@ -18,8 +18,8 @@ import dataclasses
 
 import torch
 
-from . import (DTYPE_BF16, DTYPE_F16, AdaccError, ChannelMethod, Method, KIND_NOOP, OUTLIER_NONE, alloc_blob, alloc_channel_blob,
-               alloc_channel_workspace, alloc_workspace, channel_compress, channel_compressed_bytes,
+from . import (DTYPE_BF16, DTYPE_F16, AdaccError, ChannelMethod, Method, KIND_NOOP, OUTLIER_NONE, alloc_channel_workspace,
+               alloc_workspace, channel_compress, channel_compressed_bytes,
                channel_decompress, channel_layout_of, channel_workspace_bytes, compress, compressed_bytes, decompress,
                layout_of, mask_pack, mask_packed_bytes, mask_unpack, workspace_bytes)
 
@@ -102,11 +102,12 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
     def _pack_mask(self, t):
         numel = t.numel()
         rec = {"shape": tuple(t.shape), "numel": numel, "method": "mask", "events": {}}
-        ev = self._events(rec, "compress")
+        stream = torch.cuda.current_stream()
+        ev = self._events(rec, "compress", stream)
         bits = torch.empty(mask_packed_bytes(numel), dtype=torch.uint8, device=t.device)
-        mask_pack(t, bits, numel)
+        mask_pack(t, bits, numel, stream=stream)
         if ev:
-            ev[1].record()
+            ev[1].record(stream)
         self.records.append(rec)
         return _SavedMask(bits, t.shape, numel, rec)
 
@@ -125,38 +126,39 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         numel = t.numel()
         try:  # a shape the method can not take is no error of the training run: the tensor is retained
             if isinstance(m, ChannelMethod):
-                channel_layout_of(m, numel // t.shape[-1], t.shape[-1])
+                layout = channel_layout_of(m, numel // t.shape[-1], t.shape[-1])
             else:
-                layout_of(m, numel)
+                layout = layout_of(m, numel)
         except AdaccError as e:
             self.retained.append((tuple(t.shape), str(e)))
             return t
         rec = {"shape": tuple(t.shape), "numel": numel, "method": m, "events": {}}
-        ev = self._events(rec, "compress")
+        # the stream is looked up once: asking torch for it costs as much as a launch, and it is needed four times
+        stream = torch.cuda.current_stream()
+        ev = self._events(rec, "compress", stream)
+        blob = torch.empty(max(int(layout.total_bytes), 256), dtype=torch.uint8, device=t.device)
         if isinstance(m, ChannelMethod):
             hidden = t.shape[-1]
             tokens = numel // hidden
-            blob, layout = alloc_channel_blob(m, tokens, hidden, device=t.device)
             if self._cws is None or self._cws.numel() < channel_workspace_bytes(tokens, hidden):
                 self._cws = alloc_channel_workspace(tokens, hidden, device=t.device)
-            channel_compress(m, t, tokens, hidden, blob, self._cws)
+            channel_compress(m, t, tokens, hidden, blob, self._cws, stream=stream)
         else:
-            blob, layout = alloc_blob(m, numel, device=t.device)
             ws = None
             if m.outlier_mode != OUTLIER_NONE:
                 want = workspace_bytes(m, numel)
                 if self._ws is None or self._ws.c.bytes < want:
                     self._ws = alloc_workspace(want, device=t.device)
                 ws = self._ws
-            compress(m, t, blob, ws)
+            compress(m, t, blob, ws, stream=stream)
         if ev:
-            ev[1].record()
+            ev[1].record(stream)
         # the record keeps a host copy of the 16 status bytes, not the blob: the compressed activation is
         # freed as soon as autograd drops it
         rec["status"] = self._status.take()
         rec["status"].copy_(blob[layout.status_off:layout.status_off + 16].view(torch.int32), non_blocking=True)
         rec["status_ready"] = torch.cuda.Event()
-        rec["status_ready"].record()
+        rec["status_ready"].record(stream)
         if self.on_overflow == "retain" and self._lost(rec):
             rec["retained"] = True
             self.records.append(rec)
@@ -174,36 +176,42 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
     def _unpack(self, s):
         if isinstance(s, _SavedMask):
             out = torch.empty(s.shape, dtype=torch.bool, device=s.bits.device)
-            ev = self._events(s.record, "decompress")
-            mask_unpack(s.bits, out, s.numel)
+            stream = torch.cuda.current_stream()
+            ev = self._events(s.record, "decompress", stream)
+            mask_unpack(s.bits, out, s.numel, stream=stream)
             if ev:
-                ev[1].record()
+                ev[1].record(stream)
             return out
         if not isinstance(s, _Saved):
             return s
+        out = torch.empty(s.shape, dtype=torch.float16 if s.method.dtype == DTYPE_F16 else torch.bfloat16,
+                          device=s.blob.device)
+        stream = torch.cuda.current_stream()
+        ev = self._events(s.record, "decompress", stream)
+        if isinstance(s.method, ChannelMethod):
+            hidden = s.shape[-1]
+            channel_decompress(s.method, s.blob, s.numel // hidden, hidden, out, stream=stream)
+        else:
+            decompress(s.method, s.blob, out, stream=stream)
+        if ev:
+            ev[1].record(stream)
+        # The status is waited for when the restoration is already enqueued, so that the GPU has work while the host
+        # waits (a blob that does not hold its tensor is restored without harm, up to what fits), and before
+        # anybody sees the result.
         if self._lost(s.record):
+            s.record["events"].pop("decompress", None)
             m = s.method
             room = m.max_channels if isinstance(m, ChannelMethod) else m.max_outliers
             raise CompressedActivationLost(
                 f"saved activation of shape {tuple(s.shape)}: {s.record['status'][0].item()} outliers found, the method "
                 f"has room for {room}; raise max_outliers / max_channels or use on_overflow='retain'")
-        out = torch.empty(s.shape, dtype=torch.float16 if s.method.dtype == DTYPE_F16 else torch.bfloat16,
-                          device=s.blob.device)
-        ev = self._events(s.record, "decompress")
-        if isinstance(s.method, ChannelMethod):
-            hidden = s.shape[-1]
-            channel_decompress(s.method, s.blob, s.numel // hidden, hidden, out)
-        else:
-            decompress(s.method, s.blob, out)
-        if ev:
-            ev[1].record()
         return out
 
-    def _events(self, rec, key):
+    def _events(self, rec, key, stream):
         if not self.timing:
             return None
         ev = (torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
-        ev[0].record()
+        ev[0].record(stream)
         rec["events"][key] = ev
         return ev
 
