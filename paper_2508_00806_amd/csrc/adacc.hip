@@ -995,6 +995,7 @@ int adacc_channel_compress(const adacc_channel_method* method, const void* src, 
   fill_desc(&cp.quant, cp.numel, cp.plan, cp.quant_layout, src, blob, nullptr, 0, nullptr, &d);
   ChannelDesc c;
   fill_channel_desc(method, tokens, hidden, L, blob, &c);
+  d.status = c.status;  // (octets behind the matrix's end go to the unused part of this block; the plain blob's has the channel mask in its place)
   float* partial = static_cast<float*>(workspace);
   double* S = reinterpret_cast<double*>(static_cast<unsigned char*>(workspace) + channel_partial_bytes(cp.n_chunks, hidden));
   const bool half = cp.plan.half;

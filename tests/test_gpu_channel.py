@@ -158,3 +158,14 @@ def test_repeat_launches_give_the_same_blob():
         for k in ("codes", "scales", "ch_mask", "ch_base"):
             assert torch.equal(sec[k], blobs[0][1][k]), k
         assert torch.equal(sec["ch_idx"][:n_ch], blobs[0][1]["ch_idx"][:n_ch])
+
+
+@pytest.mark.parametrize("tokens,hidden,bits,asym", [(11, 1000, 4, 0), (3, 1416, 8, 1)])
+def test_mask_of_a_matrix_that_is_no_multiple_of_a_tile(tokens, hidden, bits, asym):
+    """Octets behind the end of the last tile are stored to a scrap area: not over the channel mask (bytes 64 .. 99 of
+    it, channels 512 .. 799)."""
+    x = torch.randn((tokens, hidden), generator=torch.Generator().manual_seed(hidden)).to(torch.bfloat16)
+    for ch in (5, 520, 575, 640, 671, 770):
+        x[:, ch] *= 60.0
+    oc, _ = run_channel_parity(x, bits, 8, asym)
+    assert oc.n_ch == 6
