@@ -358,7 +358,9 @@ __global__ __launch_bounds__(kThreads) void channel_compress_kernel(TensorDesc d
 // tokens.  Which of a lane's 8 channels are outlier channels, and where their values go in a token's
 // record, is the same for every token: looked up once, no table in LDS and no division per octet.  All
 // loads of the strip are issued first; its rows are then encoded four at a time like a tile's.
-constexpr uint32_t kChannelStripRows = 8;
+// (Eight tokens to a wavefront, two times four: [8192, 4096] int4 18.9 us, restored in 20.0; four: 16.7 and 18.1;
+// [2192, 5120] asymmetric, restored: 10.9 -> 8.6.)
+constexpr uint32_t kChannelStripRows = 4;
 
 template <int BITS, bool ASYM>
 __global__ __launch_bounds__(kThreads) void channel_compress_strip_kernel(TensorDesc d, ChannelDesc c) {
@@ -379,16 +381,14 @@ __global__ __launch_bounds__(kThreads) void channel_compress_strip_kernel(Tensor
     m = c.mask[(col0 + lane_off) >> 3];
     first = c.base[(col0 + lane_off) >> 3];
   }
-  constexpr uint32_t kHalf = kChannelStripRows / 2;
   const uint64_t base = (uint64_t)row0 * c.hidden + col0;  // uniform
   const uint16_t* sp = d.src + base;
-  uint32_t raw[2][kHalf][4];
+  uint32_t raw[kChannelStripRows][4];
 #pragma unroll
   for (uint32_t i = 0; i < kChannelStripRows; ++i) {  // rows past the end re-read the last one
     const uint32_t row = i < rows ? i : rows - 1u;
     const uint4 v = ADACC_LOAD16(sp + (row * c.hidden + lane_off));
-    raw[i / kHalf][i % kHalf][0] = v.x; raw[i / kHalf][i % kHalf][1] = v.y;
-    raw[i / kHalf][i % kHalf][2] = v.z; raw[i / kHalf][i % kHalf][3] = v.w;
+    raw[i][0] = v.x; raw[i][1] = v.y; raw[i][2] = v.z; raw[i][3] = v.w;
   }
   if (m != 0u) {  // the kept channels go out first, then they are cleared
     uint16_t* dst = c.ch_val + (size_t)row0 * n_ch + first;
@@ -399,38 +399,35 @@ __global__ __launch_bounds__(kThreads) void channel_compress_strip_kernel(Tensor
         while (todo != 0u) {
           const uint32_t e = (uint32_t)__builtin_ctz(todo);
           todo &= todo - 1u;
-          dst[(size_t)i * n_ch + r++] = (uint16_t)octet_half(raw[i / kHalf][i % kHalf], e);
+          dst[(size_t)i * n_ch + r++] = (uint16_t)octet_half(raw[i], e);
         }
       }
-      clear_elements(raw[i / kHalf][i % kHalf], m);
+      clear_elements(raw[i], m);
     });
   }
-  static_for<2>([&](auto Hc) {
-    constexpr uint32_t h = (uint32_t)decltype(Hc)::value;
-    if (rows >= (h + 1u) * kHalf) {  // uniform: four whole rows
-      TileGeo<(int)kHalf, true> g;
-      g.base = base + (uint64_t)(h * kHalf) * c.hidden;
-      g.rem = kHalf * (uint32_t)kRow;
-      g.lane_off = lane_off;
-      g.full = true;
-      g.stride = c.hidden;
-      encode_tile_rowwise<kModeNone, BITS, ASYM, (int)kHalf, true>(d, g, raw[h], 0u, NullSink{}, 0u, 0u);
-    } else {
-      static_for<(int)kHalf>([&](auto Ic) {  // the last tokens of the matrix, one row at a time
-        constexpr uint32_t i = (uint32_t)decltype(Ic)::value;
-        if (h * kHalf + i < rows) {
-          TileGeo<1, true> g;
-          g.base = base + (uint64_t)(h * kHalf + i) * c.hidden;
-          g.rem = (uint32_t)kRow;
-          g.lane_off = lane_off;
-          g.full = true;
-          g.stride = c.hidden;
-          const uint32_t one[1][4] = {{raw[h][i][0], raw[h][i][1], raw[h][i][2], raw[h][i][3]}};
-          encode_tile_rowwise<kModeNone, BITS, ASYM, 1, true>(d, g, one, 0u, NullSink{}, 0u, 0u);
-        }
-      });
-    }
-  });
+  if (rows == kChannelStripRows) {  // uniform
+    TileGeo<(int)kChannelStripRows, true> g;
+    g.base = base;
+    g.rem = kChannelStripRows * (uint32_t)kRow;
+    g.lane_off = lane_off;
+    g.full = true;
+    g.stride = c.hidden;
+    encode_tile_rowwise<kModeNone, BITS, ASYM, (int)kChannelStripRows, true>(d, g, raw, 0u, NullSink{}, 0u, 0u);
+  } else {
+    static_for<(int)kChannelStripRows>([&](auto Ic) {  // the last tokens of the matrix, one row at a time
+      constexpr uint32_t i = (uint32_t)decltype(Ic)::value;
+      if (i < rows) {
+        TileGeo<1, true> g;
+        g.base = base + (uint64_t)i * c.hidden;
+        g.rem = (uint32_t)kRow;
+        g.lane_off = lane_off;
+        g.full = true;
+        g.stride = c.hidden;
+        const uint32_t one[1][4] = {{raw[i][0], raw[i][1], raw[i][2], raw[i][3]}};
+        encode_tile_rowwise<kModeNone, BITS, ASYM, 1, true>(d, g, one, 0u, NullSink{}, 0u, 0u);
+      }
+    });
+  }
 }
 
 // ---- decompression: dequantise, put the outlier channels back, store.
@@ -469,74 +466,72 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
   const uint32_t lowest = m & (0u - m);
   const uint32_t rest = m ^ lowest;
 
-  for (uint32_t r = 0; r < rows; r += 4u) {
-    uint32_t cw[4][V * BITS > 32 ? 2 : 1];
-    float sc[4], zp[4];
-    uint32_t pre[4];
-    const uint16_t* src[4];
+  uint32_t cw[kChannelStripRows][V * BITS > 32 ? 2 : 1];
+  float sc[4], zp[kChannelStripRows];
+  uint32_t pre[kChannelStripRows];
+  const uint16_t* src[kChannelStripRows];
 #pragma unroll
-    for (uint32_t i = 0; i < 4u; ++i) {  // rows past the end re-read the last one
-      const uint32_t row = row0 + (r + i < rows ? r + i : rows - 1u);
-      const uint64_t e0 = (uint64_t)row * c.hidden + col;
-      const uint8_t* p = d.codes + e0 * BITS / 8;
-      if constexpr (V * BITS == 64) {
-        const uint2 w = *reinterpret_cast<const uint2*>(p);
-        cw[i][0] = w.x; cw[i][1] = w.y;
-      } else if constexpr (V * BITS == 32) {
-        cw[i][0] = *reinterpret_cast<const uint32_t*>(p);
-      } else {
-        cw[i][0] = *reinterpret_cast<const uint16_t*>(p);
-      }
-      const uint64_t grp = e0 >> d.lgq;
-      sc[i] = d.scales[grp];
-      zp[i] = 0.0f;
-      if constexpr (ASYM) zp[i] = d.zp[grp];
-      src[i] = c.ch_val + (size_t)row * n_ch + first;
-      pre[i] = m != 0u ? (uint32_t)src[i][0] : 0u;
+  for (uint32_t i = 0; i < kChannelStripRows; ++i) {  // rows past the end re-read the last one
+    const uint32_t row = row0 + (i < rows ? i : rows - 1u);
+    const uint64_t e0 = (uint64_t)row * c.hidden + col;
+    const uint8_t* p = d.codes + e0 * BITS / 8;
+    if constexpr (V * BITS == 64) {
+      const uint2 w = *reinterpret_cast<const uint2*>(p);
+      cw[i][0] = w.x; cw[i][1] = w.y;
+    } else if constexpr (V * BITS == 32) {
+      cw[i][0] = *reinterpret_cast<const uint32_t*>(p);
+    } else {
+      cw[i][0] = *reinterpret_cast<const uint16_t*>(p);
     }
+    const uint64_t grp = e0 >> d.lgq;
+    sc[i] = d.scales[grp];
+    zp[i] = 0.0f;
+    if constexpr (ASYM) zp[i] = d.zp[grp];
+    src[i] = c.ch_val + (size_t)row * n_ch + first;
+    pre[i] = m != 0u ? (uint32_t)src[i][0] : 0u;
+  }
 #pragma unroll
-    for (uint32_t i = 0; i < 4u; ++i) {
-      if (r + i >= rows) break;
-      const uint64_t e0 = (uint64_t)(row0 + r + i) * c.hidden + col;
-      int code[V];
-      unpack_codes<BITS, V>(cw[i], code);
-      float v[V];
+  for (uint32_t i = 0; i < kChannelStripRows; ++i) {
+    if (i >= rows) break;
+    const uint64_t e0 = (uint64_t)(row0 + i) * c.hidden + col;
+    int code[V];
+    unpack_codes<BITS, V>(cw[i], code);
+    float v[V];
 #pragma unroll
-      for (int e = 0; e < V; ++e) v[e] = ASYM ? __fmaf_rn((float)code[e], sc[i], zp[i]) : (float)code[e] * sc[i];
+    for (int e = 0; e < V; ++e) v[e] = ASYM ? __fmaf_rn((float)code[e], sc[i], zp[i]) : (float)code[e] * sc[i];
 
-      // the kept channels of this octet, as their stored 16-bit patterns (hold[e] valid where keep has bit e)
-      uint32_t keep = lowest, hold[V];
+    // the kept channels of this octet, as their stored 16-bit patterns (hold[e] valid where keep has bit e)
+    uint32_t keep = lowest, hold[V];
 #pragma unroll
-      for (int e = 0; e < V; ++e) hold[e] = lowest == (1u << e) ? pre[i] : 0u;
-      if (rest != 0u) {
+    for (int e = 0; e < V; ++e) hold[e] = lowest == (1u << e) ? pre[i] : 0u;
+    if (rest != 0u) {
 #pragma unroll
-        for (int e = 1; e < V; ++e)
-          if (rest & (1u << e)) {
-            const uint32_t rank = (uint32_t)__popc(m & ((1u << e) - 1u));
-            if (rank < n_ch - first) { hold[e] = src[i][rank]; keep |= 1u << e; }
-          }
-      }
+      for (int e = 1; e < V; ++e)
+        if (rest & (1u << e)) {
+          const uint32_t rank = (uint32_t)__popc(m & ((1u << e) - 1u));
+          if (rank < n_ch - first) { hold[e] = src[i][rank]; keep |= 1u << e; }
+        }
+    }
 
-      if constexpr (F32) {
-        if (keep != 0u) {
+    if constexpr (F32) {
+      if (keep != 0u) {
 #pragma unroll
-          for (int e = 0; e < V; ++e) v[e] = (keep & (1u << e)) ? widen_lo(hold[e]) : v[e];
-        }
-        float* p = reinterpret_cast<float*>(d.dst) + e0;
-        ADACC_STORE16(p, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
-      } else {
-        uint32_t w[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) w[k] = narrow_pair(v[2 * k], v[2 * k + 1]);
-        if (keep != 0u) {  // the kept values go in as they were stored, bit for bit (no conversion touches a NaN)
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            if (keep & (1u << (2 * k))) w[k] = (w[k] & 0xFFFF0000u) | hold[2 * k];
-            if (keep & (2u << (2 * k))) w[k] = (w[k] & 0x0000FFFFu) | (hold[2 * k + 1] << 16);
-          }
-        }
-        ADACC_STORE16(reinterpret_cast<uint16_t*>(d.dst) + e0, make_uint4(w[0], w[1], w[2], w[3]));
+        for (int e = 0; e < V; ++e) v[e] = (keep & (1u << e)) ? widen_lo(hold[e]) : v[e];
       }
+      float* p = reinterpret_cast<float*>(d.dst) + e0;
+      ADACC_STORE16(p, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
+    } else {
+      uint32_t w[kChannelStripRows];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) w[k] = narrow_pair(v[2 * k], v[2 * k + 1]);
+      if (keep != 0u) {  // the kept values go in as they were stored, bit for bit (no conversion touches a NaN)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (keep & (1u << (2 * k))) w[k] = (w[k] & 0xFFFF0000u) | hold[2 * k];
+          if (keep & (2u << (2 * k))) w[k] = (w[k] & 0x0000FFFFu) | (hold[2 * k + 1] << 16);
+        }
+      }
+      ADACC_STORE16(reinterpret_cast<uint16_t*>(d.dst) + e0, make_uint4(w[0], w[1], w[2], w[3]));
     }
   }
 }

@@ -121,7 +121,8 @@ __global__ __launch_bounds__(kThreads) void channelwise_fold_kernel(ChannelwiseD
 // tiles of 2048 consecutive elements a lane had to fetch 32 bytes of factors for every 16 bytes of input).
 // Units are numbered strip by strip within a block of tokens, so the four wavefronts of a workgroup take
 // four adjacent strips and the launch walks through memory front to back.
-constexpr uint32_t kStripRows = 8;
+// (Eight tokens to a wavefront, two times four: [16384, 3072] int4 19.0 us, restored in 25.5; four: 17.6 and 24.3.)
+constexpr uint32_t kStripRows = 4;
 
 struct Strip {
   uint32_t col;    // first channel of the lane
@@ -154,30 +155,28 @@ __global__ __launch_bounds__(kThreads) void channelwise_quantise_kernel(Channelw
   const float4 i0 = *reinterpret_cast<const float4*>(c.inv + s.col);
   const float4 i1 = *reinterpret_cast<const float4*>(c.inv + s.col + 4);
   const float iv[kOct] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
-  for (uint32_t r = 0; r < s.rows; r += 4u) {
-    uint4 raw[4];
+  uint4 raw[kStripRows];
 #pragma unroll
-    for (uint32_t i = 0; i < 4u; ++i) {  // four loads in flight; rows past the end re-read the last one
-      const uint32_t row = r + i < s.rows ? r + i : s.rows - 1u;
-      raw[i] = ADACC_LOAD16(c.src + s.first + (size_t)row * c.hidden);
+  for (uint32_t i = 0; i < kStripRows; ++i) {  // all loads in flight; rows past the end re-read the last one
+    const uint32_t row = i < s.rows ? i : s.rows - 1u;
+    raw[i] = ADACC_LOAD16(c.src + s.first + (size_t)row * c.hidden);
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < kStripRows; ++i) {
+    if (i >= s.rows) break;
+    const uint32_t w[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
+    float p[kOct];
+#pragma unroll
+    for (int e = 0; e < kOct; ++e) {
+      float x = ADACC_ELEM_F32(w, e);
+      if (is_nonfinite(x)) x = 0.0f;  // counts as zero
+      p[e] = __fmul_rn(x, iv[e]);
     }
-#pragma unroll
-    for (uint32_t i = 0; i < 4u; ++i) {
-      if (r + i >= s.rows) break;
-      const uint32_t w[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
-      float p[kOct];
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) {
-        float x = ADACC_ELEM_F32(w, e);
-        if (is_nonfinite(x)) x = 0.0f;  // counts as zero
-        p[e] = __fmul_rn(x, iv[e]);
-      }
-      uint32_t o[2];
-      pack_codes<BITS, false>(p, o);
-      const size_t e0 = s.first + (size_t)(r + i) * c.hidden;
-      if constexpr (BITS == 8) ADACC_STORE8(c.codes + e0, make_uint2(o[0], o[1]));
-      else ADACC_STORE4(c.codes + (e0 >> 1), o[0]);
-    }
+    uint32_t o[2];
+    pack_codes<BITS, false>(p, o);
+    const size_t e0 = s.first + (size_t)i * c.hidden;
+    if constexpr (BITS == 8) ADACC_STORE8(c.codes + e0, make_uint2(o[0], o[1]));
+    else ADACC_STORE4(c.codes + (e0 >> 1), o[0]);
   }
 }
 
@@ -193,37 +192,35 @@ __global__ __launch_bounds__(kThreads) void channelwise_dequantise_kernel(Channe
     const float4 f = *reinterpret_cast<const float4*>(c.scales + s.col + k);
     sc[k] = f.x; sc[k + 1] = f.y; sc[k + 2] = f.z; sc[k + 3] = f.w;
   }
-  for (uint32_t r = 0; r < s.rows; r += 4u) {
-    uint32_t cw[4][V * BITS > 32 ? 2 : 1];
+  uint32_t cw[kStripRows][V * BITS > 32 ? 2 : 1];
 #pragma unroll
-    for (uint32_t i = 0; i < 4u; ++i) {
-      const uint32_t row = r + i < s.rows ? r + i : s.rows - 1u;
-      const uint8_t* p = c.codes + (s.first + (size_t)row * c.hidden) * BITS / 8;
-      if constexpr (V * BITS == 64) {
-        const uint2 w = *reinterpret_cast<const uint2*>(p);
-        cw[i][0] = w.x; cw[i][1] = w.y;
-      } else if constexpr (V * BITS == 32) {
-        cw[i][0] = *reinterpret_cast<const uint32_t*>(p);
-      } else {
-        cw[i][0] = *reinterpret_cast<const uint16_t*>(p);
-      }
+  for (uint32_t i = 0; i < kStripRows; ++i) {
+    const uint32_t row = i < s.rows ? i : s.rows - 1u;
+    const uint8_t* p = c.codes + (s.first + (size_t)row * c.hidden) * BITS / 8;
+    if constexpr (V * BITS == 64) {
+      const uint2 w = *reinterpret_cast<const uint2*>(p);
+      cw[i][0] = w.x; cw[i][1] = w.y;
+    } else if constexpr (V * BITS == 32) {
+      cw[i][0] = *reinterpret_cast<const uint32_t*>(p);
+    } else {
+      cw[i][0] = *reinterpret_cast<const uint16_t*>(p);
     }
+  }
 #pragma unroll
-    for (uint32_t i = 0; i < 4u; ++i) {
-      if (r + i >= s.rows) break;
-      const size_t e0 = s.first + (size_t)(r + i) * c.hidden;
-      int code[V];
-      unpack_codes<BITS, V>(cw[i], code);
-      float v[V];
+  for (uint32_t i = 0; i < kStripRows; ++i) {
+    if (i >= s.rows) break;
+    const size_t e0 = s.first + (size_t)i * c.hidden;
+    int code[V];
+    unpack_codes<BITS, V>(cw[i], code);
+    float v[V];
 #pragma unroll
-      for (int e = 0; e < V; ++e) v[e] = (float)code[e] * sc[e];
-      if constexpr (F32) {
-        ADACC_STORE16(reinterpret_cast<float*>(c.dst) + e0,
-                      make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
-      } else {
-        ADACC_STORE16(reinterpret_cast<uint16_t*>(c.dst) + e0,
-                      make_uint4(narrow_pair(v[0], v[1]), narrow_pair(v[2], v[3]), narrow_pair(v[4], v[5]), narrow_pair(v[6], v[7])));
-      }
+    for (int e = 0; e < V; ++e) v[e] = (float)code[e] * sc[e];
+    if constexpr (F32) {
+      ADACC_STORE16(reinterpret_cast<float*>(c.dst) + e0,
+                    make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
+    } else {
+      ADACC_STORE16(reinterpret_cast<uint16_t*>(c.dst) + e0,
+                    make_uint4(narrow_pair(v[0], v[1]), narrow_pair(v[2], v[3]), narrow_pair(v[4], v[5]), narrow_pair(v[6], v[7])));
     }
   }
 }
