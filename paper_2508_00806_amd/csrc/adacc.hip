@@ -18,18 +18,15 @@ namespace adacc {
 // ===================================================================== kernels
 
 // ---- utilities
-// The table of a batch reaches the device as kernel arguments, a slice per launch: the runtime
-// copies kernel arguments when the launch is enqueued, so the host buffer may go away at once
+// The table of a batch and the member lists behind it reach the device as kernel arguments, a slice per launch: the
+// runtime copies kernel arguments when the launch is enqueued, so the host buffer may go away at once
 // and the host never waits for the stream (a copy from pageable memory would).
-constexpr uint32_t kDescsPerUpload = 3968 / sizeof(TensorDesc);
-struct DescSlice { TensorDesc d[kDescsPerUpload]; };
-static_assert(sizeof(DescSlice) <= 3968, "kernel arguments are limited to 4 KiB");
+constexpr uint32_t kWordsPerUpload = 992;
+struct WordSlice { uint32_t w[kWordsPerUpload]; };
+static_assert(sizeof(WordSlice) <= 3968, "kernel arguments are limited to 4 KiB");
 static_assert(sizeof(TensorDesc) % 4 == 0, "copied as 32-bit words");
-__global__ __launch_bounds__(kThreads) void table_upload_kernel(DescSlice slice, TensorDesc* dst, uint32_t count) {
-  const uint32_t words = count * (uint32_t)(sizeof(TensorDesc) / 4);
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(&slice);
-  uint32_t* out = reinterpret_cast<uint32_t*>(dst);
-  for (uint32_t i = threadIdx.x; i < words; i += kThreads) out[i] = src[i];
+__global__ __launch_bounds__(kThreads) void words_upload_kernel(WordSlice slice, uint32_t* dst, uint32_t count) {
+  for (uint32_t i = threadIdx.x; i < count; i += kThreads) dst[i] = slice.w[i];
 }
 
 // clears a workspace (a kernel rather than a memset node, so that callers may capture it in a graph)
@@ -37,13 +34,6 @@ __global__ __launch_bounds__(kThreads) void workspace_clear_kernel(uint4* p, uin
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += stride)
     p[i] = make_uint4(0, 0, 0, 0);
-}
-
-// small arrays of 32-bit words (the first-tile / first-block arrays of a batch) travel the same way
-constexpr uint32_t kWordsPerUpload = 960;
-struct WordSlice { uint32_t w[kWordsPerUpload]; };
-__global__ __launch_bounds__(kThreads) void words_upload_kernel(WordSlice slice, uint32_t* dst, uint32_t count) {
-  for (uint32_t i = threadIdx.x; i < count; i += kThreads) dst[i] = slice.w[i];
 }
 
 // Streams of known size in the shape the tensor kernels use (one piece of 4 KiB per wavefront per
@@ -423,25 +413,19 @@ static int launch_check(const char* what) {
   return e == hipSuccess ? ADACC_OK : hip_fail(e, what);
 }
 
-static int upload_table(const std::vector<TensorDesc>& table, TensorDesc* dst, hipStream_t s) {
-  for (size_t i = 0; i < table.size(); i += kDescsPerUpload) {
-    DescSlice slice;
-    const uint32_t count = (uint32_t)std::min<size_t>(kDescsPerUpload, table.size() - i);
-    std::memset(&slice, 0, sizeof slice);
-    std::memcpy(slice.d, table.data() + i, count * sizeof(TensorDesc));
-    hipLaunchKernelGGL(table_upload_kernel, dim3(1), dim3(kThreads), 0, s, slice, dst + i, count);
-    const int rc = launch_check("table_upload_kernel");
-    if (rc != ADACC_OK) return rc;
-  }
-  return ADACC_OK;
-}
-
-static int upload_words(const std::vector<uint32_t>& words, uint32_t* dst, hipStream_t s) {
+// The table to the start of the batch workspace and the member lists to their place behind it (two launches for each of
+// a batch of two layers, 4.5 us apiece, before they went up together).
+static int upload_batch(const std::vector<TensorDesc>& table, const std::vector<uint32_t>& members, uint64_t members_off,
+                        void* device_mem, hipStream_t s) {
+  const size_t table_words = table.size() * sizeof(TensorDesc) / 4;
+  std::vector<uint32_t> words(members.empty() ? table_words : members_off / 4 + members.size(), 0u);
+  std::memcpy(words.data(), table.data(), table.size() * sizeof(TensorDesc));
+  if (!members.empty()) std::memcpy(words.data() + members_off / 4, members.data(), members.size() * 4);
   for (size_t i = 0; i < words.size(); i += kWordsPerUpload) {
     WordSlice slice;
     const uint32_t count = (uint32_t)std::min<size_t>(kWordsPerUpload, words.size() - i);
     std::memcpy(slice.w, words.data() + i, count * sizeof(uint32_t));
-    hipLaunchKernelGGL(words_upload_kernel, dim3(1), dim3(kThreads), 0, s, slice, dst + i, count);
+    hipLaunchKernelGGL(words_upload_kernel, dim3(1), dim3(kThreads), 0, s, slice, static_cast<uint32_t*>(device_mem) + i, count);
     const int rc = launch_check("words_upload_kernel");
     if (rc != ADACC_OK) return rc;
   }
@@ -470,6 +454,10 @@ static BatchPlan batch_plan(uint32_t n_active, uint64_t region_bytes) {
   return b;
 }
 
+// The block sums and the placement of a batch are one launch each up to this many workgroups, two tensors of 44032 tiles
+// next to four of 8192 for instance: a workgroup without tiles leaves at once, at about 2 ns, a launch takes 4.5 us.
+constexpr uint64_t kPlaceTogether = 8192;
+
 // A launch over a group of table entries: grid.y = the group's entries, grid.x covers the largest.
 struct GroupLaunch {
   uint32_t first_member, n_members, max_units;
@@ -477,13 +465,20 @@ struct GroupLaunch {
 };
 // Groups the entries for which units[i] > 0 by kind[i] and by size (unit counts within a factor of
 // two of each other, at most 65535 entries per launch) and appends their member lists to `members`.
+// `together` > 0: whatever their size, as long as the grid of a kind has at most that many units - for kernels
+// whose empty workgroups cost less than another launch.
 static void group_launches(const std::vector<uint32_t>& units, const std::vector<int>& kind,
-                           std::vector<uint32_t>* members, std::vector<GroupLaunch>* launches) {
+                           std::vector<uint32_t>* members, std::vector<GroupLaunch>* launches, uint64_t together = 0) {
   for (int k = 0; k < 2 * kBatchKinds; ++k) {  // kinds of the second half: the same for binary16 tensors
-    for (uint32_t bucket = 0; bucket <= 32; ++bucket) {
+    uint64_t most = 0, n = 0;
+    for (uint32_t i = 0; i < units.size(); ++i)
+      if (units[i] != 0 && kind[i] == k) { most = std::max<uint64_t>(most, units[i]); ++n; }
+    if (n == 0) continue;
+    const bool one = most * n <= together;
+    for (uint32_t bucket = 0; bucket <= (one ? 0u : 32u); ++bucket) {
       GroupLaunch g = {(uint32_t)members->size(), 0u, 0u, k};
       for (uint32_t i = 0; i < units.size(); ++i) {
-        if (units[i] == 0 || kind[i] != k || ilog2(units[i]) != bucket) continue;
+        if (units[i] == 0 || kind[i] != k || (!one && ilog2(units[i]) != bucket)) continue;
         if (g.n_members == 65535u) {
           launches->push_back(g);
           g = GroupLaunch{(uint32_t)members->size(), 0u, 0u, k};
@@ -865,9 +860,9 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
     units[i] = (!descs[i].generic && needs_block_sums(&methods[origin[i]], plans[origin[i]])) ? blocks_of(descs[i].n_tiles, kSumTiles) : 0u;
     kind[i] = plans[origin[i]].half ? kBatchKinds : 0;
   }
-  group_launches(units, kind, &members, &sums);
+  group_launches(units, kind, &members, &sums, kPlaceTogether);
   for (uint32_t i = 0; i < nt; ++i) units[i] = descs[i].generic ? 0u : place_grid(&methods[origin[i]], plans[origin[i]]);
-  group_launches(units, kind, &members, &places);
+  group_launches(units, kind, &members, &places, kPlaceTogether);
   for (uint32_t j = n_listed; j < (uint32_t)members.size(); ++j) members[j] = place[members[j]];
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   uint32_t epoch = 0;
@@ -875,8 +870,7 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
   if (rc != ADACC_OK) return rc;
   TensorDesc* dt = reinterpret_cast<TensorDesc*>(mem);
   uint32_t* dm = reinterpret_cast<uint32_t*>(mem + bp.members_off);
-  rc = upload_table(ordered, dt, s);
-  if (rc == ADACC_OK && members.size() > n_listed) rc = upload_words(members, dm, s);
+  rc = upload_batch(ordered, members.size() > n_listed ? members : std::vector<uint32_t>(), bp.members_off, mem, s);
   if (rc != ADACC_OK) return rc;
   for (const GroupLaunch& g : tiles)
     hipLaunchKernelGGL(compress_batch_fn(g.kind >= kBatchKinds, g.kind % kBatchKinds),
@@ -938,7 +932,7 @@ int adacc_decompress_batch(uint32_t n, const adacc_method* methods, const void* 
   for (const uint32_t i : members) ordered.push_back(descs[i]);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   TensorDesc* dt = static_cast<TensorDesc*>(ws->device_mem);
-  rc = upload_table(ordered, dt, s);
+  rc = upload_batch(ordered, std::vector<uint32_t>(), 0, dt, s);
   if (rc != ADACC_OK) return rc;
   for (const GroupLaunch& g : launches)
     hipLaunchKernelGGL(ADACC_PICK(g.kind >= kBatchKinds, decompress_batch_fn(dst_dtype == ADACC_DST_F32)),
