@@ -333,18 +333,20 @@ __device__ __forceinline__ uint32_t topk_rounds(const SegmentGeo& g, SegmentShar
   return limit;
 }
 
-// The k-th largest key of a segment that is one group, k <= 8.  A magnitude that at least k lanes of a wavefront reach
-// (found by halving, with ballots: the vector unit compares once per step, the rest is scalar) is a lower bound of the
-// k-th largest; with the highest of the four wavefronts' bounds some 15 to 30 octets are left.  They meet in LDS,
+// TOPK over a segment that is one group, k <= 8: the k largest leave for entries pos0 .. of the sink (those at or past
+// `limit` are dropped), and are cleared in raw (omag: what is left).  A magnitude that at least k lanes of a wavefront
+// reach (found by halving, with ballots: the vector unit compares once per step, the rest is scalar) is a lower bound of
+// the k-th largest; with the highest of the four wavefronts' bounds some 15 to 30 octets are left.  They meet in LDS,
 // and one wavefront - another one for every segment, so that no SIMD has them all - takes an octet per lane, finds the
 // k-th largest magnitude by halving again, over the lanes' two largest first (and over all where a lane holds more
-// of the k), and the last of its equals that still belongs to the k.  Returns false (uniform) when more than 64
-// octets are left, a constant segment for one.
-// (The rounds, k dependent maxima over the wavefront three times over, took 60 of the 103 us that [8192, 11008] with
-// k = 8 took; 88 us with the halving.)
+// of the k), and the last of its equals that still belongs to the k; it writes the k to the stream in index order and
+// zeroes them in the list, and the octets' owners read those back.  Returns false (uniform), nothing done, when more
+// than 64 octets are left, a constant segment for one, or when the k-th largest is not finite.
+// (k dependent maxima over the wavefront three times over, and masks, counts and emission by all four wavefronts, took
+// 103 us for [8192, 11008] with k = 8; the halving 77 us; 65 us with the list.)
 template <int SL>
-__device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh, const uint32_t (&raw)[SL][4],
-                                         const uint32_t (&omag)[SL], uint32_t k, uint32_t& limit) {
+__device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh, uint32_t (&raw)[SL][4], uint32_t (&omag)[SL],
+                                         uint32_t k, const StreamSink& sink, uint32_t pos0, uint32_t limit) {
   const uint32_t tid = threadIdx.x, lane = (uint32_t)lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / (uint32_t)kWave);
   uint32_t m = 0u;
@@ -357,15 +359,18 @@ __device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh,
   uint32_t bound = 0u;
 #pragma unroll
   for (uint32_t w = 0; w < kSegWaves; ++w) bound = sh.head[40u + w] > bound ? sh.head[40u + w] : bound;
-  uint4* list = reinterpret_cast<uint4*>(sh.a);
+  uint4* list = reinterpret_cast<uint4*>(sh.a);                 // 64 octets, in any order
+  uint32_t* where = sh.b;                                       // their numbers
+  uint8_t* entry_of = reinterpret_cast<uint8_t*>(sh.b + kWave);  // and back
 #pragma unroll
   for (int j = 0; j < SL; ++j) {
     const uint32_t o = tid + (uint32_t)j * kSegThreads;
     if (omag[j] >= bound && o < g.octs) {
-      const uint32_t entry = atomicAdd(&sh.head[0], 1u);  // in any order
+      const uint32_t entry = atomicAdd(&sh.head[0], 1u);
       if (entry < (uint32_t)kWave) {
         list[entry] = make_uint4(raw[j][0], raw[j][1], raw[j][2], raw[j][3]);
-        sh.b[entry] = o;
+        where[entry] = o;
+        entry_of[o] = (uint8_t)entry;
       }
     }
   }
@@ -378,14 +383,12 @@ __device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh,
   if (wave == (blockIdx.x & (kSegWaves - 1u))) {  // uniform
     int32_t mag[kOct];  // -1: does not exist
     uint32_t o = 0u;
-    {
-      uint4 v = make_uint4(0u, 0u, 0u, 0u);
-      if (lane < n) { v = list[lane]; o = sh.b[lane]; }
-      const uint32_t nv = lane < n ? octet_valid(g, o) : 0u;
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (lane < n) { v = list[lane]; o = where[lane]; }
+    const uint32_t nv = lane < n ? octet_valid(g, o) : 0u;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int e = 0; e < kOct; ++e) mag[e] = (uint32_t)e < nv ? (int32_t)ADACC_ELEM_MAG(w, e) : -1;
-    }
+    for (int e = 0; e < kOct; ++e) mag[e] = (uint32_t)e < nv ? (int32_t)ADACC_ELEM_MAG(w, e) : -1;
     int32_t m1 = -1, m2 = -1;  // the lane's two largest
 #pragma unroll
     for (int e = 0; e < kOct; ++e) {
@@ -405,31 +408,69 @@ __device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh,
       t = kth_by_halving(k, [&](uint32_t c) { return reach((int32_t)c); });
       above = reach((int32_t)t + 1);
     }
-    uint32_t last = 0u;  // reversed index of the last element of magnitude t that belongs to the k (0: all do)
-    const uint32_t need = k - above;
-    if (reach((int32_t)t) - above != need) {  // uniform: more equals than are needed, the lowest indices are taken
-      last = 0xFFFFFFFFu;
-      for (uint32_t r = 0; r < need; ++r) {
-        uint32_t best = 0u;
+    const bool finite = t < kNonfiniteMag;  // uniform
+    if (finite) {
+      uint32_t last = 0u;  // reversed index of the last element of magnitude t that belongs to the k (0: all do)
+      const uint32_t need = k - above;
+      if (reach((int32_t)t) - above != need) {  // uniform: more equals than are needed, the lowest indices are taken
+        last = 0xFFFFFFFFu;
+        for (uint32_t r = 0; r < need; ++r) {
+          uint32_t best = 0u;
 #pragma unroll
-        for (int e = 0; e < kOct; ++e) {
-          const uint32_t rev = 0xFFFFu - (o * (uint32_t)kOct + (uint32_t)e);
-          best = (mag[e] == (int32_t)t && rev < last && rev > best) ? rev : best;
+          for (int e = 0; e < kOct; ++e) {
+            const uint32_t rev = 0xFFFFu - (o * (uint32_t)kOct + (uint32_t)e);
+            best = (mag[e] == (int32_t)t && rev < last && rev > best) ? rev : best;
+          }
+          last = wave_max_u32_scalar(best);
         }
-        last = wave_max_u32_scalar(best);
       }
+      // the k: index above the pattern, to the first k words of a list, zeroed where they were ...
+      uint32_t* found = sh.head + 8u;
+      uint16_t* elem = reinterpret_cast<uint16_t*>(list) + lane * (uint32_t)kOct;
+      uint32_t before = 0u;
+#pragma unroll
+      for (int e = 0; e < kOct; ++e) {
+        const uint32_t i = o * (uint32_t)kOct + (uint32_t)e;
+        const bool hit = mag[e] > (int32_t)t || (mag[e] == (int32_t)t && 0xFFFFu - i >= last);
+        const uint64_t b = __builtin_amdgcn_ballot_w64(hit);
+        if (b != 0ull) {  // uniform
+          if (hit) {
+            found[before + lanes_below(b)] = (i << 16) | ((e & 1) ? w[e >> 1] >> 16 : w[e >> 1] & 0xFFFFu);
+            elem[e] = 0;
+          }
+          before += (uint32_t)__builtin_popcountll(b);
+        }
+      }
+      lds_in_order();
+      // ... and to the stream, a lane each, in the order of their indices
+      const uint32_t one = lane < k ? found[lane] : 0xFFFFFFFFu;
+      uint32_t rank = 0u;
+      for (uint32_t r = 0; r < k; ++r) rank += (uint32_t)__builtin_amdgcn_readlane((int)one, (int)r) < one ? 1u : 0u;
+      if (lane < k && pos0 + rank < limit) sink(pos0 + rank, (uint32_t)g.first_elem + (one >> 16), one & 0xFFFFu);
     }
-    if (lane == 0u) sh.head[44] = (t << 16) | last;
+    if (lane == 0u) sh.head[44] = finite ? t : 0xFFFFFFFFu;
   }
   __syncthreads();
-  limit = sh.head[44];
-  return true;
+  const uint32_t t = sh.head[44];
+  if (t != 0xFFFFFFFFu) {  // uniform
+#pragma unroll
+    for (int j = 0; j < SL; ++j) {
+      const uint32_t o = tid + (uint32_t)j * kSegThreads;
+      if (omag[j] >= t && o < g.octs) {  // few octets get here
+        const uint4 v = list[entry_of[o]];
+        raw[j][0] = v.x; raw[j][1] = v.y; raw[j][2] = v.z; raw[j][3] = v.w;
+        omag[j] = octet_magnitude(raw[j]);
+      }
+    }
+  }
+  __syncthreads();  // head, a, b are free again
+  return t != 0xFFFFFFFFu;
 }
 
 // How a segment's outliers are chosen, as a template argument of the compression: the mode, or kSegTopkWhole where the
 // segment is one TOPK group (kModeTopk: several), or kSegAny: by the descriptor.  (One kernel for all modes held the
 // registers of the hungriest: 128 for 6 octets per thread, four wavefronts per SIMD, where 84 are enough for TOPK over
-// the segment; [8192, 11008]: 88 -> 77 us.)
+// the segment; [8192, 11008]: 88 -> 77 us at the time.)
 constexpr int kSegTopkWhole = 4, kSegAny = 5;
 
 // ---- a2 / a3: mask[j] bit e = element e of the thread's octet j is an outlier by the method's rule
@@ -496,13 +537,9 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
     __syncthreads();  // a, b, g0, g1 are free again
   } else if (mode == kModeTopk) {
     if (whole) {
-      // The segment is one group.  The threshold is the k-th largest key (magnitude above the reversed element index:
-      // unique, ties go to the lower index): an element is an outlier if its key reaches it.  Few keep k <= 8:
-      // topk_few; otherwise, and where too many octets come into question there, by rounds:
-      // topk_rounds.
-      const uint32_t rounds = d.topk < g.cnt ? d.topk : g.cnt;  // at most 32
-      uint32_t limit = 0u;
-      if (rounds > 8u || !topk_few<SL>(g, sh, raw, omag, rounds, limit)) limit = topk_rounds<SL>(g, sh, raw, omag, rounds);  // uniform
+      // The segment is one group: an element is an outlier if its key (magnitude above the reversed element index: unique,
+      // ties go to the lower index) reaches the k-th largest.
+      const uint32_t limit = topk_rounds<SL>(g, sh, raw, omag, d.topk < g.cnt ? d.topk : g.cnt);  // at most 32
 #pragma unroll
       for (int j = 0; j < SL; ++j) {
         const uint32_t o = tid + (uint32_t)j * kSegThreads;
@@ -832,11 +869,10 @@ __device__ __forceinline__ const TensorDesc& descriptor_again() {
   return *(const TensorDesc*)p;
 }
 
-// One segment (d.tile_elems elements, the last one of the tensor may be short), loaded, its outliers known.
+// One segment (d.tile_elems elements, the last one of the tensor may be short), loaded; omag: its octets' magnitudes.
 // d: the kernel's first argument
-template <int SL, int KIND>
-__device__ __forceinline__ SegmentGeo load_and_select(const TensorDesc& d, SegmentShared& sh, uint32_t seg, uint32_t (&raw)[SL][4],
-                                                      uint32_t (&omag)[SL], uint32_t (&mask)[SL]) {
+template <int SL>
+__device__ __forceinline__ SegmentGeo load_segment(const TensorDesc& d, uint32_t seg, uint32_t (&raw)[SL][4], uint32_t (&omag)[SL]) {
   SegmentGeo g;
   g.first_elem = (uint64_t)seg * d.tile_elems;
   const uint64_t left = d.numel - g.first_elem;
@@ -846,6 +882,12 @@ __device__ __forceinline__ SegmentGeo load_and_select(const TensorDesc& d, Segme
   segment_load(d, g, raw);
 #pragma unroll
   for (int j = 0; j < SL; ++j) omag[j] = octet_magnitude(raw[j]);
+  return g;
+}
+// its outliers, values that are not finite among them
+template <int SL, int KIND>
+__device__ __forceinline__ void segment_outliers(const TensorDesc& d, const SegmentGeo& g, SegmentShared& sh, const uint32_t (&raw)[SL][4],
+                                                 const uint32_t (&omag)[SL], uint32_t (&mask)[SL]) {
   if (KIND == kSegAny ? d.mode != kModeNone : KIND != (int)kModeNone) {
     segment_select<SL, KIND>(descriptor_again(), g, sh, raw, omag, mask);
   } else {
@@ -855,21 +897,44 @@ __device__ __forceinline__ SegmentGeo load_and_select(const TensorDesc& d, Segme
 #pragma unroll
   for (int j = 0; j < SL; ++j)  // what cannot be quantised at all is always kept exactly
     if (omag[j] >= kNonfiniteMag) mask[j] |= octet_nonfinite(raw[j]);
-  return g;
+}
+// a5: the outliers, and every value that is not finite, count as zero from here on
+template <int SL>
+__device__ __forceinline__ void segment_clear(uint32_t (&raw)[SL][4], uint32_t (&omag)[SL], const uint32_t (&mask)[SL]) {
+  forget_derived<SL>(raw);  // (nothing widened for the selection is kept for the codes)
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (mask[j] != 0u) {
+      clear_elements(raw[j], mask[j]);
+      omag[j] = octet_magnitude(raw[j]);
+    }
+  }
 }
 
 template <int SL, int KIND>
 __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentShared& sh, uint32_t seg, uint32_t epoch) {
   const uint32_t tid = threadIdx.x;
   uint32_t raw[SL][4], mask[SL], omag[SL];
-  const SegmentGeo g = load_and_select<SL, KIND>(d, sh, seg, raw, omag, mask);
+  const SegmentGeo g = load_segment<SL>(d, seg, raw, omag);
   if constexpr (KIND == (int)kModeTopk || KIND == kSegTopkWhole) {
     const uint32_t gps = d.tile_elems / d.gs;  // groups of a whole segment
     const uint32_t pos0 = seg * gps * d.topk;
     const uint32_t whole = g.cnt / d.gs, rest = g.cnt - whole * d.gs;
     const uint32_t expected = whole * d.topk + (rest < d.topk ? rest : d.topk);
     const uint32_t end = pos0 + expected;
-    const uint32_t total = segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
+    const StreamSink sink{d.idx, d.val};
+    const uint32_t limit = end < d.cap ? end : d.cap;
+    uint32_t total = expected;
+    bool done = false;  // uniform
+    if constexpr (KIND == kSegTopkWhole) {
+      if (expected <= 8u) done = topk_few<SL>(g, sh, raw, omag, expected, sink, pos0, limit);
+    }
+    if (!done) {
+      segment_outliers<SL, KIND>(d, g, sh, raw, omag, mask);
+      total = segment_emit(g, sh, raw, mask, sink, pos0, limit);
+      segment_clear<SL>(raw, omag, mask);
+    }
     if (tid == 0u) {
       d.tile_ptr[seg] = pos0;
       d.cnt[seg] = total;
@@ -879,24 +944,18 @@ __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentSha
         d.status[0] = end; d.status[1] = end > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u;
       }
     }
-  } else if constexpr (KIND != (int)kModeNone) {
-    const SlotSink sink{d.slot + (uint64_t)seg * (uint64_t)kSlot, (uint32_t)g.first_elem};
-    const uint32_t total = segment_emit(g, sh, raw, mask, sink, 0u, (uint32_t)kSlot);
-    if (tid == 0u) d.cnt[seg] = total;
-  } else if (seg == 0u && tid == 0u) {
-    d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u;
+  } else {
+    segment_outliers<SL, KIND>(d, g, sh, raw, omag, mask);
+    if constexpr (KIND != (int)kModeNone) {
+      const SlotSink sink{d.slot + (uint64_t)seg * (uint64_t)kSlot, (uint32_t)g.first_elem};
+      const uint32_t total = segment_emit(g, sh, raw, mask, sink, 0u, (uint32_t)kSlot);
+      if (tid == 0u) d.cnt[seg] = total;
+    } else if (seg == 0u && tid == 0u) {
+      d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u;
+    }
+    segment_clear<SL>(raw, omag, mask);
   }
   const TensorDesc& again = descriptor_again();
-  forget_derived<SL>(raw);  // (nothing widened for the selection is kept for the codes)
-  // a5: from here on the outliers, and every value that is not finite, count as zero
-#pragma unroll
-  for (int j = 0; j < SL; ++j) {
-    __builtin_amdgcn_sched_barrier(0);
-    if (mask[j] != 0u) {
-      clear_elements(raw[j], mask[j]);
-      omag[j] = octet_magnitude(raw[j]);
-    }
-  }
   if (again.bits == 8u) {
     if (again.asym) segment_quantise<8, true, SL>(again, g, sh, raw, omag); else segment_quantise<8, false, SL>(again, g, sh, raw, omag);
   } else {
@@ -933,7 +992,8 @@ __global__ __launch_bounds__(kSegThreads, SL <= 4 ? 4 : 2) void place_generic_ke
     const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j);
     if (n <= room) continue;  // uniform over the workgroup
     uint32_t raw[SL][4], mask[SL], omag[SL];
-    const SegmentGeo g = load_and_select<SL, kSegAny>(d, sh, p.first + j, raw, omag, mask);
+    const SegmentGeo g = load_segment<SL>(d, p.first + j, raw, omag);
+    segment_outliers<SL, kSegAny>(d, g, sh, raw, omag, mask);
     const uint32_t pos0 = p.base + (uint32_t)__builtin_amdgcn_readlane((int)p.excl, (int)j), end = pos0 + n;
     segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
   }
