@@ -1122,7 +1122,7 @@ int adacc_channelwise_compress(uint32_t bits, uint32_t scale_rule, uint32_t dtyp
   c.partial = static_cast<uint16_t*>(workspace);
   c.inv = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + channelwise_partial_bytes(tokens, hidden));
   ChannelwiseFn quant = ADACC_PICK(half, channelwise_quantise_fn(bits));
-  const uint32_t grid = strip_grid(tokens, hidden, ADACC_PICK(half, channelwise_strip_rows()));
+  const uint32_t grid = strip_grid(tokens, hidden, ADACC_PICK(half, channelwise_strip_rows(false, c.numel)));
   int rc = ADACC_OK;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const uint32_t strips = (hidden / 8 + kWave - 1) / kWave;  // a workgroup: one chunk of a strip of 512 channels
@@ -1153,7 +1153,8 @@ int adacc_channelwise_decompress(uint32_t bits, uint32_t dtype, const void* blob
   channelwise_desc(bits, 0, tokens, hidden, L, const_cast<void*>(blob), &c);
   c.dst = dst;
   ChannelwiseFn fn = ADACC_PICK(dtype == ADACC_DTYPE_F16, channelwise_dequantise_fn(bits, dst_dtype == ADACC_DST_F32));
-  const uint32_t grid = strip_grid(tokens, hidden, ADACC_PICK(dtype == ADACC_DTYPE_F16, channelwise_strip_rows()), strip_width(dst_dtype));
+  c.strip_rows = ADACC_PICK(dtype == ADACC_DTYPE_F16, channelwise_strip_rows(true, c.numel));
+  const uint32_t grid = strip_grid(tokens, hidden, c.strip_rows, strip_width(dst_dtype));
   hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, static_cast<hipStream_t>(hip_stream), c);
   return launch_check("channelwise_dequantise_kernel");
 }

@@ -140,6 +140,7 @@ struct ChannelwiseDesc {
   uint16_t* partial;    // workspace [n_chunks][hidden]: chunk maxima of the finite magnitudes
   uint64_t numel;
   uint32_t tokens, hidden, n_chunks;
+  uint32_t strip_rows;   // decompress: tokens a wavefront takes
   float divisor, inv_divisor;  // D of Eq. 2 and, when D is a power of two, 1/D (else 0)
 };
 

@@ -70,7 +70,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   ChannelwiseItemsFn channelwise_partial_fn(bool stream);                              \
   ChannelwiseFn channelwise_fold_fn();                                                 \
   uint32_t channelwise_fold_octets();                                                  \
-  uint32_t channelwise_strip_rows();                                                   \
+  uint32_t channelwise_strip_rows(bool restore, uint64_t numel);                       \
   uint32_t channelwise_partial_threads();                                              \
   ChannelwiseFn channelwise_quantise_fn(uint32_t bits);                                \
   ChannelwiseFn channelwise_dequantise_fn(uint32_t bits, bool f32);

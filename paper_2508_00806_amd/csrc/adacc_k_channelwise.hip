@@ -121,8 +121,11 @@ __global__ __launch_bounds__(kThreads) void channelwise_fold_kernel(ChannelwiseD
 // tiles of 2048 consecutive elements a lane had to fetch 32 bytes of factors for every 16 bytes of input).
 // Units are numbered strip by strip within a block of tokens, so the four wavefronts of a workgroup take
 // four adjacent strips and the launch walks through memory front to back.
-// (Eight tokens to a wavefront, two times four: [16384, 3072] int4 19.0 us, restored in 25.5; four: 17.6 and 24.3.)
+// (Eight tokens to a wavefront, two times four: [16384, 3072] int4 19.0 us, restored in 25.5; four: 17.6 and 24.3.  A
+// restoration of more than kLongStrips values, which is a stream and nothing else, keeps eight: [16384, 16384]
+// 118 us, 126 with four.)
 constexpr uint32_t kStripRows = 4;
+constexpr uint64_t kLongStrips = 1ull << 27;
 
 struct Strip {
   uint32_t col;    // first channel of the lane
@@ -131,18 +134,19 @@ struct Strip {
   bool live;
 };
 // V: channels per lane (8, or 4 for a binary32 output: one 16-byte access per token either way), strips of 64 * V
+// channels and `strip_rows` tokens
 template <int V>
-__device__ __forceinline__ Strip strip_of(const ChannelwiseDesc& c) {
+__device__ __forceinline__ Strip strip_of(const ChannelwiseDesc& c, uint32_t strip_rows) {
   constexpr uint32_t W = (uint32_t)(kWave * V);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t strips = (c.hidden + W - 1u) / W;
   const uint32_t unit = blockIdx.x * kWavesPerWg + wave;
   const uint32_t block = unit / strips;
-  const uint32_t row0 = block * kStripRows;
+  const uint32_t row0 = block * strip_rows;
   Strip s;
   s.col = (unit - block * strips) * W + (uint32_t)(lane_id() * V);
   s.live = row0 < c.tokens && s.col < c.hidden;
-  s.rows = s.live ? (c.tokens - row0 < kStripRows ? c.tokens - row0 : kStripRows) : 0u;
+  s.rows = s.live ? (c.tokens - row0 < strip_rows ? c.tokens - row0 : strip_rows) : 0u;
   s.first = (size_t)row0 * c.hidden + s.col;
   return s;
 }
@@ -150,7 +154,7 @@ __device__ __forceinline__ Strip strip_of(const ChannelwiseDesc& c) {
 // ---- step 3: code = clip(round(x * (D / max_h))), packed, in the tensor's own order
 template <int BITS>
 __global__ __launch_bounds__(kThreads) void channelwise_quantise_kernel(ChannelwiseDesc c) {
-  const Strip s = strip_of<kOct>(c);
+  const Strip s = strip_of<kOct>(c, kStripRows);
   if (!s.live) return;
   const float4 i0 = *reinterpret_cast<const float4*>(c.inv + s.col);
   const float4 i1 = *reinterpret_cast<const float4*>(c.inv + s.col + 4);
@@ -184,7 +188,7 @@ __global__ __launch_bounds__(kThreads) void channelwise_quantise_kernel(Channelw
 template <int BITS, bool F32>
 __global__ __launch_bounds__(kThreads) void channelwise_dequantise_kernel(ChannelwiseDesc c) {
   constexpr int V = chunk_elems<F32>();
-  const Strip s = strip_of<V>(c);
+  const Strip s = strip_of<V>(c, c.strip_rows);
   if (!s.live) return;
   float sc[V];
 #pragma unroll
@@ -192,40 +196,42 @@ __global__ __launch_bounds__(kThreads) void channelwise_dequantise_kernel(Channe
     const float4 f = *reinterpret_cast<const float4*>(c.scales + s.col + k);
     sc[k] = f.x; sc[k + 1] = f.y; sc[k + 2] = f.z; sc[k + 3] = f.w;
   }
-  uint32_t cw[kStripRows][V * BITS > 32 ? 2 : 1];
+  for (uint32_t r = 0; r < s.rows; r += kStripRows) {
+    uint32_t cw[kStripRows][V * BITS > 32 ? 2 : 1];
 #pragma unroll
-  for (uint32_t i = 0; i < kStripRows; ++i) {
-    const uint32_t row = i < s.rows ? i : s.rows - 1u;
-    const uint8_t* p = c.codes + (s.first + (size_t)row * c.hidden) * BITS / 8;
-    if constexpr (V * BITS == 64) {
-      const uint2 w = *reinterpret_cast<const uint2*>(p);
-      cw[i][0] = w.x; cw[i][1] = w.y;
-    } else if constexpr (V * BITS == 32) {
-      cw[i][0] = *reinterpret_cast<const uint32_t*>(p);
-    } else {
-      cw[i][0] = *reinterpret_cast<const uint16_t*>(p);
+    for (uint32_t i = 0; i < kStripRows; ++i) {
+      const uint32_t row = r + i < s.rows ? r + i : s.rows - 1u;
+      const uint8_t* p = c.codes + (s.first + (size_t)row * c.hidden) * BITS / 8;
+      if constexpr (V * BITS == 64) {
+        const uint2 w = *reinterpret_cast<const uint2*>(p);
+        cw[i][0] = w.x; cw[i][1] = w.y;
+      } else if constexpr (V * BITS == 32) {
+        cw[i][0] = *reinterpret_cast<const uint32_t*>(p);
+      } else {
+        cw[i][0] = *reinterpret_cast<const uint16_t*>(p);
+      }
     }
-  }
 #pragma unroll
-  for (uint32_t i = 0; i < kStripRows; ++i) {
-    if (i >= s.rows) break;
-    const size_t e0 = s.first + (size_t)i * c.hidden;
-    int code[V];
-    unpack_codes<BITS, V>(cw[i], code);
-    float v[V];
+    for (uint32_t i = 0; i < kStripRows; ++i) {
+      if (r + i >= s.rows) break;
+      const size_t e0 = s.first + (size_t)(r + i) * c.hidden;
+      int code[V];
+      unpack_codes<BITS, V>(cw[i], code);
+      float v[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) v[e] = (float)code[e] * sc[e];
-    if constexpr (F32) {
-      ADACC_STORE16(reinterpret_cast<float*>(c.dst) + e0,
-                    make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
-    } else {
-      ADACC_STORE16(reinterpret_cast<uint16_t*>(c.dst) + e0,
-                    make_uint4(narrow_pair(v[0], v[1]), narrow_pair(v[2], v[3]), narrow_pair(v[4], v[5]), narrow_pair(v[6], v[7])));
+      for (int e = 0; e < V; ++e) v[e] = (float)code[e] * sc[e];
+      if constexpr (F32) {
+        ADACC_STORE16(reinterpret_cast<float*>(c.dst) + e0,
+                      make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
+      } else {
+        ADACC_STORE16(reinterpret_cast<uint16_t*>(c.dst) + e0,
+                      make_uint4(narrow_pair(v[0], v[1]), narrow_pair(v[2], v[3]), narrow_pair(v[4], v[5]), narrow_pair(v[6], v[7])));
+      }
     }
   }
 }
 
-uint32_t channelwise_strip_rows() { return kStripRows; }
+uint32_t channelwise_strip_rows(bool restore, uint64_t numel) { return restore && numel > kLongStrips ? 2u * kStripRows : kStripRows; }
 uint32_t channelwise_partial_threads() { return kPartialWaves * (uint32_t)kWave; }
 ChannelwiseItemsFn channelwise_partial_fn(bool stream) {
   return stream ? channelwise_partial_kernel<true> : channelwise_partial_kernel<false>;
