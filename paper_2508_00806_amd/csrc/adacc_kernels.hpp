@@ -129,6 +129,10 @@ __global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const Tensor
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
   const TensorDesc d = table[members ? members[blockIdx.y] : blockIdx.y];
   const uint32_t piece = blockIdx.x * kWavesPerWg + wave;
+  // all of the descriptor that a piece needs is asked for together with n_tiles: one round trip to memory ahead of the
+  // first load of the codes, where a wait for n_tiles alone would make it two
+  asm volatile("" ::"s"(d.codes), "s"(d.scales), "s"(d.zp), "s"(d.dst), "s"(d.numel), "s"(d.lgq), "s"(d.variant), "s"(d.tile_ptr),
+               "s"(d.idx), "s"(d.val), "s"(d.cap), "s"(d.per_tile), "s"(d.mode), "s"(d.ptr_shift));
   if (piece >= d.n_tiles) return;
   const bool ho = (d.variant >> 3) != kModeNone;
   __shared__ DecompressShared shared;
