@@ -101,8 +101,8 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
 
     def _pack_mask(self, t):
         numel = t.numel()
-        rec = {"shape": tuple(t.shape), "numel": numel, "method": "mask", "events": {}}
         stream = torch.cuda.current_stream()
+        rec = {"shape": tuple(t.shape), "numel": numel, "method": "mask", "events": {}, "stream": stream}
         ev = self._events(rec, "compress", stream)
         bits = torch.empty(mask_packed_bytes(numel), dtype=torch.uint8, device=t.device)
         mask_pack(t, bits, numel, stream=stream)
@@ -132,9 +132,9 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         except AdaccError as e:
             self.retained.append((tuple(t.shape), str(e)))
             return t
-        rec = {"shape": tuple(t.shape), "numel": numel, "method": m, "events": {}}
         # the stream is looked up once: asking torch for it costs as much as a launch, and it is needed four times
         stream = torch.cuda.current_stream()
+        rec = {"shape": tuple(t.shape), "numel": numel, "method": m, "events": {}, "stream": stream}
         ev = self._events(rec, "compress", stream)
         blob = torch.empty(max(int(layout.total_bytes), 256), dtype=torch.uint8, device=t.device)
         if isinstance(m, ChannelMethod):
@@ -177,6 +177,8 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         if isinstance(s, _SavedMask):
             out = torch.empty(s.shape, dtype=torch.bool, device=s.bits.device)
             stream = torch.cuda.current_stream()
+            if stream != s.record["stream"]:  # (no event of its own: masks have no status to wait for)
+                stream.wait_stream(s.record["stream"])
             ev = self._events(s.record, "decompress", stream)
             mask_unpack(s.bits, out, s.numel, stream=stream)
             if ev:
@@ -187,6 +189,8 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         out = torch.empty(s.shape, dtype=torch.float16 if s.method.dtype == DTYPE_F16 else torch.bfloat16,
                           device=s.blob.device)
         stream = torch.cuda.current_stream()
+        if stream != s.record["stream"]:  # the restoration goes behind the compression, wherever that ran
+            stream.wait_event(s.record["status_ready"])
         ev = self._events(s.record, "decompress", stream)
         if isinstance(s.method, ChannelMethod):
             hidden = s.shape[-1]

@@ -285,3 +285,31 @@ def test_float16_activations_are_compressed_in_their_own_format():
         assert torch.allclose(w.grad.float(), want, rtol=2e-2, atol=2e-2 * float(want.abs().max()))
         rep = ctx.report()
         assert len(rep) == 1 and not rep[0]["overflow"] and rep[0]["crate"] < 0.3
+
+
+@pytest.mark.parametrize("kind", ["std", "channel", "mask"])
+def test_a_tensor_packed_on_another_stream_is_restored_behind_it(kind):
+    """Packed on a side stream behind queued work, unpacked on the current stream at once: the restoration has to wait for
+    the compression by itself."""
+    print(f"[hooks] two streams, {kind}", flush=True)
+    torch.manual_seed(21)
+    x = (torch.randn(256, 1024) * 1.5).to(torch.bfloat16)
+    if kind == "mask":
+        x = torch.rand(256, 1024) < 0.9
+    m = (adacc.ChannelMethod(bits=8, quant_group=64, z_thresh=2.5, max_channels=64) if kind == "channel" else
+         adacc.Method(bits=8, quant_group=64, outlier_mode=adacc.OUTLIER_STD, stat_group=64, thresh=3.0, max_outliers=1 << 14))
+    ctx = SavedActivationCompression(lambda t: m, timing=False)
+    xd = x.cuda()
+    work = torch.zeros(1 << 27, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for _ in range(40):  # some 10 ms of copies
+            work.add_(1.0)
+        saved = ctx._pack(xd)
+    back = ctx._unpack(saved)
+    if kind == "mask":
+        assert torch.equal(back.cpu(), x)
+    else:
+        assert np.array_equal(bits_of(back), bits_of(oracle_roundtrip(x, m)[0]))
+    torch.cuda.synchronize()
