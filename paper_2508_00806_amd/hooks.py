@@ -179,6 +179,7 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
             stream = torch.cuda.current_stream()
             if stream != s.record["stream"]:  # (no event of its own: masks have no status to wait for)
                 stream.wait_stream(s.record["stream"])
+                s.bits.record_stream(stream)  # the graph may let go of it while this stream still reads it
             ev = self._events(s.record, "decompress", stream)
             mask_unpack(s.bits, out, s.numel, stream=stream)
             if ev:
@@ -191,6 +192,7 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         stream = torch.cuda.current_stream()
         if stream != s.record["stream"]:  # the restoration goes behind the compression, wherever that ran
             stream.wait_event(s.record["status_ready"])
+            s.blob.record_stream(stream)  # the graph may let go of it while this stream still reads it
         ev = self._events(s.record, "decompress", stream)
         if isinstance(s.method, ChannelMethod):
             hidden = s.shape[-1]
