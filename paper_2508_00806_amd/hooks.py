@@ -88,8 +88,9 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         self.records = []
         self.retained = []   # (shape, reason) of tensors offered to the policy and saved as they are
         self._status = _StatusPool()
-        self._ws = None      # workspace of compression with outliers, grown on demand, reused by every tensor (one stream)
-        self._cws = None     # workspace of the channel statistics
+        # by stream, grown on demand, reused by every tensor that is packed there (compressions of two streams may overlap):
+        self._ws = {}        # workspace of compression with outliers
+        self._cws = {}       # workspace of the channel statistics
         super().__init__(self._pack, self._unpack)
 
     # ---- hooks
@@ -140,16 +141,17 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         if isinstance(m, ChannelMethod):
             hidden = t.shape[-1]
             tokens = numel // hidden
-            if self._cws is None or self._cws.numel() < channel_workspace_bytes(tokens, hidden):
-                self._cws = alloc_channel_workspace(tokens, hidden, device=t.device)
-            channel_compress(m, t, tokens, hidden, blob, self._cws, stream=stream)
+            cws = self._cws.get(stream)
+            if cws is None or cws.numel() < channel_workspace_bytes(tokens, hidden):
+                cws = self._cws[stream] = alloc_channel_workspace(tokens, hidden, device=t.device)
+            channel_compress(m, t, tokens, hidden, blob, cws, stream=stream)
         else:
             ws = None
             if m.outlier_mode != OUTLIER_NONE:
                 want = workspace_bytes(m, numel)
-                if self._ws is None or self._ws.c.bytes < want:
-                    self._ws = alloc_workspace(want, device=t.device)
-                ws = self._ws
+                ws = self._ws.get(stream)
+                if ws is None or ws.c.bytes < want:
+                    ws = self._ws[stream] = alloc_workspace(want, device=t.device)
             compress(m, t, blob, ws, stream=stream)
         if ev:
             ev[1].record(stream)

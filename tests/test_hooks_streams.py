@@ -22,7 +22,7 @@ class Stream:
 def world(monkeypatch):
     """log, a switch for the current stream, and a context whose library calls only write to the log."""
     log = []
-    streams = {n: Stream(n, log) for n in ("a", "b")}
+    streams = {n: Stream(n, log) for n in ("a", "b")}  # (hashed and compared by identity)
     now = {"stream": streams["a"]}
 
     class Event:
@@ -91,3 +91,33 @@ def test_one_stream_waits_for_nothing(kind, world):
     ctx, saved = saved_on_a(METHODS[kind], world, mask)
     ctx._unpack(saved)
     assert not [e for e in log if e[0] in ("wait", "keeps memory for")], log
+
+
+@pytest.mark.parametrize("kind", ["groups", "channels"])
+def test_streams_do_not_share_a_workspace(kind, world, monkeypatch):
+    """Two compressions that may overlap need different workspaces; one stream keeps its own."""
+    log, now, streams = world
+    method = METHODS[kind] if kind == "channels" else adacc.Method(bits=4, quant_group=128, outlier_mode=adacc.OUTLIER_ABS, thresh=1.0,
+                                                                   max_outliers=64)
+    used = []
+
+    class Workspace:
+        def __init__(self, nbytes):
+            self.c = type("c", (), {"bytes": nbytes})
+
+    monkeypatch.setattr(hooks, "alloc_workspace", lambda nbytes, device=None: Workspace(nbytes))
+    call = hooks.compress if kind == "groups" else hooks.channel_compress
+
+    def note(*args, **kw):
+        used.append(args[-1])
+        call(*args[:-1], **kw)
+        for t in args:  # the blob's status words
+            if isinstance(t, torch.Tensor) and t.dtype == torch.uint8:
+                t.zero_()
+    monkeypatch.setattr(hooks, "compress" if kind == "groups" else "channel_compress", note)
+    ctx = hooks.SavedActivationCompression(lambda t: method, timing=False, pack_masks=False)
+    t = torch.zeros(64, 1024, dtype=torch.bfloat16)
+    for name in "aabab":
+        now["stream"] = streams[name]
+        ctx._pack(t)
+    assert used[0] is used[1] is used[3] and used[2] is used[4] and used[0] is not used[2]
