@@ -88,7 +88,7 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         self.records = []
         self.retained = []   # (shape, reason) of tensors offered to the policy and saved as they are
         self._status = _StatusPool()
-        # by stream, grown on demand, reused by every tensor that is packed there (compressions of two streams may overlap):
+        # by device and stream, grown on demand, reused by every tensor that is packed there (compressions of two streams may overlap):
         self._ws = {}        # workspace of compression with outliers
         self._cws = {}       # workspace of the channel statistics
         super().__init__(self._pack, self._unpack)
@@ -138,20 +138,21 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         rec = {"shape": tuple(t.shape), "numel": numel, "method": m, "events": {}, "stream": stream}
         ev = self._events(rec, "compress", stream)
         blob = torch.empty(max(int(layout.total_bytes), 256), dtype=torch.uint8, device=t.device)
+        at = (t.get_device(), stream.cuda_stream)  # (a Stream's own hash builds a device object on every look-up)
         if isinstance(m, ChannelMethod):
             hidden = t.shape[-1]
             tokens = numel // hidden
-            cws = self._cws.get(stream)
+            cws = self._cws.get(at)
             if cws is None or cws.numel() < channel_workspace_bytes(tokens, hidden):
-                cws = self._cws[stream] = alloc_channel_workspace(tokens, hidden, device=t.device)
+                cws = self._cws[at] = alloc_channel_workspace(tokens, hidden, device=t.device)
             channel_compress(m, t, tokens, hidden, blob, cws, stream=stream)
         else:
             ws = None
             if m.outlier_mode != OUTLIER_NONE:
                 want = workspace_bytes(m, numel)
-                ws = self._ws.get(stream)
+                ws = self._ws.get(at)
                 if ws is None or ws.c.bytes < want:
-                    ws = self._ws[stream] = alloc_workspace(want, device=t.device)
+                    ws = self._ws[at] = alloc_workspace(want, device=t.device)
             compress(m, t, blob, ws, stream=stream)
         if ev:
             ev[1].record(stream)
