@@ -630,7 +630,7 @@ static int launch_generic_compress(const adacc_method* method, const Plan& p, co
   const bool topk = method->outlier_mode == ADACC_OUTLIER_TOPK;
   const uint32_t lds = ADACC_PICK(p.half, generic_lds_bytes(p.tile_elems, method->quant_group, topk && d.gs < p.tile_elems));
   const uint32_t threads = ADACC_PICK(p.half, generic_threads());
-  hipLaunchKernelGGL(ADACC_PICK(p.half, compress_generic_fn(p.tile_elems, method->outlier_mode, d.gs >= p.tile_elems)), dim3(p.n_tiles), dim3(threads), lds, s, d, epoch);
+  hipLaunchKernelGGL(ADACC_PICK(p.half, compress_generic_fn(p.tile_elems, method->outlier_mode, d.gs)), dim3(p.n_tiles), dim3(threads), lds, s, d, epoch);
   int rc = launch_check("compress_generic_kernel");
   if (rc != ADACC_OK || !p.outliers) return rc;
   rc = launch_block_sums(method, p, d, s);

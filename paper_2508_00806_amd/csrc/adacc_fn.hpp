@@ -30,8 +30,8 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
 //   generic: groups that the tile kernels do not take
 //   kind: kBatch* of adacc_common.hpp
 //   generic_threads, generic_lds_bytes: workgroup size and dynamic LDS of the fallback kernels (one segment per workgroup;
-//     topk_groups: TOPK over several statistics groups of a segment); compress_generic_fn(whole): TOPK over a group
-//     that is the segment; place_generic_fn: their placement
+//     topk_groups: TOPK over several statistics groups of a segment); compress_generic_fn: by segment, mode and
+//     statistics group; place_generic_fn: their placement
 //   stream: the statistics pass reads with the streaming hint (tensors beyond kStatsKeepBytes)
 //   channel_score_channels: channels per workgroup of the score kernel
 //   channel_select_threads: size of the one workgroup of the select kernel
@@ -53,7 +53,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   PlaceFn place_fn();                                                                  \
   PlaceSumBatchFn place_sum_batch_fn();                                                \
   PlaceBatchFn place_batch_fn();                                                       \
-  CompressFn compress_generic_fn(uint32_t tile_elems, uint32_t mode, bool whole);      \
+  CompressFn compress_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs);     \
   CompressFn place_generic_fn(uint32_t tile_elems);                                    \
   uint32_t generic_threads();                                                          \
   uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups);      \

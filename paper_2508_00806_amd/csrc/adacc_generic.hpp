@@ -467,11 +467,15 @@ __device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh,
   return t != 0xFFFFFFFFu;
 }
 
-// How a segment's outliers are chosen, as a template argument of the compression: the mode, or kSegTopkWhole where the
-// segment is one TOPK group (kModeTopk: several), or kSegAny: by the descriptor.  (One kernel for all modes held the
-// registers of the hungriest: 128 for 6 octets per thread, four wavefronts per SIMD, where 84 are enough for TOPK over
-// the segment; [8192, 11008]: 88 -> 77 us at the time.)
-constexpr int kSegTopkWhole = 4, kSegAny = 5;
+// How a segment's outliers are chosen, as a template argument of the compression: the mode, where kModeTopk is several
+// TOPK groups of at most kShortGroup values, kSegTopkLong several longer ones and kSegTopkWhole one; or kSegAny: by the
+// descriptor.  (One kernel for all modes held the registers of the hungriest: 128 for 6 octets per thread, four
+// wavefronts per SIMD, where 84 are enough for TOPK over the segment; [8192, 11008]: 88 -> 77 us at the time.  Long and
+// short TOPK groups in one kernel parked 49 scalar registers in vector lanes, for the 32 keys a lane of the long ones:
+// 268 M values, the largest of every 24: 831 us, 745 us like this.)
+constexpr int kSegTopkWhole = 4, kSegAny = 5, kSegTopkLong = 6;
+constexpr uint32_t kShortGroup = 8u * (uint32_t)kWave;
+constexpr bool kind_is_topk(int kind) { return kind == (int)kModeTopk || kind == kSegTopkLong || kind == kSegTopkWhole; }
 
 // ---- a2 / a3: mask[j] bit e = element e of the thread's octet j is an outlier by the method's rule
 // omag[j]: the largest magnitude of octet j, as the 15 low bits of the pattern
@@ -483,7 +487,7 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
 #pragma unroll
   for (int j = 0; j < SL; ++j) mask[j] = 0u;
   const bool whole = KIND == kSegTopkWhole || (KIND == kSegAny && d.gs >= d.tile_elems);
-  const uint32_t mode = KIND == kSegAny ? d.mode : KIND == kSegTopkWhole ? (uint32_t)kModeTopk : (uint32_t)KIND;
+  const uint32_t mode = KIND == kSegAny ? d.mode : kind_is_topk(KIND) ? (uint32_t)kModeTopk : (uint32_t)KIND;
   if (mode == kModeAbs) {
 #pragma unroll
     for (int j = 0; j < SL; ++j) {
@@ -555,8 +559,8 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
       __syncthreads();  // head, a, b are free again
     } else {
       // Several groups (of at most 2048 elements): the patterns go to LDS, a wavefront takes a group at a time
-      // with the keys of its elements in registers (2, 8 or 32 per lane by the size of the groups), k rounds of a
-      // maximum over the wavefront.
+      // with the keys of its elements in registers (2, 8 or, kSegTopkLong, 32 per lane by the size of the groups), k
+      // rounds of a maximum over the wavefront.
       uint16_t* pat = reinterpret_cast<uint16_t*>(sh.a);
 #pragma unroll
       for (int j = 0; j < SL; ++j) {
@@ -593,9 +597,9 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
           }
         }
       };
-      if (d.gs <= 2u * (uint32_t)kWave) groups_of(std::integral_constant<int, 2>());       // uniform
-      else if (d.gs <= 8u * (uint32_t)kWave) groups_of(std::integral_constant<int, 8>());
-      else groups_of(std::integral_constant<int, 32>());
+      if (KIND == kSegTopkLong || (KIND == kSegAny && d.gs > kShortGroup)) groups_of(std::integral_constant<int, 32>());  // uniform
+      else if (d.gs <= 2u * (uint32_t)kWave) groups_of(std::integral_constant<int, 2>());
+      else groups_of(std::integral_constant<int, (int)(kShortGroup / (uint32_t)kWave)>());
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < SL; ++j) {
@@ -917,7 +921,7 @@ __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentSha
   const uint32_t tid = threadIdx.x;
   uint32_t raw[SL][4], mask[SL], omag[SL];
   const SegmentGeo g = load_segment<SL>(d, seg, raw, omag);
-  if constexpr (KIND == (int)kModeTopk || KIND == kSegTopkWhole) {
+  if constexpr (kind_is_topk(KIND)) {
     const uint32_t gps = d.tile_elems / d.gs;  // groups of a whole segment
     const uint32_t pos0 = seg * gps * d.topk;
     const uint32_t whole = g.cnt / d.gs, rest = g.cnt - whole * d.gs;

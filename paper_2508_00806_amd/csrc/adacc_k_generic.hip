@@ -6,24 +6,25 @@ namespace adacc {
 namespace ADACC_DT_NS {
 
 template <int SL>
-static CompressFn pick(uint32_t mode, bool whole) {
-  switch (mode) {
-    case kModeNone: return compress_generic_kernel<SL, (int)kModeNone>;
-    case kModeAbs: return compress_generic_kernel<SL, (int)kModeAbs>;
-    case kModeStd: return compress_generic_kernel<SL, (int)kModeStd>;
-    default: return whole ? compress_generic_kernel<SL, kSegTopkWhole> : compress_generic_kernel<SL, (int)kModeTopk>;
+static CompressFn pick(uint32_t tile_elems, uint32_t mode, uint32_t gs) {
+  if (mode == kModeNone) return compress_generic_kernel<SL, (int)kModeNone>;
+  if (mode == kModeAbs) return compress_generic_kernel<SL, (int)kModeAbs>;
+  if (mode == kModeStd) return compress_generic_kernel<SL, (int)kModeStd>;
+  if constexpr (SL == 2) {  // several TOPK groups: their segments are of at most 4096 elements, two octets per thread
+    if (gs < tile_elems) return gs <= kShortGroup ? compress_generic_kernel<SL, (int)kModeTopk> : compress_generic_kernel<SL, kSegTopkLong>;
   }
+  return compress_generic_kernel<SL, kSegTopkWhole>;
 }
 static uint32_t slices_of(uint32_t tile_elems) {  // octets per thread
   const uint32_t slices = ((tile_elems + 7u) / 8u + kSegThreads - 1u) / kSegThreads;
   return slices <= 2u ? 2u : slices <= 4u ? 4u : slices <= 6u ? 6u : 8u;
 }
-CompressFn compress_generic_fn(uint32_t tile_elems, uint32_t mode, bool whole) {
+CompressFn compress_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs) {
   switch (slices_of(tile_elems)) {
-    case 2u: return pick<2>(mode, whole);
-    case 4u: return pick<4>(mode, whole);
-    case 6u: return pick<6>(mode, whole);
-    default: return pick<8>(mode, whole);
+    case 2u: return pick<2>(tile_elems, mode, gs);
+    case 4u: return pick<4>(tile_elems, mode, gs);
+    case 6u: return pick<6>(tile_elems, mode, gs);
+    default: return pick<8>(tile_elems, mode, gs);
   }
 }
 CompressFn place_generic_fn(uint32_t tile_elems) {

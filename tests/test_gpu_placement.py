@@ -42,3 +42,15 @@ def test_the_end_of_a_tensor_that_its_groups_do_not_divide(mode, rest):
             print(f"[end] {mode} rest={rest} gq={gq} bits={bits} asym={asym} whole={whole}", flush=True)
             run_parity(x, dict(bits=bits, quant_group=gq, asym=asym, outlier_mode=mode, stat_group=gs,
                                thresh=2.0 if mode in ("abs", "std") else 0.0, topk=7 if mode == "topk" else 0))
+
+
+@pytest.mark.parametrize("group", [24, 504, 512 + 8, 1000, 2040])
+def test_topk_groups_of_the_fallback_kernels(group):
+    """Short and long groups have kernels of their own; regular, and with a group that has more infinities than k."""
+    for extra in (0, 9):
+        for k in (1, 5):
+            n = group * 41 - 13
+            x = torch.randn(n, generator=torch.Generator().manual_seed(group + k)).to(torch.float16)
+            x[7 * group:7 * group + extra] = float("inf")
+            print(f"[placement] topk {k} of {group}, {extra} infinities", flush=True)
+            run_parity(x, dict(bits=4, quant_group=group, asym=1, outlier_mode="topk", stat_group=group, thresh=0.0, topk=k))
