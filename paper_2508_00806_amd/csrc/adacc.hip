@@ -278,12 +278,20 @@ static WsPlan ws_plan(const adacc_method* m, const Plan& p) {
 static bool needs_block_sums(const adacc_method* m, const Plan& p) {
   return p.outliers && m->outlier_mode != ADACC_OUTLIER_TOPK && p.n_tiles > kPlaceDirectTiles;
 }
-// workgroups of the placement: one per kPlaceTiles tiles (kSumTiles of a long tensor), one more for the end that the
-// groups do not divide
+// tiles (segments) that a workgroup of the placement takes, and its workgroups: one more for the end that the groups do
+// not divide
+static uint32_t place_per(const adacc_method* m, const Plan& p) {
+  if (!p.generic) return needs_block_sums(m, p) ? (uint32_t)kSumTiles : (uint32_t)kPlaceTiles;
+  const bool topk = m->outlier_mode == ADACC_OUTLIER_TOPK;
+  const uint32_t workgroups = topk && p.tile_elems <= 4096 ? 4u * kPlaceWorkgroups : kPlaceWorkgroups;
+  uint32_t per = 1;
+  while (per < (uint32_t)kPlaceSegments && per * workgroups < p.n_tiles) per *= 2;
+  if (topk && per * workgroups < p.n_tiles) per *= blocks_of(p.n_tiles, (int)(per * workgroups));
+  return per;
+}
 static uint32_t place_grid(const adacc_method* m, const Plan& p) {
   if (!p.outliers) return 0u;
-  if (p.generic) return blocks_of(p.n_tiles, kPlaceSegments);
-  return blocks_of(p.n_tiles, needs_block_sums(m, p) ? kSumTiles : kPlaceTiles) + (p.tail != 0 ? 1u : 0u);
+  return blocks_of(p.n_tiles, (int)place_per(m, p)) + (!p.generic && p.tail != 0 ? 1u : 0u);
 }
 // wavefronts of the tile launch: one per tile, one more for the end of a tensor without outliers
 static uint32_t tile_waves(const Plan& p) { return p.n_tiles + (!p.outliers && p.tail != 0 ? 1u : 0u); }
@@ -321,6 +329,7 @@ static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, cons
   d->tile_elems = p.tile_elems;
   d->generic = p.generic ? 1u : 0u;
   d->from_sums = needs_block_sums(m, p) ? 1u : 0u;
+  d->place_per = p.outliers ? place_per(m, p) : 0u;
   d->lgt = p.tile_elems == 4096 ? 12u : 11u;
   if (dst) {  // decompression counts pieces of 2048 elements of the whole tensor
     d->numel = numel;
@@ -635,7 +644,7 @@ static int launch_generic_compress(const adacc_method* method, const Plan& p, co
   if (rc != ADACC_OK || !p.outliers) return rc;
   rc = launch_block_sums(method, p, d, s);
   if (rc != ADACC_OK) return rc;
-  hipLaunchKernelGGL(ADACC_PICK(p.half, place_generic_fn(p.tile_elems)), dim3(place_grid(method, p)), dim3(threads), lds, s, d, epoch);
+  hipLaunchKernelGGL(ADACC_PICK(p.half, place_generic_fn(p.tile_elems, method->outlier_mode, d.gs)), dim3(place_grid(method, p)), dim3(threads), lds, s, d, epoch);
   return launch_check("place_generic_kernel");
 }
 

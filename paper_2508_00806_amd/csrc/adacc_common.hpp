@@ -98,6 +98,7 @@ struct TensorDesc {
   uint32_t tile_elems;      // elements per tile of the blob
   uint32_t generic;         // 1: the method goes through the fallback kernels
   uint32_t from_sums;       // compress: 1 = the placement starts from block_sum (a kernel of its own forms them)
+  uint32_t place_per;       // compress: tiles (fallback: segments) that a workgroup of the placement takes
   uint32_t lgt;             // log2(elements per tile): 11 or 12
   uint32_t lgq;         // log2(quant group)
   uint32_t lgs;         // log2(stat group) (STD / TOPK)
@@ -147,11 +148,19 @@ struct ChannelwiseDesc {
 // Outliers of a tile that travel through the tile's slot in the workspace (ABS / STD); a tile with
 // more is selected a second time by the placement kernel.
 constexpr int kSlot = 64;
-// The placement kernels: a workgroup of kPlaceThreads threads takes kPlaceTiles consecutive tiles, or kPlaceSegments
-// segments of the fallback kernels (which the whole workgroup selects again where a slot does not do).
+// The placement kernels: a workgroup of kPlaceThreads threads takes kPlaceTiles consecutive tiles.
 constexpr int kPlaceThreads = 256;
 constexpr int kPlaceTiles = 64;
+// Of the fallback kernels' segments, which the whole workgroup selects again where a slot does not do, one after the
+// other, it takes 1, 2, 4, .. kPlaceSegments: the fewest with which kPlaceWorkgroups workgroups, as many as the device
+// holds at once, are enough.  (Always 16, at half the wavefronts: 128 rows of 11008 values with some 94 outliers each
+// 113 us, 1024 of them 126 and 8192 of them 201; 19, 27 and 146 us like this.)  TOPK, where only values that are not
+// finite make the placement do anything, and then all segments go through it: four times the workgroups for short
+// segments, of which a CU holds twice as many and which leave at once in every other call (0.6 us for 4096 of them);
+// and several times 16 segments rather than more workgroups, because it has no block sums: every workgroup adds up all
+// counts before its own.  (67 M values in groups of 24, one of them with 33 infinities: 619 us, 427 us like this.)
 constexpr int kPlaceSegments = 16;
+constexpr uint32_t kPlaceWorkgroups = 1024;
 // Tensors of more tiles than this add their counts up in blocks of kSumTiles first, in a kernel of its own, and a
 // workgroup of the placement takes such a block.  Below, every workgroup adds up all counts before its own: at most
 // four rounds of eight loads of 16 bytes per thread, about as long as that launch (4.5 us).  (Blocks of 64 tiles

@@ -1537,15 +1537,18 @@ __device__ __forceinline__ void reselect_tile(const TensorDesc& d, uint32_t tile
 struct PlacedTiles {
   uint32_t first, n_here;  // uniform
   uint32_t base;           // uniform: outliers of all tiles before the window
+  uint32_t after;          // uniform: and with those of the window (a window of the whole workgroup only)
   uint32_t count, excl;    // outliers of the lane's tile, and of the window's tiles before it
 };
 
 // The offsets of TILES tiles from the counts: tile_ptr, and by the workgroup that holds the last tile the total and the
 // overflow flag (unless elements behind the last tile still have to be added, then those do it).  `move`: the records
 // of tiles that fit their slot go to the stream.  TILES <= 64: the window of all wavefronts is the workgroup's tiles,
-// each moves its share; TILES = 256: a window per wavefront.
+// each moves its share; TILES = 256: a window per wavefront.  first: the first tile, `most`: at most that many of the
+// TILES; before: the outliers of all tiles before them, where the caller knows (`known`).
 template <int TILES, class Shared>
-__device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t block, bool from_sums, bool move, Shared& sh) {
+__device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t first, uint32_t most, bool known, uint32_t before,
+                                                   bool from_sums, bool move, Shared& sh) {
   constexpr bool OWN = TILES > kWave;  // a window per wavefront
   constexpr int WINDOW = OWN ? kWave : TILES;
   constexpr int WAVES = kPlaceThreads / kWave;
@@ -1553,16 +1556,16 @@ __device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   PlacedTiles p;
-  const uint32_t first = block * (uint32_t)TILES;
   p.first = first + (OWN ? wave * (uint32_t)kWave : 0u);
   const uint32_t left = p.first < d.n_tiles ? d.n_tiles - p.first : 0u;
   p.n_here = left < (uint32_t)WINDOW ? left : (uint32_t)WINDOW;
+  if constexpr (!OWN) p.n_here = p.n_here < most ? p.n_here : most;
   p.count = lane < p.n_here ? d.cnt[p.first + lane] : 0u;  // (asked for ahead of the sums)
   if constexpr (OWN) {
     const uint32_t mine = wave_sum_u32(p.count);
     if (lane == 0u) sh.window[wave] = mine;  // (read behind the barriers of outliers_before)
   }
-  p.base = outliers_before(d, first, from_sums, sh);
+  p.base = known ? before : outliers_before(d, first, from_sums, sh);  // uniform
   if constexpr (OWN) {
 #pragma unroll
     for (int w = 0; w < WAVES - 1; ++w) p.base += (uint32_t)w < wave ? sh.window[w] : 0u;
@@ -1574,6 +1577,7 @@ __device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t
     if (lane >= (uint32_t)off) incl += up;
   }
   p.excl = incl - p.count;
+  p.after = p.base + (uint32_t)__builtin_amdgcn_readlane((int)incl, WINDOW - 1);
   if ((OWN || wave == 0u) && p.n_here != 0u) {  // uniform
     if (lane < p.n_here) d.tile_ptr[p.first + lane] = p.base + p.excl;
     if (p.first + p.n_here == d.n_tiles && lane == p.n_here - 1u) {  // the blob's last tile closes it

@@ -54,7 +54,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   PlaceSumBatchFn place_sum_batch_fn();                                                \
   PlaceBatchFn place_batch_fn();                                                       \
   CompressFn compress_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs);     \
-  CompressFn place_generic_fn(uint32_t tile_elems);                                    \
+  CompressFn place_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs);        \
   uint32_t generic_threads();                                                          \
   uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups);      \
   ChannelPartialFn channel_partial_fn(bool stream);                                    \

@@ -469,10 +469,10 @@ __device__ __forceinline__ bool topk_few(const SegmentGeo& g, SegmentShared& sh,
 
 // How a segment's outliers are chosen, as a template argument of the compression: the mode, where kModeTopk is several
 // TOPK groups of at most kShortGroup values, kSegTopkLong several longer ones and kSegTopkWhole one; or kSegAny: by the
-// descriptor.  (One kernel for all modes held the registers of the hungriest: 128 for 6 octets per thread, four
-// wavefronts per SIMD, where 84 are enough for TOPK over the segment; [8192, 11008]: 88 -> 77 us at the time.  Long and
-// short TOPK groups in one kernel parked 49 scalar registers in vector lanes, for the 32 keys a lane of the long ones:
-// 268 M values, the largest of every 24: 831 us, 745 us like this.)
+// descriptor, for a segment that is one statistics group.  (One kernel for all modes held the registers of the
+// hungriest: 128 for 6 octets per thread, four wavefronts per SIMD, where 84 are enough for TOPK over the segment;
+// [8192, 11008]: 88 -> 77 us at the time.  Long and short TOPK groups in one kernel parked 49 scalar registers in vector
+// lanes, for the 32 keys a lane of the long ones; 268 M values, the largest of every 24: 831 us, 745 us like this.)
 constexpr int kSegTopkWhole = 4, kSegAny = 5, kSegTopkLong = 6;
 constexpr uint32_t kShortGroup = 8u * (uint32_t)kWave;
 constexpr bool kind_is_topk(int kind) { return kind == (int)kModeTopk || kind == kSegTopkLong || kind == kSegTopkWhole; }
@@ -486,7 +486,7 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
   const uint32_t tid = threadIdx.x;
 #pragma unroll
   for (int j = 0; j < SL; ++j) mask[j] = 0u;
-  const bool whole = KIND == kSegTopkWhole || (KIND == kSegAny && d.gs >= d.tile_elems);
+  constexpr bool whole = KIND == kSegTopkWhole || KIND == kSegAny;
   const uint32_t mode = KIND == kSegAny ? d.mode : kind_is_topk(KIND) ? (uint32_t)kModeTopk : (uint32_t)KIND;
   if (mode == kModeAbs) {
 #pragma unroll
@@ -540,7 +540,7 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
     }
     __syncthreads();  // a, b, g0, g1 are free again
   } else if (mode == kModeTopk) {
-    if (whole) {
+    if constexpr (whole) {
       // The segment is one group: an element is an outlier if its key (magnitude above the reversed element index: unique,
       // ties go to the lower index) reaches the k-th largest.
       const uint32_t limit = topk_rounds<SL>(g, sh, raw, omag, d.topk < g.cnt ? d.topk : g.cnt);  // at most 32
@@ -569,7 +569,8 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
           *reinterpret_cast<uint4*>(pat + o * (uint32_t)kOct) = make_uint4(raw[j][0], raw[j][1], raw[j][2], raw[j][3]);
       }
       __syncthreads();
-      const uint32_t lane = (uint32_t)lane_id();
+      uint32_t lane = (uint32_t)lane_id();
+      asm volatile("" : "+v"(lane));  // what follows from it is formed here: ahead of a loop over segments it would fill 60 registers
       // KC: keys per lane, 64 * KC elements at most in a group
       auto groups_of = [&](auto KCc) {
         constexpr int KC = decltype(KCc)::value;
@@ -597,8 +598,8 @@ __device__ __forceinline__ void segment_select(const TensorDesc& d, const Segmen
           }
         }
       };
-      if (KIND == kSegTopkLong || (KIND == kSegAny && d.gs > kShortGroup)) groups_of(std::integral_constant<int, 32>());  // uniform
-      else if (d.gs <= 2u * (uint32_t)kWave) groups_of(std::integral_constant<int, 2>());
+      if constexpr (KIND == kSegTopkLong) groups_of(std::integral_constant<int, 32>());
+      else if (d.gs <= 2u * (uint32_t)kWave) groups_of(std::integral_constant<int, 2>());  // uniform
       else groups_of(std::integral_constant<int, (int)(kShortGroup / (uint32_t)kWave)>());
       __syncthreads();
 #pragma unroll
@@ -978,28 +979,39 @@ __global__ __launch_bounds__(kSegThreads, (generic_min_waves<SL, KIND>())) void 
   compress_segment<SL, KIND>(d, sh, blockIdx.x, epoch);
 }
 
-// The placement of kPlaceSegments segments, and those that no slot held once more from the source, the whole workgroup
-// on one after the other.  (That was a launch of its own behind the placement, in which nearly every workgroup left at
-// once: 4.5 us on every call.)
-template <int SL>
-__global__ __launch_bounds__(kSegThreads, SL <= 4 ? 4 : 2) void place_generic_kernel(TensorDesc d, uint32_t epoch) {
+// The placement of d.place_per segments, and those that no slot held once more from the source, the whole workgroup on
+// one after the other.  (That was a launch of its own behind the placement, in which nearly every workgroup left at
+// once: 4.5 us on every call.)  A kernel per kind, and wavefronts per SIMD as many as do without a spill: nothing but
+// another workgroup fills the round trips, and one kernel for all kinds left room for two.
+template <int SL, int KIND>
+constexpr int place_min_waves() { return SL <= 2 ? (KIND == kSegTopkLong ? 6 : 7) : SL <= 6 ? 4 : 3; }
+template <int SL, int KIND>
+__global__ __launch_bounds__(kSegThreads, (place_min_waves<SL, KIND>())) void place_generic_kernel(TensorDesc d, uint32_t epoch) {
   static_assert(kSegThreads == (uint32_t)kPlaceThreads, "one workgroup for both");
   extern __shared__ __attribute__((aligned(16))) unsigned char segment_lds[];
   __shared__ PlaceShared place;
-  const bool topk = d.mode == kModeTopk;
+  constexpr bool topk = kind_is_topk(KIND);
   if (topk && __hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) return;  // uniform
-  const PlacedTiles p = place_tiles<kPlaceSegments>(d, blockIdx.x, d.from_sums != 0u, !topk, place);
   const uint32_t room = topk ? 0u : (uint32_t)kSlot;
-  if (__builtin_amdgcn_ballot_w64(p.count > room) == 0ull) return;  // the same in every wavefront
-  SegmentShared sh = segment_shared<SL>(segment_lds, d.tile_elems, d.gq);
-  for (uint32_t j = 0; j < p.n_here; ++j) {
-    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j);
-    if (n <= room) continue;  // uniform over the workgroup
-    uint32_t raw[SL][4], mask[SL], omag[SL];
-    const SegmentGeo g = load_segment<SL>(d, p.first + j, raw, omag);
-    segment_outliers<SL, kSegAny>(d, g, sh, raw, omag, mask);
-    const uint32_t pos0 = p.base + (uint32_t)__builtin_amdgcn_readlane((int)p.excl, (int)j), end = pos0 + n;
-    segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
+  const uint32_t first = blockIdx.x * d.place_per;
+  const uint32_t end = d.n_tiles - first < d.place_per ? d.n_tiles : first + d.place_per;
+  uint32_t before = 0u;
+  for (uint32_t at = first; at < end; at += (uint32_t)kPlaceSegments) {  // uniform; once, but for TOPK of very many segments
+    const TensorDesc& desc = topk ? descriptor_again() : d;
+    const PlacedTiles p = place_tiles<kPlaceSegments>(desc, at, end - at, at != first, before, desc.from_sums != 0u, !topk, place);
+    before = p.after;
+    for (uint32_t j = 0; j < p.n_here; ++j) {
+      const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j);
+      if (n <= room) continue;  // uniform over the workgroup
+      const TensorDesc& again = descriptor_again();
+      SegmentShared sh = segment_shared<SL>(segment_lds, again.tile_elems, again.gq);
+      uint32_t raw[SL][4], mask[SL], omag[SL];
+      const SegmentGeo g = load_segment<SL>(again, p.first + j, raw, omag);
+      segment_outliers<SL, KIND>(again, g, sh, raw, omag, mask);
+      const uint32_t pos0 = p.base + (uint32_t)__builtin_amdgcn_readlane((int)p.excl, (int)j), last = pos0 + n;
+      segment_emit(g, sh, raw, mask, StreamSink{again.idx, again.val}, pos0, last < again.cap ? last : again.cap);
+    }
+    if constexpr (!topk) break;
   }
 }
 

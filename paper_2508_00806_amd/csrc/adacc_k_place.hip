@@ -73,8 +73,8 @@ __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t blo
   }
   if (regular) return;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const PlacedTiles p = from_sums ? place_tiles<kSumTiles>(d, block, true, !topk, lds.place)
-                                  : place_tiles<kPlaceTiles>(d, block, false, !topk, lds.place);
+  const PlacedTiles p = from_sums ? place_tiles<kSumTiles>(d, block * per, per, false, 0u, true, !topk, lds.place)
+                                  : place_tiles<kPlaceTiles>(d, block * per, per, false, 0u, false, !topk, lds.place);
   const uint32_t room = topk ? 0u : (uint32_t)kSlot;
   if (__builtin_amdgcn_ballot_w64(p.count > room) == 0ull) return;  // the usual case: every tile is in its slot
   const uint32_t j = from_sums ? 0u : wave, step = from_sums ? 1u : (uint32_t)(kPlaceThreads / kWave);

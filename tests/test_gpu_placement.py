@@ -44,6 +44,29 @@ def test_the_end_of_a_tensor_that_its_groups_do_not_divide(mode, rest):
                                thresh=2.0 if mode in ("abs", "std") else 0.0, topk=7 if mode == "topk" else 0))
 
 
+# a workgroup of the placement takes 1, 2, 4, 8, 16 segments of the fallback kernels, TOPK of very many several times 16
+SEGMENTS = ([("std", 2056, s) for s in (1, 5, 1024, 1025, 2049, 4097, 8193, 32769 + 15)] +
+            [("topk", 2056, s) for s in (1, 5, 4096, 4097, 16385, 65537 + 21)] + [("topk", 4104, s) for s in (1025, 16385 + 18)])
+
+
+@pytest.mark.parametrize("mode,group,segments", SEGMENTS)
+def test_segments_selected_again(mode, group, segments):
+    """Some segments beyond their slot (STD), all of them once more because one is irregular (TOPK)."""
+    n = group * segments - 700
+    g = torch.Generator().manual_seed(segments)
+    x = (torch.rand(n, generator=g) - 0.5).to(torch.bfloat16)
+    at = {0, segments // 2, max(segments - 2, 0), segments - 1} | set(range(3, min(segments, 40), 5))
+    for t in at:
+        first = group * t
+        k = min(70 + t % 7, n - first)
+        x[first:first + k] = 9.0 + (torch.arange(k) % 5).to(torch.bfloat16)
+    if mode == "topk":
+        x[group * (segments // 2) + 100:group * (segments // 2) + 105] = float("inf")
+    print(f"[placement] {segments} segments of {group}, {mode}", flush=True)
+    oc, *_ = run_parity(x, dict(bits=8, quant_group=group, asym=0, outlier_mode=mode, stat_group=group, thresh=2.0, topk=2))
+    assert oc.n_out > (64 if mode == "std" else 2 * segments)
+
+
 @pytest.mark.parametrize("group", [24, 504, 512 + 8, 1000, 2040])
 def test_topk_groups_of_the_fallback_kernels(group):
     """Short and long groups have kernels of their own; regular, and with a group that has more infinities than k."""
