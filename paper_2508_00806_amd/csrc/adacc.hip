@@ -281,7 +281,7 @@ static bool needs_block_sums(const adacc_method* m, const Plan& p) {
 // tiles (segments) that a workgroup of the placement takes, and its workgroups: one more for the end that the groups do
 // not divide
 static uint32_t place_per(const adacc_method* m, const Plan& p) {
-  if (!p.generic) return needs_block_sums(m, p) ? (uint32_t)kSumTiles : (uint32_t)kPlaceTiles;
+  if (!p.generic) return p.n_tiles > kPlaceDirectTiles ? (uint32_t)kSumTiles : (uint32_t)kPlaceTiles;
   const bool topk = m->outlier_mode == ADACC_OUTLIER_TOPK;
   const uint32_t workgroups = topk && p.tile_elems <= 4096 ? 4u * kPlaceWorkgroups : kPlaceWorkgroups;
   uint32_t per = 1;

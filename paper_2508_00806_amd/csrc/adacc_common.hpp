@@ -161,11 +161,13 @@ constexpr int kPlaceTiles = 64;
 // counts before its own.  (67 M values in groups of 24, one of them with 33 infinities: 619 us, 427 us like this.)
 constexpr int kPlaceSegments = 16;
 constexpr uint32_t kPlaceWorkgroups = 1024;
-// Tensors of more tiles than this add their counts up in blocks of kSumTiles first, in a kernel of its own, and a
-// workgroup of the placement takes such a block.  Below, every workgroup adds up all counts before its own: at most
-// four rounds of eight loads of 16 bytes per thread, about as long as that launch (4.5 us).  (Blocks of 64 tiles
-// behind the sums: 524288 tiles with an outlier each take 24.6 us, 8192 workgroups of which a CU holds four; blocks of
-// 256 10.8 us, where a thread per record and a bisection took 14.1.)
+// In a tensor of more tiles than this a workgroup of the placement takes kSumTiles of them, and the counts are added up in
+// blocks of that many first, in a kernel of its own (ABS / STD: TOPK, whose placement does nothing in ordinary calls, has
+// none).  Below, and for TOPK, every workgroup adds up all counts before its own: at most four rounds of eight loads of
+// 16 bytes per thread up to this many tiles, about as long as that launch (4.5 us).  (Blocks of 64 tiles behind the sums:
+// 524288 tiles with an outlier each take 24.6 us, 8192 workgroups of which a CU holds four; blocks of 256 10.8 us, where a
+// thread per record and a bisection took 14.1.  TOPK of 1000000 tiles, one of them irregular, with 64 to a workgroup: 2.53
+// ms, most of it counts that 15625 workgroups add up; with 256 1.80.)
 constexpr int kSumTiles = 256;
 constexpr uint32_t kPlaceDirectTiles = 32768;
 // The workspace's launch counter ("epoch", kept on the host in adacc_workspace) marks what a launch

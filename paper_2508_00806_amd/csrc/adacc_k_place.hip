@@ -63,7 +63,8 @@ __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t blo
   const bool topk = d.mode == kModeTopk;
   // TOPK: regular counts everywhere (the usual case): the compression kernel has placed everything already
   const bool regular = topk && __hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch;
-  const uint32_t per = from_sums ? (uint32_t)kSumTiles : (uint32_t)kPlaceTiles;
+  const bool wide = d.place_per == (uint32_t)kSumTiles;
+  const uint32_t per = wide ? (uint32_t)kSumTiles : (uint32_t)kPlaceTiles;
   const uint32_t blocks = (d.n_tiles + per - 1u) / per;
   if (block >= blocks) {
     if (d.tail == 0u || block != blocks) return;
@@ -73,11 +74,11 @@ __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t blo
   }
   if (regular) return;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const PlacedTiles p = from_sums ? place_tiles<kSumTiles>(d, block * per, per, false, 0u, true, !topk, lds.place)
-                                  : place_tiles<kPlaceTiles>(d, block * per, per, false, 0u, false, !topk, lds.place);
+  const PlacedTiles p = wide ? place_tiles<kSumTiles>(d, block * per, per, false, 0u, from_sums, !topk, lds.place)
+                             : place_tiles<kPlaceTiles>(d, block * per, per, false, 0u, false, !topk, lds.place);
   const uint32_t room = topk ? 0u : (uint32_t)kSlot;
   if (__builtin_amdgcn_ballot_w64(p.count > room) == 0ull) return;  // the usual case: every tile is in its slot
-  const uint32_t j = from_sums ? 0u : wave, step = from_sums ? 1u : (uint32_t)(kPlaceThreads / kWave);
+  const uint32_t j = wide ? 0u : wave, step = wide ? 1u : (uint32_t)(kPlaceThreads / kWave);
   const bool e8 = (d.variant & 1u) != 0u;
   switch (d.variant >> 3) {
     case kModeAbs:

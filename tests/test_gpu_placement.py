@@ -77,3 +77,15 @@ def test_topk_groups_of_the_fallback_kernels(group):
             x[7 * group:7 * group + extra] = float("inf")
             print(f"[placement] topk {k} of {group}, {extra} infinities", flush=True)
             run_parity(x, dict(bits=4, quant_group=group, asym=1, outlier_mode="topk", stat_group=group, thresh=0.0, topk=k))
+
+
+@pytest.mark.parametrize("tiles,rest", [(32768, 0), (32768 + 261, 1999)])
+def test_long_topk_tensor_with_irregular_groups(tiles, rest):
+    """Where a workgroup of the placement begins to take 256 tiles: groups with more infinities than k next to its borders."""
+    n = 2048 * tiles + rest
+    x = (torch.rand(n, generator=torch.Generator().manual_seed(tiles)) - 0.5).to(torch.bfloat16)
+    for t in (0, 63, 64, 255, 256, 257, 32767, tiles - 1):
+        x[2048 * t + 5:2048 * t + 9 + t % 3] = float("-inf")
+    print(f"[placement] topk, {tiles} tiles", flush=True)
+    oc, *_ = run_parity(x, dict(bits=4, quant_group=128, asym=0, outlier_mode="topk", stat_group=2048, thresh=0.0, topk=2))
+    assert oc.n_out > 2 * tiles
