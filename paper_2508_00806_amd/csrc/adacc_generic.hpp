@@ -810,6 +810,10 @@ __device__ __forceinline__ void segment_quantise(const TensorDesc& d, const Segm
       if (lane == 0u) { sh.head[40u + wave] = (uint32_t)hi; sh.head[44u + wave] = (uint32_t)lo; }
     }
     __syncthreads();
+    // (binary16, where widening is a conversion: the compiler kept the widened values of all octets over the barrier for
+    // the codes; 6 octets per thread without outliers spilled 112 registers, [3048, 11008] int4 took 51 us, 17 us like
+    // this)
+    if constexpr (ADACC_F16 != 0) forget_derived<SL>(raw);
 #pragma unroll
     for (uint32_t w = 0; w < kSegWaves; ++w) {
       if constexpr (!ASYM) {
