@@ -47,6 +47,9 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(TensorDesc d, uint
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
   __shared__ DecompressShared shared;
   const uint32_t piece = blockIdx.x * kWavesPerWg + wave;  // (no loop over pieces: it would cost 20 registers)
+  // what the first loads need is asked for together with n_tiles, one round trip to the kernel's arguments instead of two
+  // (2^25 values of int8 codes: 15.3 -> 15.1 us from a blob in the caches, 15.7 -> 15.5 from memory)
+  asm volatile("" ::"s"(d.codes), "s"(d.scales), "s"(d.zp), "s"(d.dst), "s"(d.numel), "s"(d.lgq));
   if (piece < d.n_tiles) decompress_piece<BITS, ASYM, F32, GENERIC>(d, piece, has_outliers != 0u, shared);
 }
 
