@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
   const uint32_t rest = m ^ lowest;
 
   uint32_t cw[kChannelStripRows][V * BITS > 32 ? 2 : 1];
-  float sc[4], zp[kChannelStripRows];
+  float sc[kChannelStripRows], zp[kChannelStripRows];
   uint32_t pre[kChannelStripRows];
   const uint16_t* src[kChannelStripRows];
 #pragma unroll
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
       float* p = reinterpret_cast<float*>(d.dst) + e0;
       ADACC_STORE16(p, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
     } else {
-      uint32_t w[kChannelStripRows];
+      uint32_t w[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) w[k] = narrow_pair(v[2 * k], v[2 * k + 1]);
       if (keep != 0u) {  // the kept values go in as they were stored, bit for bit (no conversion touches a NaN)
