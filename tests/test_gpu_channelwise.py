@@ -77,3 +77,36 @@ def test_values_that_need_care():
 def test_full_size_c2_shape():
     print("[channelwise] full C2 shape", flush=True)
     run(workloads.make("c2", "cpu"), 4)
+
+
+@pytest.mark.parametrize("rest", [1, 4, 5, 8])
+def test_long_restoration_takes_eight_tokens_at_a_time(rest):
+    """More than 2^27 values: a wavefront goes through eight tokens in two turns of four.  The last block of tokens is full
+    or ends in either turn, the last strip is short; codes and scales are drawn, and every value is compared."""
+    hidden = 8200  # 16 strips of 512 (32 of 256, binary32) and one octet
+    tokens = 8 * 2046 + rest
+    n = tokens * hidden
+    assert n > 1 << 27
+    g = torch.Generator(device="cuda").manual_seed(rest)
+    for bits, dtype in ((8, torch.bfloat16), (4, torch.float16)):
+        print(f"[channelwise] long restoration, rows={tokens} bits={bits}", flush=True)
+        L = adacc.channelwise_layout_of(bits, tokens, hidden)
+        blob = torch.randint(0, 256, (int(L.total_bytes),), dtype=torch.uint8, device="cuda", generator=g)
+        scale = torch.rand(hidden, device="cuda", generator=g) + 2.0 ** -10
+        blob[L.scales_off:L.scales_off + 4 * hidden].view(torch.float32).copy_(scale)
+        packed = blob[L.codes_off:L.codes_off + n * bits // 8]
+        d32 = torch.full((n,), 7.0, dtype=torch.float32, device="cuda")
+        d16 = torch.full((n,), 7.0, dtype=dtype, device="cuda")
+        adacc.channelwise_decompress(bits, blob, tokens, hidden, d32)
+        adacc.channelwise_decompress(bits, blob, tokens, hidden, d16)
+        for t0 in range(0, tokens, 4096):
+            t1 = min(t0 + 4096, tokens)
+            p = packed[t0 * hidden * bits // 8:t1 * hidden * bits // 8]
+            if bits == 8:
+                codes = p.view(torch.int8)
+            else:
+                codes = torch.stack((p & 15, p >> 4), dim=1).view(-1).to(torch.int8)
+                codes = torch.where(codes > 7, codes - 16, codes)
+            want = codes.view(t1 - t0, hidden).to(torch.float32) * scale
+            assert torch.equal(d32[t0 * hidden:t1 * hidden].view(t1 - t0, hidden), want)
+            assert torch.equal(d16[t0 * hidden:t1 * hidden].view(t1 - t0, hidden), want.to(dtype))
