@@ -1004,6 +1004,7 @@ __global__ __launch_bounds__(kSegThreads, (place_min_waves<SL, KIND>())) void pl
     const TensorDesc& desc = topk ? descriptor_again() : d;
     const PlacedTiles p = place_tiles<kPlaceSegments>(desc, at, end - at, at != first, before, desc.from_sums != 0u, !topk, place);
     before = p.after;
+    if (!topk && __builtin_amdgcn_ballot_w64(p.count > room) == 0ull) return;  // the usual case; the same in every wavefront
     for (uint32_t j = 0; j < p.n_here; ++j) {
       const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j);
       if (n <= room) continue;  // uniform over the workgroup
