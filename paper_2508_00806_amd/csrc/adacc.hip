@@ -86,7 +86,7 @@ static int env_int(const char* name, int dflt) {
 
 // Run-time knobs for measurements, read from the environment once per process.
 struct Knobs {
-  int grid_rounds;      // ADACC_GRID_ROUNDS: limit grids of independent tiles to this many rounds of resident workgroups
+  int grid_rounds;      // ADACC_GRID_ROUNDS: rounds of resident workgroups in the grid of a kernel that loops over tiles
   int wgs_per_cu;       // ADACC_WGS_PER_CU: overrides the occupancy query behind that limit
   int mask_wgs_per_cu;  // ADACC_MASK_WGS_PER_CU: grid of the mask kernels
 };
@@ -119,7 +119,7 @@ struct Plan {  // everything derived from (method, numel)
   bool outliers;
   uint32_t tile_elems, lgq, lgs, variant;
   uint64_t numel_main;   // the whole groups of the larger kind: what the tile kernels take
-  uint32_t tail;         // elements after those, done by the tail kernels
+  uint32_t tail;         // elements after those: one short group, an extra wavefront's or workgroup's share of a launch
   uint32_t n_tiles;      // tiles of the main part
   uint32_t n_tiles_all;  // tiles of the whole tensor (what the layout reports)
   bool rowwise;  // every group lies inside a 512-element row and both kinds of group coincide
@@ -297,7 +297,7 @@ static uint32_t place_grid(const adacc_method* m, const Plan& p) {
 static uint32_t tile_waves(const Plan& p) { return p.n_tiles + (!p.outliers && p.tail != 0 ? 1u : 0u); }
 
 static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, const adacc_layout& L, const void* src,
-                      void* blob, void* dst, int dst_dtype, void* ws_region, TensorDesc* d) {
+                      void* blob, void* dst, void* ws_region, TensorDesc* d) {
   std::memset(d, 0, sizeof *d);
   unsigned char* b = static_cast<unsigned char*>(blob);
   d->src = static_cast<const uint16_t*>(src);
@@ -356,20 +356,16 @@ static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, cons
   }
   d->variant = p.variant;
   d->rowwise = p.rowwise ? 1u : 0u;
-  d->dst_f32 = dst_dtype == ADACC_DST_F32 ? 1u : 0u;
 }
 
 static bool misaligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
 
-// Grid for kernels whose tiles are independent (grid-stride loop).  By default one workgroup per
-// four tiles, i.e. every wavefront takes one tile: with streaming accesses the hardware's own
-// order of workgroups, which walks through memory front to back, beat every grid of resident
-// workgroups that loop (C4 decompression: 0.308 ms with one round of resident workgroups, 0.275 ms
-// like this).  ADACC_GRID_ROUNDS=r limits the grid to r times the workgroups the device holds at
-// once, for comparison.
-// `resident_rounds` > 0: the kernel has a set-up cost per workgroup (the outlier-channel kernels stage
-// tables in LDS), so its grid is limited to that many times the resident workgroups.
-static int grid_for(uint32_t n_tiles, const void* kernel, uint32_t* grid, int resident_rounds = 0) {
+// Grid of the tile form of the outlier-channel compression, the one kernel that still loops over tiles: it stages
+// tables in LDS, a cost per workgroup, so its grid is limited to `resident_rounds` times the workgroups that the device
+// holds at once (ADACC_GRID_ROUNDS overrides that).  All others take one tile or piece per wavefront: with
+// streaming accesses the hardware's own order of workgroups, which walks through memory front to back, beat every
+// grid of resident workgroups that loop (C4 decompression: 0.308 ms with one round of them, 0.275 ms without).
+static int grid_for(uint32_t n_tiles, const void* kernel, uint32_t* grid, int resident_rounds) {
   const uint64_t want = ((uint64_t)n_tiles + kWavesPerWg - 1) / kWavesPerWg;
   uint64_t cap = want;
   const int rounds = knobs().grid_rounds > 0 ? knobs().grid_rounds : resident_rounds;
@@ -669,7 +665,7 @@ static int compress_one(const adacc_method* method, const void* src, uint64_t nu
   rc = device_cus(&cus);  // also: fail here, before any state changes, when there is no device
   if (rc != ADACC_OK) return rc;
   TensorDesc d;
-  fill_desc(method, numel, p, L, src, blob, nullptr, 0, p.outliers ? ws->device_mem : nullptr, &d);
+  fill_desc(method, numel, p, L, src, blob, nullptr, p.outliers ? ws->device_mem : nullptr, &d);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   if (p.generic) {
     uint32_t epoch = 0;
@@ -763,7 +759,7 @@ int adacc_decompress(const adacc_method* method, const void* blob, uint64_t blob
   if (blob_bytes < L.total_bytes) return ADACC_ESIZE;
   if (misaligned(dst, 16) || misaligned(blob, 256)) return ADACC_EALIGN;
   TensorDesc d;
-  fill_desc(method, numel, p, L, nullptr, const_cast<void*>(blob), dst, dst_dtype, nullptr, &d);
+  fill_desc(method, numel, p, L, nullptr, const_cast<void*>(blob), dst, nullptr, &d);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   return launch_decompress(method, p, d, dst_dtype, s);
 }
@@ -800,7 +796,7 @@ uint64_t adacc_batch_workspace_bytes(uint32_t n, const adacc_method* methods, co
 // Descriptors of the active tensors of a batch.
 static int batch_table(uint32_t n, const adacc_method* methods, const std::vector<Plan>& plans, const uint64_t* numels,
                        const void* const* srcs, void* const* blobs, const uint64_t* blob_bytes, void* const* dsts,
-                       int dst_dtype, bool compress, unsigned char* regions, std::vector<TensorDesc>* descs,
+                       bool compress, unsigned char* regions, std::vector<TensorDesc>* descs,
                        std::vector<uint32_t>* origin) {
   uint64_t region_off = 0;
   for (uint32_t i = 0; i < n; ++i) {
@@ -814,7 +810,7 @@ static int batch_table(uint32_t n, const adacc_method* methods, const std::vecto
     if (compress ? misaligned(srcs[i], 16) : misaligned(dsts[i], 16)) return ADACC_EALIGN;
     TensorDesc d;
     fill_desc(&methods[i], numels[i], plans[i], L, compress ? srcs[i] : nullptr, blobs[i], compress ? nullptr : dsts[i],
-              dst_dtype, compress ? regions + region_off : nullptr, &d);
+              compress ? regions + region_off : nullptr, &d);
     descs->push_back(d);
     origin->push_back(i);
     if (compress) region_off += ws_plan(&methods[i], plans[i]).bytes;
@@ -839,7 +835,7 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
   unsigned char* mem = static_cast<unsigned char*>(ws->device_mem);
   std::vector<TensorDesc> descs;
   std::vector<uint32_t> origin;
-  rc = batch_table(n, methods, plans, numels, srcs, blobs, blob_bytes, nullptr, 0, true, mem + bp.regions_off, &descs,
+  rc = batch_table(n, methods, plans, numels, srcs, blobs, blob_bytes, nullptr, true, mem + bp.regions_off, &descs,
                    &origin);
   if (rc != ADACC_OK) return rc;  // every argument is checked before the device is touched
   int cus = 0;
@@ -884,7 +880,7 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
   for (const GroupLaunch& g : tiles)
     hipLaunchKernelGGL(compress_batch_fn(g.kind >= kBatchKinds, g.kind % kBatchKinds),
                        dim3((g.max_units + kWavesPerWg - 1) / kWavesPerWg, g.n_members),
-                       dim3(kThreads), 0, s, dt + g.first_member, static_cast<const uint32_t*>(nullptr), epoch);
+                       dim3(kThreads), 0, s, dt + g.first_member, epoch);
   rc = launch_check("compress_batch_kernel");
   if (rc != ADACC_OK) return rc;
   for (const GroupLaunch& g : sums)
@@ -918,7 +914,7 @@ int adacc_decompress_batch(uint32_t n, const adacc_method* methods, const void* 
   if (misaligned(ws->device_mem, 256)) return ADACC_EALIGN;
   std::vector<TensorDesc> descs;
   std::vector<uint32_t> origin;
-  rc = batch_table(n, methods, plans, numels, nullptr, const_cast<void* const*>(blobs), blob_bytes, dsts, dst_dtype,
+  rc = batch_table(n, methods, plans, numels, nullptr, const_cast<void* const*>(blobs), blob_bytes, dsts,
                    false, nullptr, &descs, &origin);
   if (rc != ADACC_OK) return rc;
   int cus = 0;
@@ -946,7 +942,7 @@ int adacc_decompress_batch(uint32_t n, const adacc_method* methods, const void* 
   for (const GroupLaunch& g : launches)
     hipLaunchKernelGGL(ADACC_PICK(g.kind >= kBatchKinds, decompress_batch_fn(dst_dtype == ADACC_DST_F32)),
                        dim3((g.max_units + kWavesPerWg - 1) / kWavesPerWg, g.n_members), dim3(kThreads), 0, s,
-                       dt + g.first_member, static_cast<const uint32_t*>(nullptr));
+                       dt + g.first_member);
   rc = launch_check("decompress_batch_kernel");
   for (uint32_t i = 0; i < nt && rc == ADACC_OK; ++i)
     if (descs[i].generic) rc = launch_decompress(&methods[origin[i]], plans[origin[i]], descs[i], dst_dtype, s);
@@ -995,7 +991,7 @@ int adacc_channel_compress(const adacc_channel_method* method, const void* src, 
   if (workspace_bytes < adacc_channel_workspace_bytes(tokens, hidden)) return ADACC_ESIZE;
   if (misaligned(src, 16) || misaligned(blob, 256) || misaligned(workspace, 256)) return ADACC_EALIGN;
   TensorDesc d;
-  fill_desc(&cp.quant, cp.numel, cp.plan, cp.quant_layout, src, blob, nullptr, 0, nullptr, &d);
+  fill_desc(&cp.quant, cp.numel, cp.plan, cp.quant_layout, src, blob, nullptr, nullptr, &d);
   ChannelDesc c;
   fill_channel_desc(method, tokens, hidden, L, blob, &c);
   d.status = c.status;  // (octets behind the matrix's end go to the unused part of this block; the plain blob's has the channel mask in its place)
@@ -1047,8 +1043,7 @@ int adacc_channel_decompress(const adacc_channel_method* method, const void* blo
   if (blob_bytes < L.total_bytes) return ADACC_ESIZE;
   if (misaligned(dst, 16) || misaligned(blob, 256)) return ADACC_EALIGN;
   TensorDesc d;
-  fill_desc(&cp.quant, cp.numel, cp.plan, cp.quant_layout, nullptr, const_cast<void*>(blob), dst, dst_dtype, nullptr,
-            &d);
+  fill_desc(&cp.quant, cp.numel, cp.plan, cp.quant_layout, nullptr, const_cast<void*>(blob), dst, nullptr, &d);
   ChannelDesc c;
   fill_channel_desc(method, tokens, hidden, L, const_cast<void*>(blob), &c);
   ChannelFn fn = ADACC_PICK(cp.plan.half, channel_decompress_fn(method->bits, method->asym, dst_dtype == ADACC_DST_F32));

@@ -6,8 +6,9 @@
 //     instruction, fully coalesced (1 KiB);
 //   - a tile is E rows (E = 4 or 8, i.e. 2048 or 4096 elements) and belongs to ONE
 //     wavefront; every statistics / quantisation group lies inside one tile, so all
-//     reductions are wavefront-local and no kernel here needs a workgroup barrier.
-//   - a workgroup is just 4 independent wavefronts.
+//     reductions are wavefront-local, and a workgroup is just 4 independent wavefronts.
+// (The tile and piece kernels; the placement, the fallback kernels and the statistics passes of the channel schemes
+// share work over a workgroup, with barriers.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -110,7 +111,6 @@ struct TensorDesc {
   uint32_t pow2_divisor;  // 1 when D is a power of two
   uint32_t rowwise;     // compress: 1 = every group lies inside a row (row-at-a-time encoder)
   uint32_t variant;     // index into the instantiation table
-  uint32_t dst_f32;     // decompress: 1 = binary32 output
   uint32_t ptr_shift;   // decompress: works on pieces of 2048 elements; piece u belongs to tile u >> ptr_shift
 };
 

@@ -1377,7 +1377,7 @@ __device__ __forceinline__ uint32_t encode_tile(const TensorDesc& d, const TileG
 // ------------------------------------------------------------------ one tile with outliers (ABS / STD / TOPK)
 // Tiles are independent: a wavefront compresses one tile and never waits for another.  What the
 // ordered outlier stream needs from all tiles together - the offset of every tile - is settled
-// afterwards by place_block (below), from the per-tile counts written here.
+// afterwards by place_tiles (below), from the per-tile counts written here.
 //
 // ABS / STD: the tile's outliers (ascending) go to the tile's own slot of kSlot records in the
 // workspace; the placement kernel moves them to their final position.  A tile with more than
@@ -1442,8 +1442,9 @@ __device__ __forceinline__ void compress_tile_outliers(const TensorDesc& d, uint
 // segments; kSumTiles tiles of a long tensor).  It needs the number of outliers in all tiles before them: a workgroup
 // adds up the counts itself, or, for a long tensor, the sums of blocks of kSumTiles counts that a kernel in between has
 // formed.  Nobody waits for anybody.  Every wavefront then scans counts, a lane per tile, and moves the outliers of its
-// share of the tiles from the slots to their final positions, a lane per record.  Tiles that hold more outliers than a slot takes (or all tiles,
-// `reselect_all`) are selected again from the source, one wavefront per tile, and written straight to the stream.
+// share of the tiles from the slots to their final positions, a lane per record.  Tiles that hold more outliers than a
+// slot takes (TOPK: all tiles) are selected again from the source (reselect_tiles), one wavefront per tile, and written
+// straight to the stream.
 // (Bound by round trips to memory and by how few workgroups there are: with 256 tiles to a workgroup, a thread per
 // output position found by bisection and slots of 32 records, 8203 tiles of 20 outliers took 17.8 us on 33
 // workgroups, and 4.5 us for the sums, 6.5 us now; the two-byte index in the tile makes a record one word, so that a slot of 256 bytes

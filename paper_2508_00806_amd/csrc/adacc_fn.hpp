@@ -8,8 +8,8 @@ namespace adacc {
 
 typedef void (*CompressFn)(TensorDesc, uint32_t);
 typedef void (*DecompressFn)(TensorDesc, uint32_t);
-typedef void (*BatchCompressFn)(const TensorDesc*, const uint32_t*, uint32_t);
-typedef void (*BatchDecompressFn)(const TensorDesc*, const uint32_t*);
+typedef void (*BatchCompressFn)(const TensorDesc*, uint32_t);
+typedef void (*BatchDecompressFn)(const TensorDesc*);
 typedef void (*PlaceSumFn)(TensorDesc);
 typedef void (*PlaceFn)(TensorDesc, uint32_t);
 typedef void (*PlaceSumBatchFn)(const TensorDesc*, const uint32_t*);

@@ -974,10 +974,10 @@ __device__ __forceinline__ void compress_segment(const TensorDesc& d, SegmentSha
 
 // wavefronts per SIMD (= workgroups per CU) the registers are held to: the kernel is a chain of memory and LDS
 // round trips with barriers between, which only other resident workgroups can fill
-template <int SL, int KIND>
+template <int SL>
 constexpr int generic_min_waves() { return SL <= 4 ? 8 : SL <= 6 ? 5 : 4; }
 template <int SL, int KIND>
-__global__ __launch_bounds__(kSegThreads, (generic_min_waves<SL, KIND>())) void compress_generic_kernel(TensorDesc d, uint32_t epoch) {
+__global__ __launch_bounds__(kSegThreads, (generic_min_waves<SL>())) void compress_generic_kernel(TensorDesc d, uint32_t epoch) {
   extern __shared__ __attribute__((aligned(16))) unsigned char segment_lds[];
   SegmentShared sh = segment_shared<SL>(segment_lds, d.tile_elems, d.gq);
   compress_segment<SL, KIND>(d, sh, blockIdx.x, epoch);

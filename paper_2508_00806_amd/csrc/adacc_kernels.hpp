@@ -54,8 +54,7 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(TensorDesc d, uint
 }
 
 // ---- batch
-// One launch for a group of tensors of a table: blockIdx.y picks the tensor (members[] holds the
-// group's table entries), blockIdx.x its tiles, four per workgroup; workgroups past the end of a
+// One launch for a group of tensors of a table: blockIdx.y picks the tensor, blockIdx.x its tiles, four per workgroup; workgroups past the end of a
 // shorter tensor leave at once.  The host groups the tensors by kernel and by size (tile counts
 // within a factor of two), so few workgroups are empty; within a launch the hardware goes through
 // the tensors one after the other, front to back.
@@ -92,12 +91,11 @@ constexpr int batch_min_waves() {
 }
 
 template <int KIND>
-__global__ __launch_bounds__(kThreads, (batch_min_waves<KIND>())) void compress_batch_kernel(const TensorDesc* table, const uint32_t* members,
-                                                                  uint32_t epoch) {
+__global__ __launch_bounds__(kThreads, (batch_min_waves<KIND>())) void compress_batch_kernel(const TensorDesc* table, uint32_t epoch) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
-  // members == nullptr: the group's entries are table[0 .. gridDim.y) themselves (the host lays the table out in the
-  // order of these launches): one round trip to memory less before the wavefront's first load
-  const TensorDesc d = table[members ? members[blockIdx.y] : blockIdx.y];
+  // the group's entries are table[0 .. gridDim.y) themselves (the host lays the table out in the order of these
+  // launches): no list of members to look up before the wavefront's first load
+  const TensorDesc d = table[blockIdx.y];
   const uint32_t tile = blockIdx.x * kWavesPerWg + wave;
   if (tile >= d.n_tiles) {
     if (tile == d.n_tiles && d.tail != 0u && d.variant >> 3 == kModeNone) {  // the end of a tensor without outliers
@@ -125,12 +123,11 @@ __global__ __launch_bounds__(kThreads, (batch_min_waves<KIND>())) void compress_
 }
 
 // Batch decompression: the same grouping, over the 2048-element pieces of the tensors.
-// members == nullptr: the group's entries are table[0 .. gridDim.y) themselves (the host lays the table out in
-// the order of the launches), which saves the wavefront one of its two round trips to memory before its first load.
+// The group's entries are table[0 .. gridDim.y) themselves here too.
 template <bool F32>
-__global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const TensorDesc* table, const uint32_t* members) {
+__global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const TensorDesc* table) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
-  const TensorDesc d = table[members ? members[blockIdx.y] : blockIdx.y];
+  const TensorDesc d = table[blockIdx.y];
   const uint32_t piece = blockIdx.x * kWavesPerWg + wave;
   // all of the descriptor that a piece needs is asked for together with n_tiles: one round trip to memory ahead of the
   // first load of the codes, where a wait for n_tiles alone would make it two
