@@ -70,7 +70,7 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
 
     The number of outliers moves while a model trains (Section 3.4), so a method's `max_outliers` /
     `max_channels` can turn out too small.  The status words of every blob are copied to the host as
-    soon as the blob is written (asynchronously), and looked at before the blob is used:
+    soon as the blob is written (asynchronously), and looked at before anybody sees what was restored from it:
     on_overflow="raise" (the default) makes the backward pass raise `CompressedActivationLost`;
     on_overflow="retain" waits for the status right after compression and saves the tensor as it is when
     the blob can not hold it (one synchronisation per compressed tensor in the forward pass).
