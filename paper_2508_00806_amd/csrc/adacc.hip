@@ -644,6 +644,15 @@ static int launch_generic_compress(const adacc_method* method, const Plan& p, co
   return launch_check("place_generic_kernel");
 }
 
+// LDS that a tile kernel does not use but that bounds the workgroups of a CU to five, half of what its registers allow.
+// For asymmetric ABS over whole rows, a stream with few instructions, fewer wavefronts that read and write 1.5 bytes for
+// every 2 keep the memory's pages open longer: 2^29 softmax values, 541 us with eight, 535 / 533.5 / 531.6 with seven,
+// six and five, 543 with four.  The other encoders gain nothing from it (GELU, 2^28 values: the same) or lose (TOPK of
+// 2048, [32768, 2048]: 61.6 -> 65.6 us).
+static uint32_t residency_lds(const adacc_method* m, const Plan& p) {
+  return m->outlier_mode == ADACC_OUTLIER_ABS && m->asym && !p.rowwise && p.tile_elems == 2048 ? 32000u : 0u;
+}
+
 static int compress_one(const adacc_method* method, const void* src, uint64_t numel, void* blob, uint64_t blob_bytes,
                         adacc_workspace* ws, void* hip_stream) {
   if (!method) return ADACC_ENULL;
@@ -683,7 +692,7 @@ static int compress_one(const adacc_method* method, const void* src, uint64_t nu
     if (rc != ADACC_OK) return rc;
   }
   if (grid != 0) {
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, s, d, epoch);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), residency_lds(method, p), s, d, epoch);
     rc = launch_check("compress_kernel");
     if (rc != ADACC_OK) return rc;
   }

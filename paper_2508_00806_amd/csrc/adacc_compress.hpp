@@ -53,8 +53,8 @@ __device__ __forceinline__ float key_float(int32_t k) {
   return __uint_as_float((uint32_t)(k ^ ((k >> 31) & 0x7FFFFFFF)));
 }
 
-// value of the partner lane of one xor-butterfly step.  Steps 1..8 are DPP lane permutes
-// (they fuse into the arithmetic instruction); 16 and 32 go through the LDS crossbar.
+// value of the partner lane of one xor-butterfly step over 1, 2, 4 or 8 lanes: DPP lane permutes (they fuse into the
+// arithmetic instruction).
 // row_half_mirror / row_mirror stand in for xor 4 / xor 8: after the lower steps every
 // value is uniform within its 4 resp. 8 lanes, so reversing the order is the same exchange.
 template <int CTRL, class T>
@@ -62,9 +62,26 @@ __device__ __forceinline__ T dpp_move(T v) {
   const int i = __builtin_bit_cast(int, v);
   return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(i, i, CTRL, 0xF, 0xF, true));
 }
-template <class T>
-__device__ __forceinline__ T swap16(T v) {  // lane ^ 16
-  return __builtin_bit_cast(T, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));
+// The steps over 16 and 32 lanes: STEP lanes of `a` change places with STEP lanes of `b`, so that an operation on the two
+// then takes in every lane's partner: with a = b a step of the butterfly, with two different values a step of two
+// butterflies at once, whose results lie STEP lanes apart (a: the groups of STEP lanes with an even number, b: odd).
+// (gfx950 swaps lanes between registers; through the LDS crossbar each step was a round trip of some 60 clocks.)
+template <int STEP, class T>
+__device__ __forceinline__ void exchange(T& a, T& b) {
+  static_assert(STEP == 16 || STEP == 32, "lanes of one row or one half");
+  const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+  if constexpr (STEP == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    a = __builtin_bit_cast(T, (uint32_t)r[0]); b = __builtin_bit_cast(T, (uint32_t)r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    a = __builtin_bit_cast(T, (uint32_t)r[0]); b = __builtin_bit_cast(T, (uint32_t)r[1]);
+  }
+}
+template <int STEP, class T, class Op>
+__device__ __forceinline__ T meet(T a, T b, Op op) {
+  exchange<STEP>(a, b);
+  return op(a, b);
 }
 
 // all-reduce over LANES adjacent lanes (power of two) by xor butterfly, masks 1, 2, 4, ...
@@ -76,59 +93,36 @@ __device__ __forceinline__ T lanes_reduce(T v, Op op) {
   if constexpr (LANES > 2) v = op(v, dpp_move<0x4E>(v));   // quad_perm [2,3,0,1]
   if constexpr (LANES > 4) v = op(v, dpp_move<0x141>(v));  // row_half_mirror
   if constexpr (LANES > 8) v = op(v, dpp_move<0x140>(v));  // row_mirror
-  if constexpr (LANES > 16) v = op(v, swap16(v));
-  if constexpr (LANES > 32) v = op(v, __shfl_xor(v, 32));
+  if constexpr (LANES > 16) v = meet<16>(v, v, op);
+  if constexpr (LANES > 32) v = meet<32>(v, v, op);
   return v;
 }
 
-// s[j] for the first row of every group of R rows <- op over the group's rows (tree order)
-template <int E, int R, class T, class Op>
-__device__ __forceinline__ void rows_combine(T (&s)[E], Op op) {
-#pragma unroll
-  for (int r = 1; r < R; r <<= 1) {
-#pragma unroll
-    for (int j = 0; j < E; j += 2 * r) s[j] = op(s[j], s[j + r]);
-  }
-}
-// copy the group's value from its first row to its other rows
-template <int E, int R, class T>
-__device__ __forceinline__ void rows_broadcast(T (&s)[E]) {
-#pragma unroll
-  for (int r = R / 2; r >= 1; r >>= 1) {
-#pragma unroll
-    for (int j = 0; j < E; j += 2 * r) s[j + r] = s[j];
-  }
-}
-
+// Per-row, per-lane values -> those of groups of 2^lg elements, in every lane of the group.  lg <= 9: the group is
+// 2^(lg-3) adjacent lanes of one row; sums are formed in the order of the balanced tree over lanes.  lg > 9: the group is
+// 2^(lg-9) whole rows, combined in the lane first (for operations that any order suits).
+// The group size is a run-time value of the method; one switch selects straight-line code for it, so that the
+// butterflies themselves carry no branches.
 template <int E, int LANES, class T, class Op>
 __device__ __forceinline__ void each_row_reduce(T (&s)[E], Op op) {
 #pragma unroll
   for (int j = 0; j < E; ++j) s[j] = lanes_reduce<LANES>(s[j], op);
 }
-// ORDERED: reduce every row over all 64 lanes first, then combine rows pairwise (sums: the
-// canonical tree, 512-element blocks first, then blocks two by two).  Otherwise the rows are
-// combined in the lane first and only one butterfly per group is needed.
-template <int E, int R, bool ORDERED, class T, class Op>
+template <int E, int R, class T, class Op>
 __device__ __forceinline__ void row_groups_reduce(T (&s)[E], Op op) {
   if constexpr (R <= E) {
-    if constexpr (ORDERED) {
-      each_row_reduce<E, kWave>(s, op);
-      rows_combine<E, R>(s, op);
-    } else {
-      rows_combine<E, R>(s, op);
 #pragma unroll
-      for (int j = 0; j < E; j += R) s[j] = lanes_reduce<kWave>(s[j], op);
+    for (int j = 0; j < E; j += R) {
+#pragma unroll
+      for (int i = 1; i < R; ++i) s[j] = op(s[j], s[j + i]);
+      s[j] = lanes_reduce<kWave>(s[j], op);
+#pragma unroll
+      for (int i = 1; i < R; ++i) s[j + i] = s[j];
     }
-    rows_broadcast<E, R>(s);
   }
 }
-
-// Reduce per-row, per-lane partials over groups of 2^lg elements.  lg <= 9: the group is
-// 2^(lg-3) adjacent lanes of one row.  lg > 9: the group is 2^(lg-9) whole rows.  The group
-// size is a run-time value of the method; one switch selects straight-line code for it, so
-// that the butterflies themselves carry no branches.
-template <int E, bool ORDERED, class T, class Op>
-__device__ __forceinline__ void groups_reduce_impl(T (&s)[E], uint32_t lg, Op op) {
+template <int E, class T, class Op>
+__device__ __forceinline__ void groups_reduce(T (&s)[E], uint32_t lg, Op op) {
   switch (lg) {
     case 3: break;
     case 4: each_row_reduce<E, 2>(s, op); break;
@@ -137,18 +131,31 @@ __device__ __forceinline__ void groups_reduce_impl(T (&s)[E], uint32_t lg, Op op
     case 7: each_row_reduce<E, 16>(s, op); break;
     case 8: each_row_reduce<E, 32>(s, op); break;
     case 9: each_row_reduce<E, 64>(s, op); break;
-    case 10: row_groups_reduce<E, 2, ORDERED>(s, op); break;
-    case 11: row_groups_reduce<E, 4, ORDERED>(s, op); break;
-    default: row_groups_reduce<E, 8, ORDERED>(s, op); break;
+    case 10: row_groups_reduce<E, 2>(s, op); break;
+    default: row_groups_reduce<E, 4>(s, op); break;
   }
 }
-template <int E, class T, class Op>
-__device__ __forceinline__ void groups_reduce(T (&s)[E], uint32_t lg, Op op) {
-  groups_reduce_impl<E, true>(s, lg, op);
+// one value, groups inside a row: LANES = 2^lg adjacent lanes, lg a run-time (uniform) value
+template <class T, class Op>
+__device__ __forceinline__ T lanes_reduce_lg(T v, uint32_t lg, Op op) {
+  switch (lg) {
+    case 0: break;
+    case 1: v = lanes_reduce<2>(v, op); break;
+    case 2: v = lanes_reduce<4>(v, op); break;
+    case 3: v = lanes_reduce<8>(v, op); break;
+    case 4: v = lanes_reduce<16>(v, op); break;
+    case 5: v = lanes_reduce<32>(v, op); break;
+    default: v = lanes_reduce<64>(v, op); break;
+  }
+  return v;
 }
-template <int E, class T, class Op>
-__device__ __forceinline__ void groups_reduce_any_order(T (&s)[E], uint32_t lg, Op op) {
-  groups_reduce_impl<E, false>(s, lg, op);
+// The sums of four rows over all their lanes, row j's in the lanes 16 j .. 16 j + 15: the balanced tree over lane order, two
+// rows sharing a step over 16 lanes and all four the one over 32.
+template <class T, class Op>
+__device__ __forceinline__ T four_rows_reduce(T r0, T r1, T r2, T r3, Op op) {
+  const T r01 = meet<16>(lanes_reduce<16>(r0, op), lanes_reduce<16>(r1, op), op);
+  const T r23 = meet<16>(lanes_reduce<16>(r2, op), lanes_reduce<16>(r3, op), op);
+  return meet<32>(r01, r23, op);
 }
 
 // maximum over the whole wavefront, returned in a scalar register: four butterfly steps inside
@@ -248,7 +255,7 @@ struct TileGeo {
   uint64_t base;      // uniform: index of the tile's first element
   uint32_t rem;       // uniform: elements of the tensor from `base` on, at most E*512 (a multiple of 8, > 0)
   uint32_t lane_off;  // lane * 8
-  bool full;          // uniform: rem == E*512
+  bool full;          // known to the compiler: rem is E*512 (else it may be less)
   uint32_t stride;    // uniform, STRIP only: elements from one row to the next
   __device__ __forceinline__ uint32_t row_offset(int j) const {
     if constexpr (STRIP) return (uint32_t)j * stride;
@@ -269,7 +276,7 @@ __device__ __forceinline__ TileGeo<E> tile_geo(const TensorDesc& d, uint32_t til
   } else {
     const uint64_t left = d.numel - g.base;
     g.rem = left < (uint64_t)(E * kRow) ? (uint32_t)left : (uint32_t)(E * kRow);
-    g.full = g.rem == (uint32_t)(E * kRow);
+    g.full = false;  // (known here, so that the code for the last tile holds no copy of that for the others)
   }
   return g;
 }
@@ -359,17 +366,6 @@ __device__ __forceinline__ void store_row(const TensorDesc& d, const TileGeo<E, 
   }
 }
 
-// What a tile leaves behind for the outlier stream.
-template <int E>
-struct TileOutliers {
-  uint32_t mask[E];       // bit e of mask[j]: element e of this lane's octet in row j is an outlier
-  uint32_t lane_excl[E];  // outliers of row j in lower lanes
-  uint32_t row_off[E];    // outliers of the tile in rows before j (uniform)
-  uint32_t row_cnt[E];    // outliers of row j (uniform)
-  uint32_t total;         // outliers of the tile (uniform)
-  uint32_t sparse;        // bit j: no lane holds more than one outlier of row j (uniform)
-};
-
 // ------------------------------------------------------------------ per-row pieces shared by both tile encoders
 constexpr float kFltMax = 3.402823466e+38f;
 
@@ -449,12 +445,6 @@ __device__ __forceinline__ void group_scale(const TensorDesc& d, uint32_t r0, in
   }
 }
 
-template <int MODE>
-__device__ __forceinline__ bool outlier_test(float x, float param_or_limit) {
-  if constexpr (MODE == kModeNone) return !(fabsf(x) < __builtin_inff());  // Inf / NaN: zeroed, reported nowhere
-  else if constexpr (MODE == kModeAbs) return !(fabsf(x) <= param_or_limit);  // |x| > tau, and also Inf / NaN
-  else return x * x > param_or_limit;                                         // STD
-}
 __device__ __forceinline__ bool is_nonfinite(float x) { return (__float_as_uint(x) & 0x7FFFFFFFu) >= 0x7F800000u; }
 
 // ---- a4: where the outliers of a tile go.  Entry `pos` of the stream of the blob (two arrays) ...
@@ -505,19 +495,6 @@ __device__ __forceinline__ void emit_row(const uint32_t (&oct)[4], uint32_t mask
   }
 }
 
-// the outliers of a whole tile whose bookkeeping was kept (general encoder); only rows that have any are visited
-template <int E, class Sink>
-__device__ __forceinline__ void emit_outliers(const uint32_t (&raw)[E][4], const TileOutliers<E>& out, uint32_t tile,
-                                              const Sink& sink, uint32_t pos0, uint32_t limit) {
-  const uint32_t lane_first = tile * (uint32_t)(E * kRow) + (uint32_t)lane_id() * kOct;
-  static_for<E>([&](auto J) {
-    constexpr int j = decltype(J)::value;
-    if (out.row_cnt[j] != 0u)  // uniform
-      emit_row(raw[j], out.mask[j], out.lane_excl[j], ((out.sparse >> j) & 1u) != 0u, lane_first + (uint32_t)(j * kRow),
-               sink, pos0 + out.row_off[j], limit);
-  });
-}
-
 // ------------------------------------------------------------------ rows without outliers
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
@@ -541,6 +518,97 @@ __device__ __forceinline__ uint32_t octet_magnitude(const uint32_t (&oct)[4]) {
   const uint32_t m = pk_max_u16(pk_max_u16(oct[0] & kMag2, oct[1] & kMag2), pk_max_u16(oct[2] & kMag2, oct[3] & kMag2));
   const uint32_t hi = m >> 16, lo = m & 0xFFFFu;
   return hi > lo ? hi : lo;
+}
+
+// ------------------------------------------------------------------ outliers by a threshold on the magnitude
+// ABS and STD select what exceeds a limit that depends on the group alone, and both tests are monotonic in the magnitude:
+// the limit becomes a pattern once per group, the largest 15-bit magnitude that does not pass, and the tests are packed
+// 16-bit integer operations on the raw octets, two elements at a time.  Inf and NaN lie above every such pattern, so the
+// values that are always outliers need no test of their own.
+
+// m, m + 1 or m - 1: the largest magnitude t with f(t) <= limit, f monotonic, where m is that close
+template <class F>
+__device__ __forceinline__ uint32_t settle_magnitude(uint32_t m, float limit, F f) {
+  const float above = f(__uint_as_float(mag_bits32(m + 1u))), at = f(__uint_as_float(mag_bits32(m)));
+  return above <= limit ? m + 1u : (at <= limit ? m : m - 1u);
+}
+__device__ __forceinline__ uint32_t narrow_magnitude(float v) { return narrow_pair(v, 0.0f) & 0x7FFFu; }
+// ABS: the largest magnitude not above tau (>= 0, finite)
+__device__ __forceinline__ uint32_t magnitude_limit(float tau) {
+  const float t = fabsf(tau);  // (-0 is accepted for 0)
+  const uint32_t m = narrow_magnitude(t);  // rounds, perhaps to infinity; the largest finite one is above a tau beyond the format
+  const uint32_t least = m < kNonfiniteMag ? m : kNonfiniteMag - 1u;
+  return __uint_as_float(mag_bits32(least)) <= t ? least : least - 1u;
+}
+// STD: the largest magnitude whose square, in binary32, is not above `limit` (never negative); every finite one for a limit that is
+// infinite or NaN.  The hardware's square root is within a unit in the last place of binary32, its rounding to the format
+// within one of the format, so that three candidates decide; squares below 2^-100 may be subnormal or zero, where equal
+// squares belong to many magnitudes: there, bit by bit.
+__device__ __forceinline__ uint32_t magnitude_limit_squared(float limit) {
+  auto square = [](float v) { return v * v; };
+  uint32_t t = settle_magnitude(narrow_magnitude(__builtin_amdgcn_sqrtf(limit)), limit, square);
+  if constexpr (ADACC_F16 == 0) {  // (binary16 has no square below 2^-48)
+    if (__builtin_amdgcn_ballot_w64(limit < 0x1p-100f) != 0ull) {  // uniform, rare
+      uint32_t s = 0u;
+      for (int bit = 14; bit >= 0; --bit) {
+        const uint32_t c = s | (1u << bit);
+        s = square(__uint_as_float(mag_bits32(c))) <= limit ? c : s;
+      }
+      t = limit < 0x1p-100f ? s : t;
+    }
+  }
+  return limit < __builtin_inff() ? t : kNonfiniteMag - 1u;
+}
+__device__ __forceinline__ uint32_t both_halves(uint32_t m) { return m | m << 16; }
+
+// The elements of a row whose magnitude exceeds the threshold (t2: in both halves) are cleared; with a sink they go
+// there first, in index order, to positions pos, pos + 1, .. (entries at or past `limit` are dropped).  i0: index of the lane's first
+// element.  Returns their number (uniform).
+template <class Sink>
+__device__ __forceinline__ uint32_t take_above(uint32_t (&oct)[4], uint32_t t2, uint32_t i0, const Sink& sink, uint32_t pos, uint32_t limit) {
+  // All ones in the halves that exceed it: the sign of (threshold - magnitude).  (The threshold goes through an empty asm:
+  // where the compiler knows its range it makes compares and selects of this, half by half.)
+  asm("" : "+v"(t2));
+  uint32_t over[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const u16x2_t left = __builtin_bit_cast(u16x2_t, t2) - __builtin_bit_cast(u16x2_t, oct[k] & 0x7FFF7FFFu);
+    over[k] = __builtin_bit_cast(uint32_t, (i16x2_t)(__builtin_bit_cast(i16x2_t, left) >> 15));
+  }
+  uint32_t count = 0u;
+  if constexpr (!std::is_same_v<Sink, NullSink>) {
+    // bit e: element e (the low halves are the even elements)
+    const uint32_t two = (over[0] & 0x00020001u) | (over[1] & 0x00080004u) | (over[2] & 0x00200010u) | (over[3] & 0x00800040u);
+    uint32_t todo = (two | two >> 16) & 0xFFu;
+    uint64_t any = __builtin_amdgcn_ballot_w64(todo != 0u);
+    uint32_t at = pos;
+    if (__builtin_amdgcn_ballot_w64((todo & (todo - 1u)) != 0u) == 0ull) {  // uniform: no two in one octet
+      count = (uint32_t)__builtin_popcountll(any);
+      at += lanes_below(any);
+    } else {
+      const uint32_t n = (uint32_t)__builtin_popcount(todo);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {  // at most 8: the bits of the lanes' numbers
+        const uint64_t m = __builtin_amdgcn_ballot_w64((n >> b & 1u) != 0u);
+        count += (uint32_t)__builtin_popcountll(m) << b;
+        at += lanes_below(m) << b;
+      }
+    }
+    while (any != 0ull) {  // uniform: mostly once; an octet's first, then its second, ..
+      if (todo != 0u && at < limit) {
+        const uint32_t e = (uint32_t)__builtin_ctz(todo);
+        const uint32_t lo = (e & 4u) ? oct[2] : oct[0], hi = (e & 4u) ? oct[3] : oct[1];
+        const uint32_t word = (e & 2u) ? hi : lo;
+        sink(at, i0 + e, (e & 1u) ? word >> 16 : word & 0xFFFFu);
+      }
+      ++at;
+      todo &= todo - 1u;
+      any = __builtin_amdgcn_ballot_w64(todo != 0u);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) oct[k] &= ~over[k];
+  return count;
 }
 
 // a6, symmetric, for a row free of outliers and of values that are not finite: S and D / max from
@@ -639,11 +707,10 @@ __device__ __forceinline__ uint32_t encode_rows(const TensorDesc& d, const TileG
     // First a test per lane that is cheap and errs on the safe side: can this lane's octet hold an
     // outlier (or, without outliers, a value that is not finite)?  If no lane says yes - nearly
     // every row - the row is quantised as it is.  am_bits: the lane's largest |x| (symmetric).
-    float q[kOct];
     float limit_sq = 0.0f;
     uint32_t am_bits = 0u;
     bool suspect;
-    uint64_t b[kOct];
+    uint64_t b[kOct];  // TOPK
     if constexpr (MODE == kModeTopk) {
       suspect = true;  // every group has outliers: its k largest
       topk_row_ballots<LANES>(d, raw[j], b);
@@ -653,8 +720,9 @@ __device__ __forceinline__ uint32_t encode_rows(const TensorDesc& d, const TileG
         for (int e = 0; e < kOct; ++e) b[e] &= valid;
       }
     } else if constexpr (MODE == kModeStd) {
+      float q[kOct];
 #pragma unroll
-      for (int e = 0; e < kOct; ++e) q[e] = x[e] * x[e];  // exact: two 8-bit significands
+      for (int e = 0; e < kOct; ++e) q[e] = x[e] * x[e];  // exact: two significands of at most 11 bits
       float s1 = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
       float s2 = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
       s1 = lanes_reduce<LANES>(s1, OpAdd());
@@ -679,50 +747,24 @@ __device__ __forceinline__ uint32_t encode_rows(const TensorDesc& d, const TileG
         continue;
       }
     }
-    // the 8 outlier tests of the row as wavefront ballots (scalar registers)
+    uint32_t oct[4] = {raw[j][0], raw[j][1], raw[j][2], raw[j][3]};
+    const uint32_t i0 = lane_first + (uint32_t)(j * kRow);
     if constexpr (MODE == kModeTopk) {
-      // formed above
-    } else if constexpr (MODE == kModeStd) {
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) b[e] = __builtin_amdgcn_ballot_w64(q[e] > limit_sq);
-      if (__builtin_amdgcn_ballot_w64(limit_sq != limit_sq) != 0ull) {  // then every element is tested for Inf / NaN
-#pragma unroll
-        for (int e = 0; e < kOct; ++e) b[e] |= __builtin_amdgcn_ballot_w64(is_nonfinite(x[e]));
+      uint32_t mask, lane_excl, row_cnt;
+      bool any, sparse;
+      row_bookkeeping(b, mask, lane_excl, row_cnt, any, sparse);
+      if (any) {  // uniform: the row's outliers leave at once, nothing about them is kept
+        emit_row(oct, mask, lane_excl, sparse, i0, sink, pos0 + total, limit);
+        total += row_cnt;
+        clear_elements(oct, mask);
       }
     } else {
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) b[e] = __builtin_amdgcn_ballot_w64(outlier_test<MODE>(x[e], d.param));
+      uint32_t most = kNonfiniteMag - 1u;  // NONE: what is not finite is zeroed, and reported nowhere
+      if constexpr (MODE == kModeStd) most = magnitude_limit_squared(limit_sq);
+      if constexpr (MODE == kModeAbs) most = magnitude_limit(d.param);
+      total += take_above(oct, both_halves(most), i0, sink, pos0 + total, limit);
     }
-    uint32_t mask, lane_excl, row_cnt;
-    bool any, sparse;
-    row_bookkeeping(b, mask, lane_excl, row_cnt, any, sparse);
-    if constexpr (STORE) {
-      float y[kOct];
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) y[e] = __builtin_amdgcn_inverse_ballot_w64(b[e]) ? 0.0f : x[e];
-      float ext0, ext1;
-      row_extremes<ASYM>(y, ext0, ext1);
-      float scl, inv, off;
-      if constexpr (!ASYM) {
-        const uint32_t r0 = lanes_reduce<LANES>(__float_as_uint(ext0), OpUMax());
-        group_scale<false>(d, r0, 0, 0, scl, inv, off);
-      } else {
-        const int32_t k0 = lanes_reduce<LANES>(float_key(ext0), OpIMax());
-        const int32_t k1 = lanes_reduce<LANES>(float_key(ext1), OpIMin());
-        group_scale<true>(d, 0u, k0, k1, scl, inv, off);
-      }
-      if constexpr (ASYM) {
-#pragma unroll
-        for (int e = 0; e < kOct; ++e) y[e] = y[e] - off;
-      }
-      store_row<BITS, ASYM, E>(d, g, j, y, scl, inv, off);
-    }
-    if constexpr (MODE != kModeNone) {
-      if (any) {  // uniform: the row's outliers leave at once, nothing about them is kept
-        emit_row(raw[j], mask, lane_excl, sparse, lane_first + (uint32_t)(j * kRow), sink, pos0 + total, limit);
-        total += row_cnt;
-      }
-    }
+    if constexpr (STORE) encode_clean_row<BITS, ASYM, E, LANES>(d, g, j, oct, mag_bits32(octet_magnitude(oct)));
   }
   return total;
 }
@@ -743,33 +785,9 @@ __device__ __forceinline__ uint32_t encode_tile_rowwise(const TensorDesc& d, con
 }
 
 // ------------------------------------------------------------------ TOPK selection
-// Magnitudes are the 15 low bits of the patterns.  Two ways to find a group's k largest:
-//
-// By lane maxima (groups of whole rows, small k): every lane takes the largest magnitude among
-// its own elements of the group, and the k-th largest of these lane maxima, w, is found by k
-// max-reductions over the lanes.  At least k elements are >= w.  If exactly k are, they are the
-// k largest of the group whatever their order, and the selection is the plain test |x| >= w.
-// Otherwise (two of the largest in one lane, or a tie at the boundary) the caller falls back to
-// the rounds below.
-//
-// By rounds (any group, any k): k max-reductions over keys (magnitude above, inverted position
-// below, so ties go to the lower index), each restricted to the keys below the previous winner.
-// largest magnitude (15 low bits of the patterns) among the lane's 8 elements of every row:
-// two 16-bit lanes at a time.  An Inf or NaN shows as a value >= kNonfiniteMag.
-template <int E>
-__device__ __forceinline__ void row_magnitudes(const uint32_t (&raw)[E][4], uint32_t (&rowmag)[E]) {
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    constexpr uint32_t kMag2 = 0x7FFF7FFFu;
-    const uint32_t m =
-        pk_max_u16(pk_max_u16(raw[j][0] & kMag2, raw[j][1] & kMag2), pk_max_u16(raw[j][2] & kMag2, raw[j][3] & kMag2));
-    const uint32_t hi = m >> 16, lo = m & 0xFFFFu;
-    rowmag[j] = hi > lo ? hi : lo;
-  }
-}
-
-// The same two rows to a word (row 2i in the low half of pm[i], row 2i + 1 in the high half): half the registers, and
-// the maxima of a lane's rows come two at a time.
+// Magnitudes are the 15 low bits of the patterns.  The largest magnitude of a lane's 8 elements in every row, two
+// rows to a word (row 2i in the low half of pm[i], row 2i + 1 in the high half): half the registers, and
+// the maxima of a lane's rows come two at a time.  An Inf or NaN shows as a value >= kNonfiniteMag.
 __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t,
                             __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
@@ -831,329 +849,6 @@ __device__ __forceinline__ bool topk_whole_threshold(const TensorDesc& d, const 
   return finite;
 }
 
-// thr[j] <- the k-th largest lane maximum of row j's group, as the bits of a binary32 value.
-// Returns (uniform) false when the tile holds an Inf or NaN.
-template <int E>
-__device__ __forceinline__ bool topk_lane_maxima(const TensorDesc& d, const uint32_t (&rowmag)[E], uint32_t (&thr)[E]) {
-  const uint32_t lane = (uint32_t)lane_id();
-  const int R = 1 << (d.lgs - 9);  // rows per group (the caller guarantees lgs >= 9)
-  uint32_t m[E];
-#pragma unroll
-  for (int j = 0; j < E; ++j) m[j] = rowmag[j];
-  // rows of a group -> its first row
-#pragma unroll
-  for (int r = 1; r < E; r <<= 1) {
-    if (r < R) {
-#pragma unroll
-      for (int j = 0; j < E; j += 2 * r) m[j] = m[j] > m[j + r] ? m[j] : m[j + r];
-    }
-  }
-  uint32_t cur[E], win[E];  // win[] is uniform
-  bool nonfinite = false;
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    if ((j & (R - 1)) == 0) nonfinite |= m[j] >= kNonfiniteMag;
-    cur[j] = (m[j] << 6) | lane;
-    win[j] = 0u;
-  }
-  for (uint32_t r = 0; r < d.topk; ++r) {
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      if ((j & (R - 1)) != 0) continue;  // uniform: a group's state lives in its first row
-      win[j] = wave_max_u32_scalar(cur[j]);
-      cur[j] = (cur[j] == win[j]) ? 0u : cur[j];
-    }
-  }
-#pragma unroll
-  for (int r = E / 2; r >= 1; r >>= 1) {
-    if (r < R) {
-#pragma unroll
-      for (int j = 0; j < E; j += 2 * r) win[j + r] = win[j];
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < E; ++j) thr[j] = mag_bits32(win[j] >> 6);
-  return __builtin_amdgcn_ballot_w64(nonfinite) == 0ull;
-}
-
-// Rounds: thr[j] <- the k-th largest key of row j's group.  Returns (uniform) whether some group's
-// k-th largest is Inf / NaN: then there may be more than k outliers.
-template <int E>
-__device__ __forceinline__ bool topk_select_rounds(const TensorDesc& d, const uint32_t (&raw)[E][4], uint32_t (&kth)[E],
-                                                   uint32_t lane_pos, int R) {
-#pragma unroll
-  for (int j = 0; j < E; ++j) kth[j] = 0xFFFFFFFFu;
-  for (uint32_t r = 0; r < d.topk; ++r) {
-    forget_derived<E>(raw);  // the keys are formed again in every round: holding them would cost 8 registers per row
-    asm volatile("" : "+v"(lane_pos));  // and so are the position codes
-    uint32_t best[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      const uint32_t row_pos = ((uint32_t)(j & (R - 1)) << 9) | lane_pos;
-      uint32_t m = 0u;
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) {
-        const uint32_t key = (ADACC_ELEM_MAG(raw[j], e) << 16) | (0xFFFFu - (row_pos | (uint32_t)e));
-        const uint32_t cand = (key < kth[j]) ? key : 0u;
-        m = (cand > m) ? cand : m;
-      }
-      best[j] = m;
-    }
-    groups_reduce_any_order<E>(best, d.lgs, OpUMax());
-#pragma unroll
-    for (int j = 0; j < E; ++j) kth[j] = best[j];
-  }
-  bool many = false;
-#pragma unroll
-  for (int j = 0; j < E; ++j) many |= (kth[j] >> 16) >= kNonfiniteMag;
-  return __builtin_amdgcn_ballot_w64(many) != 0ull;
-}
-
-// ------------------------------------------------------------------ general tile encoder
-// Groups of any supported size (up to the whole tile).  Works in phases over all rows; between
-// the phases only the raw octets and a few values per row stay in registers, the widened
-// values are formed again where needed (one instruction each).
-// a3 + a5 for all rows of a tile: the outlier tests (as wavefront ballots, which live in scalar
-// registers, so the run-time choices between tests are uniform branches that cost no vector
-// registers), the bookkeeping of the rows that have outliers, and the per-lane extremes of the
-// inlier view.  `by_magnitude` (TOPK): thr[j] holds the bits of a binary32 magnitude threshold,
-// else the smallest selected key.  `poisoned`: every element is also tested for Inf / NaN.
-template <int MODE, bool ASYM, int E>
-__device__ __forceinline__ void outlier_phase(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4],
-                                              const float (&limit)[E], const uint32_t (&thr)[E], bool by_magnitude,
-                                              bool poisoned, uint32_t lane_pos, int R,
-                                              const uint32_t (&rowmag)[E], float (&ext0)[E], float (&ext1)[E],
-                                              TileOutliers<E>& out, int row0 = 0) {
-  out.sparse = 0u;
-  forget_derived<E>(raw);  // nothing formed from the octets so far is worth its registers
-  // uniform, as an integer so that it stays in a scalar register: rows may be skipped on the strength
-  // of their largest magnitude (not when keys decide, nor when Inf / NaN are about)
-  const uint32_t can_skip = ((MODE != kModeTopk || by_magnitude) && !poisoned) ? 1u : 0u;
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    if constexpr (!ASYM) {
-      // Symmetric: one test of the lane's largest magnitude of the row tells whether the row can
-      // hold an outlier at all; if not, that magnitude is also the lane's share of max |y|, and
-      // neither the widened values nor the 8 tests are needed.
-      const uint32_t top = mag_bits32(rowmag[j]);  // bits of the largest |x|
-      bool maybe;
-      if constexpr (MODE == kModeTopk) maybe = top >= thr[j];
-      else if constexpr (MODE == kModeAbs) maybe = top > __float_as_uint(d.param);  // tau >= 0; Inf / NaN are above every tau
-      else if constexpr (MODE == kModeStd) maybe = __uint_as_float(top) * __uint_as_float(top) > limit[j];
-      else maybe = top >= 0x7F800000u;
-      if ((__builtin_amdgcn_ballot_w64(maybe) == 0ull) & (can_skip != 0u)) {
-        out.mask[j] = 0u; out.lane_excl[j] = 0u; out.row_cnt[j] = 0u;
-        out.sparse |= 1u << j;
-        ext0[j] = __uint_as_float(top);
-        ext1[j] = 0.0f;
-        continue;
-      }
-    }
-    float x[kOct];
-    widen_row(raw[j], x);
-    uint64_t b[kOct];
-    if constexpr (MODE == kModeTopk) {
-      if (__builtin_expect(by_magnitude, 1)) {
-        // rows past the end of the tensor are all selected here, which the caller's count check rejects
-        const float t = __uint_as_float(thr[j]);
-#pragma unroll
-        for (int e = 0; e < kOct; ++e) b[e] = __builtin_amdgcn_ballot_w64(fabsf(x[e]) >= t);
-      } else {
-        const bool valid = g.lane_off + (uint32_t)(j * kRow) < g.rem;  // blanked octets would be ranked too
-        const uint32_t row_pos = ((uint32_t)((row0 + j) & (R - 1)) << 9) | lane_pos;
-#pragma unroll
-        for (int e = 0; e < kOct; ++e) {
-          const uint32_t key = (ADACC_ELEM_MAG(raw[j], e) << 16) | (0xFFFFu - (row_pos | (uint32_t)e));
-          b[e] = __builtin_amdgcn_ballot_w64((key >= thr[j]) && valid);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < kOct; ++e)
-        b[e] = __builtin_amdgcn_ballot_w64(outlier_test<MODE>(x[e], MODE == kModeStd ? limit[j] : d.param));
-    }
-    if (poisoned) {
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) b[e] |= __builtin_amdgcn_ballot_w64(is_nonfinite(x[e]));
-    }
-    bool any, sparse;
-    row_bookkeeping(b, out.mask[j], out.lane_excl[j], out.row_cnt[j], any, sparse);
-    out.sparse |= sparse ? (1u << j) : 0u;
-    if (any) {
-      float y[kOct];
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) y[e] = __builtin_amdgcn_inverse_ballot_w64(b[e]) ? 0.0f : x[e];
-      row_extremes<ASYM>(y, ext0[j], ext1[j]);
-    } else {
-      row_extremes<ASYM>(x, ext0[j], ext1[j]);
-    }
-  }
-}
-
-// ---- a6 .. a8 for a tile (or a piece of one) whose outliers are known: scales from the per-lane
-// extremes of the inlier view, then quantise, pack, store.
-template <int BITS, bool ASYM, int E>
-__device__ __forceinline__ void finish_tile(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4],
-                                            const float (&ext0)[E], const float (&ext1)[E],
-                                            const TileOutliers<E>& out) {
-  // ---- a6: per-group scale (and offset).  Cross-lane max / min run on integer images of the floats.
-  // Every lane of a group would compute the same scale; with at least 4 lanes per group and 4 rows,
-  // lane l of every quad takes row l instead, so that one division serves the whole tile, and the
-  // results go back to the rows by a broadcast inside the quad.
-  float inv[E], off[E], scl[E];
-  const bool transposed = (E == 4) && d.lgq >= 5u;
-  const bool row1 = __builtin_amdgcn_inverse_ballot_w64(0x2222222222222222ull);
-  const bool row2 = __builtin_amdgcn_inverse_ballot_w64(0x4444444444444444ull);
-  const bool row3 = __builtin_amdgcn_inverse_ballot_w64(0x8888888888888888ull);
-  if constexpr (!ASYM) {
-    uint32_t a[E];  // max |y| as bit patterns: for non-negative floats the integer order is the float order
-#pragma unroll
-    for (int j = 0; j < E; ++j) a[j] = __float_as_uint(ext0[j]);
-    groups_reduce_any_order<E>(a, d.lgq, OpUMax());
-    if (transposed) {
-      uint32_t am = row1 ? a[1 % E] : a[0];
-      am = row2 ? a[2 % E] : am;
-      am = row3 ? a[3 % E] : am;
-      float s, i, o;
-      group_scale<false>(d, am, 0, 0, s, i, o);
-      scl[0] = dpp_move<0x00>(s); scl[1 % E] = dpp_move<0x55>(s); scl[2 % E] = dpp_move<0xAA>(s); scl[3 % E] = dpp_move<0xFF>(s);
-      inv[0] = dpp_move<0x00>(i); inv[1 % E] = dpp_move<0x55>(i); inv[2 % E] = dpp_move<0xAA>(i); inv[3 % E] = dpp_move<0xFF>(i);
-#pragma unroll
-      for (int j = 0; j < E; ++j) off[j] = 0.0f;
-    } else {
-#pragma unroll
-      for (int j = 0; j < E; ++j) group_scale<false>(d, a[j], 0, 0, scl[j], inv[j], off[j]);
-    }
-  } else {
-    int32_t hi[E], lo[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) { hi[j] = float_key(ext0[j]); lo[j] = float_key(ext1[j]); }
-    groups_reduce_any_order<E>(hi, d.lgq, OpIMax());
-    groups_reduce_any_order<E>(lo, d.lgq, OpIMin());
-    if (transposed) {
-      int32_t h = row1 ? hi[1 % E] : hi[0], l = row1 ? lo[1 % E] : lo[0];
-      h = row2 ? hi[2 % E] : h; l = row2 ? lo[2 % E] : l;
-      h = row3 ? hi[3 % E] : h; l = row3 ? lo[3 % E] : l;
-      float s, i, o;
-      group_scale<true>(d, 0u, h, l, s, i, o);
-      scl[0] = dpp_move<0x00>(s); scl[1 % E] = dpp_move<0x55>(s); scl[2 % E] = dpp_move<0xAA>(s); scl[3 % E] = dpp_move<0xFF>(s);
-      inv[0] = dpp_move<0x00>(i); inv[1 % E] = dpp_move<0x55>(i); inv[2 % E] = dpp_move<0xAA>(i); inv[3 % E] = dpp_move<0xFF>(i);
-      off[0] = dpp_move<0x00>(o); off[1 % E] = dpp_move<0x55>(o); off[2 % E] = dpp_move<0xAA>(o); off[3 % E] = dpp_move<0xFF>(o);
-    } else {
-#pragma unroll
-      for (int j = 0; j < E; ++j) group_scale<true>(d, 0u, hi[j], lo[j], scl[j], inv[j], off[j]);
-    }
-  }
-
-  // ---- a7 + a8: quantise, pack, store codes and scales
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    float y[kOct];
-    widen_row(raw[j], y);
-    if (out.row_cnt[j] != 0u) {  // uniform: the inlier view is zero where the mask says so
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) {
-        const uint32_t keep = (uint32_t)(((int32_t)(~out.mask[j] << (31 - e))) >> 31);  // all ones unless bit e is set
-        y[e] = __uint_as_float(__float_as_uint(y[e]) & keep);
-      }
-    }
-    if constexpr (ASYM) {
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) y[e] = y[e] - off[j];
-    }
-    store_row<BITS, ASYM, E>(d, g, j, y, scl[j], inv[j], off[j]);
-  }
-}
-
-template <int MODE, int BITS, bool ASYM, int E, bool STORE>
-__device__ __forceinline__ void encode_tile_general(const TensorDesc& d, const TileGeo<E>& g,
-                                                    const uint32_t (&raw)[E][4], TileOutliers<E>& out) {
-  // ---- a2: statistics of the statistics groups
-  float limit[E];   // STD: k^2 * var of the row's group
-  uint32_t thr[E];  // TOPK: selection threshold of the row's group
-  bool poisoned = false;  // uniform: Inf / NaN met in some group's statistics
-  uint32_t lane_pos = 0u;
-  int R = 1;
-  uint32_t rowmag[E];  // symmetric only: the lane's largest magnitude of every row
-  if constexpr (!ASYM) {
-    row_magnitudes<E>(raw, rowmag);
-  } else {
-#pragma unroll
-    for (int j = 0; j < E; ++j) rowmag[j] = 0u;
-  }
-  if constexpr (MODE == kModeStd) {
-    float s1[E], s2[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      float x[kOct];
-      widen_row(raw[j], x);
-      s1[j] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
-      // squares of 16-bit values (at most 11 significant bits) are exact in binary32
-      s2[j] = ((x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3])) +
-              ((x[4] * x[4] + x[5] * x[5]) + (x[6] * x[6] + x[7] * x[7]));
-    }
-    groups_reduce<E>(s1, d.lgs, OpAdd());
-    groups_reduce<E>(s2, d.lgs, OpAdd());
-    const float inv_gs = __uint_as_float((127u - d.lgs) << 23);  // 2^-lgs, exact
-    bool nan_seen = false;
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      limit[j] = std_limit(s1[j], s2[j], inv_gs, d.param);
-      nan_seen |= (limit[j] != limit[j]);
-    }
-    poisoned = __builtin_amdgcn_ballot_w64(nan_seen) != 0ull;
-  } else if constexpr (MODE == kModeTopk) {
-    const uint32_t lane = (uint32_t)lane_id();
-    R = (d.lgs > 9) ? (1 << (d.lgs - 9)) : 1;
-    lane_pos = (d.lgs > 9) ? (lane << 3) : ((lane & ((1u << (d.lgs - 3)) - 1u)) << 3);
-  }
-
-  // ---- a3 + a5: outlier test row by row; extremes of the inlier view per lane
-  float ext0[E], ext1[E];
-  if constexpr (MODE == kModeTopk) {
-    // First the selection by lane maxima where it applies; if it does not stand, once more by rounds.
-    // One copy of the code in a loop (rather than two in a row) keeps the registers of the rare second
-    // pass from adding to those of the first.
-    bool try_maxima = d.lgs >= 9u && d.topk <= 8u;
-#pragma nounroll
-    while (true) {
-      bool by_magnitude = false;
-      if (try_maxima) {
-        if constexpr (ASYM) row_magnitudes<E>(raw, rowmag);
-        by_magnitude = topk_lane_maxima<E>(d, rowmag, thr);
-      }
-      if (!by_magnitude) {
-        // nothing on this rare path may be prepared outside the loop over tiles (32 position codes
-        // would otherwise sit in registers for the whole run)
-        asm volatile("" : "+v"(lane_pos));
-        poisoned = topk_select_rounds<E>(d, raw, thr, lane_pos, R);
-      }
-      outlier_phase<MODE, ASYM, E>(d, g, raw, limit, thr, by_magnitude, poisoned, lane_pos, R, rowmag, ext0, ext1, out);
-      if (!by_magnitude) break;
-      // the selection stands if every group has exactly k elements at or above its threshold
-      bool exact = true;
-      uint32_t in_group = 0u;
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        in_group += out.row_cnt[j];
-        if ((j & (R - 1)) == R - 1) { exact = exact && (in_group == d.topk); in_group = 0u; }
-      }
-      if (exact) break;
-      try_maxima = false;
-    }
-  } else {
-    outlier_phase<MODE, ASYM, E>(d, g, raw, limit, thr, false, poisoned, lane_pos, R, rowmag, ext0, ext1, out);
-  }
-  out.total = 0u;
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    out.row_off[j] = out.total;
-    if constexpr (MODE != kModeNone) out.total += out.row_cnt[j];
-  }
-
-  if constexpr (STORE) finish_tile<BITS, ASYM, E>(d, g, raw, ext0, ext1, out);
-}
-
 // Rounds over a tile that is one statistics group: the k-th largest key, uniform.  Returns whether
 // it belongs to an Inf / NaN (then there may be more than k outliers).
 template <int E>
@@ -1180,22 +875,20 @@ __device__ __forceinline__ bool topk_select_rounds_whole(const TensorDesc& d, co
   return (kth >> 16) >= kNonfiniteMag;
 }
 
-// ------------------------------------------------------------------ TOPK over a whole tile, quantisation groups inside a row
-// The tile is one statistics group (so it is complete: group sizes divide the tensor) and every
-// quantisation group lies inside a 512-element row.  The paper's order, literally: the outliers
-// are found, handed to the sink, and set to zero in the registers that hold the tile; what is left
-// is quantised row by row with no thought of outliers.  Nothing but the raw octets and the lane's
-// largest magnitude per row lives across rows.  LANES = lanes per quantisation group.
+// ------------------------------------------------------------------ TOPK over a tile, or over a part of one of whole rows
+// The E rows are one statistics group (so they are complete: group sizes divide what the tile kernels take).  The paper's
+// order, literally: the outliers are found, handed to the sink, and set to zero in the registers that hold the rows; what is left
+// is quantised row by row with no thought of outliers.  first: the index of the group's first element.
 
 // Extraction by keys (any tile): the k largest keys (magnitude above, inverted position below), and
 // every value that is not finite when those are more than k.  Returns the number of outliers.
 template <int E, class Sink>
-__device__ __forceinline__ uint32_t topk_extract_by_keys(const TensorDesc& d, uint32_t (&raw)[E][4], uint32_t tile,
+__device__ __forceinline__ uint32_t topk_extract_by_keys(const TensorDesc& d, uint32_t (&raw)[E][4], uint32_t first,
                                                         const Sink& sink, uint32_t pos0, uint32_t limit) {
   uint32_t lane_pos = (uint32_t)lane_id() << 3;
   uint32_t kth;
   const bool poisoned = topk_select_rounds_whole<E>(d, raw, kth, lane_pos);
-  const uint32_t lane_first = tile * (uint32_t)(E * kRow) + (uint32_t)lane_id() * kOct;
+  const uint32_t lane_first = first + (uint32_t)lane_id() * kOct;
   uint32_t total = 0u;
 #pragma unroll
   for (int j = 0; j < E; ++j) {
@@ -1238,7 +931,7 @@ struct TopkList {
 };
 template <int E, bool STORE, class Sink>
 __device__ __forceinline__ uint32_t topk_extract(const TensorDesc& d, uint32_t (&raw)[E][4], RowMags<E>& rowmag,
-                                                 uint32_t tile, const Sink& sink, uint32_t pos0, uint32_t limit) {
+                                                 uint32_t first, const Sink& sink, uint32_t pos0, uint32_t limit) {
   __shared__ TopkList lists[kWavesPerWg];
   rowmag.of(raw);
   const uint32_t lane = (uint32_t)lane_id();
@@ -1282,16 +975,15 @@ __device__ __forceinline__ uint32_t topk_extract(const TensorDesc& d, uint32_t (
           else { hit_b |= eq_b & (0ull - eq_b); eq_b &= eq_b - 1ull; }
         }
       }
-      const uint32_t tile_first = tile * (uint32_t)(E * kRow);
       if (__builtin_amdgcn_inverse_ballot_w64(hit_a)) {
         const uint32_t pos = pos0 + lanes_below(hit_a);
-        if (pos < limit) sink(pos, tile_first + list.where[lane >> 3] + (lane & 7u), pa);
+        if (pos < limit) sink(pos, first + list.where[lane >> 3] + (lane & 7u), pa);
         if constexpr (STORE) elem[lane] = 0;
       }
       if (hit_b != 0ull) {  // uniform
         if (__builtin_amdgcn_inverse_ballot_w64(hit_b)) {
           const uint32_t pos = pos0 + (uint32_t)__builtin_popcountll(hit_a) + lanes_below(hit_b);
-          if (pos < limit) sink(pos, tile_first + list.where[8u + (lane >> 3)] + (lane & 7u), pb);
+          if (pos < limit) sink(pos, first + list.where[8u + (lane >> 3)] + (lane & 7u), pb);
           if constexpr (STORE) elem[kWave + lane] = 0;
         }
       }
@@ -1312,20 +1004,127 @@ __device__ __forceinline__ uint32_t topk_extract(const TensorDesc& d, uint32_t (
       return k;
     }
   }
-  const uint32_t total = topk_extract_by_keys<E>(d, raw, tile, sink, pos0, limit);
+  const uint32_t total = topk_extract_by_keys<E>(d, raw, first, sink, pos0, limit);
   if constexpr (STORE) rowmag.of(raw);
   return total;
 }
 
-template <int BITS, bool ASYM, int E, int LANES>
-__device__ __forceinline__ void encode_clean_rows(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4],
-                                                  const RowMags<E>& rowmag) {
+// ------------------------------------------------------------------ a6 .. a8 for a tile without outliers
+// (none left, and nothing that is not finite), quantisation groups of any size.  top: symmetric, the lane's largest magnitude
+// of every row.  Four rows at a time: their extremes meet group by group, the one step that depends on the size of the groups; lane
+// l of every quad forms the scale of row l (every lane of a group would form the same one), and the quad's lanes pass
+// them around; then the codes.
+template <int BITS, bool ASYM, int E>
+__device__ __forceinline__ void quantise_tile(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4], const uint32_t (&top)[E]) {
+  constexpr int B = E < 4 ? E : 4;
+  static_assert(E % B == 0 && (B == 4 || B == 1), "rows in fours");
+  // a group of 4096 takes both fours: its extremes in the lane first
+  const bool all = E == 8 && d.lgq == 12u;  // uniform
+  const uint32_t lg = all ? 11u : d.lgq;
+  uint32_t top_all = 0u;
+  int32_t hi_all = 0, lo_all = 0;
+  if (all) {
+    float hi = 0.0f, lo = 0.0f;
 #pragma unroll
-  for (int j = 0; j < E; ++j) {
-    // one row after the other: the compiler shall not start on the next rows to hide this row's
-    // latencies (other wavefronts do that), it would pay for it with the registers of a wavefront
-    __builtin_amdgcn_sched_barrier(0);
-    encode_clean_row<BITS, ASYM, E, LANES>(d, g, j, raw[j], mag_bits32(rowmag.at(j)));
+    for (int j = 0; j < E; ++j) {
+      if constexpr (!ASYM) {
+        top_all = OpUMax()(top_all, top[j]);
+      } else {
+        __builtin_amdgcn_sched_barrier(0);
+        float x[kOct], h, l;
+        widen_row(raw[j], x);
+        row_extremes<true>(x, h, l);
+        hi = j == 0 ? h : fmaxf(hi, h);
+        lo = j == 0 ? l : fminf(lo, l);
+      }
+    }
+    hi_all = float_key(hi);
+    lo_all = float_key(lo);
+  }
+  static_for<E / B>([&](auto Fc) {
+    constexpr int first = decltype(Fc)::value * B;
+    uint32_t t[B];
+    int32_t hi[B], lo[B];
+    if constexpr (!ASYM) {
+#pragma unroll
+      for (int i = 0; i < B; ++i) t[i] = all ? top_all : top[first + i];
+      groups_reduce<B>(t, lg, OpUMax());
+    } else {
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (all) {
+          hi[i] = hi_all;
+          lo[i] = lo_all;
+        } else {
+          float x[kOct], h, l;
+          widen_row(raw[first + i], x);
+          row_extremes<true>(x, h, l);
+          hi[i] = float_key(h);
+          lo[i] = float_key(l);
+        }
+      }
+      groups_reduce<B>(hi, lg, OpIMax());
+      groups_reduce<B>(lo, lg, OpIMin());
+      forget_derived<E>(raw);  // nothing widened for the extremes is kept for the codes
+    }
+    float scl[B], inv[B], off[B];
+    auto scale_of = [&](uint32_t tt, int32_t h, int32_t l, float& s, float& v, float& o) {
+      o = 0.0f;
+      if constexpr (!ASYM) scale_sym_clean(d, mag_bits32(tt), s, v);
+      else group_scale<true>(d, 0u, h, l, s, v, o);
+    };
+    auto pick = [&](auto a, auto b, auto c, auto e) {  // lane l of a quad: argument l
+      const bool second = __builtin_amdgcn_inverse_ballot_w64(0x2222222222222222ull);
+      const bool third = __builtin_amdgcn_inverse_ballot_w64(0x4444444444444444ull);
+      const bool fourth = __builtin_amdgcn_inverse_ballot_w64(0x8888888888888888ull);
+      auto v = second ? b : a;
+      v = third ? c : v;
+      return fourth ? e : v;
+    };
+    if (B == 4 && d.lgq >= 5u) {  // uniform: a group has four lanes at least
+      float s, v, o;
+      if constexpr (!ASYM) scale_of(pick(t[0], t[1 % B], t[2 % B], t[3 % B]), 0, 0, s, v, o);
+      else scale_of(0u, pick(hi[0], hi[1 % B], hi[2 % B], hi[3 % B]), pick(lo[0], lo[1 % B], lo[2 % B], lo[3 % B]), s, v, o);
+      scl[0] = dpp_move<0x00>(s); scl[1 % B] = dpp_move<0x55>(s); scl[2 % B] = dpp_move<0xAA>(s); scl[3 % B] = dpp_move<0xFF>(s);
+      inv[0] = dpp_move<0x00>(v); inv[1 % B] = dpp_move<0x55>(v); inv[2 % B] = dpp_move<0xAA>(v); inv[3 % B] = dpp_move<0xFF>(v);
+      off[0] = dpp_move<0x00>(o); off[1 % B] = dpp_move<0x55>(o); off[2 % B] = dpp_move<0xAA>(o); off[3 % B] = dpp_move<0xFF>(o);
+    } else {
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        if constexpr (!ASYM) scale_of(t[i], 0, 0, scl[i], inv[i], off[i]);
+        else scale_of(0u, hi[i], lo[i], scl[i], inv[i], off[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      // one row after the other: the compiler shall not start on the next rows to hide this row's
+      // latencies (other wavefronts do that), it would pay for it with the registers of a wavefront
+      __builtin_amdgcn_sched_barrier(0);
+      float x[kOct];
+      widen_row(raw[first + i], x);
+      if constexpr (ASYM) {
+#pragma unroll
+        for (int e = 0; e < kOct; ++e) x[e] = x[e] - off[i];
+      }
+      store_row<BITS, ASYM, E>(d, g, first + i, x, scl[i], inv[i], off[i]);
+    }
+  });
+}
+
+// BITS = kBitsAny: as the descriptor says (the batch kernels: the selection before it is the same code for all)
+constexpr int kBitsAny = 0;
+template <int BITS, bool ASYM, int E>
+__device__ __forceinline__ void quantise_tile_as(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4], uint32_t (&top)[E]) {
+  if constexpr (BITS != kBitsAny) {
+    quantise_tile<BITS, ASYM, E>(d, g, raw, top);
+  } else {
+    switch (d.variant & 6u) {
+      case 0: quantise_tile<4, false, E>(d, g, raw, top); break;
+      case 2: quantise_tile<4, true, E>(d, g, raw, top); break;
+      case 4: quantise_tile<8, false, E>(d, g, raw, top); break;
+      default: quantise_tile<8, true, E>(d, g, raw, top); break;
+    }
   }
 }
 
@@ -1334,18 +1133,164 @@ __device__ __forceinline__ uint32_t encode_tile_topk_whole(const TensorDesc& d, 
                                                            uint32_t (&raw)[E][4], uint32_t tile, const Sink& sink,
                                                            uint32_t pos0, uint32_t limit) {
   RowMags<E> rowmag;
-  const uint32_t total = topk_extract<E, STORE>(d, raw, rowmag, tile, sink, pos0, limit);
+  const uint32_t total = topk_extract<E, STORE>(d, raw, rowmag, tile * (uint32_t)(E * kRow), sink, pos0, limit);
   if constexpr (STORE) {
-    switch (d.lgq) {  // one switch per tile selects straight-line code for the group size
-      case 3: encode_clean_rows<BITS, ASYM, E, 1>(d, g, raw, rowmag); break;
-      case 4: encode_clean_rows<BITS, ASYM, E, 2>(d, g, raw, rowmag); break;
-      case 5: encode_clean_rows<BITS, ASYM, E, 4>(d, g, raw, rowmag); break;
-      case 6: encode_clean_rows<BITS, ASYM, E, 8>(d, g, raw, rowmag); break;
-      case 7: encode_clean_rows<BITS, ASYM, E, 16>(d, g, raw, rowmag); break;
-      case 8: encode_clean_rows<BITS, ASYM, E, 32>(d, g, raw, rowmag); break;
-      default: encode_clean_rows<BITS, ASYM, E, 64>(d, g, raw, rowmag); break;
+    uint32_t top[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) top[j] = rowmag.at(j);
+    quantise_tile_as<BITS, ASYM, E>(d, g, raw, top);
+  }
+  return total;
+}
+
+// ------------------------------------------------------------------ general tile encoder
+// Groups of any supported size (up to the whole tile), the two kinds of any sizes.  Two steps with nothing but the raw
+// octets and the lane's largest magnitude per row between them: the outliers are found, leave for the sink and are cleared in
+// the octets, group by group; what is left is quantised by the code of tiles without outliers.
+// Bound by instruction issue beside memory.  (Tests on widened values with ballots, masks and counts of all rows kept
+// for an emission behind the codes, and widened values masked anew for them, at 2 to 7 wavefronts per SIMD: STD over 512
+// with int8 groups of 64 and some 20 outliers a tile, 824 vector + 287 scalar instructions, 664 + 109 like this; [8191,
+// 2051] 16.0 -> 13.4 us.  STD over 4096, [726, 4096]: 10.5 -> 8.0 us; over 1024, [4346, 1024]: 9.4 -> 7.5 us; the four
+// largest of 1024, [9968, 1024]: 16.1 -> 11.4 us.)
+
+// STD: the thresholds of the rows, in both halves of a word
+template <int E>
+__device__ __forceinline__ void std_thresholds(const TensorDesc& d, const uint32_t (&raw)[E][4], uint32_t (&t2)[E]) {
+  float s1[E], s2[E];
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    float x[kOct];
+    widen_row(raw[j], x);
+    s1[j] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+    // squares of 16-bit values (at most 11 significant bits) are exact in binary32
+    s2[j] = ((x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3])) +
+            ((x[4] * x[4] + x[5] * x[5]) + (x[6] * x[6] + x[7] * x[7]));
+  }
+  const float inv_gs = __uint_as_float((127u - d.lgs) << 23);  // 2^-lgs, exact
+  if (E == 8 || d.lgs >= 9u) {  // groups of whole rows: one threshold for four rows, a quarter of the lanes each
+    // the canonical tree: every row over its lanes, then rows two by two
+    float a1 = four_rows_reduce(s1[0], s1[1], s1[2], s1[3], OpAdd()), a2 = four_rows_reduce(s2[0], s2[1], s2[2], s2[3], OpAdd());
+    if (E == 8 || d.lgs >= 10u) { a1 = meet<16>(a1, a1, OpAdd()); a2 = meet<16>(a2, a2, OpAdd()); }
+    if (E == 8 || d.lgs >= 11u) { a1 = meet<32>(a1, a1, OpAdd()); a2 = meet<32>(a2, a2, OpAdd()); }
+    if constexpr (E == 8) {  // one group of 4096
+      float b1 = four_rows_reduce(s1[4], s1[5], s1[6], s1[7], OpAdd()), b2 = four_rows_reduce(s2[4], s2[5], s2[6], s2[7], OpAdd());
+      b1 = meet<16>(b1, b1, OpAdd()); b2 = meet<16>(b2, b2, OpAdd());
+      b1 = meet<32>(b1, b1, OpAdd()); b2 = meet<32>(b2, b2, OpAdd());
+      a1 = a1 + b1;
+      a2 = a2 + b2;
+    }
+    const uint32_t t = both_halves(magnitude_limit_squared(std_limit(a1, a2, inv_gs, d.param)));
+#pragma unroll
+    for (int j = 0; j < E; ++j) t2[j] = (uint32_t)__builtin_amdgcn_readlane((int)t, 16 * (j & 3));
+  } else {
+    groups_reduce<E>(s1, d.lgs, OpAdd());
+    groups_reduce<E>(s2, d.lgs, OpAdd());
+#pragma unroll
+    for (int j = 0; j < E; ++j) t2[j] = both_halves(magnitude_limit_squared(std_limit(s1[j], s2[j], inv_gs, d.param)));
+  }
+  forget_derived<E>(raw);  // nothing widened for the sums is kept for the codes
+}
+
+// TOPK over groups inside a row that are longer than the quantisation groups: by ballots, row by row
+template <int E, int LANES, class Sink>
+__device__ __forceinline__ uint32_t topk_rows_extract(const TensorDesc& d, const TileGeo<E>& g, uint32_t (&raw)[E][4], uint32_t tile,
+                                                      const Sink& sink, uint32_t pos0, uint32_t limit) {
+  const uint32_t lane_first = tile * (uint32_t)(E * kRow) + g.lane_off;
+  uint32_t total = 0u;
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    __builtin_amdgcn_sched_barrier(0);
+    uint64_t b[kOct];
+    topk_row_ballots<LANES>(d, raw[j], b);
+    if (!g.full) {  // uniform; groups past the end of the tensor (blanked) have no outliers
+      const uint64_t valid = __builtin_amdgcn_ballot_w64(g.lane_off + g.row_offset(j) < g.rem);
+#pragma unroll
+      for (int e = 0; e < kOct; ++e) b[e] &= valid;
+    }
+    uint32_t mask, lane_excl, row_cnt;
+    bool any, sparse;
+    row_bookkeeping(b, mask, lane_excl, row_cnt, any, sparse);
+    if (any) {  // uniform
+      emit_row(raw[j], mask, lane_excl, sparse, lane_first + (uint32_t)(j * kRow), sink, pos0 + total, limit);
+      total += row_cnt;
+      clear_elements(raw[j], mask);
     }
   }
+  return total;
+}
+// TOPK over groups of R whole rows, one after the other
+template <int E, int R, bool STORE, class Sink>
+__device__ __forceinline__ uint32_t topk_spans_extract(const TensorDesc& d, const TileGeo<E>& g, uint32_t (&raw)[E][4], uint32_t tile,
+                                                       const Sink& sink, uint32_t pos0, uint32_t limit) {
+  uint32_t total = 0u;
+  static_for<E / R>([&](auto Sc) {
+    constexpr int first = decltype(Sc)::value * R;
+    if (first == 0 || g.full || g.rem > (uint32_t)(first * kRow)) {  // uniform; groups past the end of the tensor have no outliers
+      uint32_t rows[R][4];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rows[j][k] = raw[first + j][k];
+      }
+      RowMags<R> mags;
+      total += topk_extract<R, STORE>(d, rows, mags, tile * (uint32_t)(E * kRow) + (uint32_t)(first * kRow), sink, pos0 + total, limit);
+      lds_in_order();  // the next group uses the same list
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) raw[first + j][k] = rows[j][k];
+      }
+    }
+  });
+  return total;
+}
+
+template <int MODE, int BITS, bool ASYM, int E, bool STORE, class Sink>
+__device__ __forceinline__ uint32_t encode_tile_general(const TensorDesc& d, const TileGeo<E>& g, uint32_t (&raw)[E][4], uint32_t tile,
+                                                        const Sink& sink, uint32_t pos0, uint32_t limit) {
+  uint32_t top[E];  // the lane's largest magnitude of every row of what is left
+  uint32_t total = 0u;
+  if constexpr (MODE == kModeTopk) {
+    if constexpr (E == 8) {  // one group of 4096 (with quantisation groups longer than a row)
+      total = topk_spans_extract<E, 8, STORE>(d, g, raw, tile, sink, pos0, limit);
+    } else {
+      switch (d.lgs) {
+        case 4: total = topk_rows_extract<E, 2>(d, g, raw, tile, sink, pos0, limit); break;
+        case 5: total = topk_rows_extract<E, 4>(d, g, raw, tile, sink, pos0, limit); break;
+        case 6: total = topk_rows_extract<E, 8>(d, g, raw, tile, sink, pos0, limit); break;
+        case 7: total = topk_rows_extract<E, 16>(d, g, raw, tile, sink, pos0, limit); break;
+        case 8: total = topk_rows_extract<E, 32>(d, g, raw, tile, sink, pos0, limit); break;
+        case 9: total = topk_rows_extract<E, 64>(d, g, raw, tile, sink, pos0, limit); break;
+        case 10: total = topk_spans_extract<E, 2, STORE>(d, g, raw, tile, sink, pos0, limit); break;
+        default: total = topk_spans_extract<E, 4, STORE>(d, g, raw, tile, sink, pos0, limit); break;
+      }
+    }
+    if constexpr (STORE) {
+#pragma unroll
+      for (int j = 0; j < E; ++j) top[j] = octet_magnitude(raw[j]);
+    }
+  } else {
+    uint32_t t2[E];
+    if constexpr (MODE == kModeStd) {
+      std_thresholds<E>(d, raw, t2);
+    } else {
+      // NONE: what is not finite is zeroed, and reported nowhere
+      const uint32_t t = both_halves(MODE == kModeAbs ? magnitude_limit(d.param) : kNonfiniteMag - 1u);
+#pragma unroll
+      for (int j = 0; j < E; ++j) t2[j] = t;
+    }
+    const uint32_t lane_first = tile * (uint32_t)(E * kRow) + g.lane_off;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
+      top[j] = octet_magnitude(raw[j]);
+      if (__builtin_amdgcn_ballot_w64(top[j] > (t2[j] & 0xFFFFu)) != 0ull) {  // uniform
+        total += take_above(raw[j], t2[j], lane_first + (uint32_t)(j * kRow), sink, pos0 + total, limit);
+        top[j] = octet_magnitude(raw[j]);
+      }
+    }
+  }
+  if constexpr (STORE) quantise_tile_as<BITS, ASYM, E>(d, g, raw, top);
   return total;
 }
 
@@ -1365,12 +1310,7 @@ __device__ __forceinline__ uint32_t encode_tile(const TensorDesc& d, const TileG
   } else if constexpr (WHOLE) {
     return encode_tile_topk_whole<BITS, ASYM, E, STORE>(d, g, raw, tile, sink, pos0, limit);
   } else {
-    TileOutliers<E> out;
-    encode_tile_general<MODE, BITS, ASYM, E, STORE>(d, g, raw, out);
-    if constexpr (MODE != kModeNone) {
-      if (out.total != 0u) emit_outliers<E>(raw, out, tile, sink, pos0, limit);
-    }
-    return out.total;
+    return encode_tile_general<MODE, BITS, ASYM, E, STORE>(d, g, raw, tile, sink, pos0, limit);
   }
 }
 

@@ -92,21 +92,6 @@ __device__ __forceinline__ uint32_t octet_valid(const SegmentGeo& g, uint32_t o)
   return first >= g.cnt ? 0u : (g.cnt - first < (uint32_t)kOct ? g.cnt - first : (uint32_t)kOct);
 }
 
-// reduce over LANES = 2^lg adjacent lanes, lg a run-time (uniform) value
-template <class T, class Op>
-__device__ __forceinline__ T lanes_reduce_lg(T v, uint32_t lg, Op op) {
-  switch (lg) {
-    case 0: break;
-    case 1: v = lanes_reduce<2>(v, op); break;
-    case 2: v = lanes_reduce<4>(v, op); break;
-    case 3: v = lanes_reduce<8>(v, op); break;
-    case 4: v = lanes_reduce<16>(v, op); break;
-    case 5: v = lanes_reduce<32>(v, op); break;
-    default: v = lanes_reduce<64>(v, op); break;
-  }
-  return v;
-}
-
 // For every group of `opg` consecutive octets (the last group of the segment may have fewer; n_oct octets in
 // all): the balanced binary tree `op` over the group's words w[], padded with `pad` to the next power of two;
 // finish(group, result) is called by one thread per group.  Groups of up to 64 octets are taken by as many

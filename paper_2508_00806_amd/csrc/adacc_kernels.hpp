@@ -13,17 +13,16 @@ namespace ADACC_DT_NS {
 
 // ---- single tensor, compress: tiles are independent, one tile per wavefront, workgroups in the
 // hardware's own order (which walks through memory front to back).
-// Wavefronts per SIMD the register allocation of a variant is held to (the compiler would otherwise
-// spend registers on overlapping the rows of a tile, which pays less than another resident
-// wavefront): encoders that take a tile row by row need little beyond the raw octets.
-template <int E, bool ROWWISE, bool WHOLE>
+// Wavefronts per SIMD the register allocation of a variant is held to, as many as do without a spill (the compiler would
+// otherwise spend registers on overlapping the rows of a tile, which pays less than another resident wavefront).
+template <int MODE, bool ASYM, int E, bool WHOLE>
 constexpr int compress_min_waves() {
-  if (ROWWISE) return 6;
-  if (WHOLE) return E == 8 ? 6 : 8;
-  return E == 8 ? 2 : 4;
+  if (E == 4) return 8;
+  if (WHOLE) return 6;
+  return (ASYM ? 4 : 5) - (MODE == (int)kModeTopk ? 1 : 0);
 }
 template <int MODE, int BITS, bool ASYM, int E, bool ROWWISE, bool WHOLE = false>
-__global__ __launch_bounds__(kThreads, (compress_min_waves<E, ROWWISE, WHOLE>())) void compress_kernel(TensorDesc d, uint32_t epoch) {
+__global__ __launch_bounds__(kThreads, (compress_min_waves<MODE, ASYM, E, WHOLE>())) void compress_kernel(TensorDesc d, uint32_t epoch) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
   // one tile per wavefront and no loop: inside a loop over tiles the compiler would prepare, ahead of
   // the loop, the lane's addresses for every group size the encoders can be asked for
@@ -68,7 +67,10 @@ __global__ __launch_bounds__(kThreads) void decompress_kernel(TensorDesc d, uint
 
 template <int MODE, int E, bool ROWWISE, bool WHOLE>
 __device__ __forceinline__ void compress_dispatch(const TensorDesc& d, uint32_t tile, uint32_t epoch) {
-  if constexpr (MODE == kModeNone) {
+  if constexpr (!ROWWISE && !WHOLE) {  // (the codes' form is looked at behind the selection)
+    if constexpr (MODE == kModeNone) compress_tile_plain<kBitsAny, false, E, false>(d, tile);
+    else compress_tile_outliers<MODE, kBitsAny, false, E, false>(d, tile, epoch);
+  } else if constexpr (MODE == kModeNone) {
     switch (d.variant & 6u) {
       case 0: compress_tile_plain<4, false, E, ROWWISE>(d, tile); break;
       case 2: compress_tile_plain<4, true, E, ROWWISE>(d, tile); break;
@@ -87,7 +89,7 @@ __device__ __forceinline__ void compress_dispatch(const TensorDesc& d, uint32_t 
 
 template <int KIND>
 constexpr int batch_min_waves() {
-  return KIND == kBatchRows4 ? 6 : KIND == kBatchTopk4 ? 8 : KIND == kBatchTopk8 ? 6 : KIND == kBatchAny4 ? 4 : 2;
+  return KIND == kBatchAny8 ? 3 : KIND == kBatchTopk8 ? 6 : KIND == kBatchTopk4 ? 8 : 7;
 }
 
 template <int KIND>

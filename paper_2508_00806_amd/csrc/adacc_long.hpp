@@ -1,0 +1,255 @@
+// Compression of long groups: statistics groups of more than half a segment of the fallback kernels (2049 to 11264 elements:
+// a whole row of 11008 values as one STD / TOPK group), with quantisation groups that are the statistics group or a power of
+// two up to a 512-element row.
+//
+// A wavefront takes a group, all of it in registers: row j, octet of lane l, as a tile of up to 22 rows.  Every step is the
+// tile kernels': the k largest by lane maxima, halving and a short list in LDS; sums over lanes, then rows two by two; thresholds
+// on the 16-bit magnitude; four scales at a time.  No barrier, and no octet that exists only to fill a workgroup's slices.
+// (A workgroup per group, adacc_generic.hpp, holds 1376 octets in 6 slices of 256, issues for all 1536 of them, and three of
+// its wavefronts wait while one selects: FIGURES.)
+// 22 rows are what four wavefronts per SIMD hold without a spill; longer groups, and quantisation groups of other
+// sizes, whose lanes do not line up with a row, stay with the workgroup.
+// The blob, its tiles and the workspace are those of adacc_generic.hpp, whose placement kernel follows here too.
+#pragma once
+
+#include "adacc_common.hpp"
+#include "adacc_compress.hpp"
+#include "adacc_dtype.hpp"
+
+namespace adacc {
+namespace ADACC_DT_NS {
+
+struct LongGeo {
+  uint64_t first;     // uniform: index of the group's first element
+  uint32_t cnt;       // uniform: its elements, a multiple of 8 (the tensor's last group may be short)
+  uint32_t lane_off;  // lane * 8
+};
+
+// What does not exist reads as +0.  The loads are issued without a branch between them (an octet that does not exist
+// reads the last one again).
+template <int E>
+__device__ __forceinline__ void load_long(const TensorDesc& d, const LongGeo& g, uint32_t (&raw)[E][4]) {
+  const uint16_t* sp = d.src + g.first;
+  const uint32_t last = g.cnt - (uint32_t)kOct;
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    const uint32_t off = g.lane_off + (uint32_t)(j * kRow);
+    const uint4 v = ADACC_LOAD16(sp + (off < last ? off : last));
+    raw[j][0] = v.x; raw[j][1] = v.y; raw[j][2] = v.z; raw[j][3] = v.w;
+  }
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    if ((uint32_t)((j + 1) * kRow) > g.cnt) {  // uniform
+      const bool there = g.lane_off + (uint32_t)(j * kRow) < g.cnt;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) raw[j][k] = there ? raw[j][k] : 0u;
+    }
+  }
+}
+
+// The sum of a group from the lanes' sums of its rows: the balanced tree over octets padded with +0 to a power of two
+template <int E>
+__device__ __forceinline__ float long_sum(const float (&s)[E]) {
+  constexpr int Q = (E + 3) / 4;
+  float b[Q];
+  static_for<Q>([&](auto Qc) {
+    constexpr int q = decltype(Qc)::value;
+    auto row = [&](auto Ic) { constexpr int j = 4 * q + decltype(Ic)::value; if constexpr (j < E) return s[j]; else return 0.0f; };
+    float v = four_rows_reduce(row(std::integral_constant<int, 0>()), row(std::integral_constant<int, 1>()),
+                               row(std::integral_constant<int, 2>()), row(std::integral_constant<int, 3>()), OpAdd());
+    v = meet<16>(v, v, OpAdd());
+    b[q] = meet<32>(v, v, OpAdd());
+  });
+#pragma unroll
+  for (int w = 1; w < Q; w <<= 1) {
+#pragma unroll
+    for (int q = 0; q + w < Q; q += 2 * w) b[q] = b[q] + b[q + w];
+  }
+  return b[0];
+}
+
+template <int E>
+__device__ __forceinline__ uint32_t long_std_threshold(const TensorDesc& d, const LongGeo& g, const uint32_t (&raw)[E][4]) {
+  float s1[E], s2[E];
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    __builtin_amdgcn_sched_barrier(0);
+    float x[kOct];
+    widen_row(raw[j], x);
+    s1[j] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+    s2[j] = ((x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3])) +
+            ((x[4] * x[4] + x[5] * x[5]) + (x[6] * x[6] + x[7] * x[7]));
+  }
+  const float n = (float)g.cnt;
+  const float m = __fdiv_rn(long_sum<E>(s1), n);
+  float var = __fmaf_rn(-m, m, __fdiv_rn(long_sum<E>(s2), n));
+  var = (var < 0.0f) ? 0.0f : var;  // a NaN stays a NaN: then nothing passes the test
+  forget_derived<E>(raw);           // nothing widened for the sums is kept for the codes
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)magnitude_limit_squared(d.param * var));  // param = k * k
+}
+
+// a6 .. a8, outliers and what is not finite gone.  top(j): the lane's largest magnitude of row j.
+template <int BITS, bool ASYM, int E, class Top>
+__device__ __forceinline__ void quantise_long(const TensorDesc& d, const LongGeo& g, uint32_t seg, const uint32_t (&raw)[E][4], const Top& top) {
+  const bool single = d.gq >= d.tile_elems;  // uniform: one scale for the whole group
+  const uint32_t lg = single ? 9u : d.lgq;
+  uint8_t* codes = d.codes + g.first * BITS / 8;
+  float* scales = d.scales + (single ? (uint64_t)seg : g.first >> d.lgq);
+  float* zp = d.zp + (single ? (uint64_t)seg : g.first >> d.lgq);
+  auto scale_of = [&](uint32_t t, int32_t h, int32_t l, float& s, float& v, float& o) {
+    o = 0.0f;
+    if constexpr (!ASYM) scale_sym_clean(d, mag_bits32(t), s, v);
+    else group_scale<true>(d, 0u, h, l, s, v, o);
+  };
+  auto extremes = [&](int j, int32_t& h, int32_t& l) {  // a lane without an octet brings the identity
+    float x[kOct], hi, lo;
+    widen_row(raw[j], x);
+    row_extremes<true>(x, hi, lo);
+    const bool there = g.lane_off + (uint32_t)(j * kRow) < g.cnt;
+    h = there ? float_key(hi) : (int32_t)0x80000000;
+    l = there ? float_key(lo) : (int32_t)0x7FFFFFFF;
+  };
+  float one_s = 0.0f, one_v = 0.0f, one_o = 0.0f;
+  if (single) {
+    uint32_t t = 0u;
+    int32_t h = (int32_t)0x80000000, l = (int32_t)0x7FFFFFFF;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      if constexpr (!ASYM) {
+        t = OpUMax()(t, top(j));
+      } else {
+        __builtin_amdgcn_sched_barrier(0);
+        int32_t hj, lj;
+        extremes(j, hj, lj);
+        h = OpIMax()(h, hj);
+        l = OpIMin()(l, lj);
+      }
+    }
+    if constexpr (!ASYM) t = lanes_reduce<kWave>(t, OpUMax());
+    else { h = lanes_reduce<kWave>(h, OpIMax()); l = lanes_reduce<kWave>(l, OpIMin()); }
+    scale_of(t, h, l, one_s, one_v, one_o);
+    if (lane_id() == 0) {
+      scales[0] = one_s;
+      if constexpr (ASYM) zp[0] = one_o;
+    }
+    if constexpr (ASYM) forget_derived<E>(raw);
+  }
+  static_for<(E + 3) / 4>([&](auto Fc) {
+    constexpr int first = decltype(Fc)::value * 4;
+    if ((uint32_t)(first * kRow) >= g.cnt) return;  // uniform
+    float scl[4], inv[4], off[4];
+    if (single) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { scl[i] = one_s; inv[i] = one_v; off[i] = one_o; }
+    } else {
+      uint32_t t[4];
+      int32_t h[4], l[4];
+      static_for<4>([&](auto Ic) {
+        constexpr int i = decltype(Ic)::value;
+        t[i] = 0u; h[i] = (int32_t)0x80000000; l[i] = (int32_t)0x7FFFFFFF;
+        if constexpr (first + i < E) {
+          if constexpr (!ASYM) t[i] = top(first + i);
+          else extremes(first + i, h[i], l[i]);
+        }
+      });
+      if constexpr (!ASYM) {
+        groups_reduce<4>(t, lg, OpUMax());
+      } else {
+        groups_reduce<4>(h, lg, OpIMax());
+        groups_reduce<4>(l, lg, OpIMin());
+        forget_derived<E>(raw);
+      }
+      four_scales<ASYM>(d, lg, t, h, l, scl, inv, off);
+    }
+    static_for<4>([&](auto Ic) {
+      constexpr int i = decltype(Ic)::value, j = first + i;
+      if constexpr (j < E) {
+        __builtin_amdgcn_sched_barrier(0);  // one row after the other
+        if ((uint32_t)(j * kRow) >= g.cnt) return;  // uniform
+        float x[kOct];
+        widen_row(raw[j], x);
+#pragma unroll
+        for (int e = 0; e < kOct; ++e) x[e] = __fmul_rn(ASYM ? x[e] - off[i] : x[e], inv[i]);
+        uint32_t w[2];
+        pack_codes<BITS, ASYM>(x, w);
+        const uint32_t at = g.lane_off + (uint32_t)(j * kRow);
+        if (at < g.cnt) {
+          if constexpr (BITS == 8) ADACC_STORE8(codes + at, make_uint2(w[0], w[1]));
+          else ADACC_STORE4(codes + at / 2u, w[0]);
+          if (!single) {  // uniform; all lanes of a group store the same
+            scales[at >> lg] = scl[i];
+            if constexpr (ASYM) zp[at >> lg] = off[i];
+          }
+        }
+      }
+    });
+  });
+}
+
+template <int E>
+__device__ __forceinline__ void compress_long(const TensorDesc& d, uint32_t seg, uint32_t epoch) {
+  LongGeo g;
+  g.first = (uint64_t)seg * d.tile_elems;
+  const uint64_t left = d.numel - g.first;
+  g.cnt = left < (uint64_t)d.tile_elems ? (uint32_t)left : d.tile_elems;
+  g.lane_off = (uint32_t)lane_id() * kOct;
+  const bool lane0 = lane_id() == 0, last = seg + 1u == d.n_tiles;
+  uint32_t raw[E][4];
+  load_long<E>(d, g, raw);
+  RowMags<E> mags;
+  if (d.mode == kModeTopk) {  // uniform
+    const uint32_t pos0 = seg * d.topk;
+    const uint32_t expected = d.topk < g.cnt ? d.topk : g.cnt;
+    const uint32_t end = pos0 + expected;
+    const uint32_t total = topk_extract<E, true>(expected, raw, mags, (uint32_t)g.first, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
+    if (lane0) {
+      d.tile_ptr[seg] = pos0;
+      d.cnt[seg] = total;
+      if (total != expected) *d.flag = epoch;
+      if (last) {
+        d.tile_ptr[d.n_tiles] = end;
+        d.status[0] = end; d.status[1] = end > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u;
+      }
+    }
+  } else {
+    uint32_t most = kNonfiniteMag - 1u;  // NONE: what is not finite is zeroed, and reported nowhere
+    if (d.mode == kModeStd) most = long_std_threshold<E>(d, g, raw);
+    if (d.mode == kModeAbs) most = magnitude_limit(d.param);
+    mags.of(raw);
+    const uint32_t t2 = both_halves(most);
+    uint32_t total = 0u;
+    const SlotSink sink{d.slot + (uint64_t)seg * (uint64_t)kSlot, (uint32_t)g.first};
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (__builtin_amdgcn_ballot_w64(mags.at(j) > most) == 0ull) continue;  // uniform
+      if (d.mode == kModeNone) take_above(raw[j], t2, 0u, NullSink{}, 0u, 0u);
+      else total += take_above(raw[j], t2, (uint32_t)g.first + g.lane_off + (uint32_t)(j * kRow), sink, total, (uint32_t)kSlot);
+      mags.set(j, octet_magnitude(raw[j]));
+    }
+    if (lane0) {
+      if (d.mode != kModeNone) d.cnt[seg] = total;
+      else if (seg == 0u) { d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u; }
+    }
+  }
+  auto top = [&](int j) { return mags.at(j); };
+  switch (d.variant & 6u) {
+    case 0: quantise_long<4, false, E>(d, g, seg, raw, top); break;
+    case 2: quantise_long<4, true, E>(d, g, seg, raw, top); break;
+    case 4: quantise_long<8, false, E>(d, g, seg, raw, top); break;
+    default: quantise_long<8, true, E>(d, g, seg, raw, top); break;
+  }
+}
+
+// wavefronts per SIMD the registers are held to: four registers a row for the values, and some forty beside them
+template <int E>
+constexpr int long_min_waves() { return E <= 8 ? 7 : E <= 12 ? 5 : 4; }
+template <int E>
+__global__ __launch_bounds__(kThreads, (long_min_waves<E>())) void compress_long_kernel(TensorDesc d, uint32_t epoch) {
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
+  const uint32_t seg = blockIdx.x * kWavesPerWg + wave;
+  if (seg < d.n_tiles) compress_long<E>(d, seg, epoch);
+}
+
+}  // namespace ADACC_DT_NS
+}  // namespace adacc
