@@ -125,8 +125,17 @@ struct Plan {  // everything derived from (method, numel)
   bool rowwise;  // every group lies inside a 512-element row and both kinds of group coincide
   bool half;     // the tensor is binary16 (else bf16)
   bool generic;  // group sizes the tile kernels do not take: the fallback kernels do the whole tensor
+  bool wave_groups;  // generic: a wavefront per group instead of a workgroup
   float param, divisor;
 };
+
+// Groups from which on a wavefront for each is faster than a workgroup, three for every SIMD of the device.  (STD over rows
+// of 2200 / 5160 / 8000 / 11008, us by workgroups and by wavefronts: 1024 rows 10.6 9.7 / 12.8 12.7 / 14.0 15.6 / 16.9 19.8; 2048
+// rows 13.2 11.3 / 16.9 15.4 / 19.1 19.6 / 26.2 24.7; 3072 rows 16.9 12.7 / 21.3 17.9 / 24.4 23.2 / 33.2 29.5.)
+constexpr uint64_t kLongGroups = 3072;
+static CompressFn long_fn(const adacc_method* m, const Plan& p) {
+  return ADACC_PICK(p.half, compress_long_fn(p.tile_elems, m->outlier_mode, m->bits, m->asym));
+}
 
 constexpr uint32_t kGenericMaxGroup = 16384;  // the longest segment of the fallback kernels
 
@@ -164,6 +173,11 @@ static int make_plan(const adacc_method* m, uint64_t numel, Plan* p) {
     const uint64_t segs = (numel + p->tile_elems - 1) / p->tile_elems;
     if (segs >= (1ull << 31)) return ADACC_EINVAL;
     p->n_tiles = p->n_tiles_all = (uint32_t)segs;
+    // One group to a segment, quantisation groups that are the segment or line up with its 512-element rows, whole octets,
+    // and groups enough: a wavefront per group (adacc_long.hpp) does the compression, if it can hold the group.
+    p->lgq = is_pow2(m->quant_group) ? ilog2(m->quant_group) : 0;
+    p->wave_groups = gs > 2048 && segs >= kLongGroups && numel % 8 == 0 &&
+                     (m->quant_group == gs || (is_pow2(m->quant_group) && m->quant_group <= 512)) && long_fn(m, *p) != nullptr;
   } else {
     p->tile_elems = gs > 2048 ? 4096u : 2048u;
     p->numel_main = numel - numel % gs;
@@ -635,8 +649,12 @@ static int launch_generic_compress(const adacc_method* method, const Plan& p, co
   const bool topk = method->outlier_mode == ADACC_OUTLIER_TOPK;
   const uint32_t lds = ADACC_PICK(p.half, generic_lds_bytes(p.tile_elems, method->quant_group, topk && d.gs < p.tile_elems));
   const uint32_t threads = ADACC_PICK(p.half, generic_threads());
-  hipLaunchKernelGGL(ADACC_PICK(p.half, compress_generic_fn(p.tile_elems, method->outlier_mode, d.gs)), dim3(p.n_tiles), dim3(threads), lds, s, d, epoch);
-  int rc = launch_check("compress_generic_kernel");
+  if (p.wave_groups) {
+    hipLaunchKernelGGL(long_fn(method, p), dim3(blocks_of(p.n_tiles, kWavesPerWg)), dim3(kThreads), 0, s, d, epoch);
+  } else {
+    hipLaunchKernelGGL(ADACC_PICK(p.half, compress_generic_fn(p.tile_elems, method->outlier_mode, d.gs)), dim3(p.n_tiles), dim3(threads), lds, s, d, epoch);
+  }
+  int rc = launch_check("compression of the fallback methods");
   if (rc != ADACC_OK || !p.outliers) return rc;
   rc = launch_block_sums(method, p, d, s);
   if (rc != ADACC_OK) return rc;

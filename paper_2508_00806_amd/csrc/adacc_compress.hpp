@@ -818,7 +818,7 @@ struct RowMags {
 // Every lane offers its two largest row maxima: the threshold then fails to cut off exactly k
 // elements only when a lane holds three of the k largest, or two of them in one octet, or on a tie.
 template <int E>
-__device__ __forceinline__ bool topk_whole_threshold(const TensorDesc& d, const RowMags<E>& rowmag, uint32_t& t16) {
+__device__ __forceinline__ bool topk_whole_threshold(uint32_t k, const RowMags<E>& rowmag, uint32_t& t16) {
   uint32_t p1 = rowmag.pm[0], p2 = 0u;  // the two largest of the even and of the odd rows
 #pragma unroll
   for (int i = 1; i < E / 2; ++i) {
@@ -834,17 +834,17 @@ __device__ __forceinline__ bool topk_whole_threshold(const TensorDesc& d, const 
   // The k-th largest of the 128.  Two rounds of a maximum over the wavefront take 22 vector instructions, more of them 11
   // each; halving takes 30 comparisons whatever k is, and scalar work.  ([32768, 2048], k = 2: 31.1 us by rounds, 31.7 by
   // halving; [8192, 4096], k = 4, is faster by halving.)
-  if (d.topk <= 2u) {  // uniform
+  if (k <= 2u) {  // uniform
     const uint32_t lane = (uint32_t)lane_id();
     uint32_t cur = (m1 << 6) | lane;  // unique per lane: equal maxima are taken one after the other
     uint32_t win = wave_max_u32_scalar(cur);
-    if (d.topk == 2u) {
+    if (k == 2u) {
       cur = cur == win ? (m2 << 6) | lane : cur;
       win = wave_max_u32_scalar(cur);
     }
     t16 = win >> 6;
   } else {
-    t16 = kth_by_halving(d.topk, [&](uint32_t t) { return lanes_where(m1 >= t) + lanes_where(m2 >= t); });
+    t16 = kth_by_halving(k, [&](uint32_t t) { return lanes_where(m1 >= t) + lanes_where(m2 >= t); });
   }
   return finite;
 }
@@ -852,15 +852,17 @@ __device__ __forceinline__ bool topk_whole_threshold(const TensorDesc& d, const 
 // Rounds over a tile that is one statistics group: the k-th largest key, uniform.  Returns whether
 // it belongs to an Inf / NaN (then there may be more than k outliers).
 template <int E>
-__device__ __forceinline__ bool topk_select_rounds_whole(const TensorDesc& d, const uint32_t (&raw)[E][4], uint32_t& kth_out,
+__device__ __forceinline__ bool topk_select_rounds_whole(uint32_t k, const uint32_t (&raw)[E][4], uint32_t& kth_out,
                                                          uint32_t lane_pos) {
   uint32_t kth = 0xFFFFFFFFu;
-  for (uint32_t r = 0; r < d.topk; ++r) {
+  for (uint32_t r = 0; r < k; ++r) {
     forget_derived<E>(raw);  // the keys are formed again in every round ...
     asm volatile("" : "+v"(lane_pos));  // ... and so are the position codes: 8 per row would sit in registers otherwise
     uint32_t m = 0u;
 #pragma unroll
     for (int j = 0; j < E; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" : "+v"(lane_pos));
       const uint32_t row_pos = ((uint32_t)j << 9) | lane_pos;
 #pragma unroll
       for (int e = 0; e < kOct; ++e) {
@@ -883,11 +885,11 @@ __device__ __forceinline__ bool topk_select_rounds_whole(const TensorDesc& d, co
 // Extraction by keys (any tile): the k largest keys (magnitude above, inverted position below), and
 // every value that is not finite when those are more than k.  Returns the number of outliers.
 template <int E, class Sink>
-__device__ __forceinline__ uint32_t topk_extract_by_keys(const TensorDesc& d, uint32_t (&raw)[E][4], uint32_t first,
+__device__ __forceinline__ uint32_t topk_extract_by_keys(uint32_t k, uint32_t (&raw)[E][4], uint32_t first,
                                                         const Sink& sink, uint32_t pos0, uint32_t limit) {
   uint32_t lane_pos = (uint32_t)lane_id() << 3;
   uint32_t kth;
-  const bool poisoned = topk_select_rounds_whole<E>(d, raw, kth, lane_pos);
+  const bool poisoned = topk_select_rounds_whole<E>(k, raw, kth, lane_pos);
   const uint32_t lane_first = first + (uint32_t)lane_id() * kOct;
   uint32_t total = 0u;
 #pragma unroll
@@ -930,14 +932,13 @@ struct TopkList {
   uint32_t where[16];  // the octet's first element, in the tile
 };
 template <int E, bool STORE, class Sink>
-__device__ __forceinline__ uint32_t topk_extract(const TensorDesc& d, uint32_t (&raw)[E][4], RowMags<E>& rowmag,
+__device__ __forceinline__ uint32_t topk_extract(uint32_t k, uint32_t (&raw)[E][4], RowMags<E>& rowmag,
                                                  uint32_t first, const Sink& sink, uint32_t pos0, uint32_t limit) {
   __shared__ TopkList lists[kWavesPerWg];
   rowmag.of(raw);
   const uint32_t lane = (uint32_t)lane_id();
-  const uint32_t k = d.topk;
   uint32_t t16;
-  if (k <= 8u && topk_whole_threshold<E>(d, rowmag, t16)) {  // false if the tile holds an Inf or a NaN
+  if (k <= 8u && topk_whole_threshold<E>(k, rowmag, t16)) {  // false if the tile holds an Inf or a NaN
     uint64_t cand[E];
     uint32_t octets = 0u;
 #pragma unroll
@@ -1004,16 +1005,53 @@ __device__ __forceinline__ uint32_t topk_extract(const TensorDesc& d, uint32_t (
       return k;
     }
   }
-  const uint32_t total = topk_extract_by_keys<E>(d, raw, first, sink, pos0, limit);
+  const uint32_t total = topk_extract_by_keys<E>(k, raw, first, sink, pos0, limit);
   if constexpr (STORE) rowmag.of(raw);
   return total;
 }
 
+// ------------------------------------------------------------------ a6 for a few rows without outliers
+// From the extremes of the rows' groups of 2^lg elements (symmetric: t, the largest magnitudes; asymmetric: the keys hi and lo),
+// which every lane of a group holds.  Four rows at a time lane l of every quad forms the scale of row l, where every lane of
+// the group would form the same one, and the quad's lanes pass them around.
+template <bool ASYM, int B>
+__device__ __forceinline__ void scales_of(const TensorDesc& d, uint32_t lg, const uint32_t (&t)[B], const int32_t (&hi)[B], const int32_t (&lo)[B],
+                                          float (&scl)[B], float (&inv)[B], float (&off)[B]) {
+  auto scale = [&](uint32_t tt, int32_t h, int32_t l, float& s, float& v, float& o) {
+    o = 0.0f;
+    if constexpr (!ASYM) scale_sym_clean(d, mag_bits32(tt), s, v);
+    else group_scale<true>(d, 0u, h, l, s, v, o);
+  };
+  if constexpr (B == 4) {
+    if (lg >= 5u) {  // uniform: a group has four lanes at least
+      auto pick = [&](auto a, auto b, auto c, auto e) {  // lane l of a quad: argument l
+        const bool second = __builtin_amdgcn_inverse_ballot_w64(0x2222222222222222ull);
+        const bool third = __builtin_amdgcn_inverse_ballot_w64(0x4444444444444444ull);
+        const bool fourth = __builtin_amdgcn_inverse_ballot_w64(0x8888888888888888ull);
+        auto v = second ? b : a;
+        v = third ? c : v;
+        return fourth ? e : v;
+      };
+      float s, v, o;
+      if constexpr (!ASYM) scale(pick(t[0], t[1], t[2], t[3]), 0, 0, s, v, o);
+      else scale(0u, pick(hi[0], hi[1], hi[2], hi[3]), pick(lo[0], lo[1], lo[2], lo[3]), s, v, o);
+      scl[0] = dpp_move<0x00>(s); scl[1] = dpp_move<0x55>(s); scl[2] = dpp_move<0xAA>(s); scl[3] = dpp_move<0xFF>(s);
+      inv[0] = dpp_move<0x00>(v); inv[1] = dpp_move<0x55>(v); inv[2] = dpp_move<0xAA>(v); inv[3] = dpp_move<0xFF>(v);
+      off[0] = dpp_move<0x00>(o); off[1] = dpp_move<0x55>(o); off[2] = dpp_move<0xAA>(o); off[3] = dpp_move<0xFF>(o);
+      return;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < B; ++i) {
+    if constexpr (!ASYM) scale(t[i], 0, 0, scl[i], inv[i], off[i]);
+    else scale(0u, hi[i], lo[i], scl[i], inv[i], off[i]);
+  }
+}
+
 // ------------------------------------------------------------------ a6 .. a8 for a tile without outliers
 // (none left, and nothing that is not finite), quantisation groups of any size.  top: symmetric, the lane's largest magnitude
-// of every row.  Four rows at a time: their extremes meet group by group, the one step that depends on the size of the groups; lane
-// l of every quad forms the scale of row l (every lane of a group would form the same one), and the quad's lanes pass
-// them around; then the codes.
+// of every row.  Four rows at a time: their extremes meet group by group, the one step that depends on the size of the groups;
+// then the scales, then the codes.
 template <int BITS, bool ASYM, int E>
 __device__ __forceinline__ void quantise_tile(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4], const uint32_t (&top)[E]) {
   constexpr int B = E < 4 ? E : 4;
@@ -1069,33 +1107,7 @@ __device__ __forceinline__ void quantise_tile(const TensorDesc& d, const TileGeo
       forget_derived<E>(raw);  // nothing widened for the extremes is kept for the codes
     }
     float scl[B], inv[B], off[B];
-    auto scale_of = [&](uint32_t tt, int32_t h, int32_t l, float& s, float& v, float& o) {
-      o = 0.0f;
-      if constexpr (!ASYM) scale_sym_clean(d, mag_bits32(tt), s, v);
-      else group_scale<true>(d, 0u, h, l, s, v, o);
-    };
-    auto pick = [&](auto a, auto b, auto c, auto e) {  // lane l of a quad: argument l
-      const bool second = __builtin_amdgcn_inverse_ballot_w64(0x2222222222222222ull);
-      const bool third = __builtin_amdgcn_inverse_ballot_w64(0x4444444444444444ull);
-      const bool fourth = __builtin_amdgcn_inverse_ballot_w64(0x8888888888888888ull);
-      auto v = second ? b : a;
-      v = third ? c : v;
-      return fourth ? e : v;
-    };
-    if (B == 4 && d.lgq >= 5u) {  // uniform: a group has four lanes at least
-      float s, v, o;
-      if constexpr (!ASYM) scale_of(pick(t[0], t[1 % B], t[2 % B], t[3 % B]), 0, 0, s, v, o);
-      else scale_of(0u, pick(hi[0], hi[1 % B], hi[2 % B], hi[3 % B]), pick(lo[0], lo[1 % B], lo[2 % B], lo[3 % B]), s, v, o);
-      scl[0] = dpp_move<0x00>(s); scl[1 % B] = dpp_move<0x55>(s); scl[2 % B] = dpp_move<0xAA>(s); scl[3 % B] = dpp_move<0xFF>(s);
-      inv[0] = dpp_move<0x00>(v); inv[1 % B] = dpp_move<0x55>(v); inv[2 % B] = dpp_move<0xAA>(v); inv[3 % B] = dpp_move<0xFF>(v);
-      off[0] = dpp_move<0x00>(o); off[1 % B] = dpp_move<0x55>(o); off[2 % B] = dpp_move<0xAA>(o); off[3 % B] = dpp_move<0xFF>(o);
-    } else {
-#pragma unroll
-      for (int i = 0; i < B; ++i) {
-        if constexpr (!ASYM) scale_of(t[i], 0, 0, scl[i], inv[i], off[i]);
-        else scale_of(0u, hi[i], lo[i], scl[i], inv[i], off[i]);
-      }
-    }
+    scales_of<ASYM, B>(d, lg, t, hi, lo, scl, inv, off);
 #pragma unroll
     for (int i = 0; i < B; ++i) {
       // one row after the other: the compiler shall not start on the next rows to hide this row's
@@ -1133,7 +1145,7 @@ __device__ __forceinline__ uint32_t encode_tile_topk_whole(const TensorDesc& d, 
                                                            uint32_t (&raw)[E][4], uint32_t tile, const Sink& sink,
                                                            uint32_t pos0, uint32_t limit) {
   RowMags<E> rowmag;
-  const uint32_t total = topk_extract<E, STORE>(d, raw, rowmag, tile * (uint32_t)(E * kRow), sink, pos0, limit);
+  const uint32_t total = topk_extract<E, STORE>(d.topk, raw, rowmag, tile * (uint32_t)(E * kRow), sink, pos0, limit);
   if constexpr (STORE) {
     uint32_t top[E];
 #pragma unroll
@@ -1233,7 +1245,7 @@ __device__ __forceinline__ uint32_t topk_spans_extract(const TensorDesc& d, cons
         for (int k = 0; k < 4; ++k) rows[j][k] = raw[first + j][k];
       }
       RowMags<R> mags;
-      total += topk_extract<R, STORE>(d, rows, mags, tile * (uint32_t)(E * kRow) + (uint32_t)(first * kRow), sink, pos0 + total, limit);
+      total += topk_extract<R, STORE>(d.topk, rows, mags, tile * (uint32_t)(E * kRow) + (uint32_t)(first * kRow), sink, pos0 + total, limit);
       lds_in_order();  // the next group uses the same list
 #pragma unroll
       for (int j = 0; j < R; ++j) {

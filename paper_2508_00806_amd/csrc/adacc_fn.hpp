@@ -32,6 +32,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
 //   generic_threads, generic_lds_bytes: workgroup size and dynamic LDS of the fallback kernels (one segment per workgroup;
 //     topk_groups: TOPK over several statistics groups of a segment); compress_generic_fn: by segment, mode and
 //     statistics group; place_generic_fn: their placement
+//   compress_long_fn: groups of more than half a segment, a wavefront each (adacc_long.hpp); null where a workgroup each is faster
 //   stream: the statistics pass reads with the streaming hint (tensors beyond kStatsKeepBytes)
 //   channel_score_channels: channels per workgroup of the score kernel
 //   channel_select_threads: size of the one workgroup of the select kernel
@@ -54,6 +55,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   PlaceSumBatchFn place_sum_batch_fn();                                                \
   PlaceBatchFn place_batch_fn();                                                       \
   CompressFn compress_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs);     \
+  CompressFn compress_long_fn(uint32_t tile_elems, uint32_t mode, uint32_t bits, uint32_t asym); \
   CompressFn place_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs);        \
   uint32_t generic_threads();                                                          \
   uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups);      \

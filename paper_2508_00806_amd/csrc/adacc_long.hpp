@@ -1,14 +1,17 @@
-// Compression of long groups: statistics groups of more than half a segment of the fallback kernels (2049 to 11264 elements:
-// a whole row of 11008 values as one STD / TOPK group), with quantisation groups that are the statistics group or a power of
-// two up to a 512-element row.
+// Compression of long groups: statistics groups of more than half a segment of the fallback kernels (2049 elements and more: a
+// whole row of 2200 or 11008 values as one group), with quantisation groups that are the statistics group or a power of two up to
+// a 512-element row.
 //
 // A wavefront takes a group, all of it in registers: row j, octet of lane l, as a tile of up to 22 rows.  Every step is the
-// tile kernels': the k largest by lane maxima, halving and a short list in LDS; sums over lanes, then rows two by two; thresholds
-// on the 16-bit magnitude; four scales at a time.  No barrier, and no octet that exists only to fill a workgroup's slices.
-// (A workgroup per group, adacc_generic.hpp, holds 1376 octets in 6 slices of 256, issues for all 1536 of them, and three of
-// its wavefronts wait while one selects: FIGURES.)
-// 22 rows are what four wavefronts per SIMD hold without a spill; longer groups, and quantisation groups of other
-// sizes, whose lanes do not line up with a row, stay with the workgroup.
+// tile kernels': sums over lanes, then rows two by two; thresholds on the 16-bit magnitude; the k largest by lane maxima,
+// halving and a list in LDS; four scales at a time.  No barrier, and no octet that exists only to fill a workgroup's
+// slices.  (A workgroup per group, adacc_generic.hpp: in us, groups of one row each, int8, workgroup -> wavefront
+//   STD   [26000, 2200] 82.5 -> 48.4   [16000, 4104] 68.6 -> 47.9   [12000, 5160] 56.8 -> 44.3   [8192, 11008] 76.7 -> 62.2
+//   TOPK  [26000, 2200] 83.0 -> 42.7   NONE  39.4 -> 31.3   ABS  62.1 -> 40.7.)
+// Where the workgroup is the better one, it stays: longer groups without STD ([8192, 11008]: NONE 44.8
+// us by workgroups, 50.0 by wavefronts; TOPK 58.4 and 88.8, whose two ways to the k largest do not fit the registers beside 22
+// rows), tensors of few groups (a wavefront each leaves the device empty), quantisation groups whose lanes do not line up
+// with a row, and more than 22 rows, which four wavefronts per SIMD would not hold without a spill.
 // The blob, its tiles and the workspace are those of adacc_generic.hpp, whose placement kernel follows here too.
 #pragma once
 
@@ -22,67 +25,83 @@ namespace ADACC_DT_NS {
 struct LongGeo {
   uint64_t first;     // uniform: index of the group's first element
   uint32_t cnt;       // uniform: its elements, a multiple of 8 (the tensor's last group may be short)
-  uint32_t lane_off;  // lane * 8
+  // elements of row j (uniform): 512, fewer in the last one, 0 behind it
+  __device__ __forceinline__ uint32_t row_elems(int j) const {
+    const uint32_t at = (uint32_t)(j * kRow);
+    return cnt <= at ? 0u : (cnt - at < (uint32_t)kRow ? cnt - at : (uint32_t)kRow);
+  }
 };
+// lane * 8, formed anew where it is called: offsets and comparisons of all rows would otherwise be kept from the loads to the
+// stores, a register each
+__device__ __forceinline__ uint32_t lane_offset() {
+  uint32_t v = (uint32_t)lane_id() * kOct;
+  asm volatile("" : "+v"(v));
+  return v;
+}
 
 // What does not exist reads as +0.  The loads are issued without a branch between them (an octet that does not exist
-// reads the last one again).
+// reads its row's last one again, a row that does not exist the first one).
 template <int E>
 __device__ __forceinline__ void load_long(const TensorDesc& d, const LongGeo& g, uint32_t (&raw)[E][4]) {
   const uint16_t* sp = d.src + g.first;
-  const uint32_t last = g.cnt - (uint32_t)kOct;
+  const uint32_t lane_off = lane_offset();
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    const uint32_t off = g.lane_off + (uint32_t)(j * kRow);
-    const uint4 v = ADACC_LOAD16(sp + (off < last ? off : last));
+    const uint32_t n = g.row_elems(j), last = n != 0u ? n - (uint32_t)kOct : 0u;
+    const uint4 v = ADACC_LOAD16(sp + (n != 0u ? j * kRow : 0) + (lane_off < last ? lane_off : last));
     raw[j][0] = v.x; raw[j][1] = v.y; raw[j][2] = v.z; raw[j][3] = v.w;
   }
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    if ((uint32_t)((j + 1) * kRow) > g.cnt) {  // uniform
-      const bool there = g.lane_off + (uint32_t)(j * kRow) < g.cnt;
+    const uint32_t n = g.row_elems(j);
+    if (n != (uint32_t)kRow) {  // uniform
+      const bool there = lane_offset() < n;
 #pragma unroll
       for (int k = 0; k < 4; ++k) raw[j][k] = there ? raw[j][k] : 0u;
     }
   }
 }
 
-// The sum of a group from the lanes' sums of its rows: the balanced tree over octets padded with +0 to a power of two
+// STD: the sums of the group as the balanced tree over octets padded with +0 to a power of two (an octet's part is its own tree,
+// then the lanes of a row, then rows two by two), four rows at a time, so that no row's part is kept; then the threshold.
 template <int E>
-__device__ __forceinline__ float long_sum(const float (&s)[E]) {
+__device__ __forceinline__ uint32_t long_std_threshold(const TensorDesc& d, const LongGeo& g, const uint32_t (&raw)[E][4]) {
   constexpr int Q = (E + 3) / 4;
-  float b[Q];
+  float b1[Q], b2[Q];
   static_for<Q>([&](auto Qc) {
     constexpr int q = decltype(Qc)::value;
-    auto row = [&](auto Ic) { constexpr int j = 4 * q + decltype(Ic)::value; if constexpr (j < E) return s[j]; else return 0.0f; };
-    float v = four_rows_reduce(row(std::integral_constant<int, 0>()), row(std::integral_constant<int, 1>()),
-                               row(std::integral_constant<int, 2>()), row(std::integral_constant<int, 3>()), OpAdd());
-    v = meet<16>(v, v, OpAdd());
-    b[q] = meet<32>(v, v, OpAdd());
+    float s1[4], s2[4];
+    static_for<4>([&](auto Ic) {
+      constexpr int i = decltype(Ic)::value, j = 4 * q + i;
+      s1[i] = 0.0f;
+      s2[i] = 0.0f;
+      if constexpr (j < E) {
+        __builtin_amdgcn_sched_barrier(0);
+        float x[kOct];
+        widen_row(raw[j], x);
+        s1[i] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+        s2[i] = ((x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3])) +
+                ((x[4] * x[4] + x[5] * x[5]) + (x[6] * x[6] + x[7] * x[7]));
+      }
+    });
+    b1[q] = four_rows_reduce(s1[0], s1[1], s1[2], s1[3], OpAdd());
+    b2[q] = four_rows_reduce(s2[0], s2[1], s2[2], s2[3], OpAdd());
+    b1[q] = meet<16>(b1[q], b1[q], OpAdd());
+    b2[q] = meet<16>(b2[q], b2[q], OpAdd());
+    b1[q] = meet<32>(b1[q], b1[q], OpAdd());
+    b2[q] = meet<32>(b2[q], b2[q], OpAdd());
   });
 #pragma unroll
   for (int w = 1; w < Q; w <<= 1) {
 #pragma unroll
-    for (int q = 0; q + w < Q; q += 2 * w) b[q] = b[q] + b[q + w];
-  }
-  return b[0];
-}
-
-template <int E>
-__device__ __forceinline__ uint32_t long_std_threshold(const TensorDesc& d, const LongGeo& g, const uint32_t (&raw)[E][4]) {
-  float s1[E], s2[E];
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    __builtin_amdgcn_sched_barrier(0);
-    float x[kOct];
-    widen_row(raw[j], x);
-    s1[j] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
-    s2[j] = ((x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3])) +
-            ((x[4] * x[4] + x[5] * x[5]) + (x[6] * x[6] + x[7] * x[7]));
+    for (int q = 0; q + w < Q; q += 2 * w) {
+      b1[q] = b1[q] + b1[q + w];
+      b2[q] = b2[q] + b2[q + w];
+    }
   }
   const float n = (float)g.cnt;
-  const float m = __fdiv_rn(long_sum<E>(s1), n);
-  float var = __fmaf_rn(-m, m, __fdiv_rn(long_sum<E>(s2), n));
+  const float m = __fdiv_rn(b1[0], n);
+  float var = __fmaf_rn(-m, m, __fdiv_rn(b2[0], n));
   var = (var < 0.0f) ? 0.0f : var;  // a NaN stays a NaN: then nothing passes the test
   forget_derived<E>(raw);           // nothing widened for the sums is kept for the codes
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)magnitude_limit_squared(d.param * var));  // param = k * k
@@ -105,7 +124,7 @@ __device__ __forceinline__ void quantise_long(const TensorDesc& d, const LongGeo
     float x[kOct], hi, lo;
     widen_row(raw[j], x);
     row_extremes<true>(x, hi, lo);
-    const bool there = g.lane_off + (uint32_t)(j * kRow) < g.cnt;
+    const bool there = lane_offset() < g.row_elems(j);
     h = there ? float_key(hi) : (int32_t)0x80000000;
     l = there ? float_key(lo) : (int32_t)0x7FFFFFFF;
   };
@@ -159,26 +178,29 @@ __device__ __forceinline__ void quantise_long(const TensorDesc& d, const LongGeo
         groups_reduce<4>(l, lg, OpIMin());
         forget_derived<E>(raw);
       }
-      four_scales<ASYM>(d, lg, t, h, l, scl, inv, off);
+      scales_of<ASYM, 4>(d, lg, t, h, l, scl, inv, off);
     }
     static_for<4>([&](auto Ic) {
       constexpr int i = decltype(Ic)::value, j = first + i;
       if constexpr (j < E) {
         __builtin_amdgcn_sched_barrier(0);  // one row after the other
-        if ((uint32_t)(j * kRow) >= g.cnt) return;  // uniform
+        const uint32_t n = g.row_elems(j);
+        if (n == 0u) return;  // uniform
         float x[kOct];
         widen_row(raw[j], x);
 #pragma unroll
         for (int e = 0; e < kOct; ++e) x[e] = __fmul_rn(ASYM ? x[e] - off[i] : x[e], inv[i]);
         uint32_t w[2];
         pack_codes<BITS, ASYM>(x, w);
-        const uint32_t at = g.lane_off + (uint32_t)(j * kRow);
-        if (at < g.cnt) {
-          if constexpr (BITS == 8) ADACC_STORE8(codes + at, make_uint2(w[0], w[1]));
-          else ADACC_STORE4(codes + at / 2u, w[0]);
+        const uint32_t lane_off = lane_offset();
+        if (lane_off < n) {
+          uint8_t* cp = codes + j * kRow * BITS / 8;
+          if constexpr (BITS == 8) ADACC_STORE8(cp + lane_off, make_uint2(w[0], w[1]));
+          else ADACC_STORE4(cp + lane_off / 2u, w[0]);
           if (!single) {  // uniform; all lanes of a group store the same
-            scales[at >> lg] = scl[i];
-            if constexpr (ASYM) zp[at >> lg] = off[i];
+            const uint32_t row_grp = (uint32_t)(j * kRow) >> lg, grp = lane_off >> lg;
+            scales[row_grp + grp] = scl[i];
+            if constexpr (ASYM) zp[row_grp + grp] = off[i];
           }
         }
       }
@@ -186,22 +208,23 @@ __device__ __forceinline__ void quantise_long(const TensorDesc& d, const LongGeo
   });
 }
 
-template <int E>
+template <int E, bool TOPK, int BITS, bool ASYM>
 __device__ __forceinline__ void compress_long(const TensorDesc& d, uint32_t seg, uint32_t epoch) {
   LongGeo g;
   g.first = (uint64_t)seg * d.tile_elems;
   const uint64_t left = d.numel - g.first;
   g.cnt = left < (uint64_t)d.tile_elems ? (uint32_t)left : d.tile_elems;
-  g.lane_off = (uint32_t)lane_id() * kOct;
   const bool lane0 = lane_id() == 0, last = seg + 1u == d.n_tiles;
   uint32_t raw[E][4];
   load_long<E>(d, g, raw);
   RowMags<E> mags;
-  if (d.mode == kModeTopk) {  // uniform
+  if constexpr (TOPK) {
     const uint32_t pos0 = seg * d.topk;
     const uint32_t expected = d.topk < g.cnt ? d.topk : g.cnt;
     const uint32_t end = pos0 + expected;
-    const uint32_t total = topk_extract<E, true>(expected, raw, mags, (uint32_t)g.first, StreamSink{d.idx, d.val}, pos0, end < d.cap ? end : d.cap);
+    const uint32_t limit = end < d.cap ? end : d.cap;
+    const StreamSink sink{d.idx, d.val};
+    const uint32_t total = topk_extract<E, true>(expected, raw, mags, (uint32_t)g.first, sink, pos0, limit);
     if (lane0) {
       d.tile_ptr[seg] = pos0;
       d.cnt[seg] = total;
@@ -224,7 +247,7 @@ __device__ __forceinline__ void compress_long(const TensorDesc& d, uint32_t seg,
       __builtin_amdgcn_sched_barrier(0);
       if (__builtin_amdgcn_ballot_w64(mags.at(j) > most) == 0ull) continue;  // uniform
       if (d.mode == kModeNone) take_above(raw[j], t2, 0u, NullSink{}, 0u, 0u);
-      else total += take_above(raw[j], t2, (uint32_t)g.first + g.lane_off + (uint32_t)(j * kRow), sink, total, (uint32_t)kSlot);
+      else total += take_above(raw[j], t2, (uint32_t)g.first + lane_offset() + (uint32_t)(j * kRow), sink, total, (uint32_t)kSlot);
       mags.set(j, octet_magnitude(raw[j]));
     }
     if (lane0) {
@@ -232,23 +255,17 @@ __device__ __forceinline__ void compress_long(const TensorDesc& d, uint32_t seg,
       else if (seg == 0u) { d.status[0] = 0u; d.status[1] = 0u; d.status[2] = 0u; d.status[3] = 0u; }
     }
   }
-  auto top = [&](int j) { return mags.at(j); };
-  switch (d.variant & 6u) {
-    case 0: quantise_long<4, false, E>(d, g, seg, raw, top); break;
-    case 2: quantise_long<4, true, E>(d, g, seg, raw, top); break;
-    case 4: quantise_long<8, false, E>(d, g, seg, raw, top); break;
-    default: quantise_long<8, true, E>(d, g, seg, raw, top); break;
-  }
+  quantise_long<BITS, ASYM, E>(d, g, seg, raw, [&](int j) { return mags.at(j); });
 }
 
 // wavefronts per SIMD the registers are held to: four registers a row for the values, and some forty beside them
-template <int E>
-constexpr int long_min_waves() { return E <= 8 ? 7 : E <= 12 ? 5 : 4; }
-template <int E>
-__global__ __launch_bounds__(kThreads, (long_min_waves<E>())) void compress_long_kernel(TensorDesc d, uint32_t epoch) {
+template <int E, bool TOPK>
+constexpr int long_min_waves() { return TOPK ? 6 : E <= 8 ? 8 : E <= 12 ? 6 : E <= 16 ? 5 : 4; }
+template <int E, bool TOPK, int BITS, bool ASYM>
+__global__ __launch_bounds__(kThreads, (long_min_waves<E, TOPK>())) void compress_long_kernel(TensorDesc d, uint32_t epoch) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
   const uint32_t seg = blockIdx.x * kWavesPerWg + wave;
-  if (seg < d.n_tiles) compress_long<E>(d, seg, epoch);
+  if (seg < d.n_tiles) compress_long<E, TOPK, BITS, ASYM>(d, seg, epoch);
 }
 
 }  // namespace ADACC_DT_NS
