@@ -5,7 +5,7 @@
 //
 // The selection is an integer decision taken by floating-point sums, so the order of the sums is
 // fixed: chunks of 64 tokens added one after the other in binary32; the chunk sums added one after
-// the other in binary64; sums over channels in 256 interleaved binary64 accumulators folded by halves.
+// the other in binary64; sums over channels in 512 binary64 accumulators, an octet of channels at a time, folded by halves.
 #pragma once
 
 #include "adacc_common.hpp"
@@ -15,7 +15,7 @@
 namespace adacc {
 namespace ADACC_DT_NS {
 
-constexpr int kSelectThreads = 1024;    // accumulators of the sums over channels
+constexpr int kSelectThreads = 512;     // accumulators of the sums over channels
 
 // ---- step 1: binary32 sums of |x| over chunks of 64 tokens, partial[chunk][hidden].  A workgroup
 // takes one chunk of a strip of 512 channels: a lane owns 8 adjacent channels (one 16-byte load per
@@ -127,15 +127,13 @@ __device__ __forceinline__ bool finite_f64(double v) {
   return ((uint64_t)__double_as_longlong(v) & 0x7FF0000000000000ull) != 0x7FF0000000000000ull;
 }
 
-// One accumulator per thread (thread j holds the sum over the channels h = j mod 1024, ascending).  They meet
-// in a fixed order: the xor butterfly inside a wavefront (both partners add the same two numbers, so every
-// lane ends with the same bits), then the wavefronts' sums through LDS, added in wavefront order by every
-// thread.  Two barriers instead of one per level of a tree over LDS.
+// The sum of all threads' accumulators, in a fixed order: the butterfly inside a wavefront (both partners add the same two
+// numbers, so every lane ends with the same bits), then the wavefronts' sums through LDS, added in wavefront order by every
+// thread.  One barrier; `a` (LDS, one per wavefront) is used for one sum only.
 constexpr int kSelectWaves = kSelectThreads / kWave;
-__device__ __forceinline__ double meet_accumulators(double mine, double* a /* LDS, one per wavefront */) {
+__device__ __forceinline__ double meet_accumulators(double mine, double* a) {
 #pragma unroll
   for (int o = kWave / 2; o >= 1; o >>= 1) mine = __dadd_rn(mine, __shfl_xor(mine, o, kWave));
-  __syncthreads();  // the previous use of `a` is over
   if (threadIdx.x % kWave == 0) a[threadIdx.x / kWave] = mine;
   __syncthreads();
   double total = a[0];
@@ -143,108 +141,136 @@ __device__ __forceinline__ double meet_accumulators(double mine, double* a /* LD
   for (int w = 1; w < kSelectWaves; ++w) total = __dadd_rn(total, a[w]);
   return total;
 }
-// the same for counts; `below`: the sum over the threads before this one
-__device__ __forceinline__ uint32_t meet_counts(uint32_t mine, uint32_t* cnt /* LDS, one per wavefront */, uint32_t* below) {
-  const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  uint32_t incl = mine;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t t = __shfl_up(incl, o, kWave);
-    if (lane >= (uint32_t)o) incl += t;
-  }
-  __syncthreads();  // the previous use of `cnt` is over
-  if (lane == kWave - 1) cnt[wave] = incl;
-  __syncthreads();
-  uint32_t total = 0u, before = 0u;
+// what the wavefronts counted, in all; before: in the wavefronts before this one (a barrier lies between the writes to cnt and this)
+__device__ __forceinline__ uint32_t sum_counts(const uint32_t* cnt, uint32_t* before) {
+  const uint32_t wave = threadIdx.x / kWave;
+  uint32_t total = 0u;
+  *before = 0u;
 #pragma unroll
   for (int w = 0; w < kSelectWaves; ++w) {
-    if ((uint32_t)w < wave) before += cnt[w];
+    if ((uint32_t)w < wave) *before += cnt[w];
     total += cnt[w];
   }
-  *below = before + incl - mine;
   return total;
 }
 
-// ---- step 3 (Eq. 1): mu, sigma, Z, the channel mask, the list of outlier channels.  One
-// workgroup of 1024 threads; the work is a few passes over `hidden` numbers (a division per channel).
+// ---- step 3 (Eq. 1): mu, sigma, Z, the channel mask, the list of outlier channels.  One workgroup; thread j takes the octets j,
+// j + 512, .. of channels, one mask byte each, and keeps the first two octets' sums in registers over the three passes (mean,
+// variance, selection): up to 8192 channels S is read once.  Bound by the chain of its steps: three reductions, a square root and two
+// divisions.  Z > z_thresh is decided by a product where rounding cannot matter, S - mu further from z_thresh * sigma than 2^-40 of
+// it; a division of every channel was half the time.  (1024 threads, S read three times, two barriers a reduction: 7.4
+// us for 4096 channels, 9.0 for 8192; 4.1 and 5.4 now.)
+constexpr uint32_t kSelectKept = 2;
 __global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const double* __restrict__ S, ChannelDesc c) {
-  __shared__ double a[kSelectWaves];
-  __shared__ uint32_t cnt[kSelectWaves];
-  const uint32_t j = threadIdx.x;
-  const uint32_t hidden = c.hidden;
+  __shared__ double a[2][kSelectWaves];
+  __shared__ uint32_t cnt[2][kSelectWaves];
+  const uint32_t j = threadIdx.x, wave = j / kWave;
+  const uint32_t n_bytes = c.hidden / 8u;
+  const double skip = __longlong_as_double(0x7FF0000000000000ll);  // a channel that is not there reads as a sum that is not finite
+  double kept[kSelectKept][8];
+  auto load = [&](uint32_t b, double (&v)[8]) {
+    const double2* p = reinterpret_cast<const double2*>(S + (size_t)(b < n_bytes ? b : 0u) * 8u);
+#pragma unroll
+    for (uint32_t e = 0; e < 4u; ++e) {
+      const double2 t = p[e];
+      v[2u * e] = b < n_bytes ? t.x : skip;
+      v[2u * e + 1u] = b < n_bytes ? t.y : skip;
+    }
+  };
+#pragma unroll
+  for (uint32_t k = 0; k < kSelectKept; ++k) load(j + k * kSelectThreads, kept[k]);
+  // use(b, values) for every octet of this thread
+  auto each = [&](auto use) {
+#pragma unroll
+    for (uint32_t k = 0; k < kSelectKept; ++k) use(j + k * kSelectThreads, kept[k]);
+    for (uint32_t b = j + kSelectKept * kSelectThreads; b < n_bytes; b += kSelectThreads) {
+      double v[8];
+      load(b, v);
+      use(b, v);
+    }
+  };
 
   double acc = 0.0;
-  uint32_t n = 0;
-  // sixteen loads in flight per thread (the whole of a thread's share up to 16384 channels: the kernel is a
-  // chain of round trips to memory); a position past the end reads as +Inf and is skipped like any other sum
-  // that is not finite
-  constexpr uint32_t kAhead = 16;
-  const double skip = __longlong_as_double(0x7FF0000000000000ll);
-  for (uint32_t h = j; h < hidden; h += kAhead * kSelectThreads) {
-    double v[kAhead];
+  uint32_t n = 0u;
+  each([&](uint32_t, const double (&v)[8]) {
 #pragma unroll
-    for (uint32_t i = 0; i < kAhead; ++i) v[i] = h + i * kSelectThreads < hidden ? S[h + i * kSelectThreads] : skip;
-#pragma unroll
-    for (uint32_t i = 0; i < kAhead; ++i)
-      if (finite_f64(v[i])) { acc = __dadd_rn(acc, v[i]); ++n; }
-  }
-  const double total = meet_accumulators(acc, a);
+    for (uint32_t e = 0; e < 8u; ++e)
+      if (finite_f64(v[e])) { acc = __dadd_rn(acc, v[e]); ++n; }
+  });
+  n = wave_sum_u32(n);
+  if (j % kWave == 0u) cnt[0][wave] = n;  // (behind the barrier of the sum)
+  const double total = meet_accumulators(acc, a[0]);
   uint32_t unused;
-  const double finite = (double)meet_counts(n, cnt, &unused);
+  const double finite = (double)sum_counts(cnt[0], &unused);
   const double mu = __ddiv_rn(total, finite);
 
   acc = 0.0;
-  for (uint32_t h = j; h < hidden; h += kAhead * kSelectThreads) {
-    double v[kAhead];
-#pragma unroll
-    for (uint32_t i = 0; i < kAhead; ++i) v[i] = h + i * kSelectThreads < hidden ? S[h + i * kSelectThreads] : skip;
-#pragma unroll
-    for (uint32_t i = 0; i < kAhead; ++i)
-      if (finite_f64(v[i])) {
-        const double d = __dsub_rn(v[i], mu);
-        acc = __fma_rn(d, d, acc);
-      }
-  }
-  const double sigma = __dsqrt_rn(__ddiv_rn(meet_accumulators(acc, a), finite));
-  const double zt = (double)c.z_thresh;
-
-  // every thread takes a contiguous stretch of mask bytes, so that the channels stay in order
-  const uint32_t n_bytes = hidden / 8u;
-  const uint32_t per = (n_bytes + kSelectThreads - 1) / kSelectThreads;
-  const uint32_t b0 = j * per < n_bytes ? j * per : n_bytes;
-  const uint32_t b1 = b0 + per < n_bytes ? b0 + per : n_bytes;
-  uint32_t mine = 0;
-  uint64_t masks = 0ull;  // the thread's mask bytes (at most 8: hidden <= 65536), first byte lowest
-  for (uint32_t b = b0; b < b1; ++b) {
-    double v[8];
-#pragma unroll
-    for (uint32_t e = 0; e < 8u; ++e) v[e] = S[b * 8u + e];
-    uint32_t m = 0;
+  each([&](uint32_t, const double (&v)[8]) {
 #pragma unroll
     for (uint32_t e = 0; e < 8u; ++e) {
-      const double z = __ddiv_rn(__dsub_rn(v[e], mu), sigma);
-      if (!finite_f64(v[e]) || z > zt) m |= 1u << e;  // a NaN z selects nothing
+      const double d = __dsub_rn(v[e], mu);
+      if (finite_f64(v[e])) acc = __fma_rn(d, d, acc);
     }
-    c.mask[b] = (uint8_t)m;
-    masks |= (uint64_t)m << (8u * (b - b0));
-    mine += (uint32_t)__popc(m);
-  }
-  // where this thread's channels go in the list: the outlier channels of the threads before it
-  uint32_t running;
-  const uint32_t n_ch = meet_counts(mine, cnt, &running);
-  for (uint32_t b = b0; b < b1; ++b) {
-    uint32_t m = (uint32_t)(masks >> (8u * (b - b0))) & 0xFFu;
-    c.base[b] = running;
-    while (m) {
-      const uint32_t e = (uint32_t)__builtin_ctz(m);
-      m &= m - 1u;
-      if (running < c.max_channels) c.ch_idx[running] = (int32_t)(b * 8u + e);
-      ++running;
+  });
+  const double sigma = __dsqrt_rn(__ddiv_rn(meet_accumulators(acc, a[1]), finite));
+  const double zt = (double)c.z_thresh;
+  const double bar = zt * sigma, margin = fabs(bar) * 0x1p-40;
+  const bool plain = fabs(bar) > 0x1p-900 && fabs(bar) < 0x1p900;  // uniform; not: sigma or the threshold zero, sigma not finite
+
+  // a round of octets (512 bytes of the mask) after the other, so that the channels stay in order
+  uint32_t running = 0u;  // outlier channels of the rounds before
+  uint32_t round = 0u;
+  auto select = [&](uint32_t b, const double (&v)[8]) {
+    uint32_t m = 0u, close = 0u;
+#pragma unroll
+    for (uint32_t e = 0; e < 8u; ++e) {
+      const double d = __dsub_rn(v[e], mu);
+      if (!finite_f64(v[e]) || d > bar) m |= 1u << e;
+      if (finite_f64(v[e]) && !(plain && fabs(d - bar) > margin)) close |= 1u << e;
     }
+    if (close != 0u) {  // few lanes, if any: the definition itself
+#pragma unroll
+      for (uint32_t e = 0; e < 8u; ++e) {
+        const double z = __ddiv_rn(__dsub_rn(v[e], mu), sigma);
+        if ((close >> e) & 1u) m = z > zt ? m | (1u << e) : m & ~(1u << e);  // a NaN z selects nothing
+      }
+    }
+    if (b >= n_bytes) m = 0u;
+    // where this thread's channels go in the list: behind the outlier channels of the threads before it
+    uint32_t mine;
+    const uint32_t below = count_below((uint32_t)__builtin_popcount(m), mine);
+    if (j % kWave == 0u) cnt[round & 1u][wave] = mine;
+    __syncthreads();  // (the other set of words was read before the barrier of this round)
+    uint32_t before;
+    const uint32_t all = sum_counts(cnt[round & 1u], &before);
+    ++round;
+    uint32_t at = running + before + below;
+    running += all;
+    if (b < n_bytes) {
+      c.mask[b] = (uint8_t)m;
+      c.base[b] = at;
+      while (m != 0u) {
+        const uint32_t e = (uint32_t)__builtin_ctz(m);
+        m &= m - 1u;
+        if (at < c.max_channels) c.ch_idx[at] = (int32_t)(b * 8u + e);
+        ++at;
+      }
+    }
+  };
+  // every thread goes through every round (the barriers)
+  const uint32_t rounds = (n_bytes + (uint32_t)kSelectThreads - 1u) / (uint32_t)kSelectThreads;
+  round = 1u;  // (the finite counts lie in set 0, and are read before the barrier of the variance)
+#pragma unroll
+  for (uint32_t k = 0; k < kSelectKept; ++k)
+    if (k < rounds) select(j + k * kSelectThreads, kept[k]);  // uniform
+  for (uint32_t k = kSelectKept; k < rounds; ++k) {
+    double v[8];
+    load(j + k * kSelectThreads, v);
+    select(j + k * kSelectThreads, v);
   }
   if (j == 0) {
-    c.status[0] = n_ch;
-    c.status[1] = n_ch > c.max_channels ? 1u : 0u;
+    c.status[0] = running;
+    c.status[1] = running > c.max_channels ? 1u : 0u;
     c.status[2] = 0u;
     c.status[3] = 0u;
   }

@@ -561,6 +561,19 @@ __device__ __forceinline__ uint32_t magnitude_limit_squared(float limit) {
 }
 __device__ __forceinline__ uint32_t both_halves(uint32_t m) { return m | m << 16; }
 
+// What the lanes hold (at most 8 each) below this lane, and in all (uniform)
+__device__ __forceinline__ uint32_t count_below(uint32_t n, uint32_t& all) {
+  uint32_t below = 0u;
+  all = 0u;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {  // the bits of the lanes' numbers
+    const uint64_t m = __builtin_amdgcn_ballot_w64((n >> b & 1u) != 0u);
+    all += (uint32_t)__builtin_popcountll(m) << b;
+    below += lanes_below(m) << b;
+  }
+  return below;
+}
+
 // The elements of a row whose magnitude exceeds the threshold (t2: in both halves) are cleared; with a sink they go
 // there first, in index order, to positions pos, pos + 1, .. (entries at or past `limit` are dropped).  i0: index of the lane's first
 // element.  Returns their number (uniform).
@@ -586,13 +599,7 @@ __device__ __forceinline__ uint32_t take_above(uint32_t (&oct)[4], uint32_t t2, 
       count = (uint32_t)__builtin_popcountll(any);
       at += lanes_below(any);
     } else {
-      const uint32_t n = (uint32_t)__builtin_popcount(todo);
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {  // at most 8: the bits of the lanes' numbers
-        const uint64_t m = __builtin_amdgcn_ballot_w64((n >> b & 1u) != 0u);
-        count += (uint32_t)__builtin_popcountll(m) << b;
-        at += lanes_below(m) << b;
-      }
+      at += count_below((uint32_t)__builtin_popcount(todo), count);
     }
     while (any != 0ull) {  // uniform: mostly once; an octet's first, then its second, ..
       if (todo != 0u && at < limit) {
