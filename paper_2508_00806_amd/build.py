@@ -10,9 +10,9 @@ CSRC = os.path.join(HERE, "csrc")
 # one translation unit per group of kernel instantiations, so that the library builds in parallel
 # Sources that touch the tensor's elements are compiled once per 16-bit format (bf16; binary16 with -DADACC_F16=1).
 PER_FORMAT = (
+    "adacc_k_batch4.hip", "adacc_k_batch8.hip",
     "adacc_k_none.hip", "adacc_k_abs.hip", "adacc_k_std.hip", "adacc_k_topk.hip",  # compress, per outlier mode
     "adacc_k_decompress.hip",
-    "adacc_k_batch4.hip", "adacc_k_batch8.hip",
     "adacc_k_place.hip",      # placement of the outliers in the stream, the end of a tensor that the groups do not divide
     "adacc_k_generic.hip",    # fallback for group sizes that are no powers of two or exceed 4096
     "adacc_k_long.hip",       # groups of more than half a segment of those, a wavefront each
@@ -24,8 +24,7 @@ ONCE = (
     "adacc_k_mask.hip",       # dropout mask, byte <-> bit
 )
 # (source, object suffix, extra flags); the long ones first
-SOURCES = ([(os.path.join(CSRC, f), "", ()) for f in PER_FORMAT] +
-           [(os.path.join(CSRC, f), "_f16", ("-DADACC_F16=1",)) for f in PER_FORMAT] +
+SOURCES = ([(os.path.join(CSRC, f), suffix, flags) for f in PER_FORMAT for suffix, flags in (("", ()), ("_f16", ("-DADACC_F16=1",)))] +
            [(os.path.join(CSRC, f), "", ()) for f in ONCE])
 HEADERS = [os.path.join(CSRC, f) for f in ("adacc_common.hpp", "adacc_dtype.hpp", "adacc_compress.hpp",
                                            "adacc_decompress.hpp", "adacc_kernels.hpp", "adacc_fn.hpp",

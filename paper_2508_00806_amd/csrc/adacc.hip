@@ -134,7 +134,7 @@ struct Plan {  // everything derived from (method, numel)
 // rows 13.2 11.3 / 16.9 15.4 / 19.1 19.6 / 26.2 24.7; 3072 rows 16.9 12.7 / 21.3 17.9 / 24.4 23.2 / 33.2 29.5.)
 constexpr uint64_t kLongGroups = 3072;
 static CompressFn long_fn(const adacc_method* m, const Plan& p) {
-  return ADACC_PICK(p.half, compress_long_fn(p.tile_elems, m->outlier_mode, m->bits, m->asym));
+  return ADACC_PICK(p.half, compress_long_fn(p.tile_elems, m->outlier_mode, m->topk, m->bits, m->asym));
 }
 
 constexpr uint32_t kGenericMaxGroup = 16384;  // the longest segment of the fallback kernels

@@ -799,6 +799,13 @@ __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t,
                             __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
 }
+__device__ __forceinline__ uint32_t pk_add_u16(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2_t, a) + __builtin_bit_cast(u16x2_t, b));
+}
+__device__ __forceinline__ uint32_t pk_sub_sat_u16(uint32_t a, uint32_t b) {  // 0 where b is larger
+  return __builtin_bit_cast(uint32_t,
+                            __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
+}
 template <int E>
 struct RowMags {
   uint32_t pm[E / 2];
@@ -938,6 +945,45 @@ struct TopkList {
   uint4 oct[16];
   uint32_t where[16];  // the octet's first element, in the tile
 };
+// The selection from the list of a wavefront: the k outliers leave for entries pos0 .. of the sink, and are zeroed in the list
+// (CLEAR).  CHECK: false (uniform), nothing done, where the k-th is not finite, since there may be more of those.
+template <bool CLEAR, bool CHECK, class Sink>
+__device__ __forceinline__ bool topk_take_from_list(TopkList& list, uint32_t octets, uint32_t k, uint32_t t16, uint32_t first,
+                                                    const Sink& sink, uint32_t pos0, uint32_t limit) {
+  const uint32_t lane = (uint32_t)lane_id();
+  uint16_t* elem = reinterpret_cast<uint16_t*>(list.oct);
+  // elements `lane` and 64 + `lane` of the list (-1: not there)
+  const uint32_t pa = elem[lane], pb = elem[kWave + lane];
+  const int32_t ma = lane < octets * kOct ? (int32_t)(pa & 0x7FFFu) : -1;
+  const int32_t mb = lane + kWave < octets * kOct ? (int32_t)(pb & 0x7FFFu) : -1;
+  uint64_t hit_a = __builtin_amdgcn_ballot_w64(ma >= (int32_t)t16), hit_b = __builtin_amdgcn_ballot_w64(mb >= (int32_t)t16);
+  if ((uint32_t)(__builtin_popcountll(hit_a) + __builtin_popcountll(hit_b)) != k) {  // uniform
+    const int32_t t = (int32_t)kth_by_halving(k, [&](uint32_t c) { return lanes_where(ma >= (int32_t)c) + lanes_where(mb >= (int32_t)c); });
+    if constexpr (CHECK) {
+      if (t >= (int32_t)kNonfiniteMag) return false;  // uniform
+    }
+    hit_a = __builtin_amdgcn_ballot_w64(ma > t);
+    hit_b = __builtin_amdgcn_ballot_w64(mb > t);
+    uint64_t eq_a = __builtin_amdgcn_ballot_w64(ma == t), eq_b = __builtin_amdgcn_ballot_w64(mb == t);
+    for (uint32_t n = (uint32_t)(__builtin_popcountll(hit_a) + __builtin_popcountll(hit_b)); n < k; ++n) {  // k <= 8 rounds
+      if (eq_a != 0ull) { hit_a |= eq_a & (0ull - eq_a); eq_a &= eq_a - 1ull; }
+      else { hit_b |= eq_b & (0ull - eq_b); eq_b &= eq_b - 1ull; }
+    }
+  }
+  if (__builtin_amdgcn_inverse_ballot_w64(hit_a)) {
+    const uint32_t pos = pos0 + lanes_below(hit_a);
+    if (pos < limit) sink(pos, first + list.where[lane >> 3] + (lane & 7u), pa);
+    if constexpr (CLEAR) elem[lane] = 0;
+  }
+  if (hit_b != 0ull) {  // uniform
+    if (__builtin_amdgcn_inverse_ballot_w64(hit_b)) {
+      const uint32_t pos = pos0 + (uint32_t)__builtin_popcountll(hit_a) + lanes_below(hit_b);
+      if (pos < limit) sink(pos, first + list.where[8u + (lane >> 3)] + (lane & 7u), pb);
+      if constexpr (CLEAR) elem[kWave + lane] = 0;
+    }
+  }
+  return true;
+}
 template <int E, bool STORE, class Sink>
 __device__ __forceinline__ uint32_t topk_extract(uint32_t k, uint32_t (&raw)[E][4], RowMags<E>& rowmag,
                                                  uint32_t first, const Sink& sink, uint32_t pos0, uint32_t limit) {
@@ -955,7 +1001,6 @@ __device__ __forceinline__ uint32_t topk_extract(uint32_t k, uint32_t (&raw)[E][
     }
     if (octets <= 16u) {  // uniform (a constant tile, where every octet passes, is done by keys)
       TopkList& list = lists[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];
-      uint16_t* elem = reinterpret_cast<uint16_t*>(list.oct);
       uint32_t before = 0u;  // uniform
 #pragma unroll
       for (int j = 0; j < E; ++j) {
@@ -968,33 +1013,7 @@ __device__ __forceinline__ uint32_t topk_extract(uint32_t k, uint32_t (&raw)[E][
         before += (uint32_t)__builtin_popcountll(cand[j]);
       }
       lds_in_order();
-      // elements `lane` and 64 + `lane` of the list (-1: not there)
-      const uint32_t pa = elem[lane], pb = elem[kWave + lane];
-      const int32_t ma = lane < octets * kOct ? (int32_t)(pa & 0x7FFFu) : -1;
-      const int32_t mb = lane + kWave < octets * kOct ? (int32_t)(pb & 0x7FFFu) : -1;
-      uint64_t hit_a = __builtin_amdgcn_ballot_w64(ma >= (int32_t)t16), hit_b = __builtin_amdgcn_ballot_w64(mb >= (int32_t)t16);
-      if ((uint32_t)(__builtin_popcountll(hit_a) + __builtin_popcountll(hit_b)) != k) {  // uniform
-        const int32_t t = (int32_t)kth_by_halving(k, [&](uint32_t c) { return lanes_where(ma >= (int32_t)c) + lanes_where(mb >= (int32_t)c); });
-        hit_a = __builtin_amdgcn_ballot_w64(ma > t);
-        hit_b = __builtin_amdgcn_ballot_w64(mb > t);
-        uint64_t eq_a = __builtin_amdgcn_ballot_w64(ma == t), eq_b = __builtin_amdgcn_ballot_w64(mb == t);
-        for (uint32_t n = (uint32_t)(__builtin_popcountll(hit_a) + __builtin_popcountll(hit_b)); n < k; ++n) {  // k <= 8 rounds
-          if (eq_a != 0ull) { hit_a |= eq_a & (0ull - eq_a); eq_a &= eq_a - 1ull; }
-          else { hit_b |= eq_b & (0ull - eq_b); eq_b &= eq_b - 1ull; }
-        }
-      }
-      if (__builtin_amdgcn_inverse_ballot_w64(hit_a)) {
-        const uint32_t pos = pos0 + lanes_below(hit_a);
-        if (pos < limit) sink(pos, first + list.where[lane >> 3] + (lane & 7u), pa);
-        if constexpr (STORE) elem[lane] = 0;
-      }
-      if (hit_b != 0ull) {  // uniform
-        if (__builtin_amdgcn_inverse_ballot_w64(hit_b)) {
-          const uint32_t pos = pos0 + (uint32_t)__builtin_popcountll(hit_a) + lanes_below(hit_b);
-          if (pos < limit) sink(pos, first + list.where[8u + (lane >> 3)] + (lane & 7u), pb);
-          if constexpr (STORE) elem[kWave + lane] = 0;
-        }
-      }
+      topk_take_from_list<STORE, false>(list, octets, k, t16, first, sink, pos0, limit);
       if constexpr (STORE) {
         lds_in_order();
         before = 0u;

@@ -55,7 +55,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   PlaceSumBatchFn place_sum_batch_fn();                                                \
   PlaceBatchFn place_batch_fn();                                                       \
   CompressFn compress_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs);     \
-  CompressFn compress_long_fn(uint32_t tile_elems, uint32_t mode, uint32_t bits, uint32_t asym); \
+  CompressFn compress_long_fn(uint32_t tile_elems, uint32_t mode, uint32_t topk, uint32_t bits, uint32_t asym); \
   CompressFn place_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs);        \
   uint32_t generic_threads();                                                          \
   uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups);      \

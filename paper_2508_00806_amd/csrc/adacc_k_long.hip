@@ -10,11 +10,16 @@ static CompressFn pick(uint32_t bits, uint32_t asym) {
   if (bits == 4) return asym ? compress_long_kernel<E, TOPK, 4, true> : compress_long_kernel<E, TOPK, 4, false>;
   return asym ? compress_long_kernel<E, TOPK, 8, true> : compress_long_kernel<E, TOPK, 8, false>;
 }
-CompressFn compress_long_fn(uint32_t tile_elems, uint32_t mode, uint32_t bits, uint32_t asym) {
+CompressFn compress_long_fn(uint32_t tile_elems, uint32_t mode, uint32_t topk, uint32_t bits, uint32_t asym) {
   const uint32_t rows = (tile_elems + (uint32_t)kRow - 1u) / (uint32_t)kRow;
   // (nothing to select: [6144, 4000] 14.2 us by workgroups, 14.7 by wavefronts; [6144, 2200] 11.9 and 9.5)
   if (mode == kModeNone && rows > 6u) return nullptr;
   if (rows <= 8u) return mode == kModeTopk ? pick<8, true>(bits, asym) : pick<8, false>(bits, asym);
+  // (TOPK: more than 8 of the largest would all take the way that reads the group again)
+  if (mode == kModeTopk) {
+    if (topk > 8u || rows > 22u) return nullptr;
+    return rows <= 12u ? pick<12, true>(bits, asym) : rows <= 16u ? pick<16, true>(bits, asym) : pick<22, true>(bits, asym);
+  }
   // (ABS: [16000, 4104] 55.0 -> 44.3, [12000, 5160] 46.8 -> 42.2; [8000, 8192] 41.4 and 44.6, [8192, 11008] 61.9 and 59.7)
   if (mode != kModeStd && !(mode == kModeAbs && rows <= 12u)) return nullptr;
   if (rows <= 12u) return pick<12, false>(bits, asym);
