@@ -386,13 +386,14 @@ __global__ __launch_bounds__(kThreads) void channel_compress_kernel(TensorDesc d
 // loads of the strip are issued first; its rows are then encoded four at a time like a tile's.
 // (Eight tokens to a wavefront, two times four: [8192, 4096] int4 18.9 us, restored in 20.0; four: 16.7 and 18.1;
 // [2192, 5120] asymmetric, restored: 10.9 -> 8.6.)
+// The values are asked for together with the status, the mask and the ranks, in both directions, one round trip to memory instead of
+// three in a row; a wavefront lives for little more.  ([8192, 4096] int4, compressed and restored: 56.2 -> 54.9 us.)
 constexpr uint32_t kChannelStripRows = 4;
 
 template <int BITS, bool ASYM>
 __global__ __launch_bounds__(kThreads) void channel_compress_strip_kernel(TensorDesc d, ChannelDesc c) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (c.status[1] != 0u) return;  // more outlier channels than the blob holds: nothing else is produced
-  const uint32_t n_ch = __builtin_amdgcn_readfirstlane(c.status[0]);
+  const uint32_t found = c.status[0], over = c.status[1];
   const uint32_t strips = c.hidden / (uint32_t)kRow;
   const uint32_t unit = blockIdx.x * kWavesPerWg + wave;
   const uint32_t block = unit / strips;
@@ -402,11 +403,8 @@ __global__ __launch_bounds__(kThreads) void channel_compress_strip_kernel(Tensor
   const uint32_t rows = c.tokens - row0 < kChannelStripRows ? c.tokens - row0 : kChannelStripRows;
   const uint32_t lane_off = (uint32_t)lane_id() * kOct;
 
-  uint32_t m = 0u, first = 0u;
-  if (n_ch != 0u) {
-    m = c.mask[(col0 + lane_off) >> 3];
-    first = c.base[(col0 + lane_off) >> 3];
-  }
+  // everything that is read is asked for at once: the status decides what is done with it, not whether it is read
+  const uint32_t m = c.mask[(col0 + lane_off) >> 3], first = c.base[(col0 + lane_off) >> 3];
   const uint64_t base = (uint64_t)row0 * c.hidden + col0;  // uniform
   const uint16_t* sp = d.src + base;
   uint32_t raw[kChannelStripRows][4];
@@ -416,6 +414,9 @@ __global__ __launch_bounds__(kThreads) void channel_compress_strip_kernel(Tensor
     const uint4 v = ADACC_LOAD16(sp + (row * c.hidden + lane_off));
     raw[i][0] = v.x; raw[i][1] = v.y; raw[i][2] = v.z; raw[i][3] = v.w;
   }
+  asm volatile("" ::: "memory");  // (the loads stay ahead of the return)
+  if (__builtin_amdgcn_readfirstlane(over) != 0u) return;  // more outlier channels than the blob holds: nothing else is produced
+  const uint32_t n_ch = __builtin_amdgcn_readfirstlane(found);
   if (m != 0u) {  // the kept channels go out first, then they are cleared
     uint16_t* dst = c.ch_val + (size_t)row0 * n_ch + first;
     static_for<(int)kChannelStripRows>([&](auto Ic) {  // the data-dependent loop inside must not keep this one rolled
@@ -467,9 +468,7 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
   constexpr int V = chunk_elems<F32>();
   constexpr uint32_t W = (uint32_t)(kWave * V);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  if (c.status[1] != 0u) return;  // not a usable blob
-  uint32_t n_ch = __builtin_amdgcn_readfirstlane(c.status[0]);
-  if (n_ch > c.max_channels) n_ch = c.max_channels;  // a damaged blob must not make the reads leave it
+  const uint32_t found = c.status[0], over = c.status[1];
   const uint32_t strips = (c.hidden + W - 1u) / W;
   const uint32_t unit = blockIdx.x * kWavesPerWg + wave;
   const uint32_t block = unit / strips;
@@ -478,24 +477,11 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
   if (row0 >= c.tokens || col >= c.hidden) return;
   const uint32_t rows = c.tokens - row0 < kChannelStripRows ? c.tokens - row0 : kChannelStripRows;
 
-  // the lane's channels: which are outlier channels, and the rank of the first of them
-  uint32_t m = 0u, first = 0u;
-  if (n_ch != 0u) {
-    m = c.mask[col >> 3];
-    first = c.base[col >> 3];
-    if constexpr (V == 4) {  // the octet's lower or upper half
-      first += (col & 4u) ? (uint32_t)__popc(m & 0xFu) : 0u;
-      m = (col & 4u) ? m >> 4 : m & 0xFu;
-    }
-    if (first >= n_ch) m = 0u;  // a damaged blob must not be read past its end
-  }
-  const uint32_t lowest = m & (0u - m);
-  const uint32_t rest = m ^ lowest;
-
+  // Everything but the kept values is asked for at once: the status decides what is done with it, not whether it is read.
+  // The lane's channels: which are outlier channels, and the rank of the first of them.
+  uint32_t m = c.mask[col >> 3], first = c.base[col >> 3];
   uint32_t cw[kChannelStripRows][V * BITS > 32 ? 2 : 1];
   float sc[kChannelStripRows], zp[kChannelStripRows];
-  uint32_t pre[kChannelStripRows];
-  const uint16_t* src[kChannelStripRows];
 #pragma unroll
   for (uint32_t i = 0; i < kChannelStripRows; ++i) {  // rows past the end re-read the last one
     const uint32_t row = row0 + (i < rows ? i : rows - 1u);
@@ -513,7 +499,23 @@ __global__ __launch_bounds__(kThreads) void channel_decompress_kernel(TensorDesc
     sc[i] = d.scales[grp];
     zp[i] = 0.0f;
     if constexpr (ASYM) zp[i] = d.zp[grp];
-    src[i] = c.ch_val + (size_t)row * n_ch + first;
+  }
+  asm volatile("" ::: "memory");  // (the loads stay ahead of the return)
+  if (__builtin_amdgcn_readfirstlane(over) != 0u) return;  // not a usable blob
+  uint32_t n_ch = __builtin_amdgcn_readfirstlane(found);
+  if (n_ch > c.max_channels) n_ch = c.max_channels;  // a damaged blob must not make the reads leave it
+  if constexpr (V == 4) {  // the octet's lower or upper half
+    first += (col & 4u) ? (uint32_t)__popc(m & 0xFu) : 0u;
+    m = (col & 4u) ? m >> 4 : m & 0xFu;
+  }
+  if (first >= n_ch) m = 0u;  // no outlier channels, or a damaged blob, which must not be read past its end
+  const uint32_t lowest = m & (0u - m);
+  const uint32_t rest = m ^ lowest;
+  uint32_t pre[kChannelStripRows];
+  const uint16_t* src[kChannelStripRows];
+#pragma unroll
+  for (uint32_t i = 0; i < kChannelStripRows; ++i) {
+    src[i] = c.ch_val + (size_t)(row0 + (i < rows ? i : rows - 1u)) * n_ch + first;
     pre[i] = m != 0u ? (uint32_t)src[i][0] : 0u;
   }
 #pragma unroll
