@@ -28,10 +28,12 @@ __device__ __forceinline__ uint32_t finite_magnitudes2(uint32_t w) {
 // with all its loads in flight at once; the wavefronts' maxima meet in LDS.
 template <bool STREAM>
 __global__ __launch_bounds__(kPartialWaves * kWave) void channelwise_partial_kernel(ChannelwiseDesc c, uint32_t strips) {
-  __shared__ uint32_t meet[kPartialWaves - 1][4][kWave];
+  constexpr uint32_t kRoom = kWave + 16;  // (the threads of a maximum read 4 words of 16 lanes from banks of their own)
+  __shared__ uint32_t meet[kPartialWaves][4 * kRoom];
   const uint32_t wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const uint32_t chunk = blockIdx.x / strips;
-  const uint32_t oct = (blockIdx.x - chunk * strips) * kWave + lane;
+  const uint32_t strip = blockIdx.x - chunk * strips;
+  const uint32_t oct = strip * kWave + lane;
   const bool live = oct < c.hidden / kOct;
   const uint32_t t0 = chunk * kChunkTokens + wave * kPartialRows;
   const uint32_t rows = t0 >= c.tokens ? 0u : (c.tokens - t0 < kPartialRows ? c.tokens - t0 : kPartialRows);
@@ -50,19 +52,16 @@ __global__ __launch_bounds__(kPartialWaves * kWave) void channelwise_partial_ker
     acc[2] = pk_max_u16(acc[2], finite_magnitudes2(v[i].z));
     acc[3] = pk_max_u16(acc[3], finite_magnitudes2(v[i].w));
   }
-  if (wave != 0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) meet[wave - 1][k][lane] = acc[k];
-  }
+  for (uint32_t k = 0; k < 4u; ++k) meet[wave][k * kRoom + lane] = acc[k];
   __syncthreads();
-  if (wave == 0 && live) {
+  const uint32_t pair = threadIdx.x;  // two channels of the strip
+  if (pair < (uint32_t)kRow / 2u && strip * (uint32_t)kRow + 2u * pair < c.hidden) {
+    const uint32_t at = (pair % 4u) * kRoom + pair / 4u;
+    uint32_t most = meet[0][at];
 #pragma unroll
-    for (uint32_t w = 0; w + 1 < kPartialWaves; ++w) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) acc[k] = pk_max_u16(acc[k], meet[w][k][lane]);
-    }
-    *reinterpret_cast<uint4*>(c.partial + (size_t)chunk * c.hidden + (size_t)oct * kOct) =
-        make_uint4(acc[0], acc[1], acc[2], acc[3]);
+    for (uint32_t w = 1; w < kPartialWaves; ++w) most = pk_max_u16(most, meet[w][at]);
+    *reinterpret_cast<uint32_t*>(c.partial + (size_t)chunk * c.hidden + strip * (uint32_t)kRow + 2u * pair) = most;
   }
 }
 
