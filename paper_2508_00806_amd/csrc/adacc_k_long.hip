@@ -14,12 +14,13 @@ CompressFn compress_long_fn(uint32_t tile_elems, uint32_t mode, uint32_t topk, u
   const uint32_t rows = (tile_elems + (uint32_t)kRow - 1u) / (uint32_t)kRow;
   // (nothing to select: [6144, 4000] 14.2 us by workgroups, 14.7 by wavefronts; [6144, 2200] 11.9 and 9.5)
   if (mode == kModeNone && rows > 6u) return nullptr;
-  if (rows <= 8u) return mode == kModeTopk ? pick<8, true>(bits, asym) : pick<8, false>(bits, asym);
-  // (TOPK: more than 8 of the largest would all take the way that reads the group again)
+  // (TOPK: more than 8 of the largest take rounds over all elements here, over the octets' largest there; us by workgroups and by
+  // wavefronts, k = 9 / 16 / 32: [3072, 2200] 23.0 / 29.7 / 46.4 and 33.7 / 49.7 / 85.8, [8192, 4000] 53.4 / 70.4 / 113 and 76.1 / 117 / 209)
   if (mode == kModeTopk) {
     if (topk > 8u || rows > 22u) return nullptr;
-    return rows <= 12u ? pick<12, true>(bits, asym) : rows <= 16u ? pick<16, true>(bits, asym) : pick<22, true>(bits, asym);
+    return rows <= 8u ? pick<8, true>(bits, asym) : rows <= 12u ? pick<12, true>(bits, asym) : rows <= 16u ? pick<16, true>(bits, asym) : pick<22, true>(bits, asym);
   }
+  if (rows <= 8u) return pick<8, false>(bits, asym);
   // (ABS: [16000, 4104] 55.0 -> 44.3, [12000, 5160] 46.8 -> 42.2; [8000, 8192] 41.4 and 44.6, [8192, 11008] 61.9 and 59.7)
   if (mode != kModeStd && !(mode == kModeAbs && rows <= 12u)) return nullptr;
   if (rows <= 12u) return pick<12, false>(bits, asym);
