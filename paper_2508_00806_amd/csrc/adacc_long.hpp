@@ -108,31 +108,80 @@ __device__ __forceinline__ uint32_t long_std_threshold(const TensorDesc& d, cons
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)magnitude_limit_squared(d.param * var));  // param = k * k
 }
 
-// TOPK, k <= 8, groups of more than 8 rows: topk_extract's way over the list, what it keeps for every row (the candidates' ballots)
-// formed again where it is used.  Returns false (uniform), nothing done, for a group that the list does not take: more than
-// 16 octets that reach the bound t16, a constant or an empty row for one, or as many values that are not finite as k, or more.
 template <int E>
 __device__ __forceinline__ void forget_unpacked(RowMags<E>& mags) {  // as forget_derived: at(j) of all rows is not kept
 #pragma unroll
   for (int i = 0; i < E / 2; ++i) asm volatile("" : "+v"(mags.pm[i]));
 }
+
+// TOPK, k <= 8: which octets the list has to take when more than its 16 reach the bound t16, which coarse values, clipped ones,
+// constant and empty rows do.  t16 goes up, by halving over the octets' largest magnitudes, until at most 16 octets
+// reach it and k still do, and those are the list as they would be.  If there is no such magnitude, t16 is the largest that k octets reach,
+// fewer than k are larger, and equals of t16 are chosen by index: the first 8 octets among those whose largest is t16 hold all that can be
+// chosen.  Then mags is 1 where an octet goes to the list and 0 elsewhere.  Returns the number of octets (uniform); marked: mags is
+// that.  No value is looked at but in the list, and nothing is read again.  (us, k = 8, int4 in groups of 128, by workgroups, by a
+// wavefront that found the k-th magnitude by halving over all elements, read again for it, and like this: values rounded to
+// quarters [3072, 8192] 22.3 / 37.9 / 22.3, [8192, 11008] 65.6 / 75.4 / 52.5; three bits of significand [8192, 11008] 67.5 / 108 / 56.2;
+// clipped [8192, 2560] 45.2 / 68.7 / 19.5.)
+template <int E>
+__device__ __forceinline__ uint32_t long_topk_narrow(uint32_t k, uint32_t octets, RowMags<E>& mags, uint32_t& t16, bool& marked) {
+  uint32_t most = 0u;
+#pragma unroll
+  for (int j = 0; j < E; ++j) most = mags.at(j) > most ? mags.at(j) : most;
+  uint32_t beyond = wave_max_u32_scalar(most) + 1u;
+#pragma unroll 1
+  while (octets > 16u && beyond - t16 > 1u) {  // uniform
+    const uint32_t c = t16 + (beyond - t16) / 2u;
+    uint32_t n = 0u;
+    forget_unpacked(mags);
+#pragma unroll
+    for (int j = 0; j < E; ++j) n += lanes_where(mags.at(j) >= c);
+    if (n >= k) {
+      t16 = c;
+      octets = n;
+    } else {
+      beyond = c;
+    }
+  }
+  marked = octets > 16u;
+  if (!marked) return octets;
+  octets = 0u;
+  uint32_t equals = 0u;
+  forget_unpacked(mags);
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    __builtin_amdgcn_sched_barrier(0);
+    const uint64_t same = __builtin_amdgcn_ballot_w64(mags.at(j) == t16);
+    const bool take = mags.at(j) > t16 || (mags.at(j) == t16 && equals + lanes_below(same) < 8u);
+    equals += (uint32_t)__builtin_popcountll(same);
+    octets += lanes_where(take);
+    mags.set(j, take ? 1u : 0u);
+  }
+  return octets;
+}
+
+// TOPK, k <= 8: topk_extract's way over the list, for any group; what that keeps for every row (the candidates' ballots) is
+// formed again where it is used.  Returns false (uniform), raw and mags as they were, if k values are not finite, or more.
 template <int E, class Sink>
-__device__ __forceinline__ bool long_topk_by_list(uint32_t k, uint32_t (&raw)[E][4], RowMags<E>& mags, uint32_t& t16, uint32_t first,
+__device__ __forceinline__ bool long_topk_by_list(uint32_t k, uint32_t (&raw)[E][4], RowMags<E>& mags, uint32_t first,
                                                   const Sink& sink, uint32_t pos0, uint32_t limit) {
   __shared__ TopkList lists[kWavesPerWg];
   mags.of(raw);
-  topk_whole_threshold<E>(k, mags, t16);  // a bound: k elements reach it
+  uint32_t t16;
+  topk_whole_threshold<E>(k, mags, t16);  // a bound: k octets reach it
   uint32_t octets = 0u;
 #pragma unroll
   for (int j = 0; j < E; ++j) octets += lanes_where(mags.at(j) >= t16);
-  if (octets > 16u || t16 >= kNonfiniteMag) return false;  // uniform
+  bool marked = false;
+  if (octets > 16u) octets = long_topk_narrow<E>(k, octets, mags, t16, marked);  // uniform
+  const uint32_t reach = marked ? 1u : t16;
   TopkList& list = lists[__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)];
   uint32_t before = 0u;  // uniform
   forget_unpacked(mags);
 #pragma unroll
   for (int j = 0; j < E; ++j) {
     __builtin_amdgcn_sched_barrier(0);
-    const uint64_t cand = __builtin_amdgcn_ballot_w64(mags.at(j) >= t16);
+    const uint64_t cand = __builtin_amdgcn_ballot_w64(mags.at(j) >= reach);
     if (cand == 0ull) continue;  // uniform
     if (__builtin_amdgcn_inverse_ballot_w64(cand)) {
       const uint32_t c = before + lanes_below(cand);
@@ -142,150 +191,41 @@ __device__ __forceinline__ bool long_topk_by_list(uint32_t k, uint32_t (&raw)[E]
     before += (uint32_t)__builtin_popcountll(cand);
   }
   lds_in_order();
-  if (!topk_take_from_list<true, true>(list, octets, k, t16, first, sink, pos0, limit)) return false;
-  lds_in_order();
-  forget_unpacked(mags);
-  before = 0u;
+  const bool taken = topk_take_from_list<true, true>(list, octets, k, t16, first, sink, pos0, limit);
+  if (taken) {  // uniform
+    lds_in_order();
+    forget_unpacked(mags);
+    before = 0u;
 #pragma unroll
-  for (int j = 0; j < E; ++j) {
-    __builtin_amdgcn_sched_barrier(0);
-    const uint64_t cand = __builtin_amdgcn_ballot_w64(mags.at(j) >= t16);
-    if (cand == 0ull) continue;  // uniform
-    if (__builtin_amdgcn_inverse_ballot_w64(cand)) {
-      const uint4 v = list.oct[before + lanes_below(cand)];
-      raw[j][0] = v.x; raw[j][1] = v.y; raw[j][2] = v.z; raw[j][3] = v.w;
-      mags.set(j, octet_magnitude(raw[j]));
+    for (int j = 0; j < E; ++j) {
+      __builtin_amdgcn_sched_barrier(0);
+      const uint64_t cand = __builtin_amdgcn_ballot_w64(mags.at(j) >= reach);
+      if (cand == 0ull) continue;  // uniform
+      if (__builtin_amdgcn_inverse_ballot_w64(cand)) {
+        const uint4 v = list.oct[before + lanes_below(cand)];
+        raw[j][0] = v.x; raw[j][1] = v.y; raw[j][2] = v.z; raw[j][3] = v.w;
+        mags.set(j, octet_magnitude(raw[j]));
+      }
+      before += (uint32_t)__builtin_popcountll(cand);
     }
-    before += (uint32_t)__builtin_popcountll(cand);
   }
-  return true;
+  if (marked) mags.of(raw);  // uniform
+  return taken;
 }
 
-// two counts to a word: += the octet's elements whose magnitude is c or more; below: c - 1 in both halves
-__device__ __forceinline__ void count_from(const uint32_t (&oct)[4], uint32_t below, uint32_t& n) {
-#pragma unroll
-  for (int w = 0; w < 4; ++w) n = pk_add_u16(n, pk_min_u16(pk_sub_sat_u16(oct[w] & 0x7FFF7FFFu, below), 0x00010001u));
-}
-__device__ __forceinline__ uint32_t count_in_all(uint32_t n) {
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_sum_u32((n & 0xFFFFu) + (n >> 16)));
-}
-
-// The groups that the list does not take, by the k-th largest magnitude itself, found by halving over all elements between
-// the bound t16 and the largest: what is larger leaves, and of its equals the first ones.  Reads the group again, a few rows at
-// a time: no way over the rows in registers fits beside 22 of them without spills, which the usual groups pay for too.  ([8192, 11008],
-// k = 8, every row like that, us by workgroups and here: constant 94.9 and 82.0, 220 equals below one larger 94.9 and 81.8, values rounded
-// to quarters 67.7 and 81.1, nine Inf in every row, with the placement that writes all of it again, 144 and 166.)
-// raw and mags are what is left.  Returns the number of outliers (uniform).
+// What exceeds a threshold (t, uniform) leaves, row by row, and is cleared; mags follows.  Returns the number (uniform).
 template <int E, class Sink>
-__device__ __forceinline__ uint32_t long_topk_by_halving(const TensorDesc& d, LongGeo g, uint32_t k, uint32_t t16, uint32_t (&raw)[E][4],
-                                                         RowMags<E>& mags, const Sink& sink, uint32_t pos0, uint32_t limit) {
-  // How many lie above the bound, from the registers: as a rule where so many equal the bound, it is the k-th largest.
-  uint32_t larger = 0u;
-  forget_derived<E>(raw);
+__device__ __forceinline__ uint32_t long_take_above(uint32_t t, uint32_t (&raw)[E][4], RowMags<E>& mags, uint32_t first,
+                                                    const Sink& sink, uint32_t pos0, uint32_t limit) {
+  const uint32_t t2 = both_halves(t);
+  uint32_t total = 0u;
 #pragma unroll
   for (int j = 0; j < E; ++j) {
     __builtin_amdgcn_sched_barrier(0);
-    count_from(raw[j], both_halves(t16), larger);
+    if (__builtin_amdgcn_ballot_w64(mags.at(j) > t) == 0ull) continue;  // uniform
+    total += take_above(raw[j], t2, first + lane_offset() + (uint32_t)(j * kRow), sink, pos0 + total, limit);
+    mags.set(j, octet_magnitude(raw[j]));
   }
-  larger = count_in_all(larger);
-  asm volatile("" : "+s"(g.cnt), "+s"(g.first));  // (what the rows' loads formed from it would be kept for the second ones)
-  const uint32_t lane_off = lane_offset();
-  uint32_t most = 0u;
-#pragma unroll
-  for (int j = 0; j < E; ++j) most = mags.at(j) > most ? mags.at(j) : most;
-  most = wave_max_u32_scalar(most);
-  auto octet = [&](uint32_t at, uint32_t (&oct)[4]) {  // the lane's octet of the row that begins at element `at`; zeros behind the end
-    const uint32_t o = at + lane_off;
-    const uint4 v = *reinterpret_cast<const uint4*>(d.src + g.first + (o < g.cnt ? o : 0u));
-    const bool there = o < g.cnt;
-    oct[0] = there ? v.x : 0u; oct[1] = there ? v.y : 0u; oct[2] = there ? v.z : 0u; oct[3] = there ? v.w : 0u;
-  };
-  auto reach = [&](uint32_t c) {  // elements whose magnitude is c or more (c >= 1)
-    const uint32_t below = both_halves(c - 1u);
-    uint32_t n = 0u;
-#pragma unroll 8
-    for (uint32_t at = 0u; at < (uint32_t)(E * kRow); at += (uint32_t)kRow) {
-      uint32_t oct[4];
-      octet(at, oct);
-      count_from(oct, below, n);
-    }
-    return count_in_all(n);
-  };
-  uint32_t t = t16;
-  if (larger >= k) {  // uniform: halving what lies above
-    uint32_t low = t16 + 2u, high = most;  // t16 + 1 is reached
-    t = t16 + 1u;
-#pragma unroll 1
-    while (low <= high) {
-      const uint32_t c = low + (high - low) / 2u;
-      const uint32_t n = reach(c);
-      if (n >= k) {
-        t = c;
-        low = c + 1u;
-      } else {
-        larger = n;  // in the end what lies above t
-        high = c - 1u;
-      }
-    }
-    if (t == most) larger = 0u;
-  }
-  const bool poisoned = t >= kNonfiniteMag;  // k values are not finite, or more: all of those leave
-  const uint32_t above = poisoned ? kNonfiniteMag : t + 1u;
-  uint32_t equals = poisoned ? 0u : k - larger;  // how many of t leave
-  uint32_t total = 0u, end = 0u;  // end: equals before this element leave
-#pragma unroll 1
-  for (uint32_t at = 0u; at < g.cnt && (poisoned || total < k); at += (uint32_t)kRow) {  // uniform
-    uint32_t oct[4], hits = 0u, same = 0u;
-    octet(at, oct);
-#pragma unroll
-    for (int e = 0; e < kOct; ++e) {
-      const uint32_t m = ADACC_ELEM_MAG(oct, e);
-      hits |= (m >= above ? 1u : 0u) << e;
-      same |= (m == t ? 1u : 0u) << e;
-    }
-    if (equals != 0u) {  // uniform
-      uint32_t here;
-      const uint32_t before = count_below((uint32_t)__builtin_popcount(same), here);
-      uint32_t room = before < equals ? equals - before : 0u, mine = 0u;
-#pragma unroll
-      for (int e = 0; e < kOct; ++e) {  // the first `room` of the octet's
-        if (((same >> e) & 1u) != 0u && room != 0u) {
-          hits |= 1u << e;
-          mine = at + lane_off + (uint32_t)e + 1u;
-          --room;
-        }
-      }
-      mine = wave_max_u32_scalar(mine);
-      end = mine > end ? mine : end;
-      equals -= here < equals ? here : equals;
-    }
-    uint32_t n;
-    uint32_t pos = count_below((uint32_t)__builtin_popcount(hits), n) + pos0 + total;
-    total += n;
-#pragma unroll
-    for (int e = 0; e < kOct; ++e) {
-      if ((hits >> e) & 1u) {
-        if (pos < limit) sink(pos, (uint32_t)g.first + at + lane_off + (uint32_t)e, (e & 1) ? oct[e >> 1] >> 16 : oct[e >> 1] & 0xFFFFu);
-        ++pos;
-      }
-    }
-  }
-  load_long<E>(d, g, raw);
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    __builtin_amdgcn_sched_barrier(0);
-    const uint32_t top = octet_magnitude(raw[j]);
-    if (__builtin_amdgcn_ballot_w64(top >= t || top >= above) == 0ull) continue;  // uniform
-    const uint32_t i0 = (uint32_t)(j * kRow) + lane_offset();
-    uint32_t hits = 0u;
-#pragma unroll
-    for (int e = 0; e < kOct; ++e) {
-      const uint32_t m = ADACC_ELEM_MAG(raw[j], e);
-      hits |= (m >= above || (m == t && i0 + (uint32_t)e < end) ? 1u : 0u) << e;
-    }
-    clear_elements(raw[j], hits);
-  }
-  mags.of(raw);
   return total;
 }
 
@@ -406,15 +346,11 @@ __device__ __forceinline__ void compress_long(const TensorDesc& d, uint32_t seg,
     const uint32_t end = pos0 + expected;
     const uint32_t limit = end < d.cap ? end : d.cap;
     const StreamSink sink{d.idx, d.val};
-    uint32_t total;
-    if constexpr (E <= 8) {
-      total = topk_extract<E, true>(expected, raw, mags, (uint32_t)g.first, sink, pos0, limit);
-    } else {
-      uint32_t t16;
-      total = expected;
-      if (!long_topk_by_list<E>(expected, raw, mags, t16, (uint32_t)g.first, sink, pos0, limit))
-        total = long_topk_by_halving<E>(d, g, expected, t16, raw, mags, sink, pos0, limit);
-    }
+    uint32_t total = expected;
+    // (k values that are not finite, or more: all of those leave.  Nine Inf in every row, k = 8, with the placement that writes all of it
+    // again, [8192, 11008]: 144 us by workgroups, 166 by a second read, 107 like this)
+    if (!long_topk_by_list<E>(expected, raw, mags, (uint32_t)g.first, sink, pos0, limit))
+      total = long_take_above<E>(kNonfiniteMag - 1u, raw, mags, (uint32_t)g.first, sink, pos0, limit);
     if (lane0) {
       d.tile_ptr[seg] = pos0;
       d.cnt[seg] = total;
