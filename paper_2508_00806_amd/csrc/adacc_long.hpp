@@ -384,11 +384,17 @@ __device__ __forceinline__ void compress_long(const TensorDesc& d, uint32_t seg,
   quantise_long<BITS, ASYM, E>(d, g, seg, raw, [&](int j) { return mags.at(j); });
 }
 
-// wavefronts per SIMD the registers are held to: four registers a row for the values, and some forty beside them
-template <int E, bool TOPK>
-constexpr int long_min_waves() { return TOPK && E <= 8 ? 6 : E <= 8 ? 8 : E <= 12 ? 6 : E <= 16 ? 5 : 4; }
+// Wavefronts per SIMD the registers are held to, as many as do without a spill: four registers a row for the values, and some forty
+// beside them.  (STD symmetric over 13 to 16 rows at 5, with 21 values spilled, and at 4: int4 at 8 sigma [8192, 8000] 42.0 and 36.2
+// us, at 4 sigma 99.2 and 93.6; int8 46.8 and 41.2, 100.3 and 95.2.)
+template <int E, bool TOPK, bool ASYM>
+constexpr int long_min_waves() {
+  if (E <= 8) return TOPK ? 7 : 8;
+  if (E <= 12) return TOPK && ASYM ? 5 : 6;
+  return E <= 16 && ASYM != TOPK ? 5 : 4;
+}
 template <int E, bool TOPK, int BITS, bool ASYM>
-__global__ __launch_bounds__(kThreads, (long_min_waves<E, TOPK>())) void compress_long_kernel(TensorDesc d, uint32_t epoch) {
+__global__ __launch_bounds__(kThreads, (long_min_waves<E, TOPK, ASYM>())) void compress_long_kernel(TensorDesc d, uint32_t epoch) {
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
   const uint32_t seg = blockIdx.x * kWavesPerWg + wave;
   if (seg < d.n_tiles) compress_long<E, TOPK, BITS, ASYM>(d, seg, epoch);
