@@ -648,13 +648,11 @@ __device__ __forceinline__ void scale_sym_clean(const TensorDesc& d, uint32_t am
   }
 }
 
-// a6 .. a8 for one row of a tile from which outliers and values that are not finite are gone
-// (they are zero in `oct`).  top: symmetric, the lane's largest magnitude of the row as binary32 bits.
+// a6 .. a8 for one row of a tile without outliers and values that are not finite (they are zero in `x`).
+// top: symmetric, the lane's largest magnitude of the row as binary32 bits.
 template <int BITS, bool ASYM, int E, int LANES, bool STRIP>
-__device__ __forceinline__ void encode_clean_row(const TensorDesc& d, const TileGeo<E, STRIP>& g, int j,
-                                                 const uint32_t (&oct)[4], uint32_t top) {
-  float x[kOct];
-  widen_row(oct, x);
+__device__ __forceinline__ void encode_clean_values(const TensorDesc& d, const TileGeo<E, STRIP>& g, int j,
+                                                    float (&x)[kOct], uint32_t top) {
   float scl, inv, off = 0.0f;
   if constexpr (!ASYM) {
     scale_sym_clean(d, lanes_reduce<LANES>(top, OpUMax()), scl, inv);
@@ -670,6 +668,13 @@ __device__ __forceinline__ void encode_clean_row(const TensorDesc& d, const Tile
     for (int e = 0; e < kOct; ++e) x[e] = x[e] - off;
   }
   store_row<BITS, ASYM, E>(d, g, j, x, scl, inv, off);
+}
+template <int BITS, bool ASYM, int E, int LANES, bool STRIP>
+__device__ __forceinline__ void encode_clean_row(const TensorDesc& d, const TileGeo<E, STRIP>& g, int j,
+                                                 const uint32_t (&oct)[4], uint32_t top) {
+  float x[kOct];
+  widen_row(oct, x);
+  encode_clean_values<BITS, ASYM, E, LANES>(d, g, j, x, top);
 }
 
 // ------------------------------------------------------------------ TOPK over groups inside a row
@@ -720,11 +725,12 @@ __device__ __forceinline__ uint32_t encode_rows(const TensorDesc& d, const TileG
     widen_row(raw[j], x);
     // First a test per lane that is cheap and errs on the safe side: can this lane's octet hold an
     // outlier (or, without outliers, a value that is not finite)?  If no lane says yes - nearly
-    // every row - the row is quantised as it is.  am_bits: the lane's largest |x| (symmetric).
+    // every row - the row is quantised as it is.  am_bits: the lane's largest |x| (ABS, NONE).
     float limit_sq = 0.0f;
     uint32_t am_bits = 0u;
     bool suspect;
-    uint64_t b[kOct];  // TOPK
+    uint64_t b[kOct];  // STD, TOPK
+    float q[kOct];     // STD
     if constexpr (MODE == kModeTopk) {
       suspect = true;  // every group has outliers: its k largest
       topk_row_ballots<LANES>(d, raw[j], b);
@@ -734,7 +740,6 @@ __device__ __forceinline__ uint32_t encode_rows(const TensorDesc& d, const TileG
         for (int e = 0; e < kOct; ++e) b[e] &= valid;
       }
     } else if constexpr (MODE == kModeStd) {
-      float q[kOct];
 #pragma unroll
       for (int e = 0; e < kOct; ++e) q[e] = x[e] * x[e];  // exact: two significands of at most 11 bits
       float s1 = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
@@ -745,40 +750,56 @@ __device__ __forceinline__ uint32_t encode_rows(const TensorDesc& d, const TileG
       const float qm = fmaxf(fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3])), fmaxf(fmaxf(q[4], q[5]), fmaxf(q[6], q[7])));
       // an Inf or NaN anywhere in a group makes its limit NaN
       suspect = !(qm <= limit_sq);
-      if constexpr (!ASYM) {
-        const float am = fmaxf(fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))),
-                               fmaxf(fmaxf(fabsf(x[4]), fabsf(x[5])), fmaxf(fabsf(x[6]), fabsf(x[7]))));
-        am_bits = __float_as_uint(am);
-      }
     } else {
       am_bits = mag_bits32(octet_magnitude(raw[j]));  // Inf / NaN show as a value of 0x7F800000 or more
       if constexpr (MODE == kModeAbs) suspect = am_bits > __float_as_uint(d.param);  // tau >= 0, finite
       else suspect = am_bits >= 0x7F800000u;
     }
-    if constexpr (MODE != kModeTopk) {
+    const uint32_t i0 = lane_first + (uint32_t)(j * kRow);
+    if constexpr (MODE == kModeTopk || (MODE == kModeStd && STORE)) {
+      if (MODE == kModeTopk || __builtin_amdgcn_ballot_w64(suspect) != 0ull) {  // uniform
+        // The tests as wavefront ballots (scalar registers); the widened values are cleared as they are, and rows with and without
+        // outliers share one copy of what follows.  (Through the threshold on the magnitude, widened again behind it: 2^25 values, STD
+        // over 512, int8, at 4 sigma 30.5 us symmetric and 35.3 asymmetric, 27.5 and 28.7 like this; at 8 sigma 24.1 and 27.4, 24.0
+        // and 25.0; the largest of every 128 27.2 and 25.5.  With a second copy for rows with outliers: 29.0, 30.5; 25.1, 26.5; 25.2.)
+        if constexpr (MODE == kModeStd) {
+#pragma unroll
+          for (int e = 0; e < kOct; ++e) b[e] = __builtin_amdgcn_ballot_w64(q[e] > limit_sq);
+          if (__builtin_amdgcn_ballot_w64(limit_sq != limit_sq) != 0ull) {  // then every element is tested for Inf / NaN
+#pragma unroll
+            for (int e = 0; e < kOct; ++e) b[e] |= __builtin_amdgcn_ballot_w64(is_nonfinite(x[e]));
+          }
+        }
+        uint32_t mask, lane_excl, row_cnt;
+        bool any, sparse;
+        row_bookkeeping(b, mask, lane_excl, row_cnt, any, sparse);
+        if (any) {  // uniform: the row's outliers leave at once, nothing about them is kept
+          emit_row(raw[j], mask, lane_excl, sparse, i0, sink, pos0 + total, limit);
+          total += row_cnt;
+        }
+        if constexpr (STORE) {
+#pragma unroll
+          for (int e = 0; e < kOct; ++e) x[e] = __builtin_amdgcn_inverse_ballot_w64(b[e]) ? 0.0f : x[e];
+        }
+      }
+      if constexpr (STORE) {
+        float most = 0.0f, unused;
+        if constexpr (!ASYM) row_extremes<false>(x, most, unused);
+        encode_clean_values<BITS, ASYM, E, LANES>(d, g, j, x, __float_as_uint(most));
+      }
+    } else {
       if (__builtin_amdgcn_ballot_w64(suspect) == 0ull) {  // uniform
         if constexpr (STORE) encode_clean_row<BITS, ASYM, E, LANES>(d, g, j, raw[j], am_bits);
         continue;
       }
-    }
-    uint32_t oct[4] = {raw[j][0], raw[j][1], raw[j][2], raw[j][3]};
-    const uint32_t i0 = lane_first + (uint32_t)(j * kRow);
-    if constexpr (MODE == kModeTopk) {
-      uint32_t mask, lane_excl, row_cnt;
-      bool any, sparse;
-      row_bookkeeping(b, mask, lane_excl, row_cnt, any, sparse);
-      if (any) {  // uniform: the row's outliers leave at once, nothing about them is kept
-        emit_row(oct, mask, lane_excl, sparse, i0, sink, pos0 + total, limit);
-        total += row_cnt;
-        clear_elements(oct, mask);
-      }
-    } else {
+      // by a threshold on the magnitude, in a copy of the octets
+      uint32_t oct[4] = {raw[j][0], raw[j][1], raw[j][2], raw[j][3]};
       uint32_t most = kNonfiniteMag - 1u;  // NONE: what is not finite is zeroed, and reported nowhere
       if constexpr (MODE == kModeStd) most = magnitude_limit_squared(limit_sq);
       if constexpr (MODE == kModeAbs) most = magnitude_limit(d.param);
       total += take_above(oct, both_halves(most), i0, sink, pos0 + total, limit);
+      if constexpr (STORE) encode_clean_row<BITS, ASYM, E, LANES>(d, g, j, oct, mag_bits32(octet_magnitude(oct)));
     }
-    if constexpr (STORE) encode_clean_row<BITS, ASYM, E, LANES>(d, g, j, oct, mag_bits32(octet_magnitude(oct)));
   }
   return total;
 }
