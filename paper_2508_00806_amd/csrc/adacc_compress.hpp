@@ -1098,13 +1098,14 @@ __device__ __forceinline__ void scales_of(const TensorDesc& d, uint32_t lg, cons
 // ------------------------------------------------------------------ a6 .. a8 for a tile without outliers
 // (none left, and nothing that is not finite), quantisation groups of any size.  top: symmetric, the lane's largest magnitude
 // of every row.  Four rows at a time: their extremes meet group by group, the one step that depends on the size of the groups;
-// then the scales, then the codes.
-template <int BITS, bool ASYM, int E>
+// then the scales, then the codes.  ROWS: no group is longer than a row, and the compiler shall know it (with the code for a group of 4096
+// beside it the batch kernel for binary16 TOPK over 4096 kept 28 registers in scratch memory).
+template <int BITS, bool ASYM, int E, bool ROWS>
 __device__ __forceinline__ void quantise_tile(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4], const uint32_t (&top)[E]) {
   constexpr int B = E < 4 ? E : 4;
   static_assert(E % B == 0 && (B == 4 || B == 1), "rows in fours");
   // a group of 4096 takes both fours: its extremes in the lane first
-  const bool all = E == 8 && d.lgq == 12u;  // uniform
+  const bool all = !ROWS && E == 8 && d.lgq == 12u;  // uniform
   const uint32_t lg = all ? 11u : d.lgq;
   uint32_t top_all = 0u;
   int32_t hi_all = 0, lo_all = 0;
@@ -1173,16 +1174,16 @@ __device__ __forceinline__ void quantise_tile(const TensorDesc& d, const TileGeo
 
 // BITS = kBitsAny: as the descriptor says (the batch kernels: the selection before it is the same code for all)
 constexpr int kBitsAny = 0;
-template <int BITS, bool ASYM, int E>
+template <int BITS, bool ASYM, int E, bool ROWS>
 __device__ __forceinline__ void quantise_tile_as(const TensorDesc& d, const TileGeo<E>& g, const uint32_t (&raw)[E][4], uint32_t (&top)[E]) {
   if constexpr (BITS != kBitsAny) {
-    quantise_tile<BITS, ASYM, E>(d, g, raw, top);
+    quantise_tile<BITS, ASYM, E, ROWS>(d, g, raw, top);
   } else {
     switch (d.variant & 6u) {
-      case 0: quantise_tile<4, false, E>(d, g, raw, top); break;
-      case 2: quantise_tile<4, true, E>(d, g, raw, top); break;
-      case 4: quantise_tile<8, false, E>(d, g, raw, top); break;
-      default: quantise_tile<8, true, E>(d, g, raw, top); break;
+      case 0: quantise_tile<4, false, E, ROWS>(d, g, raw, top); break;
+      case 2: quantise_tile<4, true, E, ROWS>(d, g, raw, top); break;
+      case 4: quantise_tile<8, false, E, ROWS>(d, g, raw, top); break;
+      default: quantise_tile<8, true, E, ROWS>(d, g, raw, top); break;
     }
   }
 }
@@ -1197,7 +1198,7 @@ __device__ __forceinline__ uint32_t encode_tile_topk_whole(const TensorDesc& d, 
     uint32_t top[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) top[j] = rowmag.at(j);
-    quantise_tile_as<BITS, ASYM, E>(d, g, raw, top);
+    quantise_tile_as<BITS, ASYM, E, true>(d, g, raw, top);
   }
   return total;
 }
@@ -1349,7 +1350,7 @@ __device__ __forceinline__ uint32_t encode_tile_general(const TensorDesc& d, con
       }
     }
   }
-  if constexpr (STORE) quantise_tile_as<BITS, ASYM, E>(d, g, raw, top);
+  if constexpr (STORE) quantise_tile_as<BITS, ASYM, E, false>(d, g, raw, top);
   return total;
 }
 

@@ -35,7 +35,7 @@ def spills(tmp_path_factory):
     return found
 
 
-@pytest.mark.parametrize("kernels", ["compress_long_kernel", "compress_kernel"])
+@pytest.mark.parametrize("kernels", ["compress_long_kernel", "compress_kernel", "compress_batch_kernel"])
 def test_no_vector_register_is_spilled(spills, kernels):
     ours = {n: s for n, s in spills.items() if re.search(r"\d" + kernels + "I", n)}
     assert any("bf16" in n for n in ours) and any("3f16" in n for n in ours)
