@@ -662,13 +662,16 @@ static int launch_generic_compress(const adacc_method* method, const Plan& p, co
   return launch_check("place_generic_kernel");
 }
 
-// LDS that a tile kernel does not use but that bounds the workgroups of a CU to five, half of what its registers allow.
-// For asymmetric ABS over whole rows, a stream with few instructions, fewer wavefronts that read and write 1.5 bytes for
-// every 2 keep the memory's pages open longer: 2^29 softmax values, 541 us with eight, 535 / 533.5 / 531.6 with seven,
-// six and five, 543 with four.  The other encoders gain nothing from it (GELU, 2^28 values: the same) or lose (TOPK of
-// 2048, [32768, 2048]: 61.6 -> 65.6 us).
+// LDS that the general encoder of tiles of 4 rows does not use but that bounds the workgroups of a CU to six, where its registers
+// (41 to 60) allow eight: from three rounds of the device on, a stream reads and writes a little faster with fewer wavefronts on its way
+// at once.  ([262144, 2048], int8, us with eight / six / five and, before, with the registers' 5 to 8: without outliers in groups of
+// 1024 asymmetric 270 / 262 / 258 and 267; STD over 2048 at 6 sigma 266 / 260 / 257 and 260; softmax values, ABS, asymmetric, 268 /
+// 261 / 262 and 260.  Where a tile has many outliers issue counts for more: SiLU, ABS at 3, asymmetric, 300 / 312 / 325 and 334.
+// [28000, 2048], the same: 29.3 / 29.0 / 28.9 and 29.3; 36.2 / 36.2 / 35.8 and 36.8; 37.7 / 37.1 / 37.7 and 37.6; 42.1 / 42.9 / 44.6 and 45.9.)
+constexpr uint32_t kStreamTiles = 24576;
 static uint32_t residency_lds(const adacc_method* m, const Plan& p) {
-  return m->outlier_mode == ADACC_OUTLIER_ABS && m->asym && !p.rowwise && p.tile_elems == 2048 ? 32000u : 0u;
+  const bool general = !p.rowwise && p.tile_elems == 2048 && m->outlier_mode != ADACC_OUTLIER_TOPK;
+  return general && p.n_tiles >= kStreamTiles ? 24320u : 0u;  // (19 of the 128 pieces of 1280 bytes)
 }
 
 static int compress_one(const adacc_method* method, const void* src, uint64_t numel, void* blob, uint64_t blob_bytes,
