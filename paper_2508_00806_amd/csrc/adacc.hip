@@ -129,9 +129,11 @@ struct Plan {  // everything derived from (method, numel)
   float param, divisor;
 };
 
-// Groups from which on a wavefront for each is faster than a workgroup, three for every SIMD of the device.  (STD over rows
-// of 2200 / 5160 / 8000 / 11008, us by workgroups and by wavefronts: 1024 rows 10.6 9.7 / 12.8 12.7 / 14.0 15.6 / 16.9 19.8; 2048
-// rows 13.2 11.3 / 16.9 15.4 / 19.1 19.6 / 26.2 24.7; 3072 rows 16.9 12.7 / 21.3 17.9 / 24.4 23.2 / 33.2 29.5.)
+// Groups from which on a wavefront for each is faster than a workgroup whatever their length, three for every SIMD of the device.
+// (STD, int8, over SiLU rows of 2200 / 5160 / 8000 / 11008 at 8 sigma, us by workgroups and by wavefronts: 1024 rows 9.3 8.5 / 11.3 10.9 /
+// 12.0 12.6 / 14.2 15.6; 2048 rows 11.7 9.8 / 14.3 13.1 / 15.6 16.0 / 22.1 20.4; 3072 rows 14.8 10.9 / 18.4 15.2 / 20.5 19.3 / 27.9 25.6.
+// The 8 largest of values in quarters, int4: 1024 rows 10.1 9.2 / 11.6 12.0 / 12.7 14.2 / 14.9 18.0; 3072 rows 17.5 11.7 / 19.9 16.3 / 21.9 20.4 /
+// 29.2 26.4.)
 constexpr uint64_t kLongGroups = 3072;
 static CompressFn long_fn(const adacc_method* m, const Plan& p) {
   return ADACC_PICK(p.half, compress_long_fn(p.tile_elems, m->outlier_mode, m->topk, m->bits, m->asym));

@@ -158,8 +158,8 @@ __device__ __forceinline__ uint32_t sum_counts(const uint32_t* cnt, uint32_t* be
 // j + 512, .. of channels, one mask byte each, and keeps the first two octets' sums in registers over the three passes (mean,
 // variance, selection): up to 8192 channels S is read once.  Bound by the chain of its steps: three reductions, a square root and two
 // divisions.  Z > z_thresh is decided by a product where rounding cannot matter, S - mu further from z_thresh * sigma than 2^-40 of
-// it; a division of every channel was half the time.  (1024 threads, S read three times, two barriers a reduction: 7.4
-// us for 4096 channels, 9.0 for 8192; 4.1 and 5.4 now.)
+// it; a division of every channel was half the time.  (1024 threads, S read three times, two barriers a reduction: 7.9
+// us for 4096 channels, 9.0 for 8192; 4.8 and 5.8 now.)
 constexpr uint32_t kSelectKept = 2;
 __global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const double* __restrict__ S, ChannelDesc c) {
   __shared__ double a[2][kSelectWaves];

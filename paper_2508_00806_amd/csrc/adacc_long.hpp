@@ -10,7 +10,7 @@
 //   TOPK  [26000, 2200] 83.0 -> 42.7   NONE  39.4 -> 31.3   ABS  62.1 -> 40.7
 // and TOPK-8, int4 in groups of 128: [8192, 4104] 36.7 -> 22.3  [8192, 6144] 39.3 -> 28.5  [8192, 8192] 42.5 -> 37.0
 //   [8192, 11008] 62.9 -> 49.1, of which 36 are what its 227 MB take at 6.3 TB/s.)
-// Where the workgroup is the better one, it stays: longer groups without outliers ([8192, 11008]: NONE 44.8
+// Where the workgroup is the better one, it stays: more than 8 of the largest, longer groups without outliers ([8192, 11008]: NONE 44.8
 // us by workgroups, 50.0 by wavefronts), tensors of few groups (a wavefront each leaves the device empty), quantisation groups
 // whose lanes do not line up with a row, and more than 22 rows, which four wavefronts per SIMD would not hold without a spill.
 // The blob, its tiles and the workspace are those of adacc_generic.hpp, whose placement kernel follows here too.
