@@ -722,7 +722,8 @@ static int compress_one(const adacc_method* method, const void* src, uint64_t nu
   if (p.outliers) {
     rc = launch_block_sums(method, p, d, s);
     if (rc != ADACC_OK) return rc;
-    hipLaunchKernelGGL(ADACC_PICK(p.half, place_fn()), dim3(place_grid(method, p)), dim3(kPlaceThreads), 0, s, d, epoch);
+    const bool many = method->outlier_mode != ADACC_OUTLIER_TOPK && p.n_tiles <= kPlaceDirectTiles;
+    hipLaunchKernelGGL(ADACC_PICK(p.half, place_fn(many)), dim3(place_grid(method, p)), dim3(many ? kPlaceManyThreads : kPlaceThreads), 0, s, d, epoch);
     rc = launch_check("place_kernel");
   }
   return rc;

@@ -148,8 +148,10 @@ struct ChannelwiseDesc {
 // Outliers of a tile that travel through the tile's slot in the workspace (ABS / STD); a tile with
 // more is selected a second time by the placement kernel.
 constexpr int kSlot = 64;
-// The placement kernels: a workgroup of kPlaceThreads threads takes kPlaceTiles consecutive tiles.
+// The placement kernels: a workgroup of kPlaceThreads threads takes kPlaceTiles consecutive tiles, one of kPlaceManyThreads where
+// its wavefronts have something to share (ABS / STD, adacc_k_place.hip).
 constexpr int kPlaceThreads = 256;
+constexpr int kPlaceManyThreads = 1024;
 constexpr int kPlaceTiles = 64;
 // Of the fallback kernels' segments, which the whole workgroup selects again where a slot does not do, one after the
 // other, it takes 1, 2, 4, .. kPlaceSegments: the fewest with which kPlaceWorkgroups workgroups, as many as the device

@@ -1449,11 +1449,12 @@ __device__ __forceinline__ void compress_tile_outliers(const TensorDesc& d, uint
 // output position found by bisection and slots of 32 records, 8203 tiles of 20 outliers took 17.8 us on 33
 // workgroups, and 4.5 us for the sums, 6.5 us now; the two-byte index in the tile makes a record one word, so that a slot of 256 bytes
 // holds 64: 37 tiles of 4096 values with 35 outliers each were all selected again, 25.6 us, 5.5 us now.)
+template <int WAVES>
 struct PlaceShared {
-  uint32_t part[kPlaceThreads / kWave];
-  uint32_t window[kPlaceThreads / kWave];
+  uint32_t part[WAVES];
+  uint32_t window[WAVES];
 };
-struct PlaceListShared : PlaceShared {
+struct PlaceListShared : PlaceShared<kPlaceThreads / kWave> {
   uint16_t list[kPlaceThreads / kWave][kWave * kSlot];  // 8 KiB per wavefront: every slot of a window full
 };
 
@@ -1467,8 +1468,9 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// sum over the workgroup (kPlaceThreads threads), returned to every thread
-__device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t (&part)[kPlaceThreads / kWave]) {
+// sum over the workgroup (WAVES wavefronts), returned to every thread
+template <int WAVES>
+__device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t (&part)[WAVES]) {
   const uint32_t w = wave_sum_u32(v);
   const uint32_t wave = threadIdx.x / kWave;
   __syncthreads();  // earlier readers of part[] are done
@@ -1476,21 +1478,23 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t (&part)[k
   __syncthreads();
   uint32_t s = 0u;
 #pragma unroll
-  for (int i = 0; i < kPlaceThreads / kWave; ++i) s += part[i];
+  for (int i = 0; i < WAVES; ++i) s += part[i];
   return s;
 }
 
 // this thread's share of the sum of n 32-bit words (16-byte aligned); eight loads of 16 bytes per thread are in flight
 // at a time
+template <int WAVES>
 __device__ __forceinline__ uint32_t sum_share(const uint32_t* words, uint32_t n) {
+  constexpr uint32_t kStep = (uint32_t)(WAVES * kWave);
   const uint4* w4 = reinterpret_cast<const uint4*>(words);
   const uint32_t n4 = n / 4u;
   uint32_t acc = 0u;
-  for (uint32_t i0 = 0u; i0 < n4; i0 += 8u * (uint32_t)kPlaceThreads) {
+  for (uint32_t i0 = 0u; i0 < n4; i0 += 8u * kStep) {
     uint4 v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const uint32_t i = i0 + (uint32_t)k * (uint32_t)kPlaceThreads + threadIdx.x;
+      const uint32_t i = i0 + (uint32_t)k * kStep + threadIdx.x;
       v[k] = i < n4 ? w4[i] : make_uint4(0u, 0u, 0u, 0u);
     }
 #pragma unroll
@@ -1501,20 +1505,22 @@ __device__ __forceinline__ uint32_t sum_share(const uint32_t* words, uint32_t n)
 }
 
 // outliers in the first `tiles` tiles, to every thread of the workgroup
-__device__ __forceinline__ uint32_t outliers_before(const TensorDesc& d, uint32_t tiles, bool from_sums, PlaceShared& sh) {
+template <int WAVES>
+__device__ __forceinline__ uint32_t outliers_before(const TensorDesc& d, uint32_t tiles, bool from_sums, PlaceShared<WAVES>& sh) {
   uint32_t acc;
   if (from_sums) {  // uniform
     const uint32_t blocks = tiles / (uint32_t)kSumTiles;
     const uint32_t t = blocks * (uint32_t)kSumTiles + threadIdx.x;  // kSumTiles = kPlaceThreads
-    acc = sum_share(d.block_sum, blocks) + (t < tiles ? d.cnt[t] : 0u);
+    static_assert(WAVES * kWave >= kSumTiles, "a thread per tile of the last block");
+    acc = sum_share<WAVES>(d.block_sum, blocks) + (t < tiles ? d.cnt[t] : 0u);
   } else {
-    acc = sum_share(d.cnt, tiles);
+    acc = sum_share<WAVES>(d.cnt, tiles);
   }
   return block_sum_u32(acc, sh.part);
 }
 
 // block_sum[block] = outliers in the block's tiles
-__device__ __forceinline__ void place_sum_block(const TensorDesc& d, uint32_t block, PlaceShared& sh) {
+__device__ __forceinline__ void place_sum_block(const TensorDesc& d, uint32_t block, PlaceShared<kPlaceThreads / kWave>& sh) {
   static_assert(kSumTiles == kPlaceThreads, "a thread per tile");
   const uint32_t t = block * (uint32_t)kSumTiles + threadIdx.x;
   const uint32_t s = block_sum_u32(t < d.n_tiles ? d.cnt[t] : 0u, sh.part);
@@ -1547,12 +1553,12 @@ struct PlacedTiles {
 // of tiles that fit their slot go to the stream.  TILES <= 64: the window of all wavefronts is the workgroup's tiles,
 // each moves its share; TILES = 256: a window per wavefront.  first: the first tile, `most`: at most that many of the
 // TILES; before: the outliers of all tiles before them, where the caller knows (`known`).
-template <int TILES, class Shared>
+template <int TILES, int WAVES, class Shared>
 __device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t first, uint32_t most, bool known, uint32_t before,
                                                    bool from_sums, bool move, Shared& sh) {
   constexpr bool OWN = TILES > kWave;  // a window per wavefront
   constexpr int WINDOW = OWN ? kWave : TILES;
-  constexpr int WAVES = kPlaceThreads / kWave;
+  constexpr int PER = OWN ? 0 : TILES / WAVES;  // tiles whose records a wavefront moves
   static_assert(!OWN || TILES == WAVES * kWave, "a lane per tile");
   const uint32_t lane = (uint32_t)lane_id();
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1566,7 +1572,21 @@ __device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t
     const uint32_t mine = wave_sum_u32(p.count);
     if (lane == 0u) sh.window[wave] = mine;  // (read behind the barriers of outliers_before)
   }
-  p.base = known ? before : outliers_before(d, first, from_sums, sh);  // uniform
+  // few tiles to a wavefront: the records are asked for together with the counts, whether they are there or not, one round
+  // trip to memory less
+  constexpr bool EARLY = !OWN && PER <= 4;
+  uint32_t rec[OWN ? 1 : PER];
+  const uint32_t j0 = wave * (uint32_t)PER;
+  if constexpr (EARLY) {
+    if (move) {  // uniform
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const uint32_t t = j0 + (uint32_t)i < p.n_here ? p.first + j0 + (uint32_t)i : p.first;
+        rec[i] = d.slot[(uint64_t)t * (uint64_t)kSlot + lane];
+      }
+    }
+  }
+  p.base = known ? before : outliers_before<WAVES>(d, first, from_sums, sh);  // uniform
   if constexpr (OWN) {
 #pragma unroll
     for (int w = 0; w < WAVES - 1; ++w) p.base += (uint32_t)w < wave ? sh.window[w] : 0u;
@@ -1627,14 +1647,13 @@ __device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t
       }
     } else {
       // a lane per record, the loads of all tiles of this wavefront in flight at once
-      constexpr int PER = TILES / WAVES;
-      const uint32_t j0 = wave * (uint32_t)PER;
-      uint32_t rec[PER];
+      if constexpr (!EARLY) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {  // a lane without a record reads a tile's first word
-        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j0 + i);
-        const uint32_t t = j0 + (uint32_t)i < p.n_here ? p.first + j0 + (uint32_t)i : p.first;
-        rec[i] = d.slot[(uint64_t)t * (uint64_t)kSlot + (lane < n ? lane : 0u)];
+        for (int i = 0; i < PER; ++i) {  // a lane without a record reads a tile's first word
+          const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j0 + i);
+          const uint32_t t = j0 + (uint32_t)i < p.n_here ? p.first + j0 + (uint32_t)i : p.first;
+          rec[i] = d.slot[(uint64_t)t * (uint64_t)kSlot + (lane < n ? lane : 0u)];
+        }
       }
 #pragma unroll
       for (int i = 0; i < PER; ++i) {

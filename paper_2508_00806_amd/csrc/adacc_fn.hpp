@@ -51,7 +51,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   BatchCompressFn compress_batch_fn8(int kind);                                        \
   BatchDecompressFn decompress_batch_fn(bool f32);                                     \
   PlaceSumFn place_sum_fn();                                                           \
-  PlaceFn place_fn();                                                                  \
+  PlaceFn place_fn(bool many);                                                         \
   PlaceSumBatchFn place_sum_batch_fn();                                                \
   PlaceBatchFn place_batch_fn();                                                       \
   CompressFn compress_generic_fn(uint32_t tile_elems, uint32_t mode, uint32_t gs);     \

@@ -978,7 +978,7 @@ template <int SL, int KIND>
 __global__ __launch_bounds__(kSegThreads, (place_min_waves<SL, KIND>())) void place_generic_kernel(TensorDesc d, uint32_t epoch) {
   static_assert(kSegThreads == (uint32_t)kPlaceThreads, "one workgroup for both");
   extern __shared__ __attribute__((aligned(16))) unsigned char segment_lds[];
-  __shared__ PlaceShared place;
+  __shared__ PlaceShared<kPlaceThreads / kWave> place;
   constexpr bool topk = kind_is_topk(KIND);
   if (topk && __hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch) return;  // uniform
   const uint32_t room = topk ? 0u : (uint32_t)kSlot;
@@ -987,7 +987,7 @@ __global__ __launch_bounds__(kSegThreads, (place_min_waves<SL, KIND>())) void pl
   uint32_t before = 0u;
   for (uint32_t at = first; at < end; at += (uint32_t)kPlaceSegments) {  // uniform; once, but for TOPK of very many segments
     const TensorDesc& desc = topk ? descriptor_again() : d;
-    const PlacedTiles p = place_tiles<kPlaceSegments>(desc, at, end - at, at != first, before, desc.from_sums != 0u, !topk, place);
+    const PlacedTiles p = place_tiles<kPlaceSegments, kPlaceThreads / kWave>(desc, at, end - at, at != first, before, desc.from_sums != 0u, !topk, place);
     before = p.after;
     if (!topk && __builtin_amdgcn_ballot_w64(p.count > room) == 0ull) return;  // the usual case; the same in every wavefront
     for (uint32_t j = 0; j < p.n_here; ++j) {

@@ -15,7 +15,8 @@ namespace ADACC_DT_NS {
 // now it is hidden behind the placement.)
 constexpr int kTailOcts = 2;  // per thread: 4096 elements
 constexpr uint32_t kTailLdsBytes = kSegHeadBytes + 4u * (2u * kTailOcts * kSegThreads + 2u * 4096u / 8u);
-__device__ __forceinline__ void compress_tail(const TensorDesc& whole, uint32_t total_main, unsigned char* lds) {
+template <int WAVES>
+__device__ __forceinline__ void compress_tail(const TensorDesc& whole, bool regular, PlaceShared<WAVES>& sums, unsigned char* lds) {
   TensorDesc d = whole;
   d.tile_elems = d.gs;  // the segment is one statistics group
   SegmentShared sh = segment_shared<kTailOcts>(lds, d.tile_elems, d.gq);
@@ -25,7 +26,11 @@ __device__ __forceinline__ void compress_tail(const TensorDesc& whole, uint32_t 
   g.octs = (d.tail + (uint32_t)kOct - 1u) / (uint32_t)kOct;
   g.full = false;
   uint32_t raw[kTailOcts][4], mask[kTailOcts], omag[kTailOcts];
-  segment_load(d, g, raw);
+  const bool works = threadIdx.x < (uint32_t)kSegThreads;  // whole wavefronts
+  if (works) segment_load(d, g, raw);
+  // the counts of all tiles are asked for together with the elements, by every wavefront; those that have nothing else to do leave
+  uint32_t total_main = regular ? d.topk * (uint32_t)(d.numel >> d.lgs) : outliers_before<WAVES>(whole, d.n_tiles, d.from_sums != 0u, sums);
+  if (!works) return;
 #pragma unroll
   for (int j = 0; j < kTailOcts; ++j) omag[j] = octet_magnitude(raw[j]);
   segment_select<kTailOcts, kSegAny>(d, g, sh, raw, omag, mask);
@@ -52,33 +57,43 @@ __device__ __forceinline__ void compress_tail(const TensorDesc& whole, uint32_t 
   }
 }
 
+template <int WAVES, bool LIST>
 union PlaceLds {  // a workgroup places tiles or does the tensor's end
-  PlaceListShared place;
-  __attribute__((aligned(16))) unsigned char tail[sizeof(PlaceShared) + 16 + kTailLdsBytes];
+  typedef typename std::conditional<LIST, PlaceListShared, PlaceShared<WAVES>>::type Place;
+  Place place;
+  __attribute__((aligned(16))) unsigned char tail[(sizeof(PlaceShared<WAVES>) + 15) / 16 * 16 + kTailLdsBytes];
 };
 
 // block: of kPlaceTiles tiles (kSumTiles of a long tensor), or the one behind the last: the tensor's end
-__device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t block, uint32_t epoch, PlaceLds& lds) {
+// WAVES: of the workgroup.  DIRECT, WIDE: blocks of kPlaceTiles resp. kSumTiles tiles.  TOPK: tensors of that mode too
+template <int WAVES, bool DIRECT, bool WIDE, bool TOPK>
+__device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t block, uint32_t epoch, PlaceLds<WAVES, WIDE>& lds) {
   const bool from_sums = d.from_sums != 0u;
-  const bool topk = d.mode == kModeTopk;
+  const bool topk = TOPK && d.mode == kModeTopk;
   // TOPK: regular counts everywhere (the usual case): the compression kernel has placed everything already
   const bool regular = topk && __hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch;
-  const bool wide = d.place_per == (uint32_t)kSumTiles;
+  const bool wide = WIDE && (!DIRECT || d.place_per == (uint32_t)kSumTiles);
   const uint32_t per = wide ? (uint32_t)kSumTiles : (uint32_t)kPlaceTiles;
   const uint32_t blocks = (d.n_tiles + per - 1u) / per;
   if (block >= blocks) {
     if (d.tail == 0u || block != blocks) return;
-    const uint32_t before = regular ? d.topk * (uint32_t)(d.numel >> d.lgs) : outliers_before(d, d.n_tiles, from_sums, lds.place);
-    compress_tail(d, before, lds.tail + sizeof(PlaceShared));  // (the sums above went through the words before)
+    compress_tail<WAVES>(d, regular, lds.place, lds.tail + (sizeof(PlaceShared<WAVES>) + 15) / 16 * 16);  // (the sums go through the words before)
     return;
   }
   if (regular) return;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const PlacedTiles p = wide ? place_tiles<kSumTiles>(d, block * per, per, false, 0u, from_sums, !topk, lds.place)
-                             : place_tiles<kPlaceTiles>(d, block * per, per, false, 0u, false, !topk, lds.place);
+  PlacedTiles p;
+  if constexpr (WIDE && DIRECT) {
+    p = wide ? place_tiles<kSumTiles, WAVES>(d, block * per, per, false, 0u, from_sums, !topk, lds.place)
+             : place_tiles<kPlaceTiles, WAVES>(d, block * per, per, false, 0u, false, !topk, lds.place);
+  } else if constexpr (WIDE) {
+    p = place_tiles<kSumTiles, WAVES>(d, block * per, per, false, 0u, from_sums, !topk, lds.place);
+  } else {
+    p = place_tiles<kPlaceTiles, WAVES>(d, block * per, per, false, 0u, false, !topk, lds.place);
+  }
   const uint32_t room = topk ? 0u : (uint32_t)kSlot;
   if (__builtin_amdgcn_ballot_w64(p.count > room) == 0ull) return;  // the usual case: every tile is in its slot
-  const uint32_t j = wide ? 0u : wave, step = wide ? 1u : (uint32_t)(kPlaceThreads / kWave);
+  const uint32_t j = wide ? 0u : wave, step = wide ? 1u : (uint32_t)WAVES;
   const bool e8 = (d.variant & 1u) != 0u;
   switch (d.variant >> 3) {
     case kModeAbs:
@@ -92,12 +107,14 @@ __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t blo
       else reselect_tiles<kModeStd, 4, false, false>(d, p, room, j, step);
       break;
     case kModeTopk:
-      if (topk_whole(d)) {
-        if (e8) reselect_tiles<kModeTopk, 8, false, true>(d, p, room, j, step);
-        else reselect_tiles<kModeTopk, 4, false, true>(d, p, room, j, step);
-      } else {
-        if (e8) reselect_tiles<kModeTopk, 8, false, false>(d, p, room, j, step);
-        else reselect_tiles<kModeTopk, 4, false, false>(d, p, room, j, step);
+      if constexpr (TOPK) {
+        if (topk_whole(d)) {
+          if (e8) reselect_tiles<kModeTopk, 8, false, true>(d, p, room, j, step);
+          else reselect_tiles<kModeTopk, 4, false, true>(d, p, room, j, step);
+        } else {
+          if (e8) reselect_tiles<kModeTopk, 8, false, false>(d, p, room, j, step);
+          else reselect_tiles<kModeTopk, 4, false, false>(d, p, room, j, step);
+        }
       }
       break;
     default: break;
@@ -106,33 +123,45 @@ __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t blo
 
 // single tensor: blockIdx.x is the block of tiles
 __global__ __launch_bounds__(kPlaceThreads) void place_sum_kernel(TensorDesc d) {
-  __shared__ PlaceShared sh;
+  __shared__ PlaceShared<kPlaceThreads / kWave> sh;
   place_sum_block(d, blockIdx.x, sh);
 }
 
-// The selection code for tiles that have to be looked at again (rare) would take 173 registers and leave room
+// The selection code for tiles that have to be looked at again would take 173 registers and leave room
 // for two wavefronts per SIMD; the kernel is a chain of dependent memory round trips, so it is held to 128.
 __global__ __launch_bounds__(kPlaceThreads, 4) void place_kernel(TensorDesc d, uint32_t epoch) {
-  __shared__ PlaceLds lds;
-  place_dispatch(d, blockIdx.x, epoch, lds);
+  constexpr int WAVES = kPlaceThreads / kWave;
+  __shared__ PlaceLds<WAVES, true> lds;
+  place_dispatch<WAVES, true, true, true>(d, blockIdx.x, epoch, lds);
+}
+// ABS and STD up to kPlaceDirectTiles tiles: sixteen wavefronts to a workgroup's 64 tiles, so that those whose slot is too
+// small are selected again four after the other and not sixteen, each of them a load from memory and some 600 instructions
+// by a wavefront alone.  ([8192, 4096] int8, the placement: STD at 3 sigma over groups of 64 of GELU values, every tile with more
+// than 64 outliers, 50.4 -> 25.4 us; over 512 of SiLU values 41.8 -> 20.8.  With 256 threads as well where no tile has that many: 64
+// tiles 3.7 -> 2.6 us, 9955 tiles 4.7 -> 4.0.)  TOPK, where this launch finds nothing to do, keeps the smaller workgroups.
+__global__ __launch_bounds__(kPlaceManyThreads) void place_many_kernel(TensorDesc d, uint32_t epoch) {
+  constexpr int WAVES = kPlaceManyThreads / kWave;
+  __shared__ PlaceLds<WAVES, false> lds;
+  place_dispatch<WAVES, true, false, false>(d, blockIdx.x, epoch, lds);
 }
 
 // a group of tensors of a table: blockIdx.y picks the tensor, blockIdx.x its block of tiles
 __global__ __launch_bounds__(kPlaceThreads) void place_sum_batch_kernel(const TensorDesc* table, const uint32_t* members) {
-  __shared__ PlaceShared sh;
+  __shared__ PlaceShared<kPlaceThreads / kWave> sh;
   const TensorDesc d = table[members[blockIdx.y]];
   if (blockIdx.x < (d.n_tiles + (uint32_t)kSumTiles - 1u) / (uint32_t)kSumTiles) place_sum_block(d, blockIdx.x, sh);
 }
 
 __global__ __launch_bounds__(kPlaceThreads, 4) void place_batch_kernel(const TensorDesc* table, const uint32_t* members,
                                                                     uint32_t epoch) {
-  __shared__ PlaceLds lds;
+  constexpr int WAVES = kPlaceThreads / kWave;
+  __shared__ PlaceLds<WAVES, true> lds;
   const TensorDesc d = table[members[blockIdx.y]];
-  place_dispatch(d, blockIdx.x, epoch, lds);
+  place_dispatch<WAVES, true, true, true>(d, blockIdx.x, epoch, lds);
 }
 
 PlaceSumFn place_sum_fn() { return place_sum_kernel; }
-PlaceFn place_fn() { return place_kernel; }
+PlaceFn place_fn(bool many) { return many ? place_many_kernel : place_kernel; }
 PlaceSumBatchFn place_sum_batch_fn() { return place_sum_batch_kernel; }
 PlaceBatchFn place_batch_fn() { return place_batch_kernel; }
 
