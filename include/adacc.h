@@ -111,8 +111,8 @@ typedef struct adacc_layout {
 int adacc_layout_of(const adacc_method *method, uint64_t numel, adacc_layout *out);
 
 /* ---- workspace ----
- * Compression with outliers takes every tile on its own (no tile waits for another) and settles the
- * order of the outlier stream afterwards, in a second, small kernel.  Between the two, the number
+ * Compression with outliers takes every tile on its own (no tile waits for another; short tensors: see ADACC_SHORT_BYTES) and
+ * settles the order of the outlier stream afterwards, in a second, small kernel.  Between the two, the number
  * of outliers of every tile (4 bytes per tile) and, for ADACC_OUTLIER_ABS / _STD, the outliers
  * themselves (a slot of 256 bytes per tile) wait in a caller-owned device buffer described by an
  * adacc_workspace.  The struct is HOST memory owned by the caller; the library keeps a launch
@@ -126,8 +126,13 @@ typedef struct adacc_workspace {
   void *device_mem; /* caller-owned device buffer, 256-byte aligned            */
   uint64_t bytes;   /* its size                                                */
   uint32_t epoch;   /* launches since the last clear; maintained by the library */
-  uint32_t reserved;
+  uint32_t reserved; /* maintained by the library: 1 while no call has used the last ADACC_SHORT_BYTES */
 } adacc_workspace;
+
+/* With at least this much room behind adacc_workspace_bytes, and outside of graph capture, adacc_compress takes a short tensor
+ * in one launch: its workgroups tell each other the number of their outliers through words at the end of the workspace.  The blob
+ * is the same. */
+#define ADACC_SHORT_BYTES 12288
 
 /* Bytes of device memory a workspace needs for this tensor (0 for ADACC_OUTLIER_NONE / NOOP). */
 uint64_t adacc_workspace_bytes(const adacc_method *method, uint64_t numel);

@@ -303,6 +303,7 @@ def compress(method: Method, src, blob, workspace=None, numel=None, stream=None)
                                 _stream(stream)), "adacc_compress")
 
 
+SHORT_BYTES = 12288  # ADACC_SHORT_BYTES
 NOALLOC_MAX_NUMEL = 1 << 27
 
 
@@ -532,9 +533,9 @@ def alloc_blob(method: Method, numel: int, device="cuda"):
 
 
 def alloc_workspace(nbytes: int, device="cuda", stream=None) -> Workspace:
-    """A cleared workspace of at least nbytes."""
+    """A cleared workspace of at least nbytes, with the room for compressions of short tensors in one launch behind them."""
     import torch
-    buf = torch.empty(max((int(nbytes) + 255) // 256 * 256, 512), dtype=torch.uint8, device=device)
+    buf = torch.empty(max((int(nbytes) + 255) // 256 * 256, 512) + SHORT_BYTES, dtype=torch.uint8, device=device)
     return Workspace(buf, stream)
 
 

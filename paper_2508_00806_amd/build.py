@@ -12,6 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 PER_FORMAT = (
     "adacc_k_batch4.hip", "adacc_k_batch8.hip",
     "adacc_k_none.hip", "adacc_k_abs.hip", "adacc_k_std.hip", "adacc_k_topk.hip",  # compress, per outlier mode
+    "adacc_k_short_abs.hip", "adacc_k_short_std.hip", "adacc_k_short_topk.hip",  # short tensors, in one launch
     "adacc_k_decompress.hip",
     "adacc_k_place.hip",      # placement of the outliers in the stream, the end of a tensor that the groups do not divide
     "adacc_k_generic.hip",    # fallback for group sizes that are no powers of two or exceed 4096
@@ -28,7 +29,8 @@ SOURCES = ([(os.path.join(CSRC, f), suffix, flags) for f in PER_FORMAT for suffi
            [(os.path.join(CSRC, f), "", ()) for f in ONCE])
 HEADERS = [os.path.join(CSRC, f) for f in ("adacc_common.hpp", "adacc_dtype.hpp", "adacc_compress.hpp",
                                            "adacc_decompress.hpp", "adacc_kernels.hpp", "adacc_fn.hpp",
-                                           "adacc_channel.hpp", "adacc_generic.hpp", "adacc_long.hpp")]
+                                           "adacc_channel.hpp", "adacc_generic.hpp", "adacc_long.hpp",
+                                           "adacc_tail.hpp", "adacc_short.hpp")]
 HEADERS.append(os.path.join(ROOT, "include", "adacc.h"))
 OBJDIR = os.path.join(HERE, "_build")
 

@@ -89,10 +89,11 @@ struct Knobs {
   int grid_rounds;      // ADACC_GRID_ROUNDS: rounds of resident workgroups in the grid of a kernel that loops over tiles
   int wgs_per_cu;       // ADACC_WGS_PER_CU: overrides the occupancy query behind that limit
   int mask_wgs_per_cu;  // ADACC_MASK_WGS_PER_CU: grid of the mask kernels
+  int short_polls;      // ADACC_SHORT_POLLS: looks at a workgroup's count before its tiles are counted again (adacc_short.hpp)
 };
 static const Knobs& knobs() {
   static const Knobs k = {env_int("ADACC_GRID_ROUNDS", 0), env_int("ADACC_WGS_PER_CU", 0),
-                          env_int("ADACC_MASK_WGS_PER_CU", 128)};
+                          env_int("ADACC_MASK_WGS_PER_CU", 128), env_int("ADACC_SHORT_POLLS", 1 << 16)};
   return k;
 }
 
@@ -417,6 +418,23 @@ static CompressFn compress_fn(const adacc_method* m, bool e8, bool rowwise, bool
 
 static int clear_device(void* mem, uint64_t bytes, hipStream_t s);
 
+// The words of the one-launch compression lie at the end of a workspace, behind what any other call has used of it so far:
+// only those launches write them, so that a word which names the current epoch was written by this launch.  The host struct says
+// whether that still holds; a call that needs the whole workspace ends it.
+constexpr uint32_t kShortWordsOurs = 1;
+static_assert(kShortBytes == ADACC_SHORT_BYTES, "adacc.h says how much room that is");
+static uint64_t short_words_off(const adacc_workspace* ws) { return (ws->bytes - kShortBytes) & ~255ull; }
+static void use_workspace(adacc_workspace* ws, uint64_t bytes) {
+  if (ws->reserved == kShortWordsOurs && bytes > short_words_off(ws)) ws->reserved = 0;
+}
+// A launch that is being captured would be replayed with the same epoch.
+static bool captured(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Next epoch of a workspace; clears the buffer first when the counter is about to wrap.
 static int next_epoch(adacc_workspace* ws, hipStream_t s, uint32_t* epoch) {
   if (ws->epoch >= kEpochMax) {
@@ -634,7 +652,7 @@ int adacc_workspace_init(adacc_workspace* ws, void* device_mem, uint64_t bytes, 
   ws->device_mem = device_mem;
   ws->bytes = bytes;
   ws->epoch = 0;
-  ws->reserved = 0;
+  ws->reserved = bytes >= kShortBytes ? kShortWordsOurs : 0;
   return ADACC_OK;
 }
 
@@ -676,6 +694,22 @@ static uint32_t residency_lds(const adacc_method* m, const Plan& p) {
   return general && p.n_tiles >= kStreamTiles ? 24320u : 0u;  // (19 of the 128 pieces of 1280 bytes)
 }
 
+static CompressShortFn compress_short_fn(const adacc_method* m, const Plan& p) {
+  const bool e8 = p.tile_elems == 4096;
+  switch (m->outlier_mode) {
+    case ADACC_OUTLIER_ABS: return ADACC_PICK(p.half, compress_short_fn_abs(e8, p.rowwise));
+    case ADACC_OUTLIER_STD: return ADACC_PICK(p.half, compress_short_fn_std(e8, p.rowwise));
+    default: return ADACC_PICK(p.half, compress_short_fn_topk(e8, topk_whole_tile(m, p), topk_in_rows(m, p)));
+  }
+}
+static bool in_one_launch(const adacc_method* m, const Plan& p) {
+  if (p.generic) return false;
+  const uint32_t workgroups = blocks_of(p.n_tiles, kWavesPerWg);
+  // TOPK of more outliers a tile than its record holds would be selected twice
+  if (m->outlier_mode == ADACC_OUTLIER_TOPK) return workgroups <= kShortWorkgroupsTopk && m->topk * (p.tile_elems / m->stat_group) <= (uint32_t)kSlot;
+  return workgroups <= (p.rowwise ? kShortWorkgroupsRows : kShortWorkgroups);
+}
+
 static int compress_one(const adacc_method* method, const void* src, uint64_t numel, void* blob, uint64_t blob_bytes,
                         adacc_workspace* ws, void* hip_stream) {
   if (!method) return ADACC_ENULL;
@@ -696,6 +730,7 @@ static int compress_one(const adacc_method* method, const void* src, uint64_t nu
   int cus = 0;
   rc = device_cus(&cus);  // also: fail here, before any state changes, when there is no device
   if (rc != ADACC_OK) return rc;
+  if (p.outliers) use_workspace(ws, ws_plan(method, p).bytes);
   TensorDesc d;
   fill_desc(method, numel, p, L, src, blob, nullptr, p.outliers ? ws->device_mem : nullptr, &d);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -706,6 +741,15 @@ static int compress_one(const adacc_method* method, const void* src, uint64_t nu
       if (rc != ADACC_OK) return rc;
     }
     return launch_generic_compress(method, p, d, epoch, s);
+  }
+  if (p.outliers && ws->reserved == kShortWordsOurs && in_one_launch(method, p) && !captured(s)) {
+    uint32_t epoch = 0;
+    rc = next_epoch(ws, s, &epoch);
+    if (rc != ADACC_OK) return rc;
+    unsigned long long* words = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(ws->device_mem) + short_words_off(ws));
+    hipLaunchKernelGGL(compress_short_fn(method, p), dim3(blocks_of(p.n_tiles, kWavesPerWg) + (p.tail != 0 ? 1u : 0u)), dim3(kThreads), 0, s, d,
+                       epoch, words, (uint32_t)knobs().short_polls);
+    return launch_check("compress_short_kernel");
   }
   CompressFn fn = compress_fn(method, p.tile_elems == 4096, p.rowwise || topk_in_rows(method, p), topk_whole_tile(method, p));
   const uint32_t grid = blocks_of(tile_waves(p), kWavesPerWg);  // one tile per wavefront
@@ -736,7 +780,7 @@ int adacc_compress(const adacc_method* method, const void* src, uint64_t numel, 
 
 // ---- the same for callers that cannot allocate: the workspace is a device array of the library
 constexpr uint64_t kNoallocScratchBytes = 24ull << 20;
-static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes + kShortBytes];
 
 int adacc_compress_noalloc(const adacc_method* method, const void* src, uint64_t numel, void* blob,
                            uint64_t blob_bytes, void* hip_stream) {
@@ -762,11 +806,12 @@ int adacc_compress_noalloc(const adacc_method* method, const void* src, uint64_t
     if (e != hipSuccess || !ptr) return hip_fail(e, "hipGetSymbolAddress(scratch)");
     // the flag word of a tensor must not hold a value that a later launch counter takes: cleared by a
     // kernel on the caller's stream before the first use
-    rc = clear_device(ptr, kNoallocScratchBytes, static_cast<hipStream_t>(hip_stream));
+    rc = clear_device(ptr, sizeof scratch, static_cast<hipStream_t>(hip_stream));
     if (rc != ADACC_OK) return rc;
     ws->device_mem = ptr;
-    ws->bytes = kNoallocScratchBytes;
+    ws->bytes = sizeof scratch;
     ws->epoch = 0;
+    ws->reserved = kShortWordsOurs;
   }
   return compress_one(method, src, numel, blob, blob_bytes, ws, hip_stream);
 }
@@ -903,6 +948,7 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
   group_launches(units, kind, &members, &places, kPlaceTogether);
   for (uint32_t j = n_listed; j < (uint32_t)members.size(); ++j) members[j] = place[members[j]];
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  use_workspace(ws, bp.bytes);
   uint32_t epoch = 0;
   rc = next_epoch(ws, s, &epoch);
   if (rc != ADACC_OK) return rc;
@@ -969,6 +1015,7 @@ int adacc_decompress_batch(uint32_t n, const adacc_method* methods, const void* 
   ordered.reserve(members.size());
   for (const uint32_t i : members) ordered.push_back(descs[i]);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  use_workspace(ws, bp.bytes);
   TensorDesc* dt = static_cast<TensorDesc*>(ws->device_mem);
   rc = upload_batch(ordered, std::vector<uint32_t>(), 0, dt, s);
   if (rc != ADACC_OK) return rc;

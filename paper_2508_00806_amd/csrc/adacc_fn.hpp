@@ -8,6 +8,7 @@ namespace adacc {
 
 typedef void (*CompressFn)(TensorDesc, uint32_t);
 typedef void (*DecompressFn)(TensorDesc, uint32_t);
+typedef void (*CompressShortFn)(TensorDesc, uint32_t, unsigned long long*, uint32_t);
 typedef void (*BatchCompressFn)(const TensorDesc*, uint32_t);
 typedef void (*BatchDecompressFn)(const TensorDesc*);
 typedef void (*PlaceSumFn)(TensorDesc);
@@ -46,6 +47,9 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   CompressFn compress_fn_abs(uint32_t bits, uint32_t asym, bool e8, bool rowwise);     \
   CompressFn compress_fn_std(uint32_t bits, uint32_t asym, bool e8, bool rowwise);     \
   CompressFn compress_fn_topk(uint32_t bits, uint32_t asym, bool e8, bool whole, bool rows); \
+  CompressShortFn compress_short_fn_abs(bool e8, bool rowwise);                        \
+  CompressShortFn compress_short_fn_std(bool e8, bool rowwise);                        \
+  CompressShortFn compress_short_fn_topk(bool e8, bool whole, bool rows);              \
   DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic);    \
   BatchCompressFn compress_batch_fn4(int kind);                                        \
   BatchCompressFn compress_batch_fn8(int kind);                                        \

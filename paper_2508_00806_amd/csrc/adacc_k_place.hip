@@ -1,61 +1,11 @@
 // The kernels that place the outliers in the stream (single tensor and batch): a workgroup per kPlaceTiles (kSumTiles) tiles
 // of one tensor, whatever the method (the choice of the selection code for tiles that have to be looked at again is a uniform
 // switch), and one more for the end of a tensor that its groups do not divide.
-#include "adacc_generic.hpp"
 #include "adacc_kernels.hpp"
+#include "adacc_tail.hpp"
 
 namespace adacc {
 namespace ADACC_DT_NS {
-
-// ---- the end of a tensor with outliers: d.tail elements behind d.numel, fewer than the larger group, at most one short
-// statistics group cut into quantisation groups the last of which may be short.  A segment of the fallback kernels
-// (they know short groups) of two octets per thread, done by a workgroup of its own next to those that place the
-// tiles' outliers; its own go behind those of the tiles.  (One wavefront in a launch behind the placement, with plain
-// loops over LDS arrays, took 14 us for 141 elements of a statistics group of 512, and 41 us for 1455 of one of 4096;
-// now it is hidden behind the placement.)
-constexpr int kTailOcts = 2;  // per thread: 4096 elements
-constexpr uint32_t kTailLdsBytes = kSegHeadBytes + 4u * (2u * kTailOcts * kSegThreads + 2u * 4096u / 8u);
-template <int WAVES>
-__device__ __forceinline__ void compress_tail(const TensorDesc& whole, bool regular, PlaceShared<WAVES>& sums, unsigned char* lds) {
-  TensorDesc d = whole;
-  d.tile_elems = d.gs;  // the segment is one statistics group
-  SegmentShared sh = segment_shared<kTailOcts>(lds, d.tile_elems, d.gq);
-  SegmentGeo g;
-  g.first_elem = d.numel;
-  g.cnt = d.tail;
-  g.octs = (d.tail + (uint32_t)kOct - 1u) / (uint32_t)kOct;
-  g.full = false;
-  uint32_t raw[kTailOcts][4], mask[kTailOcts], omag[kTailOcts];
-  const bool works = threadIdx.x < (uint32_t)kSegThreads;  // whole wavefronts
-  if (works) segment_load(d, g, raw);
-  // the counts of all tiles are asked for together with the elements, by every wavefront; those that have nothing else to do leave
-  uint32_t total_main = regular ? d.topk * (uint32_t)(d.numel >> d.lgs) : outliers_before<WAVES>(whole, d.n_tiles, d.from_sums != 0u, sums);
-  if (!works) return;
-#pragma unroll
-  for (int j = 0; j < kTailOcts; ++j) omag[j] = octet_magnitude(raw[j]);
-  segment_select<kTailOcts, kSegAny>(d, g, sh, raw, omag, mask);
-#pragma unroll
-  for (int j = 0; j < kTailOcts; ++j)
-    if (omag[j] >= kNonfiniteMag) mask[j] |= octet_nonfinite(raw[j]);
-  const uint32_t total = total_main + segment_emit(g, sh, raw, mask, StreamSink{d.idx, d.val}, total_main, d.cap);
-  if (threadIdx.x == 0u) {
-    if (d.n_tiles == 0u) d.tile_ptr[0] = 0u;
-    d.tile_ptr[d.n_tiles_all] = total;
-    d.status[0] = total; d.status[1] = total > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u;
-  }
-#pragma unroll
-  for (int j = 0; j < kTailOcts; ++j) {
-    if (mask[j] != 0u) {
-      clear_elements(raw[j], mask[j]);
-      omag[j] = octet_magnitude(raw[j]);
-    }
-  }
-  if (d.bits == 8u) {
-    if (d.asym) segment_quantise<8, true, kTailOcts>(d, g, sh, raw, omag); else segment_quantise<8, false, kTailOcts>(d, g, sh, raw, omag);
-  } else {
-    if (d.asym) segment_quantise<4, true, kTailOcts>(d, g, sh, raw, omag); else segment_quantise<4, false, kTailOcts>(d, g, sh, raw, omag);
-  }
-}
 
 template <int WAVES, bool LIST>
 union PlaceLds {  // a workgroup places tiles or does the tensor's end
@@ -77,7 +27,10 @@ __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t blo
   const uint32_t blocks = (d.n_tiles + per - 1u) / per;
   if (block >= blocks) {
     if (d.tail == 0u || block != blocks) return;
-    compress_tail<WAVES>(d, regular, lds.place, lds.tail + (sizeof(PlaceShared<WAVES>) + 15) / 16 * 16);  // (the sums go through the words before)
+    // the counts of all tiles are asked for together with the elements, by every wavefront (their sums go through the words before lds.tail's)
+    compress_tail<true>(d, [&] {
+      return regular ? d.topk * (uint32_t)(d.numel >> d.lgs) : outliers_before<WAVES>(d, d.n_tiles, from_sums, lds.place);
+    }, lds.tail + (sizeof(PlaceShared<WAVES>) + 15) / 16 * 16);
     return;
   }
   if (regular) return;

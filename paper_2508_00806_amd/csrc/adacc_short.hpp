@@ -1,0 +1,143 @@
+// Compression with outliers of a short tensor in one launch.
+//
+// The order of the outlier stream needs the number of outliers in all tiles before a tile's own.  For a tensor of up to
+// kShortWorkgroups workgroups those do not wait for a second kernel: every workgroup encodes its four tiles, keeps their
+// outliers in LDS, publishes their number in a word of the workspace, and looks at the words of the workgroups before it
+// until they are there.  A word carries the number of the launch (the workspace's epoch) beside the count, is written by
+// these launches alone, and says everything by itself, so nothing has to be cleared, and no other memory has to be ordered.
+//
+// No wait is without an end, whatever order workgroups are started in: a wavefront whose patience is at an end counts the
+// outliers of the missing tiles itself, from the source.  (Workgroups are started in the order of their numbers and nobody
+// waits for a later one, so that does not happen by itself.)
+#pragma once
+
+#include "adacc_compress.hpp"
+#include "adacc_tail.hpp"
+
+namespace adacc {
+namespace ADACC_DT_NS {
+
+struct ShortShared {
+  uint32_t record[kWavesPerWg][kSlot];  // a tile's outliers: number in the tile << 16 | value
+  uint32_t count[kWavesPerWg];          // a tile's outliers, how many
+  uint32_t part[kWavesPerWg];           // of the sum over the words
+};
+
+// Which of a tile's elements are outliers, once more from the source: how many, and those below `limit` to the stream.
+template <int MODE, int E, bool ROWWISE, bool WHOLE>
+__device__ __forceinline__ uint32_t select_tile(const TensorDesc& d, uint32_t tile, uint32_t pos, uint32_t limit) {
+  uint32_t raw[E][4];
+  load_tile<E, false>(d, tile, raw);
+  const TileGeo<E> g = tile_geo<E, false>(d, tile);
+  blank_tail<E>(g, raw);
+  constexpr bool ROWS = ROWWISE && MODE != (int)kModeTopk;  // (TOPK: the encoder by rows only knows how to store)
+  return encode_tile<MODE, 8, false, E, ROWS, WHOLE, false>(d, g, raw, tile, StreamSink{d.idx, d.val}, pos, limit);
+}
+
+// a1 .. a8 of a tile, its outliers to the wavefront's record
+template <int MODE, int BITS, bool ASYM, int E, bool ROWWISE, bool WHOLE>
+__device__ __forceinline__ uint32_t short_tile(const TensorDesc& d, uint32_t tile, uint32_t* record) {
+  uint32_t raw[E][4];
+  load_tile<E, WHOLE>(d, tile, raw);
+  const TileGeo<E> g = tile_geo<E, WHOLE>(d, tile);
+  if constexpr (!WHOLE) blank_tail<E>(g, raw);
+  return encode_tile<MODE, BITS, ASYM, E, ROWWISE, WHOLE, true>(d, g, raw, tile, SlotSink{record, tile * (uint32_t)(E * kRow)}, 0u, (uint32_t)kSlot);
+}
+
+// The outliers in the tiles of the first `n` workgroups, to every thread.
+template <int MODE, int E, bool ROWWISE, bool WHOLE>
+__device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint32_t n, uint32_t epoch, uint32_t patience,
+                                                       const unsigned long long* words, uint32_t (&part)[kWavesPerWg]) {
+  uint32_t sum = 0u;
+  for (uint32_t i0 = 0u; i0 < n; i0 += (uint32_t)kThreads) {  // uniform
+    const uint32_t i = i0 + threadIdx.x;
+    bool open = i < n;
+    for (uint32_t tries = 0u; __builtin_amdgcn_ballot_w64(open) != 0ull && tries < patience; ++tries) {  // uniform
+      if (tries != 0u) __builtin_amdgcn_s_sleep(1);
+      if (open) {
+        const unsigned long long w = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)(w >> 32) == epoch) {
+          sum += (uint32_t)w;
+          open = false;
+        }
+      }
+    }
+    for (uint64_t left = __builtin_amdgcn_ballot_w64(open); __builtin_expect(left != 0ull, 0); left &= left - 1ull) {  // uniform
+      const uint32_t lane = (uint32_t)__builtin_ctzll(left);
+      const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)i, (int)lane) * (uint32_t)kWavesPerWg;
+      uint32_t found = 0u;
+      for (uint32_t t = first; t < first + (uint32_t)kWavesPerWg && t < d.n_tiles; ++t) found += select_tile<MODE, E, ROWWISE, WHOLE>(d, t, 0u, 0u);
+      if ((uint32_t)lane_id() == lane) sum += found;
+    }
+  }
+  return block_sum_u32<kWavesPerWg>(sum, part);
+}
+
+// The fallback's registers are what bounds it; a short tensor does not fill the device anyway.
+template <int MODE, int E, bool ROWWISE, bool WHOLE>
+__global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc d, uint32_t epoch, unsigned long long* words, uint32_t patience) {
+  __shared__ union {
+    ShortShared tiles;
+    struct {
+      uint32_t part[kWavesPerWg];
+      __attribute__((aligned(16))) unsigned char rest[kTailLdsBytes];
+    } tail;
+  } lds;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t lane = (uint32_t)lane_id();
+  const uint32_t tile = blockIdx.x * kWavesPerWg + wave;
+  const uint32_t workgroups = (d.n_tiles + (uint32_t)kWavesPerWg - 1u) / (uint32_t)kWavesPerWg;
+  if (blockIdx.x == workgroups) {  // the end that the groups do not divide
+    compress_tail<false>(d, [&] {
+      return outliers_of_others<MODE, E, ROWWISE, WHOLE>(d, workgroups, epoch, patience, words, lds.tail.part);
+    }, lds.tail.rest);
+    return;
+  }
+  uint32_t found = 0u;
+  if (tile < d.n_tiles) {  // uniform
+    uint32_t* record = lds.tiles.record[wave];
+    if constexpr (!ROWWISE && !WHOLE) {  // (the codes' form is looked at behind the selection)
+      found = short_tile<MODE, kBitsAny, false, E, false, false>(d, tile, record);
+    } else {
+      switch (d.variant & 6u) {
+        case 0: found = short_tile<MODE, 4, false, E, ROWWISE, WHOLE>(d, tile, record); break;
+        case 2: found = short_tile<MODE, 4, true, E, ROWWISE, WHOLE>(d, tile, record); break;
+        case 4: found = short_tile<MODE, 8, false, E, ROWWISE, WHOLE>(d, tile, record); break;
+        default: found = short_tile<MODE, 8, true, E, ROWWISE, WHOLE>(d, tile, record); break;
+      }
+    }
+  }
+  if (lane == 0u) lds.tiles.count[wave] = found;
+  __syncthreads();
+  uint32_t all = 0u, before = 0u;
+#pragma unroll
+  for (uint32_t w = 0; w < (uint32_t)kWavesPerWg; ++w) {
+    before += w < wave ? lds.tiles.count[w] : 0u;
+    all += lds.tiles.count[w];
+  }
+  if (threadIdx.x == 0u)
+    __hip_atomic_store(words + blockIdx.x, (unsigned long long)epoch << 32 | all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t pos = before + outliers_of_others<MODE, E, ROWWISE, WHOLE>(d, blockIdx.x, epoch, patience, words, lds.tiles.part);
+  if (tile >= d.n_tiles) return;
+  if (lane == 0u) {
+    d.tile_ptr[tile] = pos;
+    if (tile + 1u == d.n_tiles) {  // the blob's last tile closes it, unless elements behind it still have to be added
+      const uint32_t n_out = pos + found;
+      if (d.n_tiles_all > d.n_tiles || d.tail == 0u) d.tile_ptr[d.n_tiles] = n_out;
+      if (d.tail == 0u) { d.status[0] = n_out; d.status[1] = n_out > d.cap ? 1u : 0u; d.status[2] = 0u; d.status[3] = 0u; }
+    }
+  }
+  if (found <= (uint32_t)kSlot) {  // uniform
+    if (lane < found && pos + lane < d.cap) {
+      const uint32_t r = lds.tiles.record[wave][lane];
+      d.idx[pos + lane] = (int32_t)(tile * (uint32_t)(E * kRow) + (r >> 16));
+      d.val[pos + lane] = (uint16_t)r;
+    }
+  } else {
+    const uint32_t end = pos + found;
+    select_tile<MODE, E, ROWWISE, WHOLE>(d, tile, pos, end < d.cap ? end : d.cap);
+  }
+}
+
+}  // namespace ADACC_DT_NS
+}  // namespace adacc

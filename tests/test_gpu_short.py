@@ -1,0 +1,86 @@
+"""Short tensors whose outliers are found, ordered and stored in one launch: against the oracle, against the two launches that a
+workspace without the room for it takes, and with the wavefronts counting for each other."""
+import os
+import subprocess
+import sys
+
+import pytest
+import torch
+
+import paper_2508_00806_amd as adacc
+from helpers import adacc_method, run_parity
+
+pytestmark = pytest.mark.gpu
+
+# (quantisation group, statistics group, mode, threshold, topk, tile): the encoder by rows, the general one over 4 and 8 rows, TOPK of every kind
+METHODS = [(64, 64, "std", 3.0, 0, 2048), (128, 512, "std", 2.5, 0, 2048), (256, 4096, "std", 2.5, 0, 4096), (512, 0, "abs", 1.5, 0, 2048),
+           (4096, 0, "abs", 2.0, 0, 4096), (64, 1024, "topk", 0.0, 4, 2048), (128, 128, "topk", 0.0, 1, 2048),
+           (128, 2048, "topk", 0.0, 5, 2048), (128, 4096, "topk", 0.0, 9, 4096), (4096, 4096, "topk", 0.0, 3, 4096)]
+
+
+def _case(gq, gs, mode, thresh, k, bits, asym):
+    return dict(bits=bits, quant_group=gq, asym=asym, outlier_mode=mode, stat_group=gs, thresh=thresh, topk=k)
+
+
+def _values(n, tile, g, dtype):
+    x = torch.randn(n, generator=g).to(dtype)
+    for t in (0, 4, 5):  # tiles with more than a record holds, and one with values that are not finite
+        x[t * tile:t * tile + 90] *= 20.0
+    x[-3:] = float("nan")
+    return x
+
+
+@pytest.mark.parametrize("tiles,rest", [(0, 40), (1, 0), (3, 0), (4, 0), (5, 61), (64, 0), (257, 30), (1023, 0)])
+@pytest.mark.parametrize("method", METHODS)
+def test_against_the_oracle(method, tiles, rest):
+    gq, gs, mode, thresh, k, tile = method
+    if tiles > 300 and tile == 4096:
+        tiles //= 2
+    for bits, asym, dtype in ((8, 0, torch.bfloat16), (4, 1, torch.float16)):
+        x = _values(tiles * tile + rest, tile, torch.Generator().manual_seed(tiles + gq), dtype)
+        print(f"[short] {method} tiles={tiles} rest={rest} bits={bits}", flush=True)
+        run_parity(x, _case(gq, gs, mode, thresh, k, bits, asym))
+
+
+def _compressed(m, x, ws):
+    lay = adacc.layout_of(m, x.numel())
+    blob = torch.zeros(lay.total_bytes, dtype=torch.uint8, device="cuda")
+    adacc.compress(m, x, blob, ws)
+    return blob
+
+
+@pytest.mark.parametrize("tiles", [768 * 4, 768 * 4 + 1, 1536 * 4, 1536 * 4 + 1])
+def test_the_same_as_in_two_launches(tiles):
+    """Both sides of the lines in the number of workgroups; one workspace for all calls, with calls that need all of it between."""
+    for gq, gs in ((64, 64), (64, 512)):
+        n = tiles * 2048
+        x = _values(n, 2048, torch.Generator().manual_seed(tiles), torch.bfloat16).cuda()
+        m = adacc_method(_case(gq, gs, "std", 3.0, 0, 8, 0), n // 8)
+        need = adacc.workspace_bytes(m, n)
+        exact = adacc.Workspace(torch.empty(need, dtype=torch.uint8, device="cuda"))  # no room: two launches
+        room = adacc.alloc_workspace(need)
+        want = _compressed(m, x, exact)
+        assert torch.equal(_compressed(m, x, room), want)
+        part = x[:2048 * 9 + 64 * 5]
+        mp = adacc_method(_case(gq, gs, "std", 3.0, 0, 8, 0), part.numel())
+        short = _compressed(mp, part, room)
+        assert room.c.reserved == 1
+        assert torch.equal(_compressed(mp, part, exact), short)
+        longer = adacc.Workspace(torch.empty(need + 256, dtype=torch.uint8, device="cuda"))
+        assert torch.equal(_compressed(mp, part, longer), short)
+        assert longer.c.reserved == 1
+        assert torch.equal(_compressed(m, x, longer), want)  # needs the words' place
+        assert longer.c.reserved == 0
+        assert torch.equal(_compressed(mp, part, longer), short)
+        for _ in range(3):  # other inputs through the same words
+            x = x.flip(0)
+            assert torch.equal(_compressed(m, x, room), _compressed(m, x, exact))
+
+
+def test_wavefronts_that_count_for_others():
+    """One look at the words, then the tiles that are missing are counted by the wavefront itself."""
+    code = ("import sys; sys.path[:0] = ['tests', '.']; import torch; import test_gpu_short as t\n"
+            "for m in t.METHODS:\n    t.test_against_the_oracle(m, 257, 30)\nprint('counted')")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, ADACC_SHORT_POLLS="1"), cwd=root, capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0 and "counted" in r.stdout, r.stderr[-2000:]
