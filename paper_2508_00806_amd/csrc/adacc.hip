@@ -21,11 +21,15 @@ namespace adacc {
 // The table of a batch and the member lists behind it reach the device as kernel arguments, a slice per launch: the
 // runtime copies kernel arguments when the launch is enqueued, so the host buffer may go away at once
 // and the host never waits for the stream (a copy from pageable memory would).
+// The slices come in sizes: the host writes all of a launch's arguments, word by word, across the bus to the device, and a launch
+// whose 4 KiB are mostly padding costs more than the kernels behind it.
 constexpr uint32_t kWordsPerUpload = 992;
-struct WordSlice { uint32_t w[kWordsPerUpload]; };
-static_assert(sizeof(WordSlice) <= 3968, "kernel arguments are limited to 4 KiB");
+template <uint32_t N>
+struct WordSlice { uint32_t w[N]; };
+static_assert(sizeof(WordSlice<kWordsPerUpload>) <= 3968, "kernel arguments are limited to 4 KiB");
 static_assert(sizeof(TensorDesc) % 4 == 0, "copied as 32-bit words");
-__global__ __launch_bounds__(kThreads) void words_upload_kernel(WordSlice slice, uint32_t* dst, uint32_t count) {
+template <uint32_t N>
+__global__ __launch_bounds__(kThreads) void words_upload_kernel(WordSlice<N> slice, uint32_t* dst, uint32_t count) {
   for (uint32_t i = threadIdx.x; i < count; i += kThreads) dst[i] = slice.w[i];
 }
 
@@ -454,6 +458,13 @@ static int launch_check(const char* what) {
 
 // The table to the start of the batch workspace and the member lists to their place behind it (two launches for each of
 // a batch of two layers, 4.5 us apiece, before they went up together).
+template <uint32_t N>
+static int upload_words(const uint32_t* words, uint32_t count, uint32_t* dst, hipStream_t s) {
+  WordSlice<N> slice;
+  std::memcpy(slice.w, words, count * sizeof(uint32_t));
+  hipLaunchKernelGGL(words_upload_kernel<N>, dim3(1), dim3(kThreads), 0, s, slice, dst, count);
+  return launch_check("words_upload_kernel");
+}
 static int upload_batch(const std::vector<TensorDesc>& table, const std::vector<uint32_t>& members, uint64_t members_off,
                         void* device_mem, hipStream_t s) {
   const size_t table_words = table.size() * sizeof(TensorDesc) / 4;
@@ -461,11 +472,11 @@ static int upload_batch(const std::vector<TensorDesc>& table, const std::vector<
   std::memcpy(words.data(), table.data(), table.size() * sizeof(TensorDesc));
   if (!members.empty()) std::memcpy(words.data() + members_off / 4, members.data(), members.size() * 4);
   for (size_t i = 0; i < words.size(); i += kWordsPerUpload) {
-    WordSlice slice;
     const uint32_t count = (uint32_t)std::min<size_t>(kWordsPerUpload, words.size() - i);
-    std::memcpy(slice.w, words.data() + i, count * sizeof(uint32_t));
-    hipLaunchKernelGGL(words_upload_kernel, dim3(1), dim3(kThreads), 0, s, slice, static_cast<uint32_t*>(device_mem) + i, count);
-    const int rc = launch_check("words_upload_kernel");
+    uint32_t* dst = static_cast<uint32_t*>(device_mem) + i;
+    const uint32_t* from = words.data() + i;
+    const int rc = count <= 128u ? upload_words<128>(from, count, dst, s) : count <= 256u ? upload_words<256>(from, count, dst, s)
+                   : count <= 512u ? upload_words<512>(from, count, dst, s) : upload_words<kWordsPerUpload>(from, count, dst, s);
     if (rc != ADACC_OK) return rc;
   }
   return ADACC_OK;
@@ -496,6 +507,9 @@ static BatchPlan batch_plan(uint32_t n_active, uint64_t region_bytes) {
 // The block sums and the placement of a batch are one launch each up to this many workgroups, two tensors of 44032 tiles
 // next to four of 8192 for instance: a workgroup without tiles leaves at once, at about 2 ns, a launch takes 4.5 us.
 constexpr uint64_t kPlaceTogether = 8192;
+// Tiles and pieces of tensors of unequal sizes go in one launch up to this many wavefronts, 2048 workgroups of which as a rule fewer
+// than half have nothing to do: 1 to 2 us, where a launch takes 3.5 us of the host's time.
+constexpr uint64_t kTilesTogether = 8192;
 
 // A launch over a group of table entries: grid.y = the group's entries, grid.x covers the largest.
 struct GroupLaunch {
@@ -929,7 +943,7 @@ int adacc_compress_batch(uint32_t n, const adacc_method* methods, const void* co
     units[i] = descs[i].generic ? 0u : tile_waves(plans[origin[i]]);
     kind[i] = batch_kind(&methods[origin[i]], plans[origin[i]]) + (plans[origin[i]].half ? kBatchKinds : 0);
   }
-  group_launches(units, kind, &members, &tiles);
+  group_launches(units, kind, &members, &tiles, kTilesTogether);
   // The table goes up in the order of the tile launches' member lists, so that the tile kernels find the entry
   // of blockIdx.y at table + first_member without looking a number up first; the other kernels keep their lists.
   const uint32_t n_listed = (uint32_t)members.size();
@@ -1007,7 +1021,7 @@ int adacc_decompress_batch(uint32_t n, const adacc_method* methods, const void* 
     units[i] = descs[i].generic ? 0u : descs[i].n_tiles;  // pieces of 2048 elements
     kind[i] = plans[origin[i]].half ? kBatchKinds : 0;
   }
-  group_launches(units, kind, &members, &launches);
+  group_launches(units, kind, &members, &launches, kTilesTogether);
   // The table goes up in the order of the launches, so that the kernels find the entry of blockIdx.y at table +
   // first_member without looking a number up first.  (Tensors with groups that the batch kernel does not take are
   // launched one by one.)
