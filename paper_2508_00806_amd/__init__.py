@@ -124,6 +124,29 @@ class AdaccError(RuntimeError):
 
 
 _lib = None
+_calls = None  # csrc/adacc_calls.c, bound to the library's functions
+
+
+def calls():
+    """The native marshalling of the calls of inner loops; the same entry points as lib(), with fewer steps on the way."""
+    global _calls
+    if _calls is None:
+        import importlib.util
+        import torch
+        path = os.path.join(_HERE, "_calls.so")
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: run `python -m paper_2508_00806_amd.build` first")
+        spec = importlib.util.spec_from_file_location(__name__ + "._calls", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        L = lib()
+        module.bind(*[ctypes.cast(f, ctypes.c_void_p).value
+                      for f in (L.adacc_compress, L.adacc_decompress, L.adacc_mask_pack, L.adacc_mask_unpack, L.adacc_channel_compress,
+                                L.adacc_channel_decompress, L.adacc_channelwise_compress, L.adacc_channelwise_decompress)],
+                    torch.float32, torch.bfloat16, torch.float16, torch.cuda.is_initialized, torch._C._cuda_getDevice,
+                    torch._C._cuda_getCurrentRawStream, _stream)
+        _calls = module
+    return _calls
 
 
 def lib():
@@ -286,6 +309,7 @@ class Workspace:
         self.c = CWorkspace()
         _check(lib().adacc_workspace_init(ctypes.byref(self.c), _ptr(buffer), _nbytes(buffer), _stream(stream)),
                "adacc_workspace_init")
+        self.address = ctypes.addressof(self.c)
 
     @property
     def ref(self):
@@ -297,6 +321,13 @@ def _ws(workspace):
 
 
 def compress(method: Method, src, blob, workspace=None, numel=None, stream=None):
+    if type(method) is Method and (workspace is None or type(workspace) is Workspace):
+        try:
+            rc = calls().compress(method, src, blob, None if workspace is None else workspace.address, numel, stream)
+        except TypeError:  # (nothing was called) not what it marshals
+            pass
+        else:
+            return _check(rc, "adacc_compress")
     numel = src.numel() if numel is None else numel
     cm = method.c()
     _check(lib().adacc_compress(ctypes.byref(cm), _ptr(src), numel, _ptr(blob), _nbytes(blob), _ws(workspace),
@@ -316,7 +347,13 @@ def compress_noalloc(method: Method, src, blob, numel=None, stream=None):
 
 
 def decompress(method: Method, blob, dst, numel=None, stream=None):
-    import torch
+    if type(method) is Method:
+        try:
+            rc = calls().decompress(method, blob, dst, numel, stream)
+        except TypeError:
+            pass
+        else:
+            return _check(rc, "adacc_decompress")
     numel = dst.numel() if numel is None else numel
     dtype = _dst_dtype(dst, method.dtype)
     cm = method.c()
@@ -411,6 +448,13 @@ def channel_workspace_bytes(tokens: int, hidden: int) -> int:
 
 
 def channel_compress(method: ChannelMethod, src, tokens: int, hidden: int, blob, workspace, stream=None):
+    if type(method) is ChannelMethod:
+        try:
+            rc = calls().channel_compress(method, src, tokens, hidden, blob, workspace, stream)
+        except TypeError:
+            pass
+        else:
+            return _check(rc, "adacc_channel_compress")
     cm = method.c()
     _check(lib().adacc_channel_compress(ctypes.byref(cm), _ptr(src), tokens, hidden, _ptr(blob), _nbytes(blob),
                                         _ptr(workspace), _nbytes(workspace), _stream(stream)),
@@ -418,7 +462,13 @@ def channel_compress(method: ChannelMethod, src, tokens: int, hidden: int, blob,
 
 
 def channel_decompress(method: ChannelMethod, blob, tokens: int, hidden: int, dst, stream=None):
-    import torch
+    if type(method) is ChannelMethod:
+        try:
+            rc = calls().channel_decompress(method, blob, tokens, hidden, dst, stream)
+        except TypeError:
+            pass
+        else:
+            return _check(rc, "adacc_channel_decompress")
     dtype = _dst_dtype(dst, method.dtype)
     cm = method.c()
     _check(lib().adacc_channel_decompress(ctypes.byref(cm), _ptr(blob), _nbytes(blob), tokens, hidden, _ptr(dst),
@@ -481,6 +531,12 @@ def channelwise_workspace_bytes(tokens: int, hidden: int) -> int:
 def channelwise_compress(bits: int, src, tokens: int, hidden: int, blob, workspace, scale_rule=SCALE_PAPER, stream=None):
     import torch
     dtype = DTYPE_F16 if getattr(src, "dtype", None) == torch.float16 else DTYPE_BF16
+    try:
+        rc = calls().channelwise_compress(bits, scale_rule, dtype, src, tokens, hidden, blob, workspace, stream)
+    except TypeError:
+        pass
+    else:
+        return _check(rc, "adacc_channelwise_compress")
     _check(lib().adacc_channelwise_compress(bits, scale_rule, dtype, _ptr(src), tokens, hidden, _ptr(blob), _nbytes(blob),
                                             _ptr(workspace), _nbytes(workspace), _stream(stream)),
            "adacc_channelwise_compress")
@@ -492,6 +548,12 @@ def channelwise_decompress(bits: int, blob, tokens: int, hidden: int, dst, strea
         raise TypeError("dst must be bfloat16, float16 or float32")
     fmt = DTYPE_F16 if dst.dtype == torch.float16 else DTYPE_BF16
     dtype = DST_F32 if dst.dtype == torch.float32 else DST_16
+    try:
+        rc = calls().channelwise_decompress(bits, fmt, blob, tokens, hidden, dst, dtype, stream)
+    except TypeError:
+        pass
+    else:
+        return _check(rc, "adacc_channelwise_decompress")
     _check(lib().adacc_channelwise_decompress(bits, fmt, _ptr(blob), _nbytes(blob), tokens, hidden, _ptr(dst), dtype,
                                               _stream(stream)), "adacc_channelwise_decompress")
 
@@ -512,6 +574,12 @@ def mask_packed_bytes(n: int) -> int:
 
 def mask_pack(mask, bits, n=None, stream=None):
     """mask: bool / uint8 tensor of n elements; bits: uint8 tensor of at least mask_packed_bytes(n)."""
+    try:
+        rc = calls().mask_pack(mask, bits, n, stream)
+    except TypeError:
+        pass
+    else:
+        return _check(rc, "adacc_mask_pack")
     n = mask.numel() if n is None else n
     if _nbytes(bits) < mask_packed_bytes(n) or _nbytes(mask) < n:
         raise AdaccError(ESIZE, "adacc_mask_pack")
@@ -519,6 +587,12 @@ def mask_pack(mask, bits, n=None, stream=None):
 
 
 def mask_unpack(bits, mask, n=None, stream=None):
+    try:
+        rc = calls().mask_unpack(mask, bits, n, stream)
+    except TypeError:
+        pass
+    else:
+        return _check(rc, "adacc_mask_unpack")
     n = mask.numel() if n is None else n
     if _nbytes(bits) < mask_packed_bytes(n) or _nbytes(mask) < n:
         raise AdaccError(ESIZE, "adacc_mask_unpack")

@@ -2,10 +2,12 @@
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libadacc.so")
+CALLS = os.path.join(HERE, "_calls.so")  # the Python binding's marshalling of the calls (plain C, no HIP)
 CSRC = os.path.join(HERE, "csrc")
 # one translation unit per group of kernel instantiations, so that the library builds in parallel
 # Sources that touch the tensor's elements are compiled once per 16-bit format (bf16; binary16 with -DADACC_F16=1).
@@ -44,6 +46,15 @@ FLAGS = [
 ]
 
 
+def build_calls(verbose: bool = False) -> str:
+    cmd = ["gcc", "-std=c11", "-O2", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "adacc_calls.c"), "-o", CALLS]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALLS
+
+
 def build(verbose: bool = False, extra=(), jobs: int = 8) -> str:
     from concurrent.futures import ThreadPoolExecutor
     os.makedirs(OBJDIR, exist_ok=True)
@@ -59,6 +70,7 @@ def build(verbose: bool = False, extra=(), jobs: int = 8) -> str:
         subprocess.run(cmd, check=True)
         return obj
 
+    build_calls(verbose)
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES)))) as pool:
         objs = list(pool.map(compile_one, SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
