@@ -97,7 +97,7 @@ struct Knobs {
 };
 static const Knobs& knobs() {
   static const Knobs k = {env_int("ADACC_GRID_ROUNDS", 0), env_int("ADACC_WGS_PER_CU", 0),
-                          env_int("ADACC_MASK_WGS_PER_CU", 128), env_int("ADACC_SHORT_POLLS", 1 << 16)};
+                          env_int("ADACC_MASK_WGS_PER_CU", 256), env_int("ADACC_SHORT_POLLS", 1 << 16)};
   return k;
 }
 
@@ -1266,8 +1266,9 @@ static int mask_launch(MaskFn fn, const void* in, uint64_t n, void* out, void* h
   int cus = 0;
   const int rc = device_cus(&cus);
   if (rc != ADACC_OK) return rc;
-  const uint64_t pieces = n / 16u;  // one lane turns over 16 elements at a time, eight times per round
-  uint64_t grid = (pieces + 8ull * kThreads - 1) / (8ull * kThreads);
+  const uint64_t pieces = n / 16u;  // one lane turns over 16 elements at a time, kMaskAhead times per round
+  constexpr uint64_t per = (uint64_t)kMaskAhead * kThreads;
+  uint64_t grid = (pieces + per - 1) / per;
   const uint64_t cap = (uint64_t)cus * (uint64_t)knobs().mask_wgs_per_cu;
   if (grid > cap) grid = cap;
   if (grid == 0) grid = 1;

@@ -145,6 +145,11 @@ struct ChannelwiseDesc {
   float divisor, inv_divisor;  // D of Eq. 2 and, when D is a power of two, 1/D (else 0)
 };
 
+// The mask kernels: 16-byte pieces of the byte format that a lane has in flight, one after the other 4 KiB apart.  (us both ways with
+// 8 / 6 / 4 / 2: 268 M elements 99.1 / 98.2 / 92.2 / 95.7, 134 M 50.9 / 51.1 / 49.4 / 50.7, 64 M 23.8 / 24.0 / 23.7 / 23.6, 34 M 13.6 /
+// 13.8 / 13.0 / 13.4: with more in flight a wavefront writes further apart from its neighbours.)
+constexpr int kMaskAhead = 4;
+
 // Outliers of a tile that travel through the tile's slot in the workspace (ABS / STD); a tile with
 // more is selected a second time by the placement kernel.
 constexpr int kSlot = 64;

@@ -18,14 +18,12 @@ __device__ __forceinline__ uint32_t nibble_to_bytes(uint32_t nib) {
   return (nib * 0x00204081u) & 0x01010101u;  // bit k lands on bit 8k; the other products fall between and are masked
 }
 
-constexpr int kMaskAhead = 8;  // 16-byte pieces per lane and round
-
 // A lane turns 16 mask bytes (one 16-byte load) into 16 bits; consecutive lanes take consecutive
 // pieces, so every load instruction of a wavefront covers 1 KiB without gaps and every store 128 bytes.
 __global__ __launch_bounds__(kThreads) void mask_pack_kernel(const uint8_t* __restrict__ mask, uint64_t n,
                                                              uint8_t* __restrict__ bits) {
   const uint64_t n_pieces = n / 16u;
-  // a workgroup takes kMaskAhead * 4 KiB of mask in one piece per round
+  // a workgroup takes kMaskAhead * 4 KiB of mask in one piece per round; the grid has a round's workgroups for all but very long masks
   constexpr uint64_t stride = kThreads;
   const uint64_t me = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   for (uint64_t p0 = (uint64_t)blockIdx.x * (kThreads * kMaskAhead) + threadIdx.x; p0 < n_pieces;
