@@ -352,7 +352,7 @@ static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, cons
   d->from_sums = needs_block_sums(m, p) ? 1u : 0u;
   d->place_per = p.outliers ? place_per(m, p) : 0u;
   d->lgt = p.tile_elems == 4096 ? 12u : 11u;
-  if (dst) {  // decompression counts pieces of 2048 elements of the whole tensor
+  if (dst) {  // decompression counts pieces of the whole tensor, 2048 elements as a rule (launch_decompress)
     d->numel = numel;
     d->tail = 0;
     d->n_tiles = decompress_pieces(numel);
@@ -830,10 +830,26 @@ int adacc_compress_noalloc(const adacc_method* method, const void* src, uint64_t
   return compress_one(method, src, numel, blob, blob_bytes, ws, hip_stream);
 }
 
+// rows of a piece, see full_piece_rows; at most 2^34 elements in small pieces: a grid has fewer than 2^32 threads
+static uint32_t piece_rows(const adacc_method* m, const Plan& p, uint64_t numel, bool f32) {
+  const uint32_t full = full_piece_rows(f32);
+  if (numel > (1ull << 34)) return full;
+  if (f32) return numel < (1ull << 25) ? full : p.outliers ? 4u : 2u;
+  if (p.generic) return full;
+  if (!p.outliers) return numel < (1ull << 26) ? full : 2u;
+  return m->outlier_mode != ADACC_OUTLIER_TOPK && numel >= (1ull << 28) ? 2u : full;
+}
 static int launch_decompress(const adacc_method* m, const Plan& p, const TensorDesc& d, int dst_dtype, hipStream_t s) {
-  DecompressFn fn = ADACC_PICK(p.half, decompress_fn(m->bits, m->asym, dst_dtype == ADACC_DST_F32, p.generic));
-  const uint32_t grid = (d.n_tiles + kWavesPerWg - 1) / kWavesPerWg;  // one piece per wavefront
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, s, d, p.outliers ? 1u : 0u);
+  const bool f32 = dst_dtype == ADACC_DST_F32;
+  const uint32_t rows = piece_rows(m, p, d.numel, f32), waves = (uint32_t)piece_waves((int)rows);
+  TensorDesc own = d;
+  if (rows != full_piece_rows(f32)) {
+    const uint32_t piece = rows * (uint32_t)kWave * (f32 ? 4u : 8u);
+    own.n_tiles = (uint32_t)((d.numel + piece - 1u) / piece);
+    own.ptr_shift += ilog2(2048u / piece);  // (the fallback kernels' tiles are found by division)
+  }
+  DecompressFn fn = ADACC_PICK(p.half, decompress_fn(m->bits, m->asym, f32, p.generic, rows));
+  hipLaunchKernelGGL(fn, dim3((own.n_tiles + waves - 1u) / waves), dim3(waves * (uint32_t)kWave), 0, s, own, p.outliers ? 1u : 0u);  // one piece per wavefront
   return launch_check("decompress_kernel");
 }
 

@@ -111,7 +111,7 @@ struct TensorDesc {
   uint32_t pow2_divisor;  // 1 when D is a power of two
   uint32_t rowwise;     // compress: 1 = every group lies inside a row (row-at-a-time encoder)
   uint32_t variant;     // index into the instantiation table
-  uint32_t ptr_shift;   // decompress: works on pieces of 2048 elements; piece u belongs to tile u >> ptr_shift
+  uint32_t ptr_shift;   // decompress: works on pieces of 2048 elements or fewer; piece u belongs to tile u >> ptr_shift
 };
 
 // Outlier channels (Section 3.2, Eq. 1): what those kernels need beside the TensorDesc of the quantised part.
@@ -144,6 +144,18 @@ struct ChannelwiseDesc {
   uint32_t strip_rows;   // decompress: tokens a wavefront takes
   float divisor, inv_divisor;  // D of Eq. 2 and, when D is a power of two, 1/D (else 0)
 };
+
+// The piece of a tensor that a wavefront restores: rows of 64 chunks of 8 elements (of 4 where the output is binary32), 2048 elements
+// as a rule.  Fewer in long tensors, where what all wavefronts write at a time lies closer together; a wavefront of a
+// piece looks through all outliers of its tile.  (us of a pass both ways.  Binary32, with outliers, 8 rows / 4 / 2: STD over 4096 at 4
+// sigma, 2^25 values 56.8 / 56.4 / 60.6, 2^27 189 / 177 / 201; the 4 largest of 4096, 2^27, 164 / 158 / 172; two in a hundred outliers, 2^27,
+// 338 / 329 / 350; below 2^25 equal or slower, 2^24 31.5 / 32.1 / 34.5.  Binary32 without, 2^25 int8 47.8 / 47.5 / 46.0, 2^27 177 / 182 / 168,
+// int4 160 / 166 / 155; 2^24 25.6 / 26.2 / 26.0.  16 bits without outliers, 4 rows / 2: 2^25 int8 36.2 / 36.6, 2^26 int4 58.4 / 57.2, 2^28 222 / 218
+// and int8 256 / 254; with ABS or STD: 2^27 142.6 / 141.3 and, two in a hundred outliers, 285 / 288, 2^28 270 / 265 and 444 / 447, 2^29 533 /
+// 517; TOPK equal.)
+constexpr uint32_t full_piece_rows(bool f32) { return f32 ? 8u : 4u; }
+// wavefronts of a workgroup (two rows: with four, 2^28 values int8 256.1 where two take 253.2)
+constexpr int piece_waves(int rows) { return rows == 2 ? 2 : kWavesPerWg; }
 
 // The mask kernels: 16-byte pieces of the byte format that a lane has in flight, one after the other 4 KiB apart.  (us both ways with
 // 8 / 6 / 4 / 2: 268 M elements 99.1 / 98.2 / 92.2 / 95.7, 134 M 50.9 / 51.1 / 49.4 / 50.7, 64 M 23.8 / 24.0 / 23.7 / 23.6, 34 M 13.6 /

@@ -9,8 +9,8 @@
 namespace adacc {
 namespace ADACC_DT_NS {
 
-// Decompression always works on pieces of 2048 elements of the flat tensor, one per wavefront, whatever
-// the tile of the blob and whatever the group sizes: a piece looks through the outliers of the tiles it touches and
+// Decompression works on pieces of the flat tensor, 2048 elements or, in long tensors, fewer (full_piece_rows), one per wavefront,
+// whatever the tile of the blob and whatever the group sizes: a piece looks through the outliers of the tiles it touches and
 // takes those that fall inside it.
 //
 // A complete piece takes its outliers into the output words in registers before they are stored, so nothing is
@@ -33,12 +33,13 @@ namespace ADACC_DT_NS {
 // a row of 11008 values in 5.4 rounds with a barrier before the outliers: [8192, 11008], int4, 70 us; 43 us now.)
 // What a lane takes at a time ("chunk"): as many consecutive elements as one 16-byte store holds, V = 8 of a 16-bit
 // output and V = 4 of a binary32 one, so that every store instruction of a wavefront covers 1 KiB without gaps.  A row
-// is the 64 chunks of one such instruction; a piece has 4 resp. 8 rows.  (With octets for both, a lane wrote its 32
+// is the 64 chunks of one such instruction; a piece has 4 resp. 8 rows, or fewer.  (With octets for both, a lane wrote its 32
 // bytes of binary32 in two stores 32 bytes apart from its neighbour's: 49.5 M values of int8 codes took 68 .. 74 us,
 // 3.4 TB/s; 46 us now, 5.3 TB/s.)
-constexpr int kPiece = 2048;
 template <bool F32>
 constexpr int chunk_elems() { return F32 ? 4 : 8; }
+template <bool F32, int ROWS>
+constexpr int piece_elems() { return ROWS * kWave * chunk_elems<F32>(); }
 
 template <int BITS, int V>
 struct RowCodes {
@@ -142,9 +143,10 @@ __device__ __forceinline__ void store_row_values(const TensorDesc& d, uint64_t e
 
 // What the kernels that call decompress_piece keep in LDS for every wavefront of the workgroup (17 KiB in all: eight
 // workgroups of a CU, as many as its wavefronts allow, fit).
+template <bool F32, int ROWS, int WAVES>
 struct DecompressShared {
-  uint4 picture[kWavesPerWg][kPiece / 8];  // 16-bit patterns of the piece; its first 1 or 2 KiB serve as the mailbox
-  uint32_t bits[kWavesPerWg][kWave];       // V bits per row: elements of lane l's chunk in that row that the picture holds
+  uint4 picture[WAVES][piece_elems<F32, ROWS>() / 8];  // 16-bit patterns of the piece; its first words serve as the mailbox
+  uint32_t bits[WAVES][kWave];                         // V bits per row: elements of lane l's chunk in that row that the picture holds
 };
 
 // floor(x / n) for x < 2^39 with the host's m = ceil(2^64 / n), 1 < n <= 2^11; m = 0 stands for n = 1
@@ -169,9 +171,9 @@ __device__ __forceinline__ void narrow_entries(const TensorDesc& d, uint64_t fir
   }
 }
 
-template <int BITS, bool ASYM, bool F32, bool GENERIC>
-__device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t piece, bool has_outliers, DecompressShared& shared) {
-  constexpr int V = chunk_elems<F32>(), E = kPiece / (kWave * V), W = kWave * V;  // W: elements of a row
+template <int BITS, bool ASYM, bool F32, bool GENERIC, int ROWS, int WAVES>
+__device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t piece, bool has_outliers, DecompressShared<F32, ROWS, WAVES>& shared) {
+  constexpr int V = chunk_elems<F32>(), E = ROWS, W = kWave * V, kPiece = piece_elems<F32, ROWS>();  // W: elements of a row
   const int lane = (int)__lane_id();
   const uint64_t base = (uint64_t)piece * (uint64_t)kPiece;
   const uint64_t lane_base = base + (uint64_t)(lane * V);
@@ -275,18 +277,14 @@ __device__ __forceinline__ void decompress_piece(const TensorDesc& d, uint32_t p
     const uint32_t prev = (uint32_t)__shfl_up((int)(rel / V), 1, kWave);
     if (p1 - p0 <= (uint32_t)kWave && __builtin_amdgcn_ballot_w64(valid && lane != 0 && rel / V == prev) == 0ull) {  // uniform
       uint32_t(*box)[E] = reinterpret_cast<uint32_t(*)[E]>(shared.picture[w]);
-      uint4* mine = reinterpret_cast<uint4*>(box[lane]);
 #pragma unroll
-      for (int i = 0; i < E / 4; ++i) mine[i] = make_uint4(0u, 0u, 0u, 0u);
+      for (int j = 0; j < E; ++j) box[lane][j] = 0u;
       lds_in_order();
       if (valid) box[(rel / V) & 63u][rel / W] = kMailFull | ((rel % V) << 16) | (o_val & 0xFFFFu);
       lds_in_order();
       uint32_t m[E];
 #pragma unroll
-      for (int i = 0; i < E / 4; ++i) {
-        const uint4 mail = mine[i];
-        m[4 * i] = mail.x; m[4 * i + 1] = mail.y; m[4 * i + 2] = mail.z; m[4 * i + 3] = mail.w;
-      }
+      for (int j = 0; j < E; ++j) m[j] = box[lane][j];
       lds_in_order();  // the next piece of this wavefront clears the mailbox only after this
 #pragma unroll
       for (int j = 0; j < E; ++j)

@@ -50,7 +50,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   CompressShortFn compress_short_fn_abs(bool e8, bool rowwise);                        \
   CompressShortFn compress_short_fn_std(bool e8, bool rowwise);                        \
   CompressShortFn compress_short_fn_topk(bool e8, bool whole, bool rows);              \
-  DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic);    \
+  DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic, uint32_t rows); \
   BatchCompressFn compress_batch_fn4(int kind);                                        \
   BatchCompressFn compress_batch_fn8(int kind);                                        \
   BatchDecompressFn decompress_batch_fn(bool f32);                                     \

@@ -5,13 +5,20 @@ namespace adacc {
 namespace ADACC_DT_NS {
 
 template <int BITS, bool ASYM>
-static DecompressFn pick(bool f32, bool generic) {
-  if (generic) return f32 ? decompress_kernel<BITS, ASYM, true, true> : decompress_kernel<BITS, ASYM, false, true>;
-  return f32 ? decompress_kernel<BITS, ASYM, true, false> : decompress_kernel<BITS, ASYM, false, false>;
+static DecompressFn pick(bool f32, bool generic, uint32_t rows) {
+  if (f32) {
+    switch (rows) {
+      case 2: return generic ? decompress_kernel<BITS, ASYM, true, true, 2> : decompress_kernel<BITS, ASYM, true, false, 2>;
+      case 4: return generic ? decompress_kernel<BITS, ASYM, true, true, 4> : decompress_kernel<BITS, ASYM, true, false, 4>;
+      default: return generic ? decompress_kernel<BITS, ASYM, true, true, 8> : decompress_kernel<BITS, ASYM, true, false, 8>;
+    }
+  }
+  if (rows == 2u) return generic ? decompress_kernel<BITS, ASYM, false, true, 2> : decompress_kernel<BITS, ASYM, false, false, 2>;
+  return generic ? decompress_kernel<BITS, ASYM, false, true, 4> : decompress_kernel<BITS, ASYM, false, false, 4>;
 }
-DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic) {
-  if (bits == 4) return asym ? pick<4, true>(f32, generic) : pick<4, false>(f32, generic);
-  return asym ? pick<8, true>(f32, generic) : pick<8, false>(f32, generic);
+DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic, uint32_t rows) {
+  if (bits == 4) return asym ? pick<4, true>(f32, generic, rows) : pick<4, false>(f32, generic, rows);
+  return asym ? pick<8, true>(f32, generic, rows) : pick<8, false>(f32, generic, rows);
 }
 
 BatchDecompressFn decompress_batch_fn(bool f32) {

@@ -40,16 +40,17 @@ __global__ __launch_bounds__(kThreads, (compress_min_waves<MODE, ASYM, E, WHOLE>
 // TOPK whose statistics group is the whole tile, with quantisation groups inside a row, has an encoder of its own
 __device__ __forceinline__ bool topk_whole(const TensorDesc& d) { return d.lgs == d.lgt && d.lgq <= 9u; }
 
-// d.n_tiles counts pieces of 2048 elements here
-template <int BITS, bool ASYM, bool F32, bool GENERIC>
-__global__ __launch_bounds__(kThreads) void decompress_kernel(TensorDesc d, uint32_t has_outliers) {
+// d.n_tiles counts pieces here
+template <int BITS, bool ASYM, bool F32, bool GENERIC, int ROWS>
+__global__ __launch_bounds__(piece_waves(ROWS) * kWave) void decompress_kernel(TensorDesc d, uint32_t has_outliers) {
+  constexpr int WAVES = piece_waves(ROWS);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // uniform, and the compiler shall know it
-  __shared__ DecompressShared shared;
-  const uint32_t piece = blockIdx.x * kWavesPerWg + wave;  // (no loop over pieces: it would cost 20 registers)
+  __shared__ DecompressShared<F32, ROWS, WAVES> shared;
+  const uint32_t piece = blockIdx.x * (uint32_t)WAVES + wave;  // (no loop over pieces: it would cost 20 registers)
   // what the first loads need is asked for together with n_tiles, one round trip to the kernel's arguments instead of two
   // (2^25 values of int8 codes: 15.3 -> 15.1 us from a blob in the caches, 15.7 -> 15.5 from memory)
   asm volatile("" ::"s"(d.codes), "s"(d.scales), "s"(d.zp), "s"(d.dst), "s"(d.numel), "s"(d.lgq));
-  if (piece < d.n_tiles) decompress_piece<BITS, ASYM, F32, GENERIC>(d, piece, has_outliers != 0u, shared);
+  if (piece < d.n_tiles) decompress_piece<BITS, ASYM, F32, GENERIC, ROWS, WAVES>(d, piece, has_outliers != 0u, shared);
 }
 
 // ---- batch
@@ -137,12 +138,13 @@ __global__ __launch_bounds__(kThreads) void decompress_batch_kernel(const Tensor
                "s"(d.idx), "s"(d.val), "s"(d.cap), "s"(d.per_tile), "s"(d.mode), "s"(d.ptr_shift));
   if (piece >= d.n_tiles) return;
   const bool ho = (d.variant >> 3) != kModeNone;
-  __shared__ DecompressShared shared;
+  constexpr int ROWS = (int)full_piece_rows(F32);
+  __shared__ DecompressShared<F32, ROWS, kWavesPerWg> shared;
   switch (d.variant & 6u) {
-    case 0: decompress_piece<4, false, F32, false>(d, piece, ho, shared); break;
-    case 2: decompress_piece<4, true, F32, false>(d, piece, ho, shared); break;
-    case 4: decompress_piece<8, false, F32, false>(d, piece, ho, shared); break;
-    default: decompress_piece<8, true, F32, false>(d, piece, ho, shared); break;
+    case 0: decompress_piece<4, false, F32, false, ROWS, kWavesPerWg>(d, piece, ho, shared); break;
+    case 2: decompress_piece<4, true, F32, false, ROWS, kWavesPerWg>(d, piece, ho, shared); break;
+    case 4: decompress_piece<8, false, F32, false, ROWS, kWavesPerWg>(d, piece, ho, shared); break;
+    default: decompress_piece<8, true, F32, false, ROWS, kWavesPerWg>(d, piece, ho, shared); break;
   }
 }
 
