@@ -194,13 +194,13 @@ constexpr uint32_t kPlaceDirectTiles = 32768;
 constexpr uint32_t kEpochMax = 0x3FFFFFFFu;
 // Tensors of at most this many workgroups of tiles (and one for the end) are compressed in one launch (adacc_short.hpp), a word of
 // 8 bytes for each at the end of a workspace that has the room: the general encoder, the encoder by rows, TOPK.  The lines lie where
-// the wait for the other workgroups begins to cost more than a launch; below them a call saves the launch on the host too.  (us both
-// ways, two launches / one, [rows, 1024] STD at 6 sigma over 1024: 128 rows 13.6 / 11.0, 4096 14.3 / 13.0, 12000 21.3 / 19.7, 16000
-// 25.9 / 26.8.  STD over 512, ragged, 4000 x 2051: 18.7 / 16.8, 12000 38.5 / 39.4.  By rows, [rows, 3072], STD at 8 sigma over 64: 2000
-// rows 13.5 / 12.8, 4000 18.2 / 20.2; softmax, ABS, [12000, 512] 17.6 / 16.1.  TOPK-4 of [rows, 4096]: 300 rows 13.1 / 10.8, 1000 13.4 /
-// 12.9, 1400 13.3 / 14.4; of [rows, 1024] 1600 13.4 / 11.1, 4800 13.4 / 13.5.  Where tiles have more outliers than a slot holds,
-// [2000, 3072] STD at 3 sigma over 64 of GELU values: 61.3 / 20.1.)
-constexpr uint32_t kShortWorkgroups = 1536, kShortWorkgroupsRows = 768, kShortWorkgroupsTopk = 256;
+// the wait for the other workgroups begins to cost as much as a launch.  (us both ways, two launches / one, [rows, 1024] STD at 6 sigma over
+// 1024: 20 rows 9.7 / 7.9, 128 10.0 / 8.7, 1024 11.1 / 10.3, 4096 13.3 / 12.9, 8000 16.8 / 16.1, 12000 21.3 / 19.7, 16000 25.9 / 26.8.  STD over
+// 512, ragged, [rows, 2051]: 50 rows 12.8 / 10.2, 1100 14.6 / 12.8, 4000 18.6 / 16.6, 12000 38.5 / 39.4.  By rows, [rows, 3072], STD at 8
+// sigma over 64: 2000 rows 13.5 / 12.8, 4000 18.2 / 20.2; softmax, ABS, [rows, 512], 1200 12.1 / 11.3, 12000 16.5 / 16.0, 16000 18.6 / 18.6.
+// TOPK, whose second launch has nothing to do: [20, 1024] 9.7 / 7.9, [26, 4096] 9.5 / 9.1, [300, 4096] 9.8 / 10.7, [1200, 1024] 9.7 / 10.5.
+// Where tiles have more outliers than a slot holds, STD at 3 sigma over 64 of GELU values: [20, 3072] 20.6 / 12.9, [1200, 3072] 33.2 / 17.3.)
+constexpr uint32_t kShortWorkgroups = 1536, kShortWorkgroupsRows = 768, kShortWorkgroupsTopk = 16;
 constexpr uint64_t kShortBytes = 8ull * kShortWorkgroups;
 
 // the batch compression kernels, by the weight of the variants they hold (adacc_kernels.hpp)

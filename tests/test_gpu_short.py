@@ -30,7 +30,7 @@ def _values(n, tile, g, dtype):
     return x
 
 
-@pytest.mark.parametrize("tiles,rest", [(0, 40), (1, 0), (3, 0), (4, 0), (5, 61), (64, 0), (257, 30), (1023, 0)])
+@pytest.mark.parametrize("tiles,rest", [(0, 40), (1, 0), (3, 0), (4, 0), (5, 61), (63, 30), (64, 0), (257, 30), (1023, 0)])
 @pytest.mark.parametrize("method", METHODS)
 def test_against_the_oracle(method, tiles, rest):
     gq, gs, mode, thresh, k, tile = method
