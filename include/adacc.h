@@ -132,7 +132,7 @@ typedef struct adacc_workspace {
 /* With at least this much room behind adacc_workspace_bytes, and outside of graph capture, adacc_compress takes a short tensor
  * in one launch: its workgroups tell each other the number of their outliers through words at the end of the workspace.  The blob
  * is the same. */
-#define ADACC_SHORT_BYTES 12288
+#define ADACC_SHORT_BYTES 20480
 
 /* Bytes of device memory a workspace needs for this tensor (0 for ADACC_OUTLIER_NONE / NOOP). */
 uint64_t adacc_workspace_bytes(const adacc_method *method, uint64_t numel);

@@ -334,7 +334,7 @@ def compress(method: Method, src, blob, workspace=None, numel=None, stream=None)
                                 _stream(stream)), "adacc_compress")
 
 
-SHORT_BYTES = 12288  # ADACC_SHORT_BYTES
+SHORT_BYTES = 20480  # ADACC_SHORT_BYTES
 NOALLOC_MAX_NUMEL = 1 << 27
 
 

@@ -711,9 +711,9 @@ static uint32_t residency_lds(const adacc_method* m, const Plan& p) {
 static CompressShortFn compress_short_fn(const adacc_method* m, const Plan& p) {
   const bool e8 = p.tile_elems == 4096;
   switch (m->outlier_mode) {
-    case ADACC_OUTLIER_ABS: return ADACC_PICK(p.half, compress_short_fn_abs(e8, p.rowwise));
-    case ADACC_OUTLIER_STD: return ADACC_PICK(p.half, compress_short_fn_std(e8, p.rowwise));
-    default: return ADACC_PICK(p.half, compress_short_fn_topk(e8, topk_whole_tile(m, p), topk_in_rows(m, p)));
+    case ADACC_OUTLIER_ABS: return ADACC_PICK(p.half, compress_short_fn_abs(e8));
+    case ADACC_OUTLIER_STD: return ADACC_PICK(p.half, compress_short_fn_std(e8));
+    default: return ADACC_PICK(p.half, compress_short_fn_topk(e8, topk_whole_tile(m, p)));
   }
 }
 static bool in_one_launch(const adacc_method* m, const Plan& p) {
@@ -721,7 +721,7 @@ static bool in_one_launch(const adacc_method* m, const Plan& p) {
   const uint32_t workgroups = blocks_of(p.n_tiles, kWavesPerWg);
   // TOPK of more outliers a tile than its record holds would be selected twice
   if (m->outlier_mode == ADACC_OUTLIER_TOPK) return workgroups <= kShortWorkgroupsTopk && m->topk * (p.tile_elems / m->stat_group) <= (uint32_t)kSlot;
-  return workgroups <= (p.rowwise ? kShortWorkgroupsRows : kShortWorkgroups);
+  return workgroups <= (p.rowwise ? kShortWorkgroupsRows : p.tail != 0 ? kShortWorkgroups : kShortWorkgroupsEven);
 }
 
 static int compress_one(const adacc_method* method, const void* src, uint64_t numel, void* blob, uint64_t blob_bytes,

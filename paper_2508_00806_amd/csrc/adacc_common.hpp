@@ -193,14 +193,16 @@ constexpr uint32_t kPlaceDirectTiles = 32768;
 // wrote: a word that holds an older epoch reads as not set, so nothing has to be cleared per call.
 constexpr uint32_t kEpochMax = 0x3FFFFFFFu;
 // Tensors of at most this many workgroups of tiles (and one for the end) are compressed in one launch (adacc_short.hpp), a word of
-// 8 bytes for each at the end of a workspace that has the room: the general encoder, the encoder by rows, TOPK.  The lines lie where
-// the wait for the other workgroups begins to cost as much as a launch.  (us both ways, two launches / one, [rows, 1024] STD at 6 sigma over
-// 1024: 20 rows 9.7 / 7.9, 128 10.0 / 8.7, 1024 11.1 / 10.3, 4096 13.3 / 12.9, 8000 16.8 / 16.1, 12000 21.3 / 19.7, 16000 25.9 / 26.8.  STD over
-// 512, ragged, [rows, 2051]: 50 rows 12.8 / 10.2, 1100 14.6 / 12.8, 4000 18.6 / 16.6, 12000 38.5 / 39.4.  By rows, [rows, 3072], STD at 8
-// sigma over 64: 2000 rows 13.5 / 12.8, 4000 18.2 / 20.2; softmax, ABS, [rows, 512], 1200 12.1 / 11.3, 12000 16.5 / 16.0, 16000 18.6 / 18.6.
-// TOPK, whose second launch has nothing to do: [20, 1024] 9.7 / 7.9, [26, 4096] 9.5 / 9.1, [300, 4096] 9.8 / 10.7, [1200, 1024] 9.7 / 10.5.
-// Where tiles have more outliers than a slot holds, STD at 3 sigma over 64 of GELU values: [20, 3072] 20.6 / 12.9, [1200, 3072] 33.2 / 17.3.)
-constexpr uint32_t kShortWorkgroups = 1536, kShortWorkgroupsRows = 768, kShortWorkgroupsTopk = 16;
+// 8 bytes for each at the end of a workspace that has the room: with an end that the groups do not divide, without, methods that have
+// the encoder by rows in two launches, TOPK.  The lines lie where the wait for the other workgroups begins to cost as much as the
+// second launch.  (us both ways, two launches / one.  [rows, 1024] STD at 6 sigma over 1024: 20 rows 9.8 / 7.9, 128 10.3 / 8.2, 1024 11.0 /
+// 8.6, 4096 13.4 / 11.1, 8000 16.9 / 15.6, 12000 20.5 / 19.8, 16000 24.9 / 25.4.  [rows, 2051] at 4 sigma over 512: 3000 16.8 / 13.3, 7000
+// 24.1 / 22.7, 8191 35.3 / 33.8 (binary32), 12000 37.3 / 37.5; over 4096, [4000, 2255] 22.6 / 18.9, [12000, 2255] 41.0 / 38.4.  Where there is
+// an encoder by rows: STD at 8 sigma over 64, [300, 3072] 10.0 / 7.5, [2000, 3072] 12.4 / 11.4, [4000, 3072] 18.9 / 19.1; softmax, ABS, [1200,
+// 512] 12.1 / 9.5, [20000, 512] 21.2 / 20.1, [40000, 512] 35.0 / 36.4; with more outliers a tile than a slot holds, STD at 3 sigma over 64, [1200,
+// 3072] 33.3 / 14.9, [4000, 3072] 42.6 / 28.4.  TOPK, whose second launch finds nothing to do: [20, 1024] 10.0 / 7.9, [300, 4096] 10.1 / 9.5,
+// [1000, 4096] 11.4 / 11.2, [2000, 4096] 14.1 / 14.2.)
+constexpr uint32_t kShortWorkgroups = 2560, kShortWorkgroupsEven = 1792, kShortWorkgroupsRows = 1280, kShortWorkgroupsTopk = 256;
 constexpr uint64_t kShortBytes = 8ull * kShortWorkgroups;
 
 // the batch compression kernels, by the weight of the variants they hold (adacc_kernels.hpp)

@@ -476,6 +476,10 @@ struct NullSink {
   __device__ __forceinline__ void operator()(uint32_t, uint32_t, uint32_t) const {}
 };
 
+// What a sink is told when all outliers of a tile are found, where codes are still to be formed
+template <class Sink>
+__device__ __forceinline__ void all_found(const Sink&, uint32_t) {}
+
 // The outliers of one row, in ascending index order, to positions pos_row, pos_row + 1, ... of the
 // sink (entries at or past `limit` are dropped).  mask: this lane's outliers among its 8 elements;
 // lane_excl: the row's outliers in lower lanes; sparse (uniform): no lane holds more than one;
@@ -1195,6 +1199,7 @@ __device__ __forceinline__ uint32_t encode_tile_topk_whole(const TensorDesc& d, 
   RowMags<E> rowmag;
   const uint32_t total = topk_extract<E, STORE>(d.topk, raw, rowmag, tile * (uint32_t)(E * kRow), sink, pos0, limit);
   if constexpr (STORE) {
+    all_found(sink, total);
     uint32_t top[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) top[j] = rowmag.at(j);
@@ -1350,7 +1355,10 @@ __device__ __forceinline__ uint32_t encode_tile_general(const TensorDesc& d, con
       }
     }
   }
-  if constexpr (STORE) quantise_tile_as<BITS, ASYM, E, false>(d, g, raw, top);
+  if constexpr (STORE) {
+    all_found(sink, total);
+    quantise_tile_as<BITS, ASYM, E, false>(d, g, raw, top);
+  }
   return total;
 }
 

@@ -47,9 +47,9 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   CompressFn compress_fn_abs(uint32_t bits, uint32_t asym, bool e8, bool rowwise);     \
   CompressFn compress_fn_std(uint32_t bits, uint32_t asym, bool e8, bool rowwise);     \
   CompressFn compress_fn_topk(uint32_t bits, uint32_t asym, bool e8, bool whole, bool rows); \
-  CompressShortFn compress_short_fn_abs(bool e8, bool rowwise);                        \
-  CompressShortFn compress_short_fn_std(bool e8, bool rowwise);                        \
-  CompressShortFn compress_short_fn_topk(bool e8, bool whole, bool rows);              \
+  CompressShortFn compress_short_fn_abs(bool e8);                                      \
+  CompressShortFn compress_short_fn_std(bool e8);                                      \
+  CompressShortFn compress_short_fn_topk(bool e8, bool whole);                         \
   DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic, uint32_t rows); \
   BatchCompressFn compress_batch_fn4(int kind);                                        \
   BatchCompressFn compress_batch_fn8(int kind);                                        \

@@ -5,10 +5,7 @@
 namespace adacc {
 namespace ADACC_DT_NS {
 
-CompressShortFn compress_short_fn_std(bool e8, bool rowwise) {
-  if (e8) return compress_short_kernel<kModeStd, 8, false, false>;
-  return rowwise ? compress_short_kernel<kModeStd, 4, true, false> : compress_short_kernel<kModeStd, 4, false, false>;
-}
+CompressShortFn compress_short_fn_std(bool e8) { return e8 ? compress_short_kernel<kModeStd, 8, false> : compress_short_kernel<kModeStd, 4, false>; }
 
 }  // namespace ADACC_DT_NS
 }  // namespace adacc

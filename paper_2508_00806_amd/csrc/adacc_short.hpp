@@ -21,31 +21,50 @@ struct ShortShared {
   uint32_t record[kWavesPerWg][kSlot];  // a tile's outliers: number in the tile << 16 | value
   uint32_t count[kWavesPerWg];          // a tile's outliers, how many
   uint32_t part[kWavesPerWg];           // of the sum over the words
+  uint32_t arrived;                     // tiles whose outliers are found << 24 | those of them
 };
 
+// The wavefront's record.  The last wavefront of a workgroup to know its outliers publishes their number, ahead of the codes (all_found):
+// the word is on its way while they are formed.  That is why methods whose groups lie inside a row go through the general encoder
+// here too, and not through the one by rows, which knows its outliers at the end.  ([rows, 1024] STD over 1024, both ways: 1024 rows
+// 10.3 us with the word behind the codes, 8.6 so; [3000, 2051] STD over 512 15.1, 13.3; by rows / so: softmax, ABS, [1200, 512] 11.0, 9.5, GELU
+// at 3 sigma over 64, [1200, 3072] 17.2, 14.9.)
+struct ShortSink : SlotSink {
+  uint32_t* arrived;
+  uint32_t tiles, epoch;  // tiles of the workgroup
+  unsigned long long* word;
+  __device__ __forceinline__ void tell(uint32_t found) const {
+    if (lane_id() == 0) {
+      const uint32_t before = atomicAdd(arrived, 1u << 24 | found);
+      if ((before >> 24) + 1u == tiles)
+        __hip_atomic_store(word, (unsigned long long)epoch << 32 | ((before & 0xFFFFFFu) + found), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+};
+__device__ __forceinline__ void all_found(const ShortSink& sink, uint32_t found) { sink.tell(found); }
+
 // Which of a tile's elements are outliers, once more from the source: how many, and those below `limit` to the stream.
-template <int MODE, int E, bool ROWWISE, bool WHOLE>
+template <int MODE, int E, bool WHOLE>
 __device__ __forceinline__ uint32_t select_tile(const TensorDesc& d, uint32_t tile, uint32_t pos, uint32_t limit) {
   uint32_t raw[E][4];
   load_tile<E, false>(d, tile, raw);
   const TileGeo<E> g = tile_geo<E, false>(d, tile);
   blank_tail<E>(g, raw);
-  constexpr bool ROWS = ROWWISE && MODE != (int)kModeTopk;  // (TOPK: the encoder by rows only knows how to store)
-  return encode_tile<MODE, 8, false, E, ROWS, WHOLE, false>(d, g, raw, tile, StreamSink{d.idx, d.val}, pos, limit);
+  return encode_tile<MODE, 8, false, E, false, WHOLE, false>(d, g, raw, tile, StreamSink{d.idx, d.val}, pos, limit);
 }
 
 // a1 .. a8 of a tile, its outliers to the wavefront's record
-template <int MODE, int BITS, bool ASYM, int E, bool ROWWISE, bool WHOLE>
-__device__ __forceinline__ uint32_t short_tile(const TensorDesc& d, uint32_t tile, uint32_t* record) {
+template <int MODE, int BITS, bool ASYM, int E, bool WHOLE>
+__device__ __forceinline__ uint32_t short_tile(const TensorDesc& d, uint32_t tile, const ShortSink& sink) {
   uint32_t raw[E][4];
   load_tile<E, WHOLE>(d, tile, raw);
   const TileGeo<E> g = tile_geo<E, WHOLE>(d, tile);
   if constexpr (!WHOLE) blank_tail<E>(g, raw);
-  return encode_tile<MODE, BITS, ASYM, E, ROWWISE, WHOLE, true>(d, g, raw, tile, SlotSink{record, tile * (uint32_t)(E * kRow)}, 0u, (uint32_t)kSlot);
+  return encode_tile<MODE, BITS, ASYM, E, false, WHOLE, true>(d, g, raw, tile, sink, 0u, (uint32_t)kSlot);
 }
 
 // The outliers in the tiles of the first `n` workgroups, to every thread.
-template <int MODE, int E, bool ROWWISE, bool WHOLE>
+template <int MODE, int E, bool WHOLE>
 __device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint32_t n, uint32_t epoch, uint32_t patience,
                                                        const unsigned long long* words, uint32_t (&part)[kWavesPerWg]) {
   uint32_t sum = 0u;
@@ -66,7 +85,7 @@ __device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint
       const uint32_t lane = (uint32_t)__builtin_ctzll(left);
       const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)i, (int)lane) * (uint32_t)kWavesPerWg;
       uint32_t found = 0u;
-      for (uint32_t t = first; t < first + (uint32_t)kWavesPerWg && t < d.n_tiles; ++t) found += select_tile<MODE, E, ROWWISE, WHOLE>(d, t, 0u, 0u);
+      for (uint32_t t = first; t < first + (uint32_t)kWavesPerWg && t < d.n_tiles; ++t) found += select_tile<MODE, E, WHOLE>(d, t, 0u, 0u);
       if ((uint32_t)lane_id() == lane) sum += found;
     }
   }
@@ -74,7 +93,7 @@ __device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint
 }
 
 // The fallback's registers are what bounds it; a short tensor does not fill the device anyway.
-template <int MODE, int E, bool ROWWISE, bool WHOLE>
+template <int MODE, int E, bool WHOLE>
 __global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc d, uint32_t epoch, unsigned long long* words, uint32_t patience) {
   __shared__ union {
     ShortShared tiles;
@@ -89,35 +108,34 @@ __global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc 
   const uint32_t workgroups = (d.n_tiles + (uint32_t)kWavesPerWg - 1u) / (uint32_t)kWavesPerWg;
   if (blockIdx.x == workgroups) {  // the end that the groups do not divide
     compress_tail<false>(d, [&] {
-      return outliers_of_others<MODE, E, ROWWISE, WHOLE>(d, workgroups, epoch, patience, words, lds.tail.part);
+      return outliers_of_others<MODE, E, WHOLE>(d, workgroups, epoch, patience, words, lds.tail.part);
     }, lds.tail.rest);
     return;
   }
+  if (threadIdx.x == 0u) lds.tiles.arrived = 0u;
+  __syncthreads();
   uint32_t found = 0u;
   if (tile < d.n_tiles) {  // uniform
-    uint32_t* record = lds.tiles.record[wave];
-    if constexpr (!ROWWISE && !WHOLE) {  // (the codes' form is looked at behind the selection)
-      found = short_tile<MODE, kBitsAny, false, E, false, false>(d, tile, record);
+    const uint32_t tiles = d.n_tiles - blockIdx.x * (uint32_t)kWavesPerWg;
+    const ShortSink record{{lds.tiles.record[wave], tile * (uint32_t)(E * kRow)}, &lds.tiles.arrived,
+                           tiles < (uint32_t)kWavesPerWg ? tiles : (uint32_t)kWavesPerWg, epoch, words + blockIdx.x};
+    if constexpr (!WHOLE) {  // (the codes' form is looked at behind the selection)
+      found = short_tile<MODE, kBitsAny, false, E, false>(d, tile, record);
     } else {
       switch (d.variant & 6u) {
-        case 0: found = short_tile<MODE, 4, false, E, ROWWISE, WHOLE>(d, tile, record); break;
-        case 2: found = short_tile<MODE, 4, true, E, ROWWISE, WHOLE>(d, tile, record); break;
-        case 4: found = short_tile<MODE, 8, false, E, ROWWISE, WHOLE>(d, tile, record); break;
-        default: found = short_tile<MODE, 8, true, E, ROWWISE, WHOLE>(d, tile, record); break;
+        case 0: found = short_tile<MODE, 4, false, E, WHOLE>(d, tile, record); break;
+        case 2: found = short_tile<MODE, 4, true, E, WHOLE>(d, tile, record); break;
+        case 4: found = short_tile<MODE, 8, false, E, WHOLE>(d, tile, record); break;
+        default: found = short_tile<MODE, 8, true, E, WHOLE>(d, tile, record); break;
       }
     }
   }
   if (lane == 0u) lds.tiles.count[wave] = found;
   __syncthreads();
-  uint32_t all = 0u, before = 0u;
+  uint32_t before = 0u;
 #pragma unroll
-  for (uint32_t w = 0; w < (uint32_t)kWavesPerWg; ++w) {
-    before += w < wave ? lds.tiles.count[w] : 0u;
-    all += lds.tiles.count[w];
-  }
-  if (threadIdx.x == 0u)
-    __hip_atomic_store(words + blockIdx.x, (unsigned long long)epoch << 32 | all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const uint32_t pos = before + outliers_of_others<MODE, E, ROWWISE, WHOLE>(d, blockIdx.x, epoch, patience, words, lds.tiles.part);
+  for (uint32_t w = 0; w < (uint32_t)kWavesPerWg; ++w) before += w < wave ? lds.tiles.count[w] : 0u;
+  const uint32_t pos = before + outliers_of_others<MODE, E, WHOLE>(d, blockIdx.x, epoch, patience, words, lds.tiles.part);
   if (tile >= d.n_tiles) return;
   if (lane == 0u) {
     d.tile_ptr[tile] = pos;
@@ -135,7 +153,7 @@ __global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc 
     }
   } else {
     const uint32_t end = pos + found;
-    select_tile<MODE, E, ROWWISE, WHOLE>(d, tile, pos, end < d.cap ? end : d.cap);
+    select_tile<MODE, E, WHOLE>(d, tile, pos, end < d.cap ? end : d.cap);
   }
 }
 

@@ -49,11 +49,11 @@ def _compressed(m, x, ws):
     return blob
 
 
-@pytest.mark.parametrize("tiles", [768 * 4, 768 * 4 + 1, 1536 * 4, 1536 * 4 + 1])
+@pytest.mark.parametrize("tiles", [1280 * 4, 1280 * 4 + 1, 1792 * 4, 1792 * 4 + 1, 2560 * 4, 2560 * 4 + 1])
 def test_the_same_as_in_two_launches(tiles):
     """Both sides of the lines in the number of workgroups; one workspace for all calls, with calls that need all of it between."""
     for gq, gs in ((64, 64), (64, 512)):
-        n = tiles * 2048
+        n = tiles * 2048 + (40 if tiles > 1792 * 4 + 1 else 0)
         x = _values(n, 2048, torch.Generator().manual_seed(tiles), torch.bfloat16).cuda()
         m = adacc_method(_case(gq, gs, "std", 3.0, 0, 8, 0), n // 8)
         need = adacc.workspace_bytes(m, n)
