@@ -97,7 +97,7 @@ struct Knobs {
 };
 static const Knobs& knobs() {
   static const Knobs k = {env_int("ADACC_GRID_ROUNDS", 0), env_int("ADACC_WGS_PER_CU", 0),
-                          env_int("ADACC_MASK_WGS_PER_CU", 256), env_int("ADACC_SHORT_POLLS", 1 << 16)};
+                          env_int("ADACC_MASK_WGS_PER_CU", 256), env_int("ADACC_SHORT_POLLS", 512)};
   return k;
 }
 

@@ -7,8 +7,9 @@
 // these launches alone, and says everything by itself, so nothing has to be cleared, and no other memory has to be ordered.
 //
 // No wait is without an end, whatever order workgroups are started in: a wavefront whose patience is at an end counts the
-// outliers of the missing tiles itself, from the source.  (Workgroups are started in the order of their numbers and nobody
-// waits for a later one, so that does not happen by itself.)
+// outliers of the missing tiles itself, from the source.  Workgroups are started in the order of their numbers on every XCD and nobody
+// waits for a later one, so one such launch alone always goes on; two at a time could fill an XCD each with workgroups that wait for
+// some the other keeps out, and there the patience, some 0.5 ms where a wait as a rule takes a few microseconds, ends it.
 #pragma once
 
 #include "adacc_compress.hpp"

@@ -77,6 +77,24 @@ def test_the_same_as_in_two_launches(tiles):
             assert torch.equal(_compressed(m, x, room), _compressed(m, x, exact))
 
 
+def test_two_streams_at_a_time():
+    """Launches that wait for their own workgroups side by side, each stream with a workspace of its own."""
+    n = 2048 * 4 * 2000 + 24
+    m = adacc_method(_case(64, 512, "std", 2.5, 0, 8, 0), n // 8)
+    lay = adacc.layout_of(m, n)
+    xs = [_values(n, 2048, torch.Generator().manual_seed(s), torch.bfloat16).cuda() for s in (1, 2)]
+    spaces = [adacc.alloc_workspace(adacc.workspace_bytes(m, n)) for _ in xs]
+    want = [_compressed(m, x, w) for x, w in zip(xs, spaces)]
+    blobs = [torch.zeros(lay.total_bytes, dtype=torch.uint8, device="cuda") for _ in xs]
+    streams = [torch.cuda.Stream() for _ in xs]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for x, w, b, s in zip(xs, spaces, blobs, streams):
+            adacc.compress(m, x, b, w, stream=s)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(want, blobs))
+
+
 def test_wavefronts_that_count_for_others():
     """One look at the words, then the tiles that are missing are counted by the wavefront itself."""
     code = ("import sys; sys.path[:0] = ['tests', '.']; import torch; import test_gpu_short as t\n"
