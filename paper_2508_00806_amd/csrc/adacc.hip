@@ -1127,12 +1127,16 @@ int adacc_channel_compress(const adacc_channel_method* method, const void* src, 
                      hidden, partial, strips);
   rc = launch_check("channel_partial_kernel");
   if (rc != ADACC_OK) return rc;
-  const uint32_t per_wg = ADACC_PICK(half, channel_score_channels());
-  hipLaunchKernelGGL(ADACC_PICK(half, channel_score_fn()), dim3((hidden + per_wg - 1) / per_wg), dim3(kThreads), 0, s,
-                     static_cast<const float*>(partial), cp.n_chunks, hidden, S);
-  rc = launch_check("channel_score_kernel");
-  if (rc != ADACC_OK) return rc;
-  hipLaunchKernelGGL(ADACC_PICK(half, channel_select_fn()), dim3(1), dim3(ADACC_PICK(half, channel_select_threads())), 0, s, static_cast<const double*>(S), c);
+  const bool few = cp.n_chunks <= kFewChunks && hidden <= kFewHidden;
+  if (!few) {
+    const uint32_t per_wg = ADACC_PICK(half, channel_score_channels());
+    hipLaunchKernelGGL(ADACC_PICK(half, channel_score_fn()), dim3((hidden + per_wg - 1) / per_wg), dim3(kThreads), 0, s,
+                       static_cast<const float*>(partial), cp.n_chunks, hidden, S);
+    rc = launch_check("channel_score_kernel");
+    if (rc != ADACC_OK) return rc;
+  }
+  hipLaunchKernelGGL(ADACC_PICK(half, channel_select_fn(few)), dim3(1), dim3(ADACC_PICK(half, channel_select_threads())), 0, s,
+                     few ? static_cast<const void*>(partial) : static_cast<const void*>(S), cp.n_chunks, c);
   rc = launch_check("channel_select_kernel");
   if (rc != ADACC_OK) return rc;
   hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), by_strips ? 0u : channel_mask_lds(hidden), s, d, c);

@@ -161,7 +161,10 @@ __device__ __forceinline__ uint32_t sum_counts(const uint32_t* cnt, uint32_t* be
 // it; a division of every channel was half the time.  (1024 threads, S read three times, two barriers a reduction: 7.9
 // us for 4096 channels, 9.0 for 8192; 4.8 and 5.8 now.)
 constexpr uint32_t kSelectKept = 2;
-__global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const double* __restrict__ S, ChannelDesc c) {
+// FEW: of at most kFewChunks chunks, where no channel is read twice, the kernel adds the chunk sums up itself, the same additions in the same
+// order as step 2's, which is left out.
+template <bool FEW>
+__global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const void* __restrict__ from, uint32_t n_chunks, ChannelDesc c) {
   __shared__ double a[2][kSelectWaves];
   __shared__ uint32_t cnt[2][kSelectWaves];
   const uint32_t j = threadIdx.x, wave = j / kWave;
@@ -169,12 +172,33 @@ __global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const do
   const double skip = __longlong_as_double(0x7FF0000000000000ll);  // a channel that is not there reads as a sum that is not finite
   double kept[kSelectKept][8];
   auto load = [&](uint32_t b, double (&v)[8]) {
-    const double2* p = reinterpret_cast<const double2*>(S + (size_t)(b < n_bytes ? b : 0u) * 8u);
+    if constexpr (FEW) {
+      const float* p = static_cast<const float*>(from) + (size_t)(b < n_bytes ? b : 0u) * 8u;
 #pragma unroll
-    for (uint32_t e = 0; e < 4u; ++e) {
-      const double2 t = p[e];
-      v[2u * e] = b < n_bytes ? t.x : skip;
-      v[2u * e + 1u] = b < n_bytes ? t.y : skip;
+      for (uint32_t e = 0; e < 8u; ++e) v[e] = 0.0;
+      float4 t[kFewChunks][2];
+#pragma unroll
+      for (uint32_t i = 0; i < kFewChunks; ++i) {  // chunks past the end re-read the last one
+        const float* q = p + (size_t)(i < n_chunks ? i : n_chunks - 1u) * c.hidden;
+        t[i][0] = reinterpret_cast<const float4*>(q)[0];
+        t[i][1] = reinterpret_cast<const float4*>(q)[1];
+      }
+#pragma unroll
+      for (uint32_t i = 0; i < kFewChunks; ++i) {
+        const float w[8] = {t[i][0].x, t[i][0].y, t[i][0].z, t[i][0].w, t[i][1].x, t[i][1].y, t[i][1].z, t[i][1].w};
+#pragma unroll
+        for (uint32_t e = 0; e < 8u; ++e) v[e] = i < n_chunks ? __dadd_rn(v[e], (double)w[e]) : v[e];
+      }
+#pragma unroll
+      for (uint32_t e = 0; e < 8u; ++e) v[e] = b < n_bytes ? v[e] : skip;
+    } else {
+      const double2* p = reinterpret_cast<const double2*>(static_cast<const double*>(from) + (size_t)(b < n_bytes ? b : 0u) * 8u);
+#pragma unroll
+      for (uint32_t e = 0; e < 4u; ++e) {
+        const double2 t = p[e];
+        v[2u * e] = b < n_bytes ? t.x : skip;
+        v[2u * e + 1u] = b < n_bytes ? t.y : skip;
+      }
     }
   };
 #pragma unroll

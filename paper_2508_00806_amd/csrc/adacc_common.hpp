@@ -118,6 +118,10 @@ struct TensorDesc {
 constexpr uint32_t kChunkTokens = 64;  // tokens per binary32 partial sum of the channel statistics
 constexpr uint32_t kPartialWaves = 16;  // wavefronts that share a chunk in the statistics pass (one workgroup)
 constexpr uint32_t kPartialRows = kChunkTokens / kPartialWaves;  // tokens per wavefront there
+// Up to this many chunks and channels the selection adds the chunk sums up itself and their kernel is left out: one workgroup takes
+// that on where it costs less than a launch.  (us both ways with that kernel / without, int4, 128, 256 and 512 tokens: 1024 channels 16.6 /
+// 15.4, 16.8 / 15.9, 16.8 / 17.4; 4096 channels 17.6 / 16.4, 17.7 / 16.8, 18.4 / 19.1; 8192 19.3 / 17.9, 19.8 / 18.8, 21.9 / 23.0.)
+constexpr uint32_t kFewChunks = 4, kFewHidden = 8192;
 struct ChannelDesc {
   uint8_t* mask;        // hidden/8 bytes: bit (h & 7) of byte h >> 3 is set for an outlier channel
   uint32_t* base;       // hidden/8 words: number of outlier channels below channel 8 * (h >> 3)

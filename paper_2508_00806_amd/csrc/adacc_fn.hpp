@@ -19,7 +19,7 @@ typedef void (*PlaceBatchFn)(const TensorDesc*, const uint32_t*, uint32_t);
 // Types of the channel and channel-wise kernels
 typedef void (*ChannelPartialFn)(const uint16_t*, uint32_t, uint32_t, float*, uint32_t);
 typedef void (*ChannelScoreFn)(const float*, uint32_t, uint32_t, double*);
-typedef void (*ChannelSelectFn)(const double*, ChannelDesc);
+typedef void (*ChannelSelectFn)(const void*, uint32_t, ChannelDesc);
 typedef void (*ChannelFn)(TensorDesc, ChannelDesc);
 typedef void (*ChannelwiseItemsFn)(ChannelwiseDesc, uint32_t);
 typedef void (*ChannelwiseFn)(ChannelwiseDesc);
@@ -65,7 +65,7 @@ typedef void (*ChannelwiseFn)(ChannelwiseDesc);
   uint32_t generic_lds_bytes(uint32_t tile_elems, uint32_t gq, bool topk_groups);      \
   ChannelPartialFn channel_partial_fn(bool stream);                                    \
   ChannelScoreFn channel_score_fn();                                                   \
-  ChannelSelectFn channel_select_fn();                                                 \
+  ChannelSelectFn channel_select_fn(bool few);                                         \
   uint32_t channel_score_channels();                                                   \
   uint32_t channel_select_threads();                                                   \
   uint32_t channel_partial_threads();                                                  \
