@@ -90,14 +90,11 @@ static int env_int(const char* name, int dflt) {
 
 // Run-time knobs for measurements, read from the environment once per process.
 struct Knobs {
-  int grid_rounds;      // ADACC_GRID_ROUNDS: rounds of resident workgroups in the grid of a kernel that loops over tiles
-  int wgs_per_cu;       // ADACC_WGS_PER_CU: overrides the occupancy query behind that limit
   int mask_wgs_per_cu;  // ADACC_MASK_WGS_PER_CU: grid of the mask kernels
   int short_polls;      // ADACC_SHORT_POLLS: looks at a workgroup's count before its tiles are counted again (adacc_short.hpp)
 };
 static const Knobs& knobs() {
-  static const Knobs k = {env_int("ADACC_GRID_ROUNDS", 0), env_int("ADACC_WGS_PER_CU", 0),
-                          env_int("ADACC_MASK_WGS_PER_CU", 256), env_int("ADACC_SHORT_POLLS", 512)};
+  static const Knobs k = {env_int("ADACC_MASK_WGS_PER_CU", 256), env_int("ADACC_SHORT_POLLS", 512)};
   return k;
 }
 
@@ -220,32 +217,6 @@ static void fill_layout(const adacc_method* m, uint64_t numel, const Plan& p, ad
   L->total_bytes = off;
   L->tile_elems = p.tile_elems;
   L->n_tiles = p.n_tiles_all;
-}
-
-// Workgroups of `kernel` that one CU holds at once (cached per kernel: the query is not free).
-static int resident_wgs(const void* kernel, int* wgs_out) {
-  struct Entry { const void* kernel; int wgs; };
-  static thread_local Entry cache[64];
-  static thread_local int used = 0;
-  for (int i = 0; i < used; ++i)
-    if (cache[i].kernel == kernel) { *wgs_out = cache[i].wgs; return ADACC_OK; }
-  int wgs = 0;
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&wgs, kernel, kThreads, 0);
-  if (e != hipSuccess) return hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
-  if (wgs < 1) wgs = 1;
-  if (used < 64) cache[used++] = Entry{kernel, wgs};
-  *wgs_out = wgs;
-  return ADACC_OK;
-}
-
-// Wavefronts of `kernel` that the device can hold at once.
-static int wave_capacity(const void* kernel, int cus, uint32_t* waves) {
-  int wgs = 0;
-  const int rc = resident_wgs(kernel, &wgs);
-  if (rc != ADACC_OK) return rc;
-  if (knobs().wgs_per_cu > 0) wgs = knobs().wgs_per_cu;
-  *waves = (uint32_t)(cus * wgs * kWavesPerWg);
-  return ADACC_OK;
 }
 
 // TOPK whose statistics group is the tile, with every quantisation group inside a 512-element row, has kernels of its own
@@ -380,29 +351,6 @@ static void fill_desc(const adacc_method* m, uint64_t numel, const Plan& p, cons
 }
 
 static bool misaligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
-
-// Grid of the tile form of the outlier-channel compression, the one kernel that still loops over tiles: it stages
-// tables in LDS, a cost per workgroup, so its grid is limited to `resident_rounds` times the workgroups that the device
-// holds at once (ADACC_GRID_ROUNDS overrides that).  All others take one tile or piece per wavefront: with
-// streaming accesses the hardware's own order of workgroups, which walks through memory front to back, beat every
-// grid of resident workgroups that loop (C4 decompression: 0.308 ms with one round of them, 0.275 ms without).
-static int grid_for(uint32_t n_tiles, const void* kernel, uint32_t* grid, int resident_rounds) {
-  const uint64_t want = ((uint64_t)n_tiles + kWavesPerWg - 1) / kWavesPerWg;
-  uint64_t cap = want;
-  const int rounds = knobs().grid_rounds > 0 ? knobs().grid_rounds : resident_rounds;
-  if (rounds > 0) {
-    int cus = 0;
-    int rc = device_cus(&cus);
-    if (rc != ADACC_OK) return rc;
-    uint32_t waves = 0;
-    rc = wave_capacity(kernel, cus, &waves);
-    if (rc != ADACC_OK) return rc;
-    cap = (uint64_t)(waves / kWavesPerWg) * (uint64_t)rounds;
-  }
-  *grid = (uint32_t)(want < cap ? want : cap);
-  if (*grid == 0) *grid = 1;
-  return ADACC_OK;
-}
 
 static BatchCompressFn compress_batch_fn(bool half, int kind) {
   return kind >= kBatchAny8 ? ADACC_PICK(half, compress_batch_fn8(kind)) : ADACC_PICK(half, compress_batch_fn4(kind));
@@ -598,8 +546,6 @@ static void fill_channel_layout(const adacc_channel_method* m, uint64_t tokens, 
   L->status_off = off;   off = align256(off + 16);
   L->total_bytes = off;
 }
-
-static uint32_t channel_mask_lds(uint32_t hidden) { return (3u * (hidden / 8) + 15u) & ~15u; }  // LDS copy of mask and ranks
 
 static uint64_t channel_partial_bytes(uint32_t n_chunks, uint32_t hidden) { return align256(4ull * n_chunks * hidden); }
 
@@ -1112,13 +1058,7 @@ int adacc_channel_compress(const adacc_channel_method* method, const void* src, 
   const bool by_strips = cp.plan.rowwise && hidden % 512u == 0;
   ChannelFn fn = by_strips ? ADACC_PICK(half, channel_compress_strip_fn(method->bits, method->asym))
                            : ADACC_PICK(half, channel_compress_fn(method->bits, method->asym, cp.plan.rowwise));
-  uint32_t grid = 0;
-  if (by_strips) {
-    grid = strip_grid(tokens, hidden, ADACC_PICK(half, channel_strip_rows()));
-  } else {
-    rc = grid_for(cp.plan.n_tiles, reinterpret_cast<const void*>(fn), &grid, 2);
-    if (rc != ADACC_OK) return rc;
-  }
+  const uint32_t grid = by_strips ? strip_grid(tokens, hidden, ADACC_PICK(half, channel_strip_rows())) : blocks_of(cp.plan.n_tiles, kWavesPerWg);
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
 
   const uint32_t strips = (hidden / 8 + kWave - 1) / kWave;  // a workgroup: one chunk of a strip of 512 channels
@@ -1139,7 +1079,7 @@ int adacc_channel_compress(const adacc_channel_method* method, const void* src, 
                      few ? static_cast<const void*>(partial) : static_cast<const void*>(S), cp.n_chunks, c);
   rc = launch_check("channel_select_kernel");
   if (rc != ADACC_OK) return rc;
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), by_strips ? 0u : channel_mask_lds(hidden), s, d, c);
+  hipLaunchKernelGGL(fn, dim3(grid), dim3(kThreads), 0, s, d, c);
   return launch_check("channel_compress_kernel");
 }
 
