@@ -164,7 +164,8 @@ constexpr uint32_t kSelectKept = 2;
 // FEW: of at most kFewChunks chunks, where no channel is read twice, the kernel adds the chunk sums up itself, the same additions in the same
 // order as step 2's, which is left out.
 template <bool FEW>
-__global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const void* __restrict__ from, uint32_t n_chunks, ChannelDesc c) {
+__global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const double* __restrict__ S, ChannelDesc c, const float* __restrict__ partial,
+                                                                         uint32_t n_chunks) {
   __shared__ double a[2][kSelectWaves];
   __shared__ uint32_t cnt[2][kSelectWaves];
   const uint32_t j = threadIdx.x, wave = j / kWave;
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const vo
   double kept[kSelectKept][8];
   auto load = [&](uint32_t b, double (&v)[8]) {
     if constexpr (FEW) {
-      const float* p = static_cast<const float*>(from) + (size_t)(b < n_bytes ? b : 0u) * 8u;
+      const float* p = partial + (size_t)(b < n_bytes ? b : 0u) * 8u;
 #pragma unroll
       for (uint32_t e = 0; e < 8u; ++e) v[e] = 0.0;
       float4 t[kFewChunks][2];
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(kSelectThreads) void channel_select_kernel(const vo
 #pragma unroll
       for (uint32_t e = 0; e < 8u; ++e) v[e] = b < n_bytes ? v[e] : skip;
     } else {
-      const double2* p = reinterpret_cast<const double2*>(static_cast<const double*>(from) + (size_t)(b < n_bytes ? b : 0u) * 8u);
+      const double2* p = reinterpret_cast<const double2*>(S + (size_t)(b < n_bytes ? b : 0u) * 8u);
 #pragma unroll
       for (uint32_t e = 0; e < 4u; ++e) {
         const double2 t = p[e];

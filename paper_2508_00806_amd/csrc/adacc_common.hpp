@@ -193,6 +193,9 @@ constexpr uint32_t kPlaceWorkgroups = 1024;
 // ms, most of it counts that 15625 workgroups add up; with 256 1.80.)
 constexpr int kSumTiles = 256;
 constexpr uint32_t kPlaceDirectTiles = 32768;
+// Up to this many tiles by sixteen wavefronts to a workgroup (adacc_k_place.hip).  (us both ways by four / sixteen: [16000, 4096], 16000 tiles,
+// 71.1 / 69.9; [79977, 512] of softmax values, 19995 tiles of 13 outliers, 57.9 / 58.7.)
+constexpr uint32_t kPlaceManyTiles = 16384;
 // The workspace's launch counter ("epoch", kept on the host in adacc_workspace) marks what a launch
 // wrote: a word that holds an older epoch reads as not set, so nothing has to be cleared per call.
 constexpr uint32_t kEpochMax = 0x3FFFFFFFu;

@@ -1580,20 +1580,6 @@ __device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t
     const uint32_t mine = wave_sum_u32(p.count);
     if (lane == 0u) sh.window[wave] = mine;  // (read behind the barriers of outliers_before)
   }
-  // few tiles to a wavefront: the records are asked for together with the counts, whether they are there or not, one round
-  // trip to memory less
-  constexpr bool EARLY = !OWN && PER <= 4;
-  uint32_t rec[OWN ? 1 : PER];
-  const uint32_t j0 = wave * (uint32_t)PER;
-  if constexpr (EARLY) {
-    if (move) {  // uniform
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const uint32_t t = j0 + (uint32_t)i < p.n_here ? p.first + j0 + (uint32_t)i : p.first;
-        rec[i] = d.slot[(uint64_t)t * (uint64_t)kSlot + lane];
-      }
-    }
-  }
   p.base = known ? before : outliers_before<WAVES>(d, first, from_sums, sh);  // uniform
   if constexpr (OWN) {
 #pragma unroll
@@ -1655,13 +1641,13 @@ __device__ __forceinline__ PlacedTiles place_tiles(const TensorDesc& d, uint32_t
       }
     } else {
       // a lane per record, the loads of all tiles of this wavefront in flight at once
-      if constexpr (!EARLY) {
+      uint32_t rec[PER];
+      const uint32_t j0 = wave * (uint32_t)PER;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {  // a lane without a record reads a tile's first word
-          const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j0 + i);
-          const uint32_t t = j0 + (uint32_t)i < p.n_here ? p.first + j0 + (uint32_t)i : p.first;
-          rec[i] = d.slot[(uint64_t)t * (uint64_t)kSlot + (lane < n ? lane : 0u)];
-        }
+      for (int i = 0; i < PER; ++i) {  // a lane without a record reads a tile's first word
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)p.count, (int)j0 + i);
+        const uint32_t t = j0 + (uint32_t)i < p.n_here ? p.first + j0 + (uint32_t)i : p.first;
+        rec[i] = d.slot[(uint64_t)t * (uint64_t)kSlot + (lane < n ? lane : 0u)];
       }
 #pragma unroll
       for (int i = 0; i < PER; ++i) {

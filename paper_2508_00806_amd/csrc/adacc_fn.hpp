@@ -19,7 +19,7 @@ typedef void (*PlaceBatchFn)(const TensorDesc*, const uint32_t*, uint32_t);
 // Types of the channel and channel-wise kernels
 typedef void (*ChannelPartialFn)(const uint16_t*, uint32_t, uint32_t, float*, uint32_t);
 typedef void (*ChannelScoreFn)(const float*, uint32_t, uint32_t, double*);
-typedef void (*ChannelSelectFn)(const void*, uint32_t, ChannelDesc);
+typedef void (*ChannelSelectFn)(const double*, ChannelDesc, const float*, uint32_t);
 typedef void (*ChannelFn)(TensorDesc, ChannelDesc);
 typedef void (*ChannelwiseItemsFn)(ChannelwiseDesc, uint32_t);
 typedef void (*ChannelwiseFn)(ChannelwiseDesc);

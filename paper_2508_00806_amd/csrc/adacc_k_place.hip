@@ -87,11 +87,12 @@ __global__ __launch_bounds__(kPlaceThreads, 4) void place_kernel(TensorDesc d, u
   __shared__ PlaceLds<WAVES, true> lds;
   place_dispatch<WAVES, true, true, true>(d, blockIdx.x, epoch, lds);
 }
-// ABS and STD up to kPlaceDirectTiles tiles: sixteen wavefronts to a workgroup's 64 tiles, so that those whose slot is too
+// ABS and STD up to kPlaceManyTiles tiles: sixteen wavefronts to a workgroup's 64 tiles, so that those whose slot is too
 // small are selected again four after the other and not sixteen, each of them a load from memory and some 600 instructions
 // by a wavefront alone.  ([8192, 4096] int8, the placement: STD at 3 sigma over groups of 64 of GELU values, every tile with more
-// than 64 outliers, 50.4 -> 25.4 us; over 512 of SiLU values 41.8 -> 20.8.  With 256 threads as well where no tile has that many: 64
-// tiles 3.7 -> 2.6 us, 9955 tiles 4.7 -> 4.0.)  TOPK, where this launch finds nothing to do, keeps the smaller workgroups.
+// than 64 outliers, 50.4 -> 25.4 us; over 512 of SiLU values 41.8 -> 20.8.  Where no tile has that many, both ways: [16000, 1024] STD at 6
+// sigma over 1024 26.4 -> 25.6, [14000, 2051] at 4 sigma over 512 40.7 -> 40.3.)  Where this launch as a rule finds nothing to do, TOPK among
+// others, the smaller workgroups stay (place_many).
 __global__ __launch_bounds__(kPlaceManyThreads) void place_many_kernel(TensorDesc d, uint32_t epoch) {
   constexpr int WAVES = kPlaceManyThreads / kWave;
   __shared__ PlaceLds<WAVES, false> lds;

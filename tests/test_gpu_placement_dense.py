@@ -1,8 +1,9 @@
 """Tiles with more outliers than a slot of the workspace holds: the placement selects them again, sixteen wavefronts of a workgroup
-sharing its 64 tiles (up to 32768 tiles; a window per wavefront beyond).  Everything is compared bit by bit with the oracle."""
+sharing its 64 tiles (up to 16384 tiles; four beyond, and a window per wavefront from 32769 on).  Everything is compared bit by bit with the oracle."""
 import pytest
 import torch
 
+import paper_2508_00806_amd as adacc
 from helpers import run_parity
 
 pytestmark = pytest.mark.gpu
@@ -10,9 +11,11 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("tile,tiles,rest,dtype", [(2048, 1, 0, torch.bfloat16), (2048, 15, 300, torch.float16), (2048, 63, 0, torch.bfloat16),
                                                   (2048, 65, 511, torch.bfloat16), (4096, 17, 4095, torch.bfloat16), (4096, 129, 0, torch.float16),
-                                                  (2048, 1041, 77, torch.bfloat16), (2048, 32768, 5, torch.bfloat16),
+                                                  (2048, 1041, 77, torch.bfloat16), (2048, 16384, 5, torch.bfloat16), (2048, 16385, 5, torch.bfloat16),
                                                   (2048, 32769, 0, torch.bfloat16)])
-def test_dense_tiles(tile, tiles, rest, dtype):
+@pytest.mark.parametrize("room", [0, adacc.SHORT_BYTES])  # none: two launches for every tensor
+def test_dense_tiles(tile, tiles, rest, dtype, room, monkeypatch):
+    monkeypatch.setattr(adacc, "SHORT_BYTES", room)
     n = tile * tiles + rest
     g = torch.Generator().manual_seed(n)
     x = (torch.rand(n, generator=g) - 0.5).to(dtype)

@@ -42,6 +42,14 @@ def test_against_the_oracle(method, tiles, rest):
         run_parity(x, _case(gq, gs, mode, thresh, k, bits, asym))
 
 
+@pytest.mark.parametrize("tiles,rest", [(1, 0), (5, 61), (63, 30), (64, 0), (257, 30)])
+@pytest.mark.parametrize("method", METHODS)
+def test_two_launches_against_the_oracle(method, tiles, rest, monkeypatch):
+    """The same tensors with workspaces that have no room for the words."""
+    monkeypatch.setattr(adacc, "SHORT_BYTES", 0)
+    test_against_the_oracle(method, tiles, rest)
+
+
 def _compressed(m, x, ws):
     lay = adacc.layout_of(m, x.numel())
     blob = torch.zeros(lay.total_bytes, dtype=torch.uint8, device="cuda")
