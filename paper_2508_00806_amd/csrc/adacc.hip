@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -371,15 +372,15 @@ static CompressFn compress_fn(const adacc_method* m, bool e8, bool rowwise, bool
 static int clear_device(void* mem, uint64_t bytes, hipStream_t s);
 
 // The words of the one-launch compression lie at the end of a workspace, behind what any other call has used of it so far:
-// only those launches write them, so that a word which names the current epoch was written by this launch.  The host struct says
-// whether that still holds; a call that needs the whole workspace ends it.
+// only those launches write them, each with a number of its own, so that a word which names a launch was written by it.  The host struct
+// says whether that still holds; a call that needs the whole workspace ends it.
 constexpr uint32_t kShortWordsOurs = 1;
 static_assert(kShortBytes == ADACC_SHORT_BYTES, "adacc.h says how much room that is");
 static uint64_t short_words_off(const adacc_workspace* ws) { return (ws->bytes - kShortBytes) & ~255ull; }
 static void use_workspace(adacc_workspace* ws, uint64_t bytes) {
   if (ws->reserved == kShortWordsOurs && bytes > short_words_off(ws)) ws->reserved = 0;
 }
-// A launch that is being captured would be replayed with the same epoch.
+// A launch that is being captured would be replayed with the same number.
 static bool captured(hipStream_t s) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
@@ -711,11 +712,14 @@ static int compress_one(const adacc_method* method, const void* src, uint64_t nu
   }
   if (p.outliers && ws->reserved == kShortWordsOurs && in_one_launch(method, p) && !captured(s)) {
     uint32_t epoch = 0;
-    rc = next_epoch(ws, s, &epoch);
+    rc = next_epoch(ws, s, &epoch);  // counts this launch too
     if (rc != ADACC_OK) return rc;
+    // the words name it by a number of its own, whatever structs describe the workspace
+    static std::atomic<unsigned long long> launches{1};
+    const unsigned long long tag = launches.fetch_add(1) << kShortCountBits;
     unsigned long long* words = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(ws->device_mem) + short_words_off(ws));
     hipLaunchKernelGGL(compress_short_fn(method, p), dim3(blocks_of(p.n_tiles, kWavesPerWg) + (p.tail != 0 ? 1u : 0u)), dim3(kThreads), 0, s, d,
-                       epoch, words, (uint32_t)knobs().short_polls);
+                       tag, words, (uint32_t)knobs().short_polls);
     return launch_check("compress_short_kernel");
   }
   CompressFn fn = compress_fn(method, p.tile_elems == 4096, p.rowwise || topk_in_rows(method, p), topk_whole_tile(method, p));

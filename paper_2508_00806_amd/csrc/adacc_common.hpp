@@ -211,6 +211,7 @@ constexpr uint32_t kEpochMax = 0x3FFFFFFFu;
 // [1000, 4096] 11.4 / 11.2, [2000, 4096] 14.1 / 14.2.)
 constexpr uint32_t kShortWorkgroups = 2560, kShortWorkgroupsEven = 1792, kShortWorkgroupsRows = 1280, kShortWorkgroupsTopk = 256;
 constexpr uint64_t kShortBytes = 8ull * kShortWorkgroups;
+constexpr uint32_t kShortCountBits = 16;  // of a word; a workgroup's tiles have at most 16384 elements
 
 // the batch compression kernels, by the weight of the variants they hold (adacc_kernels.hpp)
 enum : int { kBatchRows4 = 0, kBatchAny4 = 1, kBatchTopk4 = 2, kBatchAny8 = 3, kBatchTopk8 = 4, kBatchKinds = 5 };

@@ -8,7 +8,7 @@ namespace adacc {
 
 typedef void (*CompressFn)(TensorDesc, uint32_t);
 typedef void (*DecompressFn)(TensorDesc, uint32_t);
-typedef void (*CompressShortFn)(TensorDesc, uint32_t, unsigned long long*, uint32_t);
+typedef void (*CompressShortFn)(TensorDesc, unsigned long long, unsigned long long*, uint32_t);
 typedef void (*BatchCompressFn)(const TensorDesc*, uint32_t);
 typedef void (*BatchDecompressFn)(const TensorDesc*);
 typedef void (*PlaceSumFn)(TensorDesc);

@@ -3,8 +3,8 @@
 // The order of the outlier stream needs the number of outliers in all tiles before a tile's own.  For a tensor of up to
 // kShortWorkgroups workgroups those do not wait for a second kernel: every workgroup encodes its four tiles, keeps their
 // outliers in LDS, publishes their number in a word of the workspace, and looks at the words of the workgroups before it
-// until they are there.  A word carries the number of the launch (the workspace's epoch) beside the count, is written by
-// these launches alone, and says everything by itself, so nothing has to be cleared, and no other memory has to be ordered.
+// until they are there.  A word carries the number of the launch (48 bits, of all such launches of the process) above the count, is written
+// by these launches alone, and says everything by itself, so nothing has to be cleared, and no other memory has to be ordered.
 //
 // No wait is without an end, whatever order workgroups are started in: a wavefront whose patience is at an end counts the
 // outliers of the missing tiles itself, from the source.  Workgroups are started in the order of their numbers on every XCD and nobody
@@ -32,13 +32,14 @@ struct ShortShared {
 // at 3 sigma over 64, [1200, 3072] 17.2, 14.9.)
 struct ShortSink : SlotSink {
   uint32_t* arrived;
-  uint32_t tiles, epoch;  // tiles of the workgroup
+  uint32_t tiles;  // of the workgroup
+  unsigned long long tag;
   unsigned long long* word;
   __device__ __forceinline__ void tell(uint32_t found) const {
     if (lane_id() == 0) {
       const uint32_t before = atomicAdd(arrived, 1u << 24 | found);
       if ((before >> 24) + 1u == tiles)
-        __hip_atomic_store(word, (unsigned long long)epoch << 32 | ((before & 0xFFFFFFu) + found), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(word, tag | ((before & 0xFFFFFFu) + found), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 };
@@ -66,7 +67,7 @@ __device__ __forceinline__ uint32_t short_tile(const TensorDesc& d, uint32_t til
 
 // The outliers in the tiles of the first `n` workgroups, to every thread.
 template <int MODE, int E, bool WHOLE>
-__device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint32_t n, uint32_t epoch, uint32_t patience,
+__device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint32_t n, unsigned long long tag, uint32_t patience,
                                                        const unsigned long long* words, uint32_t (&part)[kWavesPerWg]) {
   uint32_t sum = 0u;
   for (uint32_t i0 = 0u; i0 < n; i0 += (uint32_t)kThreads) {  // uniform
@@ -76,8 +77,8 @@ __device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint
       if (tries != 0u) __builtin_amdgcn_s_sleep(1);
       if (open) {
         const unsigned long long w = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((uint32_t)(w >> 32) == epoch) {
-          sum += (uint32_t)w;
+        if (w >> kShortCountBits == tag >> kShortCountBits) {
+          sum += (uint32_t)(w - tag);
           open = false;
         }
       }
@@ -95,7 +96,7 @@ __device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint
 
 // The fallback's registers are what bounds it; a short tensor does not fill the device anyway.
 template <int MODE, int E, bool WHOLE>
-__global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc d, uint32_t epoch, unsigned long long* words, uint32_t patience) {
+__global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc d, unsigned long long tag, unsigned long long* words, uint32_t patience) {
   __shared__ union {
     ShortShared tiles;
     struct {
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc 
   const uint32_t workgroups = (d.n_tiles + (uint32_t)kWavesPerWg - 1u) / (uint32_t)kWavesPerWg;
   if (blockIdx.x == workgroups) {  // the end that the groups do not divide
     compress_tail<false>(d, [&] {
-      return outliers_of_others<MODE, E, WHOLE>(d, workgroups, epoch, patience, words, lds.tail.part);
+      return outliers_of_others<MODE, E, WHOLE>(d, workgroups, tag, patience, words, lds.tail.part);
     }, lds.tail.rest);
     return;
   }
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc 
   if (tile < d.n_tiles) {  // uniform
     const uint32_t tiles = d.n_tiles - blockIdx.x * (uint32_t)kWavesPerWg;
     const ShortSink record{{lds.tiles.record[wave], tile * (uint32_t)(E * kRow)}, &lds.tiles.arrived,
-                           tiles < (uint32_t)kWavesPerWg ? tiles : (uint32_t)kWavesPerWg, epoch, words + blockIdx.x};
+                           tiles < (uint32_t)kWavesPerWg ? tiles : (uint32_t)kWavesPerWg, tag, words + blockIdx.x};
     if constexpr (!WHOLE) {  // (the codes' form is looked at behind the selection)
       found = short_tile<MODE, kBitsAny, false, E, false>(d, tile, record);
     } else {
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(kThreads, 4) void compress_short_kernel(TensorDesc 
   uint32_t before = 0u;
 #pragma unroll
   for (uint32_t w = 0; w < (uint32_t)kWavesPerWg; ++w) before += w < wave ? lds.tiles.count[w] : 0u;
-  const uint32_t pos = before + outliers_of_others<MODE, E, WHOLE>(d, blockIdx.x, epoch, patience, words, lds.tiles.part);
+  const uint32_t pos = before + outliers_of_others<MODE, E, WHOLE>(d, blockIdx.x, tag, patience, words, lds.tiles.part);
   if (tile >= d.n_tiles) return;
   if (lane == 0u) {
     d.tile_ptr[tile] = pos;

@@ -85,6 +85,19 @@ def test_the_same_as_in_two_launches(tiles):
             assert torch.equal(_compressed(m, x, room), _compressed(m, x, exact))
 
 
+def test_two_structs_of_one_workspace():
+    """Launches through copies of the host struct, whose counters repeat, on one buffer."""
+    n = 2048 * 70
+    m = adacc_method(_case(64, 512, "std", 2.5, 0, 8, 0), n // 8)
+    xs = [_values(n, 2048, torch.Generator().manual_seed(s), torch.bfloat16).cuda() for s in (1, 2)]
+    want = [_compressed(m, x, adacc.alloc_workspace(adacc.workspace_bytes(m, n))) for x in xs]
+    ws = adacc.alloc_workspace(adacc.workspace_bytes(m, n))
+    other = adacc.Workspace(ws.buffer)
+    for _ in range(4):
+        for x, w, b in zip(xs, (ws, other), want):
+            assert torch.equal(_compressed(m, x, w), b)
+
+
 def test_two_streams_at_a_time():
     """Launches that wait for their own workgroups side by side, each stream with a workspace of its own."""
     n = 2048 * 4 * 2000 + 24
