@@ -126,7 +126,8 @@ typedef struct adacc_workspace {
   void *device_mem; /* caller-owned device buffer, 256-byte aligned            */
   uint64_t bytes;   /* its size                                                */
   uint32_t epoch;   /* launches since the last clear; maintained by the library */
-  uint32_t reserved; /* maintained by the library: 1 while no call has used the last ADACC_SHORT_BYTES */
+  uint32_t reserved; /* maintained by the library: 1 while the buffer has ADACC_SHORT_BYTES at its end that no call through this
+                        struct but the one-launch compressions has needed; only adacc_workspace_init sets it again */
 } adacc_workspace;
 
 /* With at least this much room behind adacc_workspace_bytes, and outside of graph capture, adacc_compress takes a short tensor

@@ -371,9 +371,11 @@ static CompressFn compress_fn(const adacc_method* m, bool e8, bool rowwise, bool
 
 static int clear_device(void* mem, uint64_t bytes, hipStream_t s);
 
-// The words of the one-launch compression lie at the end of a workspace, behind what any other call has used of it so far:
-// only those launches write them, each with a number of its own, so that a word which names a launch was written by it.  The host struct
-// says whether that still holds; a call that needs the whole workspace ends it.
+// The words of the one-launch compression lie at the end of a workspace, each with the number of its launch, which is one of all such
+// launches of the process and has no like among what other calls write (short_tag): a word that names a launch was written by it,
+// whatever is left in the buffer by calls through other structs, replayed graphs or an earlier use.  The host struct says whether all
+// other calls through it have kept in front of the words so far; one that needed their place ends the short way of this struct, whose
+// buffer has no room to spare.
 constexpr uint32_t kShortWordsOurs = 1;
 static_assert(kShortBytes == ADACC_SHORT_BYTES, "adacc.h says how much room that is");
 static uint64_t short_words_off(const adacc_workspace* ws) { return (ws->bytes - kShortBytes) & ~255ull; }
@@ -714,9 +716,8 @@ static int compress_one(const adacc_method* method, const void* src, uint64_t nu
     uint32_t epoch = 0;
     rc = next_epoch(ws, s, &epoch);  // counts this launch too
     if (rc != ADACC_OK) return rc;
-    // the words name it by a number of its own, whatever structs describe the workspace
-    static std::atomic<unsigned long long> launches{1};
-    const unsigned long long tag = launches.fetch_add(1) << kShortCountBits;
+    static std::atomic<unsigned long long> launches{kShortFirstLaunch};
+    const unsigned long long tag = short_tag(launches.fetch_add(1));
     unsigned long long* words = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(ws->device_mem) + short_words_off(ws));
     hipLaunchKernelGGL(compress_short_fn(method, p), dim3(blocks_of(p.n_tiles, kWavesPerWg) + (p.tail != 0 ? 1u : 0u)), dim3(kThreads), 0, s, d,
                        tag, words, (uint32_t)knobs().short_polls);

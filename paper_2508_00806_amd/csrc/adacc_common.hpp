@@ -212,6 +212,18 @@ constexpr uint32_t kEpochMax = 0x3FFFFFFFu;
 constexpr uint32_t kShortWorkgroups = 2560, kShortWorkgroupsEven = 1792, kShortWorkgroupsRows = 1280, kShortWorkgroupsTopk = 256;
 constexpr uint64_t kShortBytes = 8ull * kShortWorkgroups;
 constexpr uint32_t kShortCountBits = 16;  // of a word; a workgroup's tiles have at most 16384 elements
+// A word: a one and 31 bits of the launch's number, a one and its other 15 bits, the count.  Nothing else that a call writes to a workspace looks like
+// one, so what other calls leave in its place, whatever struct they went through, does not read as a word.  Counts, their sums, launch counters
+// and a slot's records are below 2^31 and written 4 bytes at a time: either half of a word that they replace has lost its top bit.  The
+// table of a batch covers words whole, and its upper halves (sizes, upper halves of addresses, floats that are not negative) are below
+// 2^31 too, but for a capacity, which would have to be the number itself, more than any tensor's length; numbers begin at an arbitrary one.
+// (Counted from 1 in 48 bits, element number L of a slot's record beside an empty record read as a word of launch L, and under any upper half
+// that an earlier word had left there still did.)
+constexpr unsigned long long kShortFirstLaunch = 0x95A793E1ull << 15;
+constexpr unsigned long long short_tag(unsigned long long launch) {
+  return launch >> 15 << 32 | 1ull << 31 | (launch & 0x7FFFull) << kShortCountBits;
+}
+static_assert(short_tag(kShortFirstLaunch) == 0x95A793E180000000ull && short_tag(kShortFirstLaunch + 0x8001) == 0x95A793E280010000ull, "both halves");
 
 // the batch compression kernels, by the weight of the variants they hold (adacc_kernels.hpp)
 enum : int { kBatchRows4 = 0, kBatchAny4 = 1, kBatchTopk4 = 2, kBatchAny8 = 3, kBatchTopk8 = 4, kBatchKinds = 5 };

@@ -3,8 +3,9 @@
 // The order of the outlier stream needs the number of outliers in all tiles before a tile's own.  For a tensor of up to
 // kShortWorkgroups workgroups those do not wait for a second kernel: every workgroup encodes its four tiles, keeps their
 // outliers in LDS, publishes their number in a word of the workspace, and looks at the words of the workgroups before it
-// until they are there.  A word carries the number of the launch (48 bits, of all such launches of the process) above the count, is written
-// by these launches alone, and says everything by itself, so nothing has to be cleared, and no other memory has to be ordered.
+// until they are there.  A word carries the number of the launch, of all such launches of the process, above the count (short_tag) and
+// says everything by itself, so nothing has to be cleared, and no other memory has to be ordered; what other calls may have
+// left in its place does not read as one.
 //
 // No wait is without an end, whatever order workgroups are started in: a wavefront whose patience is at an end counts the
 // outliers of the missing tiles itself, from the source.  Workgroups are started in the order of their numbers on every XCD and nobody

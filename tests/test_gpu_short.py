@@ -98,6 +98,35 @@ def test_two_structs_of_one_workspace():
             assert torch.equal(_compressed(m, x, w), b)
 
 
+def _overwritten_words():
+    """Two structs of one buffer: before every short call through the one, a long call through the other leaves in the words' place slots whose
+    first record is the element whose number is that of the short call in this process."""
+    long, short = 2048 * 9000, 2048 * 7000
+    ml, ms = (adacc_method(_case(1024, 0, "abs", 2.5, 0, 8, 0), n // 8) for n in (long, short))
+    buffer = torch.empty(adacc.workspace_bytes(ml, long), dtype=torch.uint8, device="cuda")
+    one, other = adacc.Workspace(buffer), adacc.Workspace(buffer)
+    exact = adacc.Workspace(torch.empty(adacc.workspace_bytes(ms, short), dtype=torch.uint8, device="cuda"))
+    x = (torch.rand(long, generator=torch.Generator().manual_seed(1)) - 0.5).to(torch.bfloat16).cuda()
+    y = torch.randn(short, generator=torch.Generator().manual_seed(2)).to(torch.bfloat16).cuda()
+    want = _compressed(ms, y, exact)
+    for launch in range(1, 9):
+        z = x.clone()
+        z[launch::2048] = 3.0
+        _compressed(ml, z, one)
+        assert torch.equal(_compressed(ms, y, other), want), launch
+
+
+def _in_a_process_of_its_own(code, **env):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = "import sys; sys.path[:0] = ['tests', '.']; import torch; import test_gpu_short as t\n" + code + "\nprint('all done')"
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, **env), cwd=root, capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0 and "all done" in r.stdout, r.stderr[-2000:]
+
+
+def test_words_that_another_struct_has_overwritten():
+    _in_a_process_of_its_own("t._overwritten_words()")
+
+
 def test_two_streams_at_a_time():
     """Launches that wait for their own workgroups side by side, each stream with a workspace of its own."""
     n = 2048 * 4 * 2000 + 24
