@@ -66,29 +66,46 @@ __device__ __forceinline__ uint32_t short_tile(const TensorDesc& d, uint32_t til
   return encode_tile<MODE, BITS, ASYM, E, false, WHOLE, true>(d, g, raw, tile, sink, 0u, (uint32_t)kSlot);
 }
 
-// The outliers in the tiles of the first `n` workgroups, to every thread.
+// What workgroup `i` has published of this launch: true, and the count, or false.
+__device__ __forceinline__ bool look(const unsigned long long* words, uint32_t i, unsigned long long tag, uint32_t& count) {
+  const unsigned long long w = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  count = (uint32_t)(w - tag);
+  return w >> kShortCountBits == tag >> kShortCountBits;
+}
+
+// The outliers in the tiles of the first `n` workgroups, to every thread.  The patience is that of a wavefront for the whole wait; when it is at
+// an end, all words are looked at once more, and what is missing is counted here and published for all: it is the number that
+// the workgroup itself will publish.  Waiting workgroups begin at different words, so that they share the missing ones among them.
 template <int MODE, int E, bool WHOLE>
 __device__ __forceinline__ uint32_t outliers_of_others(const TensorDesc& d, uint32_t n, unsigned long long tag, uint32_t patience,
-                                                       const unsigned long long* words, uint32_t (&part)[kWavesPerWg]) {
-  uint32_t sum = 0u;
+                                                       unsigned long long* words, uint32_t (&part)[kWavesPerWg]) {
+  uint32_t sum = 0u, looks = 0u;
   for (uint32_t i0 = 0u; i0 < n; i0 += (uint32_t)kThreads) {  // uniform
     const uint32_t i = i0 + threadIdx.x;
     bool open = i < n;
-    for (uint32_t tries = 0u; __builtin_amdgcn_ballot_w64(open) != 0ull && tries < patience; ++tries) {  // uniform
-      if (tries != 0u) __builtin_amdgcn_s_sleep(1);
-      if (open) {
-        const unsigned long long w = __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (w >> kShortCountBits == tag >> kShortCountBits) {
-          sum += (uint32_t)(w - tag);
-          open = false;
-        }
+    uint64_t left = __builtin_amdgcn_ballot_w64(open);
+    for (bool first = true; left != 0ull && (first || looks < patience); first = false, ++looks) {  // uniform
+      if (!first) __builtin_amdgcn_s_sleep(1);
+      uint32_t count;
+      if (open && look(words, i, tag, count)) {
+        sum += count;
+        open = false;
       }
+      left = __builtin_amdgcn_ballot_w64(open);
     }
-    for (uint64_t left = __builtin_amdgcn_ballot_w64(open); __builtin_expect(left != 0ull, 0); left &= left - 1ull) {  // uniform
-      const uint32_t lane = (uint32_t)__builtin_ctzll(left);
-      const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)i, (int)lane) * (uint32_t)kWavesPerWg;
-      uint32_t found = 0u;
-      for (uint32_t t = first; t < first + (uint32_t)kWavesPerWg && t < d.n_tiles; ++t) found += select_tile<MODE, E, WHOLE>(d, t, 0u, 0u);
+    while (__builtin_expect(left != 0ull, 0)) {  // uniform
+      const uint32_t begin = blockIdx.x % (uint32_t)kWave;
+      const uint64_t behind = left >> begin << begin;
+      const uint32_t lane = (uint32_t)__builtin_ctzll(behind != 0ull ? behind : left);
+      left &= ~(1ull << lane);
+      const uint32_t g = (uint32_t)__builtin_amdgcn_readlane((int)i, (int)lane);
+      uint32_t found;
+      if (__builtin_amdgcn_ballot_w64(!look(words, g, tag, found)) != 0ull) {  // uniform
+        found = 0u;
+        for (uint32_t t = g * (uint32_t)kWavesPerWg; t < (g + 1u) * (uint32_t)kWavesPerWg && t < d.n_tiles; ++t)
+          found += select_tile<MODE, E, WHOLE>(d, t, 0u, 0u);
+        if (lane_id() == 0) __hip_atomic_store(words + g, tag | found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       if ((uint32_t)lane_id() == lane) sum += found;
     }
   }

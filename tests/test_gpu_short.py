@@ -152,3 +152,29 @@ def test_wavefronts_that_count_for_others():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, ADACC_SHORT_POLLS="1"), cwd=root, capture_output=True, text=True, timeout=110)
     assert r.returncode == 0 and "counted" in r.stdout, r.stderr[-2000:]
+
+
+def test_wavefronts_that_count_for_others_over_many_words():
+    """The same with more workgroups than a workgroup looks at together: every word once, what is missing counted by some and found by the rest."""
+    _in_a_process_of_its_own("for m in t.METHODS[:5]: t.test_against_the_oracle(m, 1301 if m[5] == 2048 else 2605, 30)", ADACC_SHORT_POLLS="1")
+
+
+def test_beside_kernels_that_hold_the_device():
+    """Launches on one stream while long ones on another leave them some compute units at a time."""
+    n = 2048 * 4 * 1700 + 24
+    m = adacc_method(_case(64, 512, "std", 2.5, 0, 8, 0), n // 8)
+    x = _values(n, 2048, torch.Generator().manual_seed(3), torch.bfloat16).cuda()
+    ws = adacc.alloc_workspace(adacc.workspace_bytes(m, n))
+    want = _compressed(m, x, ws)
+    plain = adacc_method(_case(64, 0, "none", 0.0, 0, 8, 0), 0)
+    y = torch.randn(1 << 27, device="cuda").to(torch.bfloat16)
+    blob = torch.zeros(adacc.layout_of(plain, y.numel()).total_bytes, dtype=torch.uint8, device="cuda")
+    blobs = [torch.zeros_like(want) for _ in range(12)]
+    torch.cuda.synchronize()
+    one, other = torch.cuda.Stream(), torch.cuda.Stream()
+    for b in blobs:
+        for _ in range(4):
+            adacc.compress(plain, y, blob, stream=one)
+        adacc.compress(m, x, b, ws, stream=other)
+    torch.cuda.synchronize()
+    assert all(torch.equal(b, want) for b in blobs)
