@@ -1,5 +1,7 @@
 """Build libadacc.so (HIP, gfx950) in-tree.  `python -m paper_2508_00806_amd.build`."""
+import importlib.machinery
 import os
+import shlex
 import subprocess
 import sys
 import sysconfig
@@ -7,7 +9,7 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libadacc.so")
-CALLS = os.path.join(HERE, "_calls.so")  # the Python binding's marshalling of the calls (plain C, no HIP)
+CALLS = os.path.join(HERE, "_calls" + importlib.machinery.EXTENSION_SUFFIXES[0])  # the Python binding's marshalling of the calls (plain C, no HIP)
 CSRC = os.path.join(HERE, "csrc")
 # one translation unit per group of kernel instantiations, so that the library builds in parallel
 # Sources that touch the tensor's elements are compiled once per 16-bit format (bf16; binary16 with -DADACC_F16=1).
@@ -46,12 +48,19 @@ FLAGS = [
 ]
 
 
-def build_calls(verbose: bool = False) -> str:
-    cmd = ["gcc", "-std=c11", "-O2", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter", "-I", os.path.join(ROOT, "include"),
+def build_calls(verbose: bool = False):
+    """The path of what was built; None where there is no C compiler or no Python.h: the binding then marshals by ctypes."""
+    cmd = [*shlex.split(os.environ.get("CC", "gcc")), "-std=c11", "-O2", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter", "-I", os.path.join(ROOT, "include"),
            "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "adacc_calls.c"), "-o", CALLS]
     if verbose:
         print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    if os.path.exists(CALLS):
+        os.remove(CALLS)  # (none is better than one of an older source)
+    try:
+        subprocess.run(cmd, check=True)
+    except (OSError, subprocess.CalledProcessError) as e:
+        print(f"{os.path.basename(CALLS)} is not built, calls go the general way: {e}", flush=True)
+        return None
     return CALLS
 
 

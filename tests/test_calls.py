@@ -1,6 +1,9 @@
 """The native marshalling of the binding's calls hands the library what the general way (ctypes) hands it, and leaves to that way what it
 does not take.  The library's functions are stand-ins that write their arguments down; no GPU is involved."""
 import ctypes
+import os
+import sysconfig
+import warnings
 
 import pytest
 import torch
@@ -131,3 +134,40 @@ def test_what_is_not_marshalled_reaches_no_library_call(world):
     with pytest.raises(AttributeError):
         native.compress(object(), x, blob, None, None, 1)
     assert seen == []
+
+
+def _broken(tmp_path, content):
+    path = tmp_path / "_calls.so"
+    if content is not None:
+        path.write_bytes(content)
+    return str(path)
+
+
+@pytest.mark.parametrize("content", [None, b"not a library"])  # not there; of another interpreter, or half written
+def test_without_the_native_marshalling_the_library_alone_serves(world, monkeypatch, tmp_path, content):
+    seen, general, answer = world
+    answer[0] = adacc.OK
+    for i, call in enumerate(_every_call()):
+        general(True)
+        want = _outcome(call), list(seen)
+        del seen[:]
+        general(False)
+        monkeypatch.setattr(adacc, "CALLS_PATH", _broken(tmp_path, content))
+        with warnings.catch_warnings(record=True) as told:
+            warnings.simplefilter("always")
+            assert (_outcome(call), list(seen)) == want
+            again = _outcome(call)
+        assert again == want[0] and len(told) <= 1  # looked for once
+        del seen[:]
+
+
+def test_the_native_marshalling_carries_the_interpreters_tag():
+    assert adacc.CALLS_PATH.endswith("_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def test_a_build_without_a_c_compiler_goes_on(monkeypatch, tmp_path, capsys):
+    from paper_2508_00806_amd import build
+    monkeypatch.setattr(build, "CALLS", _broken(tmp_path, b"an older one"))
+    monkeypatch.setenv("CC", str(tmp_path / "no-compiler"))
+    assert build.build_calls() is None
+    assert not os.path.exists(build.CALLS) and "general way" in capsys.readouterr().out
