@@ -321,7 +321,6 @@ class Workspace:
         self.c = CWorkspace()
         _check(lib().adacc_workspace_init(ctypes.byref(self.c), _ptr(buffer), _nbytes(buffer), _stream(stream)),
                "adacc_workspace_init")
-        self.address = ctypes.addressof(self.c)
 
     @property
     def ref(self):
@@ -335,7 +334,7 @@ def _ws(workspace):
 def compress(method: Method, src, blob, workspace=None, numel=None, stream=None):
     if type(method) is Method and (workspace is None or type(workspace) is Workspace):
         try:
-            rc = calls().compress(method, src, blob, None if workspace is None else workspace.address, numel, stream)
+            rc = calls().compress(method, src, blob, None if workspace is None else ctypes.addressof(workspace.c), numel, stream)
         except TypeError:  # (nothing was called) not what it marshals
             pass
         else:

@@ -171,3 +171,21 @@ def test_a_build_without_a_c_compiler_goes_on(monkeypatch, tmp_path, capsys):
     monkeypatch.setenv("CC", str(tmp_path / "no-compiler"))
     assert build.build_calls() is None
     assert not os.path.exists(build.CALLS) and "general way" in capsys.readouterr().out
+
+
+def test_a_workspace_is_handed_over_as_it_is_now(world):
+    """The struct that the workspace holds at the time of the call, not one that it held before."""
+    seen, general, answer = world
+    answer[0] = adacc.OK
+    m = adacc.Method(outlier_mode=adacc.OUTLIER_ABS, thresh=1.0, max_outliers=9)
+    x, blob, w = torch.zeros(64, dtype=torch.bfloat16), torch.zeros(4096, dtype=torch.uint8), _workspace()
+    w.c = adacc.CWorkspace(8192, 1024, 3, 0)
+    bare = adacc.Workspace.__new__(adacc.Workspace)
+    bare.c = adacc.CWorkspace(12288, 2048, 5, 0)
+    for workspace in (w, bare):
+        for on in (True, False):
+            general(on)
+            assert _outcome(lambda: adacc.compress(m, x, blob, workspace, stream=17)) is None
+        one, other = seen
+        assert one == other and one[1][5] == (workspace.c.device_mem, workspace.c.bytes, workspace.c.epoch, 0)
+        del seen[:]
