@@ -89,7 +89,7 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
         self.retained = []   # (shape, reason) of tensors offered to the policy and saved as they are
         self._status = _StatusPool()
         # by device and stream, grown on demand, reused by every tensor that is packed there (compressions of two streams may overlap):
-        self._ws = {}        # workspace of compression with outliers
+        self._ws = {}        # workspace of compression with outliers, and what it was made for
         self._cws = {}       # workspace of the channel statistics
         super().__init__(self._pack, self._unpack)
 
@@ -150,9 +150,9 @@ class SavedActivationCompression(torch.autograd.graph.saved_tensors_hooks):
             ws = None
             if m.outlier_mode != OUTLIER_NONE:
                 want = workspace_bytes(m, numel)
-                ws = self._ws.get(at)
-                if ws is None or ws.c.bytes < want:
-                    ws = self._ws[at] = alloc_workspace(want, device=t.device)
+                ws, room = self._ws.get(at, (None, 0))
+                if ws is None or room < want:  # (what was asked for: the bytes behind it belong to the one-launch compressions)
+                    ws, _ = self._ws[at] = alloc_workspace(want, device=t.device), want
             compress(m, t, blob, ws, stream=stream)
         if ev:
             ev[1].record(stream)

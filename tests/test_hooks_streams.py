@@ -121,3 +121,26 @@ def test_streams_do_not_share_a_workspace(kind, world, monkeypatch):
         now["stream"] = streams[name]
         ctx._pack(t)
     assert used[0] is used[1] is used[3] and used[2] is used[4] and used[0] is not used[2]
+
+
+def test_no_tensor_takes_the_room_behind_a_workspace(world, monkeypatch):
+    """Tensors of growing size in one context: each finds a workspace that holds it in front of the last SHORT_BYTES, which compressions of
+    short tensors in one launch use and lose once another call has reached into them."""
+    made, used = [], []
+
+    class Workspace:
+        def __init__(self, nbytes):
+            self.c = adacc.CWorkspace(256, (nbytes + 255) // 256 * 256 + adacc.SHORT_BYTES, 0, 1)
+            made.append(self)
+    monkeypatch.setattr(hooks, "alloc_workspace", lambda nbytes, device=None: Workspace(nbytes))
+
+    def compress(m, t, blob, ws, stream=None):
+        blob.zero_()
+        used.append((ws, adacc.workspace_bytes(m, t.numel())))
+    monkeypatch.setattr(hooks, "compress", compress)
+    m = adacc.Method(bits=8, quant_group=64, outlier_mode=adacc.OUTLIER_STD, stat_group=64, thresh=4.0, max_outliers=64)
+    ctx = hooks.SavedActivationCompression(lambda t: m, timing=False)
+    for rows in (64, 8, 80, 96, 128, 100):  # 20480 bytes are 79 tiles
+        ctx._pack(torch.zeros(rows, 2048, dtype=torch.bfloat16))
+    assert all(ws.c.bytes - adacc.SHORT_BYTES >= need for ws, need in used) and len(used) == 6
+    assert used[1][0] is used[0][0] and used[5][0] is used[4][0]  # kept where it is large enough
