@@ -13,8 +13,8 @@ static DecompressFn pick(bool f32, bool generic, uint32_t rows) {
       default: return generic ? decompress_kernel<BITS, ASYM, true, true, 8> : decompress_kernel<BITS, ASYM, true, false, 8>;
     }
   }
-  if (rows == 2u) return generic ? decompress_kernel<BITS, ASYM, false, true, 2> : decompress_kernel<BITS, ASYM, false, false, 2>;
-  return generic ? decompress_kernel<BITS, ASYM, false, true, 4> : decompress_kernel<BITS, ASYM, false, false, 4>;
+  if (generic) return decompress_kernel<BITS, ASYM, false, true, 4>;  // (no smaller pieces there: piece_rows)
+  return rows == 2u ? decompress_kernel<BITS, ASYM, false, false, 2> : decompress_kernel<BITS, ASYM, false, false, 4>;
 }
 DecompressFn decompress_fn(uint32_t bits, uint32_t asym, bool f32, bool generic, uint32_t rows) {
   if (bits == 4) return asym ? pick<4, true>(f32, generic, rows) : pick<4, false>(f32, generic, rows);

@@ -15,14 +15,14 @@ union PlaceLds {  // a workgroup places tiles or does the tensor's end
 };
 
 // block: of kPlaceTiles tiles (kSumTiles of a long tensor), or the one behind the last: the tensor's end
-// WAVES: of the workgroup.  DIRECT, WIDE: blocks of kPlaceTiles resp. kSumTiles tiles.  TOPK: tensors of that mode too
-template <int WAVES, bool DIRECT, bool WIDE, bool TOPK>
+// WAVES: of the workgroup.  WIDE: blocks of kSumTiles tiles too.  TOPK: tensors of that mode too
+template <int WAVES, bool WIDE, bool TOPK>
 __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t block, uint32_t epoch, PlaceLds<WAVES, WIDE>& lds) {
   const bool from_sums = d.from_sums != 0u;
   const bool topk = TOPK && d.mode == kModeTopk;
   // TOPK: regular counts everywhere (the usual case): the compression kernel has placed everything already
   const bool regular = topk && __hip_atomic_load(d.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch;
-  const bool wide = WIDE && (!DIRECT || d.place_per == (uint32_t)kSumTiles);
+  const bool wide = WIDE && d.place_per == (uint32_t)kSumTiles;
   const uint32_t per = wide ? (uint32_t)kSumTiles : (uint32_t)kPlaceTiles;
   const uint32_t blocks = (d.n_tiles + per - 1u) / per;
   if (block >= blocks) {
@@ -36,11 +36,9 @@ __device__ __forceinline__ void place_dispatch(const TensorDesc& d, uint32_t blo
   if (regular) return;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   PlacedTiles p;
-  if constexpr (WIDE && DIRECT) {
+  if constexpr (WIDE) {
     p = wide ? place_tiles<kSumTiles, WAVES>(d, block * per, per, false, 0u, from_sums, !topk, lds.place)
              : place_tiles<kPlaceTiles, WAVES>(d, block * per, per, false, 0u, false, !topk, lds.place);
-  } else if constexpr (WIDE) {
-    p = place_tiles<kSumTiles, WAVES>(d, block * per, per, false, 0u, from_sums, !topk, lds.place);
   } else {
     p = place_tiles<kPlaceTiles, WAVES>(d, block * per, per, false, 0u, false, !topk, lds.place);
   }
@@ -85,7 +83,7 @@ __global__ __launch_bounds__(kPlaceThreads) void place_sum_kernel(TensorDesc d) 
 __global__ __launch_bounds__(kPlaceThreads, 4) void place_kernel(TensorDesc d, uint32_t epoch) {
   constexpr int WAVES = kPlaceThreads / kWave;
   __shared__ PlaceLds<WAVES, true> lds;
-  place_dispatch<WAVES, true, true, true>(d, blockIdx.x, epoch, lds);
+  place_dispatch<WAVES, true, true>(d, blockIdx.x, epoch, lds);
 }
 // ABS and STD up to kPlaceManyTiles tiles: sixteen wavefronts to a workgroup's 64 tiles, so that those whose slot is too
 // small are selected again four after the other and not sixteen, each of them a load from memory and some 600 instructions
@@ -96,7 +94,7 @@ __global__ __launch_bounds__(kPlaceThreads, 4) void place_kernel(TensorDesc d, u
 __global__ __launch_bounds__(kPlaceManyThreads) void place_many_kernel(TensorDesc d, uint32_t epoch) {
   constexpr int WAVES = kPlaceManyThreads / kWave;
   __shared__ PlaceLds<WAVES, false> lds;
-  place_dispatch<WAVES, true, false, false>(d, blockIdx.x, epoch, lds);
+  place_dispatch<WAVES, false, false>(d, blockIdx.x, epoch, lds);
 }
 
 // a group of tensors of a table: blockIdx.y picks the tensor, blockIdx.x its block of tiles
@@ -111,7 +109,7 @@ __global__ __launch_bounds__(kPlaceThreads, 4) void place_batch_kernel(const Ten
   constexpr int WAVES = kPlaceThreads / kWave;
   __shared__ PlaceLds<WAVES, true> lds;
   const TensorDesc d = table[members[blockIdx.y]];
-  place_dispatch<WAVES, true, true, true>(d, blockIdx.x, epoch, lds);
+  place_dispatch<WAVES, true, true>(d, blockIdx.x, epoch, lds);
 }
 
 PlaceSumFn place_sum_fn() { return place_sum_kernel; }
