@@ -149,8 +149,8 @@ def calls():
             module = importlib.util.module_from_spec(spec)
             spec.loader.exec_module(module)
         except ImportError as e:  # libadacc.so alone serves; a call takes 1 to 2 us more of the host's time
-            warnings.warn(f"calls are marshalled by ctypes, not natively: {e}", RuntimeWarning, stacklevel=3)
             _calls = _LeavesAll()
+            warnings.warn(f"calls are marshalled by ctypes, not natively: {e}", RuntimeWarning, stacklevel=3)
             return _calls
         module.bind(*[ctypes.cast(f, ctypes.c_void_p).value
                       for f in (L.adacc_compress, L.adacc_decompress, L.adacc_mask_pack, L.adacc_mask_unpack, L.adacc_channel_compress,

@@ -61,3 +61,27 @@ def test_groups_of_any_size(case):
     narrow = torch.zeros_like(x)
     adacc.decompress(m, blob, narrow)
     assert torch.equal(wide.to(torch.bfloat16).view(torch.int16), narrow.view(torch.int16))
+
+
+def _binary16(mode, bits, asym, gq, gs, thresh, k, n):
+    m = adacc_method(dict(bits=bits, quant_group=gq, asym=asym, outlier_mode=mode, stat_group=gs, thresh=thresh, topk=k), n // 4, fmt=1)
+    return m, _tensor(n).to(torch.float16)
+
+
+@pytest.mark.parametrize("case,n,f32", [(c, n, f32) for c in CASES for n, f32 in (((1 << 25) + 777, True), ((1 << 26) + 1031, False))] +
+                         [(c, (1 << 28) + 2059, False) for c in CASES[2:4]])
+def test_small_pieces_in_binary16(case, n, f32):
+    m, x = _binary16(*case, n)
+    print(f"[pieces] binary16 {case} n={n} f32={f32}", flush=True)
+    _, one, many = _both(m, x, f32)
+    assert torch.equal(one.view(torch.int32 if f32 else torch.int16), many.view(torch.int32 if f32 else torch.int16))
+
+
+@pytest.mark.parametrize("case", [("none", 8, 0, 40, 0, 0.0, 0), ("std", 8, 0, 8200, 8200, 3.0, 0), ("topk", 4, 1, 96, 11040, 0.0, 5)])
+def test_groups_of_any_size_in_binary16(case):
+    n = (1 << 25) + 4107
+    m, x = _binary16(*case, n)
+    blob, wide, _ = _both(m, x, True)
+    narrow = torch.zeros_like(x)
+    adacc.decompress(m, blob, narrow)
+    assert torch.equal(wide.to(torch.float16).view(torch.int16), narrow.view(torch.int16))

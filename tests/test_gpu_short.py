@@ -8,6 +8,8 @@ import pytest
 import torch
 
 import paper_2508_00806_amd as adacc
+import test_gpu_placement
+import test_gpu_ragged
 from helpers import adacc_method, run_parity
 
 pytestmark = pytest.mark.gpu
@@ -83,6 +85,78 @@ def test_the_same_as_in_two_launches(tiles):
         for _ in range(3):  # other inputs through the same words
             x = x.flip(0)
             assert torch.equal(_compressed(m, x, room), _compressed(m, x, exact))
+
+
+# (method, tiles, elements behind them, one launch): both sides of every line, and what has no short way
+ROUTES = [(METHODS[0], 1280 * 4, 0, True), (METHODS[0], 1280 * 4 + 1, 0, False), (METHODS[3], 1280 * 4, 40, True), (METHODS[3], 1280 * 4 + 1, 40, False),
+          (METHODS[1], 1792 * 4, 0, True), (METHODS[1], 1792 * 4 + 1, 0, False), (METHODS[1], 1792 * 4 + 1, 40, True),
+          (METHODS[1], 2560 * 4, 40, True), (METHODS[1], 2560 * 4 + 1, 40, False), (METHODS[4], 1792 * 4, 0, True), (METHODS[4], 1792 * 4 + 1, 0, False),
+          (METHODS[5], 256 * 4, 0, True), (METHODS[5], 256 * 4 + 1, 0, False), (METHODS[8], 256 * 4, 9, True), (METHODS[8], 256 * 4 + 1, 9, False),
+          ((128, 128, "topk", 0.0, 4, 2048), 20, 0, True), ((128, 128, "topk", 0.0, 5, 2048), 20, 0, False), ((40, 40, "std", 3.0, 0, 4080), 20, 0, False),
+          (METHODS[1], 1, 0, True), (METHODS[1], 0, 40, True)]
+
+
+def _words(ws, workgroups):
+    off = (ws.c.bytes - adacc.SHORT_BYTES) // 256 * 256
+    return ws.buffer[off:off + 8 * workgroups].view(torch.int64)
+
+
+@pytest.mark.parametrize("method,tiles,rest,one", ROUTES)
+def test_which_calls_take_one_launch(method, tiles, rest, one):
+    """A call in one launch leaves its number and a count in every workgroup's word, another one leaves them alone."""
+    gq, gs, mode, thresh, k, tile = method
+    n = tiles * tile + rest
+    m = adacc_method(_case(gq, gs, mode, thresh, k, 8, 0), n // 8)
+    x = torch.randn(n, generator=torch.Generator().manual_seed(n)).to(torch.bfloat16).cuda()
+    ws = adacc.alloc_workspace(adacc.workspace_bytes(m, n))
+    words = _words(ws, max((tiles + 3) // 4, 1))
+    print(f"[route] {method} tiles={tiles} rest={rest}", flush=True)
+    found = adacc.read_status(_compressed(m, x, ws), adacc.layout_of(m, n))[0]
+    seen = words.cpu()
+    if not one or tiles == 0:
+        assert not seen.any()
+        return
+    assert bool((seen < 0).all()) and len(set((seen >> 16).tolist())) == 1  # (the top bit is part of a word)
+    counts = int((seen & 0xFFFF).sum())
+    assert counts == found if rest == 0 else counts <= found
+
+
+def test_a_captured_call_takes_two_launches():
+    n = 2048 * 70
+    m = adacc_method(_case(64, 512, "std", 2.5, 0, 8, 0), n // 8)
+    x = _values(n, 2048, torch.Generator().manual_seed(5), torch.bfloat16).cuda()
+    ws = adacc.alloc_workspace(adacc.workspace_bytes(m, n))
+    blob = torch.zeros(adacc.layout_of(m, n).total_bytes, dtype=torch.uint8, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        adacc.compress(m, x, blob, ws)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert not _words(ws, 18).any()
+        assert torch.equal(blob, _compressed(m, x, adacc.alloc_workspace(adacc.workspace_bytes(m, n))))
+
+
+# what these compare went over to one launch with the workspaces' room: the same once more without it
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("mode", ["abs", "std", "topk"])
+def test_short_last_groups_in_two_launches(mode, fmt, monkeypatch):
+    monkeypatch.setattr(adacc, "SHORT_BYTES", 0)
+    test_gpu_ragged.test_short_last_groups(mode, fmt)
+
+
+@pytest.mark.parametrize("rest", [1, 8, 1999, 2048, 2049, 4095])
+@pytest.mark.parametrize("mode", ["abs", "std", "topk"])
+def test_the_end_of_a_tensor_in_two_launches(mode, rest, monkeypatch):
+    monkeypatch.setattr(adacc, "SHORT_BYTES", 0)
+    test_gpu_placement.test_the_end_of_a_tensor_that_its_groups_do_not_divide(mode, rest)
+
+
+@pytest.mark.parametrize("shape", test_gpu_placement.SHAPES[:4])
+def test_slots_at_their_limit_in_two_launches(shape, monkeypatch):
+    monkeypatch.setattr(adacc, "SHORT_BYTES", 0)
+    test_gpu_placement.test_slots_at_their_limit(*shape)
 
 
 def test_two_structs_of_one_workspace():

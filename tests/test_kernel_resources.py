@@ -40,3 +40,11 @@ def test_no_vector_register_is_spilled(spills, kernels):
     ours = {n: s for n, s in spills.items() if re.search(r"\d" + kernels + "I", n)}
     assert any("bf16" in n for n in ours) and any("3f16" in n for n in ours)
     assert {n: s for n, s in ours.items() if s} == {}
+
+
+# those that bound their registers for reasons of their own: short tensors (four wavefronts a SIMD), the placement (four; sixteen to a workgroup)
+@pytest.mark.parametrize("kernels", ["compress_short_kernelI", "place_kernelE", "place_many_kernelE", "place_batch_kernelE", "decompress_kernelI"])
+def test_no_vector_register_is_spilled_either(spills, kernels):
+    ours = {n: s for n, s in spills.items() if re.search(r"\d" + kernels, n)}
+    assert any("bf16" in n for n in ours) and any("3f16" in n for n in ours)
+    assert {n: s for n, s in ours.items() if s} == {}
