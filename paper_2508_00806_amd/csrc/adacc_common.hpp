@@ -204,7 +204,7 @@ constexpr uint32_t kEpochMax = 0x3FFFFFFFu;
 // the encoder by rows in two launches, TOPK.  The lines lie where the wait for the other workgroups begins to cost as much as the
 // second launch.  (us both ways, two launches / one.  [rows, 1024] STD at 6 sigma over 1024: 20 rows 9.8 / 7.9, 128 10.3 / 8.2, 1024 11.0 /
 // 8.6, 4096 13.4 / 11.1, 8000 16.9 / 15.6, 12000 20.5 / 19.8, 16000 24.9 / 25.4.  [rows, 2051] at 4 sigma over 512: 3000 16.8 / 13.3, 7000
-// 24.1 / 22.7, 8191 35.3 / 33.8 (binary32), 12000 37.3 / 37.5; over 4096, [4000, 2255] 22.6 / 18.9, [12000, 2255] 41.0 / 38.4.  Where there is
+// 24.1 / 22.7, 8191 35.3 / 32.8 (binary32), 12000 37.3 / 37.5; over 4096, [4000, 2255] 22.6 / 18.9, [12000, 2255] 41.0 / 38.4.  Where there is
 // an encoder by rows: STD at 8 sigma over 64, [300, 3072] 10.0 / 7.5, [2000, 3072] 12.4 / 11.4, [4000, 3072] 18.9 / 19.1; softmax, ABS, [1200,
 // 512] 12.1 / 9.5, [20000, 512] 21.2 / 20.1, [40000, 512] 35.0 / 36.4; with more outliers a tile than a slot holds, STD at 3 sigma over 64, [1200,
 // 3072] 33.3 / 14.9, [4000, 3072] 42.6 / 28.4.  TOPK, whose second launch finds nothing to do: [20, 1024] 10.0 / 7.9, [300, 4096] 10.1 / 9.5,
