@@ -121,7 +121,8 @@ int adacc_layout_of(const adacc_method *method, uint64_t numel, adacc_layout *ou
  * epoch wraps, never per call.
  * Rules: initialise once with adacc_workspace_init; afterwards any number of calls may
  * reuse it, one at a time in stream order (calls that may overlap on the GPU, or host
- * threads that call concurrently, must use different workspaces). */
+ * threads that call concurrently, must use different workspaces).  Two structs of one buffer are one
+ * workspace in this sense. */
 typedef struct adacc_workspace {
   void *device_mem; /* caller-owned device buffer, 256-byte aligned            */
   uint64_t bytes;   /* its size                                                */

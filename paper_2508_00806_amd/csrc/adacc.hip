@@ -92,7 +92,7 @@ static int env_int(const char* name, int dflt) {
 // Run-time knobs for measurements, read from the environment once per process.
 struct Knobs {
   int mask_wgs_per_cu;  // ADACC_MASK_WGS_PER_CU: grid of the mask kernels
-  int short_polls;      // ADACC_SHORT_POLLS: looks at a workgroup's count before its tiles are counted again (adacc_short.hpp)
+  int short_polls;      // ADACC_SHORT_POLLS: a wavefront's looks at the words before it counts missing tiles itself (adacc_short.hpp)
 };
 static const Knobs& knobs() {
   static const Knobs k = {env_int("ADACC_MASK_WGS_PER_CU", 256), env_int("ADACC_SHORT_POLLS", 512)};
